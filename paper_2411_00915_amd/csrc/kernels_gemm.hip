@@ -20,10 +20,10 @@
 // consecutive k per lane).  Two kernels:
 //
 //   gemm_ring_kernel (further down): 256 x 256 tiles of large problems.  8 wavefronts, 16x16x32 MFMA,
-//     loads HBM -> LDS directly into a ring of four 32-k stages.
+//     loads HBM -> LDS directly into a ring of quarter stages of 64 k.
 //   gemm_tiled_kernel: everything else.  Loads HBM -> registers -> LDS, double buffered (dynamic LDS,
 //     2 x (BM + BT) x 128 bytes); workgroup tile = 4 wavefronts (2 x 2), each WB x WB MFMA blocks of 32 x 32:
-//     WB = 4: 256 features x 256 tokens x 64 k (K no multiple of 32)
+//     WB = 4: 256 features x 256 tokens x 64 k (large problems with K of at most 128)
 //     WB = 2: 128 x 128 x 64 (small problems, less padding waste)
 //
 // Lane roles in v_mfma_f32_32x32x16_bf16 (D = A*B + C, A 32x16, B 16x32):
@@ -472,63 +472,80 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(
 
 
 // ---------------------------------------------------------------------------------------------------------
-// Ring variant of the 256 x 256 tile: the same MFMA blocking and lane roles, but the tiles go HBM -> LDS
-// directly (global_load_lds_dwordx4, no staging registers, no LDS write instructions) into a ring of four
-// stages of 32 k, three stages ahead of the one the matrix cores work on.  A workgroup's tile walks through
-// lines that nobody has touched yet, stage after stage, so its loads see memory latency (microseconds
-// under load), not L2 latency; with register staging the fetch distance was half a 64-k stage.
+// 256 x 256 tiles of large problems.  Tiles go HBM -> LDS directly (global_load_lds_dwordx4: no staging registers, no
+// LDS write instructions) into a ring of ten granules of 16 KB, two stages of 64 k ahead of their use.
 //
-// A direct-to-LDS load puts lane i's 16 bytes at LDS address M0 + 16 i: the LDS image of one load is 1 KB
-// contiguous = 16 tile rows of 64 bytes, and the XOR swizzle is applied on the global side (lane i fetches the
-// chunk that belongs in slot i).  The loads are issued from inline assembly, so the compiler does not count
-// them: the waits for them are written out (s_waitcnt vmcnt), and since memory returns loads in order,
-// "at most 16 outstanding" means that everything but the two youngest stages has landed.
-constexpr int RK = 32;             // k per ring stage; a tile row is 64 bytes = 4 chunks of 16 bytes
-constexpr int RING = 4;            // stages in the LDS ring
-constexpr int RING_STAGE = 2048;   // uint4 per stage: 256 W rows x 4 chunks, then 256 x rows x 4 chunks
+// What bounds a compute unit's loads is the number of cache lines its requests touch, not their bytes: fetched as
+// 16 rows x 64 bytes per instruction, L2-resident data arrives at 38 GB/s per compute unit however many loads are in
+// flight; as 8 rows x 128 bytes (whole lines) at 100 - 120 GB/s.  A 256 x 256 tile at 1.2 PFLOP/s of the chip takes
+// 36 GB/s per compute unit, so stages of 32 k (64 bytes of a row) end there; hence stages of 64 k.
+//
+// Eight wavefronts, two per SIMD, each 128 features x 64 tokens (8 x 4 blocks of v_mfma_f32_16x16x32_bf16, 128
+// accumulator registers).  A stage is four phases of 16 MFMAs, one per quadrant of the wavefront's tile:
+//   phase 0: W low x x low    1: W low x x high    2: W high x x high    3: W high x x low
+// and its operands are four granules (of all wavefronts together): WL, XL, XH, WH = rows of W blocks 0..3, x blocks
+// 0..1, x blocks 2..3, W blocks 4..7, 128 rows x 64 k each.  Granule g (4 per stage, in that order) is read into
+// registers one phase before its first use, in phase g - 1, and fetched in phase g - 9.
+// A phase is a memory part (LDS reads of one granule, this wavefront's two loads of another) and a matrix part, each
+// closed by a barrier.  Wavefronts 4..7 run one part behind wavefronts 0..3, with which they share the SIMDs: while
+// one of the two wavefronts of a SIMD issues its 16 MFMAs back to back, the other does its memory part.
+//   RAW: granule k + 2 is read in memory part k + 1; every wavefront has waited for its own loads of it (vmcnt; loads
+//        return in order) at the end of its memory part k, one barrier earlier at least.
+//   WAR: granule g, read in memory part g - 1, is overwritten by loads issued in memory part g + 1; the LDS reads of
+//        the trailing wavefronts have returned before their MFMAs of phase g - 1 issued, one barrier earlier.
+// The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
+//
+// Measured against the version with stages of 32 k (same process, cold operands, bf16, T x K x N): 16384 x 5120 x 5120
+// 709 -> 594 us (1.45 PFLOP/s), 16384 x 5120 x 13824 1968 -> 1623 us, 8192 x 4096 x 11008 609 -> 534 us, 4096^3 109 ->
+// 99 us.  With all-zero operands it runs at 1.75 - 2.0 PFLOP/s: what is left is the clock the chip holds under the
+// switching of random operands.  (v_mfma_f32_32x32x16_bf16 in the same schedule: 10 % slower.)
+constexpr int RK = 64;                  // k per stage; a row of a granule is 128 bytes = 8 chunks of 16 bytes
+constexpr int GRANULES = 10;            // ring slots
+constexpr int GRANULE = 16384;          // bytes: 128 rows x 128 bytes
 
-// Chunk c of row r lives at slot 4 r + (c ^ f(r)).  An operand read (ds_read_b128) has lane l take chunk l / 16 of
-// one of 16 rows: x rows r0 + l % 16, W rows r0 + 16 (l % 16 / 4) + l % 4 (the MFMA row permutation).  The f below
-// make these reads free of bank conflicts (checked with the SQ_LDS_BANK_CONFLICT counter on a read-only kernel:
-// 0 stalled cycles, against half of all LDS cycles for f = bits 2..3 of r, or none).
-__device__ __forceinline__ int ring_f_x(int row) { return (row >> 1) & 3; }
-__device__ __forceinline__ int ring_f_w(int row) { return ((row >> 1) & 1) | ((row >> 3) & 2); }
+// Chunk c of granule row r lives at slot 8 r + (c ^ f(r)).  An operand read (ds_read_b128) has lane l take chunk
+// 4 ks + l / 16 of one of 16 rows: x rows r0 + l % 16, W rows r0 + 16 (l % 16 / 4) + l % 4 (the MFMA row
+// permutation); each f takes eight different values over the rows that eight consecutive lanes read.
+__device__ __forceinline__ int ring_f_x(int row) { return row & 7; }
+__device__ __forceinline__ int ring_f_w(int row) { return (row & 3) | ((row >> 2) & 4); }
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
 
-// lane i's 16 bytes at g -> LDS byte address lds_base + 16 i (lds_base wavefront-uniform).  M0 carries the LDS
-// address; nothing else in these kernels uses M0 (LDS instructions of gfx9 and later do not read it).
-__device__ __forceinline__ void load16_to_lds(const void* g, uint32_t lds_base)
+// lane i's 16 bytes at base + off -> LDS byte address lds_base + 16 i (base and lds_base wavefront-uniform).  M0
+// carries the LDS address; nothing else in these kernels uses M0 (LDS instructions of gfx9 and later do not read it).
+__device__ __forceinline__ void load16_to_lds(const char* base, uint32_t off, uint32_t lds_base)
 {
-    // (readfirstlane: the operand has to be a scalar register also where the compiler cannot prove it uniform)
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base) : "memory");
+}
+__device__ __forceinline__ const char* uniform_ptr(const char* p)
+{
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<const char*>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u) |
+                                         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32)) << 32));
 }
 
-template <bool DELTA>
+// KTAIL: K is no multiple of 64.  The last stage's chunks past K are fetched from the row's first chunk of that stage
+// (in bounds) and zeroed in the registers.
+template <bool DELTA, bool KTAIL>
 __global__ __launch_bounds__(512) void gemm_ring_kernel(
     int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
     bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, gemm_delta_args da)
 {
-    // Eight wavefronts, two per SIMD, each 128 features x 64 tokens = 4 x 2 MFMA blocks (128 accumulator
-    // registers).  A wavefront cannot issue an MFMA while it issues a load (each load costs it about one
-    // MFMA slot, also with all lanes masked off); with a second wavefront on the SIMD the matrix core takes
-    // that one's MFMA meanwhile.
-    //
     // DELTA: the rows of the tile are tokens in adapter-sorted order, and after the K loop every wavefront adds the
     // adapter deltas of its own 64 tokens to its accumulators by itself: for each adapter among them (one or two,
     // mostly) and each block of 32 ranks, Bt_a[its 128 features, 32 ranks] as the MFMA row operand straight from
-    // memory, and the tokens' v (its two bf16 terms) as the column operands, masked to the adapter's tokens.  No LDS, no workgroup barrier, no work for the rows of other wavefronts: a wavefront pays
-    // for the adapters of its own 64 tokens only, where a shared adapter stage would cost all eight of them a whole
-    // 256 x 256 x 32 step per adapter and block of ranks.
+    // memory, and the tokens' v (its two bf16 terms) as the column operands, masked to the adapter's tokens.  No LDS,
+    // no workgroup barrier, no work for the rows of other wavefronts: a wavefront pays for the adapters of its own 64
+    // tokens only, where a shared adapter stage would cost all eight of them a whole 256 x 256 step per adapter and
+    // block of ranks.
     constexpr int BM = 256, BT = 256, WA = 8, WX = 4;
-    uint4* ring = gemm_lds;                                          // [RING][RING_STAGE]
 
     int tile_n, tile_t;
     tile_of_workgroup(blockIdx.x, tiles_n, tiles_t, tile_n, tile_t);
     const int n0 = tile_n * BM, t0 = tile_t * BT;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = (wave & 1) * 128, wt = (wave >> 1) * 64;         // wavefront tile origin
     // Lane roles in v_mfma_f32_16x16x32_bf16 (D = A*B + C, A 16x32, B 32x16): lane l supplies A[row l%16][k 8(l/16) ..
     // +7] and B[k 8(l/16) .. +7][col l%16], and receives D[row 4(l/16) + i][col l%16], i = 0..3.  MFMA rows carry
@@ -538,24 +555,29 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
     const int l16 = lane & 15, kg = lane >> 4;
     const int frow = 16 * (l16 >> 2) + (l16 & 3);                   // feature (block 0 of a group) of MFMA row l16
 
-    // Staging role: load j of this wavefront fills slots (2 wave + j) 64 .. +63 of the W part and of the x part
-    // of a stage, i.e. rows (2 wave + j) 16 .. +15; this lane brings chunk slot lane & 3 of row .. + lane / 4.
-    const int pc = lane & 3;
-    const bf16_t* pw[2];
-    const bf16_t* px[2];
-    int cw[2];                                                       // logical chunk this lane fetches (W side)
-    const int cx = pc ^ ring_f_x(lane >> 2);                         // (x side: the same for both loads)
+    // Staging role: load j of this wavefront fills rows (2 wave + j) 8 .. +7 of a granule; this lane brings the chunk
+    // that belongs in slot lane & 7 of row .. + lane / 8.  Granule rows: WL / WH rows r are the tile's features
+    // 128 (r / 64) + r % 64 (+ 64), XL / XH rows r its tokens 64 (r / 32) + r % 32 (+ 32): every wavefront's low / high
+    // half.  (The launcher keeps N ldw and T ldx below 2^31 elements, so 32-bit byte offsets do.)
+    uint32_t off_w[2][2], off_x[2][2];                               // [high half][load]
+    int cut_w = 0, cut_x = 0;                                        // KTAIL: what takes an offset back to its row's first chunk
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const int row = (wave * 2 + j) * 16 + (lane >> 2);
-        cw[j] = pc ^ ring_f_w(row);
-        int nr = n0 + row; if (nr >= N) nr = N - 1;
-        int pos = t0 + row;
-        const bool pos_ok = pos < T;
-        if (!pos_ok) pos = T - 1;
-        const int tok = DELTA ? da.order[pos] : pos;
-        pw[j] = Wt + (int64_t)nr * ldw + cw[j] * 8;
-        px[j] = x + (int64_t)tok * ldx + cx * 8;
+        const int row = (wave * 2 + j) * 8 + (lane >> 3);
+        const int cw = (lane & 7) ^ ring_f_w(row), cx = (lane & 7) ^ ring_f_x(row);     // (the same for both j)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            int nr = n0 + (row >> 6) * 128 + (row & 63) + 64 * h; if (nr >= N) nr = N - 1;
+            int pos = t0 + (row >> 5) * 64 + (row & 31) + 32 * h; if (pos >= T) pos = T - 1;
+            const int tok = DELTA ? da.order[pos] : pos;
+            off_w[h][j] = (uint32_t)(nr * ldw * 2) + cw * 16;
+            off_x[h][j] = (uint32_t)(tok * ldx * 2) + cx * 16;
+        }
+        if (KTAIL) {
+            const int last = (K - 1) / RK * RK;
+            cut_w = last + cw * 8 >= K ? cw * 16 : 0;
+            cut_x = last + cx * 8 >= K ? cx * 16 : 0;
+        }
     }
     // DELTA: token and key of row wt + lane of the tile (this wavefront's 64 tokens, one per lane)
     int my_tok = 0, my_key = KEY_NONE;
@@ -565,8 +587,7 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
         my_key = pos < T ? da.row_key[my_tok] : KEY_NONE;
     }
 
-    const int stages_k = K / RK;                                     // K % 32 == 0, stages_k >= 4 (checked by the launcher)
-    const int stages = stages_k;
+    const int stages = (K + RK - 1) / RK;                            // at least 3 (checked by the launcher)
 
     floatx4 acc[WA][WX];
 #pragma unroll
@@ -574,105 +595,112 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
 #pragma unroll
         for (int b = 0; b < WX; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // source pointers of the stage to fetch next
-    auto advance = [&](int next) {
-        if (next < stages) {
+    // granule loads: kind 0 WL, 1 XL, 2 XH, 3 WH of stage st into ring slot `slot` (bytes)
+    const char* const xb = reinterpret_cast<const char*>(x);
+    const char* const wb = reinterpret_cast<const char*>(Wt);
+    const uint32_t lds0 = lds_address(gemm_lds), lds_load = lds0 + wave * 2048;
+    auto issue = [&](int kind, int st, uint32_t slot) {
+        const bool is_w = kind == 0 || kind == 3;
+        const int h = kind >= 2;
+        const char* base = (is_w ? wb : xb) + (int64_t)st * (RK * 2);
+        const uint32_t cut = KTAIL && st == stages - 1 ? (uint32_t)(is_w ? cut_w : cut_x) : 0u;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) { pw[j] += RK; px[j] += RK; }
-        }
+        for (int j = 0; j < 2; ++j) load16_to_lds(base, (is_w ? off_w[h][j] : off_x[h][j]) - cut, lds_load + slot + j * 1024);
     };
-    const uint32_t lds_w = __builtin_amdgcn_readfirstlane(lds_address(ring) + wave * 2048), lds_x = lds_w + 16384;
-    auto issue = [&](int buf, int j4) {                              // one of the four loads of a stage
-        const uint32_t base = (uint32_t)buf * (RING_STAGE * 16) + (j4 & 1) * 1024;
-        if (j4 < 2) load16_to_lds(pw[j4 & 1], lds_w + base);
-        else load16_to_lds(px[j4 & 1], lds_x + base);
+
+    // operand reads: lane addresses inside a granule for k-step 0; k-step 1 is 64 bytes apart by XOR
+    const uint32_t rw0 = ((wave & 1) * 64 + frow) * 128 + (kg ^ ring_f_w(frow)) * 16;
+    const uint32_t rx0 = ((wave >> 1) * 32 + l16) * 128 + (kg ^ ring_f_x(l16)) * 16;
+    const char* const lds_c = reinterpret_cast<const char*>(gemm_lds);
+    op16 wl[2][4], wh[2][4], xl[2][2], xh[2][2];                     // [k-step][block]
+    auto read_w = [&](op16 (&w)[2][4], uint32_t slot) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) w[ks][a].u = *reinterpret_cast<const uint4*>(lds_c + (slot + (rw0 ^ (ks * 64))) + a * 512);
     };
+    auto read_x = [&](op16 (&xo)[2][2], uint32_t slot) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) xo[ks][b].u = *reinterpret_cast<const uint4*>(lds_c + (slot + (rx0 ^ (ks * 64))) + b * 2048);
+    };
+    auto cut_tail = [&](op16& o, int ks) {                           // KTAIL, last stage: chunks past K are zero
+        if ((stages - 1) * RK + (ks * 4 + kg) * 8 >= K) o.u = uint4{0, 0, 0, 0};
+    };
+    auto mma = [&](const op16 (&w)[2][4], const op16 (&xo)[2][2], int a0, int b0) {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+                    acc[a0 + a][b0 + b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][a].v, xo[ks][b].v, acc[a0 + a][b0 + b], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+    };
+#define RING_BARRIER() do { __builtin_amdgcn_sched_barrier(0); asm volatile("s_barrier" ::: "memory"); __builtin_amdgcn_sched_barrier(0); } while (0)
+#define RING_WAIT_(N_) asm volatile("s_waitcnt vmcnt(" #N_ ")" ::: "memory")
+#define RING_WAIT(N_) RING_WAIT_(N_)
 
-    // operand slots of a stage: one ds_read_b128 of a wavefront is one 16 x 32 operand block (lane group kg reads
-    // chunk kg of its row); W block a = 4 G + q: + (64 G + 4 q) rows; x block b: + 16 b rows
-    const int sw0 = (wn + frow) * 4 + (kg ^ ring_f_w(frow));
-    const int sx0 = RING_STAGE / 2 + (wt + l16) * 4 + (kg ^ ring_f_x(l16));
-    // W operands are single-buffered (block a is re-read for the next stage once its four MFMAs are out), x
-    // operands double-buffered
-    op16 wa[WA], xbA[WX], xbB[WX];
-    auto read_w = [&](const uint4* st, int a) { wa[a].u = st[sw0 + ((a >> 2) * 64 + (a & 3) * 4) * 4]; };
-    auto read_x = [&](const uint4* st, int b, op16 (&xb)[WX]) { xb[b].u = st[sx0 + b * 64]; };
-#define RING_MMA(XB_, A_, B_) \
-    acc[A_][B_] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[A_].v, XB_[B_].v, acc[A_][B_], 0, 0, 0)
-#define RING_FENCE() __builtin_amdgcn_sched_barrier(0)
+    // prologue: granules 0..8 on their way, granule 0 (WL of stage 0) into registers, granule 1 landed
+#pragma unroll
+    for (int gr = 0; gr < 9; ++gr) issue(gr & 3, gr >> 2, gr * GRANULE);
+    RING_WAIT(16);
+    RING_BARRIER();
+    read_w(wl, 0);
+    RING_WAIT(14);
+    RING_BARRIER();
+    if (wave >= 4) RING_BARRIER();                                   // the trailing wavefronts: one part behind
 
-    // prologue: stages 0, 1, 2 on their way (all K stages), stage 0 landed, its first operands read
-#pragma unroll
-    for (int s0 = 0; s0 < 3; ++s0) {
-#pragma unroll
-        for (int j4 = 0; j4 < 4; ++j4) issue(s0, j4);
-        advance(s0 + 1);
-    }
-    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
-#pragma unroll
-    for (int b = 0; b < WX; ++b) read_x(ring, b, xbA);
-#pragma unroll
-    for (int a = 0; a < 4; ++a) read_w(ring, a);
-
-    // One stage = 32 MFMAs.  First half (W blocks 0..3): the reads of W blocks 4..7 of this stage and two of the
-    // four loads of stage s + 3 (into the buffer that stage s - 1 used; everybody left it before the previous
-    // barrier).  Then the wavefront waits until its own loads of stage s + 1 have landed (AHEAD = loads allowed
-    // to be still outstanding) and for its LDS reads, and meets the others.  Second half (W blocks 4..7): the
-    // reads of W blocks 0..3 and of the x blocks of stage s + 1, and the other two loads.
-#define RING_HALF_STAGE(XB_, XN_, ISSUE, AHEAD, LAST)                                                                  \
-    {                                                                                                                  \
-        const uint4* st = ring + (s & 3) * RING_STAGE;                                                                 \
-        const uint4* st_n = ring + ((s + 1) & 3) * RING_STAGE;                                                         \
-        _Pragma("unroll") for (int i = 0; i < 16; ++i) {                                                               \
-            RING_MMA(XB_, i >> 2, i & 3);                                                                              \
-            if ((i & 3) == 1 && i < 16) read_w(st, 4 + (i >> 2));                                                      \
-            if (ISSUE && (i == 7 || i == 11)) issue((s + 3) & 3, i == 7 ? 0 : 1);                                      \
-            RING_FENCE();                                                                                              \
-        }                                                                                                              \
-        if (!(LAST)) asm volatile("s_waitcnt vmcnt(" #AHEAD ") lgkmcnt(0)\n\ts_barrier" ::: "memory");                   \
-        _Pragma("unroll") for (int i = 16; i < 32; ++i) {                                                              \
-            RING_MMA(XB_, i >> 2, i & 3);                                                                              \
-            if (!(LAST) && (i & 1) == 0) { if (i < 24) read_x(st_n, (i - 16) >> 1, XN_); else read_w(st_n, (i - 24) >> 1); } \
-            if (ISSUE && (i == 21 || i == 27)) issue((s + 3) & 3, i == 21 ? 2 : 3);                                    \
-            RING_FENCE();                                                                                              \
-        }                                                                                                              \
-    }
-    // Two stages per loop iteration, so that the x operand buffers swap roles statically; an odd number of
-    // stages ahead of the last three is evened out by one stage up front and a register copy.
+    // one stage; q: slot of granule 4 s (bytes).  NI: how many of its phases issue loads; W0..W3: loads that may be
+    // outstanding at the end of the memory parts
+    auto wrap = [](uint32_t v) { return v >= GRANULES * GRANULE ? v - GRANULES * GRANULE : v; };
+    uint32_t q = 0;
     int s = 0;
-    if ((stages - 3) & 1) {
-        RING_HALF_STAGE(xbA, xbB, true, 6, false)
-        advance(4);
-        _Pragma("unroll") for (int b = 0; b < WX; ++b) xbA[b].u = xbB[b].u;
-        s = 1;
+#define RING_STAGE(NI, W0, W1, W2, W3, LAST)                                                                           \
+    {                                                                                                                  \
+        const uint32_t q2 = wrap(q + 2 * GRANULE), q4 = wrap(q + 4 * GRANULE), q9 = wrap(q + 8 * GRANULE) + GRANULE;   \
+        read_x(xl, q + GRANULE);                                                                                       \
+        if (NI > 0) issue(1, s + 2, q9);                                                                               \
+        if (KTAIL && LAST) { _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) { _Pragma("unroll") for (int a = 0; a < 4; ++a) cut_tail(wl[ks][a], ks); _Pragma("unroll") for (int b = 0; b < 2; ++b) cut_tail(xl[ks][b], ks); } } \
+        RING_WAIT(W0);                                                                                                 \
+        RING_BARRIER();                                                                                                \
+        mma(wl, xl, 0, 0);                                                                                             \
+        RING_BARRIER();                                                                                                \
+        read_x(xh, q2);                                                                                                \
+        if (NI > 1) issue(2, s + 2, q);                                                                                \
+        if (KTAIL && LAST) { _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) { _Pragma("unroll") for (int b = 0; b < 2; ++b) cut_tail(xh[ks][b], ks); } } \
+        RING_WAIT(W1);                                                                                                 \
+        RING_BARRIER();                                                                                                \
+        mma(wl, xh, 0, 2);                                                                                             \
+        RING_BARRIER();                                                                                                \
+        read_w(wh, q2 + GRANULE);                                                                                      \
+        if (NI > 2) issue(3, s + 2, q + GRANULE);                                                                      \
+        if (KTAIL && LAST) { _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) { _Pragma("unroll") for (int a = 0; a < 4; ++a) cut_tail(wh[ks][a], ks); } } \
+        RING_WAIT(W2);                                                                                                 \
+        RING_BARRIER();                                                                                                \
+        mma(wh, xh, 4, 2);                                                                                             \
+        RING_BARRIER();                                                                                                \
+        if (!(LAST)) read_w(wl, q4);                                                                                   \
+        if (NI > 3) issue(0, s + 3, q2);                                                                               \
+        RING_WAIT(W3);                                                                                                 \
+        RING_BARRIER();                                                                                                \
+        mma(wh, xl, 4, 0);                                                                                             \
+        RING_BARRIER();                                                                                                \
+        q = q4;                                                                                                        \
+        ++s;                                                                                                           \
     }
-    // K stages whose fourth successor is a K stage too: no branch in the body
-    for (; s + 5 < stages_k; s += 2) {
-        RING_HALF_STAGE(xbA, xbB, true, 6, false)
-        _Pragma("unroll") for (int j = 0; j < 2; ++j) { pw[j] += RK; px[j] += RK; }
-        ++s;
-        RING_HALF_STAGE(xbB, xbA, true, 6, false)
-        _Pragma("unroll") for (int j = 0; j < 2; ++j) { pw[j] += RK; px[j] += RK; }
-        --s;
-    }
-    // the stages whose fourth successor may lie beyond the end
-    for (; s + 4 < stages; s += 2) {
-        RING_HALF_STAGE(xbA, xbB, true, 6, false)
-        advance(s + 4);
-        ++s;
-        RING_HALF_STAGE(xbB, xbA, true, 6, false)
-        advance(s + 4);
-        --s;
-    }
-    // the last three stages fetch nothing
-    RING_HALF_STAGE(xbA, xbB, false, 4, false)
-    ++s;
-    RING_HALF_STAGE(xbB, xbA, false, 0, false)
-    ++s;
-    RING_HALF_STAGE(xbA, xbB, false, 0, true)
-#undef RING_HALF_STAGE
-#undef RING_MMA
-#undef RING_FENCE
+    while (s < stages - 3) RING_STAGE(4, 14, 14, 14, 14, false)
+    // the last three stages: the last loads go out in the first of them
+    RING_STAGE(3, 14, 14, 14, 12, false)
+    RING_STAGE(0, 10, 8, 6, 4, false)
+    RING_STAGE(0, 2, 0, 0, 0, true)
+    if (wave < 4) RING_BARRIER();
+#undef RING_STAGE
+#undef RING_BARRIER
+#undef RING_WAIT
+#undef RING_WAIT_
 
     // ---- adapter deltas of this wavefront's 64 tokens -----------------------
     if constexpr (DELTA) {
@@ -794,20 +822,20 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
     return hipGetLastError();
 }
 
-template <bool DELTA>
+template <bool DELTA, bool KTAIL>
 hipError_t launch_ring(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw,
                        void* y, int64_t ldy, const gemm_delta_args& da, hipStream_t stream)
 {
     const int tiles_n = (N + 255) / 256, tiles_t = (T + 255) / 256;
-    const size_t lds_bytes = (size_t)RING * RING_STAGE * sizeof(uint4);
+    const size_t lds_bytes = (size_t)GRANULES * GRANULE;
     static std::atomic<bool> attr_set{false};                 // dynamic LDS above 64 KB has to be allowed once per kernel
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_ring_kernel<DELTA>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_ring_kernel<DELTA, KTAIL>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    LORA_LAUNCH(DELTA ? LORA_K_GEMM_RING_DELTA : LORA_K_GEMM_RING, (gemm_ring_kernel<DELTA>),
+    LORA_LAUNCH(DELTA ? LORA_K_GEMM_RING_DELTA : LORA_K_GEMM_RING, (gemm_ring_kernel<DELTA, KTAIL>),
                 dim3(tiles_n * tiles_t), dim3(512), lds_bytes, stream, T, K, N, (const bf16_t*)x, ldx, (const bf16_t*)Wt, ldw,
                 (bf16_t*)y, ldy, tiles_n, tiles_t, da);
     return hipGetLastError();
@@ -837,9 +865,9 @@ hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int
     // 256 x 256 tiles once there are enough of them to fill the 256 compute units
     const bool big = (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192;
     const bool delta = p && (!p->perm.empty() || rm.plan);
-    // the ring kernel: whole 32-k stages, at least four of them
-    // (the ring kernel's delta part addresses the split of v by 32-bit byte offsets)
-    const bool ring_ok = big && K % RK == 0 && K / RK >= 4 &&
+    // the ring kernel: at least three stages of 64 k; rows of W and x addressed by 32-bit byte offsets, in its delta
+    // part also the split of v
+    const bool ring_ok = big && K > 2 * RK && (int64_t)N * ldw * 2 < (1ll << 32) && (int64_t)T * ldx * 2 < (1ll << 32) &&
                          (!delta || ((int64_t)T * p->R * 4 < (1ll << 32) && (!rm.plan || (int64_t)T * rm.plan->R * 4 < (1ll << 32))));
     gemm_delta_args da{};
     if (delta) {
@@ -863,10 +891,13 @@ hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int
                              (const bf16_t* const*)Bt, (const bf16_t*)d->zeros,
                              (const bf16_t*)rm.vb, rm.plan ? rm.plan->R : 0, rm.plan ? p->merged : -1};
     }
-    if (ring_ok)
-        return delta ? launch_ring<true>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
-                     : launch_ring<false>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream);
     const bool ktail = (K % BK) != 0;
+    if (ring_ok) {
+#define RING_DISPATCH(D_, KT_) launch_ring<D_, KT_>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
+        if (delta) return ktail ? RING_DISPATCH(true, true) : RING_DISPATCH(true, false);
+        return ktail ? RING_DISPATCH(false, true) : RING_DISPATCH(false, false);
+#undef RING_DISPATCH
+    }
 #define GEMM_DISPATCH(WB_, D_, KT_) launch_one<WB_, D_, KT_>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
     if (big) {
         if (delta) return ktail ? GEMM_DISPATCH(4, true, true) : GEMM_DISPATCH(4, true, false);

@@ -232,6 +232,16 @@ def test_large_tile_gemm_ragged_shapes(T, K, N):
     run_forward_case(w, n_sample=160)
 
 
+@pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])
+def test_ring_gemm_shortest_rings_and_k_tails(K):
+    """The 256 x 256 ring at its fewest stages (three of 64 k: prologue and drain only), one and two more, with and
+    without chunks past K in the last stage (one chunk in, one chunk missing); ragged T and N, so that the last tiles
+    clamp their rows; base GEMM, fused forward and mixture mode."""
+    w = wl.random_case(740 + K, 3585, K, 3600, 24, (8, 32, 64, 128), max_seg=120, frac_none=0.1, scales=(0.5, 2.0))
+    run_forward_case(w, n_sample=96)
+    run_mixture_case(w, 3, n_sample=96)
+
+
 @pytest.mark.parametrize("K", [256, 200])
 def test_large_tile_gemm_with_hundreds_of_adapters_per_tile(K):
     """Single-token segments of 400 adapters: a 256-row tile carries about 250 adapters.  K = 256: the ring kernel,
