@@ -45,6 +45,7 @@ KERNEL_KEYS = {"shrink_tiled_kernel": "shrink", "expand_tiled_kernel": "expand",
                "shrink_stream_kernel": "shrink", "expand_stream_kernel": "expand", "v_split_kernel": "v_split",
                "gemm_tiled_kernel": "gemm", "gemm_tiled_kernel<delta>": "gemm_delta",
                "gemm_ring_kernel": "gemm", "gemm_ring_kernel<delta>": "gemm_delta",
+               "gemm_small_kernel": "gemm", "gemm_small_kernel<delta>": "gemm_delta",
                "shrink_general_kernel": "shrink", "expand_general_kernel": "expand", "gemm_general_kernel": "gemm"}
 WORKLOADS = ["cfg2", "cfg3", "cfg4", "cfg4d", "cfg5", "cfg5mlp"]
 

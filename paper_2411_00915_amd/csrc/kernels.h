@@ -86,6 +86,15 @@ hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int
                              const lora_plan* p, const lora_dev_tables* d, const float* v, void* vb, bool split_done,
                              const gemm_removal& rm, const void* const* Bt, hipStream_t stream);
 
+// the contraction split over the wavefronts of a workgroup: small bf16 batches, every aligned fp32 batch
+bool gemm_small_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const void* x, int64_t ldx,
+                          const void* Wt, int64_t ldw, const void* y, int64_t ldy);
+bool gemm_small_wins(int32_t T, int32_t K, int32_t N, int32_t dtype);       // the better kernel where the tiled ones could run, too
+hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, const void* x, int64_t ldx,
+                             const void* Wt, int64_t ldw, void* y, int64_t ldy,
+                             const lora_plan* p, const lora_dev_tables* d, const float* v, const gemm_removal& rm,
+                             const void* const* Bt, hipStream_t stream);
+
 // mode switch: Wt_l += s Bt_l At_l for L layers in one launch (device arrays of L pointers each)
 hipError_t launch_merge_tiled(int32_t L, int32_t N, int32_t K, int32_t r, float s, void* const* Wt, int64_t ldw,
                               const void* const* At, const void* const* Bt, hipStream_t stream);

@@ -487,7 +487,9 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
 // Mixture mode: the removal of the merged adapter concerns every token of `unmerge`'s single adapter group; a tile
 // that holds such a token gets the merged adapter's stages once more, marked, after its own.  Tokens without adapter
 // that need the removal sort before the merged adapter's tokens, so that tiles of the latter keep no stage at all.
-static void build_gemm_tables(lora_plan* p)
+// stage_lists: also the lists of adapter stages (16-byte rows of Bt_a, i.e. ranks that are multiples of 8); the row
+// order alone serves the kernels that find the adapters of their rows themselves.
+static void build_gemm_tables(lora_plan* p, bool stage_lists)
 {
     const lora_plan* u = p->unmerge;
     p->row_key.resize((size_t)p->T);
@@ -533,6 +535,7 @@ static void build_gemm_tables(lora_plan* p)
                   p->order.begin() + (size_t)b * 256);
     std::copy(sorted.begin() + (size_t)full * 256, sorted.end(), p->order.begin() + (size_t)full * 256);
 
+    if (!stage_lists) return;
     for (int h = 0; h < 2; ++h) {
         const int32_t rows = h == 0 ? 128 : 256, cols = 64;
         std::vector<int32_t>& ptr = h == 0 ? p->extra_ptr128 : p->extra_ptr256;
@@ -623,7 +626,7 @@ static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_p
             p->shrink_tiled_only = !p->shrink_tiles.empty();
         }
         // (in mixture mode the removal's v must have the layout the GEMM's stages read, too)
-        if (p->tiled_layout_ok && p->n_a < LORA_UNMERGE_BIT && (!unmerge || unmerge->tiled_layout_ok)) build_gemm_tables(p);
+        if (p->n_a < LORA_UNMERGE_BIT) build_gemm_tables(p, p->tiled_layout_ok && (!unmerge || unmerge->tiled_layout_ok));
     } catch (const std::bad_alloc&) {
         lora_plan_destroy(p);
         return LORA_ERR_NOMEM;

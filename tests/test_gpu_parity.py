@@ -232,6 +232,51 @@ def test_large_tile_gemm_ragged_shapes(T, K, N):
     run_forward_case(w, n_sample=160)
 
 
+SMALL_GEMM_SHAPES = [(1, 8, 8), (1, 4096, 4096), (15, 72, 40), (17, 1000, 1096), (33, 64, 16), (47, 520, 4104), (65, 128, 2056),
+                     (100, 3208, 1000), (129, 584, 4096), (257, 72, 4104), (500, 640, 1480), (511, 136, 72)]
+
+
+def _small_gemm_case(T, K, N, dtype):
+    # ranks up to the largest that are no multiple of the MFMA step, or aligned ones
+    ranks = (1, 5, 8, 20, 64, 100, 256) if T % 2 else (8, 16, 64)
+    return wl.random_case(1500 + T + K, T, K, N, 9, ranks, dtype=dtype, max_seg=5, frac_none=0.15, scales=(0.5, 2.0, -1.0))
+
+
+@pytest.mark.parametrize("T,K,N", SMALL_GEMM_SHAPES)
+def test_small_batch_gemm_tiles_and_remainders(T, K, N):
+    """The GEMM that splits K over the wavefronts of a workgroup: every tile shape its rule picks, remainders of
+    tokens and features, fewer units of K than wavefronts, K tails of one chunk, tokens without adapter, mixture mode."""
+    w = _small_gemm_case(T, K, N, "bf16")
+    run_forward_case(w)
+    if T > 16:
+        run_mixture_case(w, 2)
+
+
+@pytest.mark.parametrize("T,K,N", SMALL_GEMM_SHAPES + [(70, 100, 77)])
+def test_fp32_gemm_tiles_and_remainders(T, K, N):
+    """The same kernel in fp32, also with an N that is no multiple of 4.  A sum of n = K + rank fp32 additions whose
+    partial sums stay below 4 (outputs of unit variance) carries a rounding error of at most 2^-24 * 4 * sqrt(n / 3) in
+    standard deviation; five of them over the smallest |y| that is compared, 1e-2: the elementwise bound."""
+    w = _small_gemm_case(T, K, N, "f32")
+    dl = device.to_device(w, DEV, with_w=True)
+    plan = device.make_plan(w)
+    _, _, ws_bytes = B.lora_plan_query(plan)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    tol = (1e-5, 5 * 2.0 ** -24 * 4 * np.sqrt((K + 256) / 3) / 1e-2)
+    ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=DEV)
+    y = torch.full((T + 1, N), 9.0, dtype=torch.float32, device=DEV)
+    B.lora_base_gemm(T, K, N, dl.dtype, dl.x, K, dl.Wt, K, y, N)
+    torch.cuda.synchronize()
+    _assert_close(_to_np(y)[:T], oracle.base(w.x, w.W), tol, "base gemm")
+    y.fill_(9.0)
+    B.lora_fused_forward(plan, dl.x, K, dl.Wt, K, dl.At_ptrs, dl.Bt_ptrs, y, N, ws, ws.numel())
+    torch.cuda.synchronize()
+    _assert_close(_to_np(y)[:T], oracle.forward(w.x, w.W, tok, ad), tol, "fused forward")
+    assert bool((y[T] == 9.0).all()), "written beyond the last token"
+    plan.destroy()
+
+
 @pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])
 def test_ring_gemm_shortest_rings_and_k_tails(K):
     """The 256 x 256 ring at its fewest stages (three of 64 k: prologue and drain only), one and two more, with and
