@@ -75,8 +75,9 @@
  *
  * ALIGNMENT for the tuned bf16 kernels: base pointers 16 bytes; K, ldx, ldy,
  * ldw multiples of 8; ranks multiples of 8, at most 128.  Anything else (and
- * fp32) runs through general kernels with no alignment demands, which are one
- * to two orders of magnitude slower per token; padding an adapter's factors
+ * other layouts) runs through general kernels with no alignment demands, which are one
+ * to two orders of magnitude slower per token; fp32 runs on matrix-core kernels of its own (any rank; the
+ * shrink for K and ldx multiples of 4 and a 16-byte aligned x); padding an adapter's factors
  * with zero rank rows / columns to a multiple of 8 changes no result and moves
  * it onto the tuned kernels.  The rank demands are the expand's (rows of Bt_a
  * have r elements): lora_shrink alone runs on the tuned kernels for any rank
@@ -315,7 +316,7 @@ lora_status lora_delta_static(lora_plan* plan, const void* x, int64_t ldx,
 /*
  * lora_base_gemm -- the base-model product shared by all requests of the batch
  * (section 1 / section 2, unmerged inference):  y = x W, Wt [N,K] with ldw.
- * bf16 MFMA with fp32 accumulation (fp32 dtype: VALU).  Used for the
+ * MFMA with fp32 accumulation.  Used for the
  * "separate" path base GEMM + shrink + expand.
  */
 lora_status lora_base_gemm(int32_t num_tokens, int32_t k, int32_t n, int32_t dtype,

@@ -64,6 +64,7 @@ bool misaligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p
 struct table_layout {
     size_t perm, token_adapter, row_key, rank, scale, shrink_tiles, expand_tiles, sync, sync_bytes, total;
     size_t order, extra_ptr128, extra128, extra_ptr256, extra256, zeros, shrink_rows, expand_rows;
+    size_t f32_shrink, f32_expand, f32_delta;
 };
 
 table_layout layout_of(const lora_plan* p)
@@ -86,6 +87,9 @@ table_layout layout_of(const lora_plan* p)
     L.zeros = take(256);
     L.shrink_rows = take(p->shrink_rows.size() * sizeof(int32_t));
     L.expand_rows = take(p->expand_rows.size() * sizeof(int32_t));
+    L.f32_shrink = take(p->f32_shrink_tiles.size() * sizeof(lora_tile));
+    L.f32_expand = take(p->f32_expand_tiles.size() * sizeof(lora_tile));
+    L.f32_delta = take(p->f32_delta_tiles.size() * sizeof(lora_tile));
     L.sync_bytes = p->fused_ok ? p->group_adapter.size() * 128 : 0;
     L.sync = take(L.sync_bytes);
     L.total = std::max<size_t>(off, 256);
@@ -149,6 +153,9 @@ lora_status ensure_uploaded(lora_plan* p, hipStream_t stream)
     std::memset(h + L.zeros, 0, 256);
     put(L.shrink_rows, p->shrink_rows.data(), p->shrink_rows.size() * sizeof(int32_t));
     put(L.expand_rows, p->expand_rows.data(), p->expand_rows.size() * sizeof(int32_t));
+    put(L.f32_shrink, p->f32_shrink_tiles.data(), p->f32_shrink_tiles.size() * sizeof(lora_tile));
+    put(L.f32_expand, p->f32_expand_tiles.data(), p->f32_expand_tiles.size() * sizeof(lora_tile));
+    put(L.f32_delta, p->f32_delta_tiles.data(), p->f32_delta_tiles.size() * sizeof(lora_tile));
     std::memset(h + L.sync, 0, L.sync_bytes);                    // hand-off counters start at zero
     if (hipMemcpyAsync(dbuf, hbuf, L.total, hipMemcpyHostToDevice, stream) != hipSuccess) {
         (void)hipGetLastError();
@@ -177,6 +184,9 @@ lora_status ensure_uploaded(lora_plan* p, hipStream_t stream)
     p->d_extra256 = reinterpret_cast<int32_t*>(d + L.extra256);
     p->d_shrink_rows = reinterpret_cast<int32_t*>(d + L.shrink_rows);
     p->d_expand_rows = reinterpret_cast<int32_t*>(d + L.expand_rows);
+    p->d_f32_shrink_tiles = reinterpret_cast<lora_tile*>(d + L.f32_shrink);
+    p->d_f32_expand_tiles = reinterpret_cast<lora_tile*>(d + L.f32_expand);
+    p->d_f32_delta_tiles = reinterpret_cast<lora_tile*>(d + L.f32_delta);
     return LORA_OK;
 }
 
@@ -184,7 +194,7 @@ lora_dev_tables tables_of(const lora_plan* p)
 {
     return lora_dev_tables{p->d_perm, p->d_token_adapter, p->d_row_key, p->d_rank, p->d_scale, p->d_shrink_tiles, p->d_expand_tiles,
                            p->d_sync, p->d_order, p->d_extra_ptr128, p->d_extra128, p->d_extra_ptr256, p->d_extra256, p->d_zeros,
-                           p->d_shrink_rows, p->d_expand_rows};
+                           p->d_shrink_rows, p->d_expand_rows, p->d_f32_shrink_tiles, p->d_f32_expand_tiles, p->d_f32_delta_tiles};
 }
 
 size_t elem_bytes(int32_t dtype) { return dtype == LORA_F32 ? 4 : 2; }
@@ -235,8 +245,39 @@ extern "C" lora_status lora_plan_upload(lora_plan* p, void* hip_stream)
     return ensure_uploaded(p, static_cast<hipStream_t>(hip_stream));
 }
 
-// The three calls on one plan's own tiles; the entry points below add the second batch of a plan in mixture mode.
+// Which kernels a plan's shrink and expand run on, from the plan and the layout of the call.
 // vb / split_done: see launch_shrink_tiled
+static lora_status run_shrink(lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* d_At_ptrs, float* v,
+                              hipStream_t stream, void* vb = nullptr, bool* split_done = nullptr)
+{
+    hipError_t e;
+    if ((p->family == LORA_VARIANT_TILED || p->shrink_tiled_only) && tiled_call_ok(x, ldx))
+        e = launch_shrink_tiled(p, d, x, ldx, d_At_ptrs, v, stream, vb, split_done);
+    else if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED)
+        return LORA_ERR_UNSUPPORTED;                           // tiled kernels were demanded but x is not laid out for them
+    else if (shrink_f32_supported(p, x, ldx))
+        e = launch_shrink_f32(p, d, x, ldx, d_At_ptrs, v, stream);
+    else
+        e = launch_shrink_general(p, d, x, ldx, d_At_ptrs, v, stream);
+    return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+}
+
+static lora_status run_expand(lora_plan* p, const lora_dev_tables& d, const float* v, const void* const* d_Bt_ptrs, void* y, int64_t ldy,
+                              float beta, hipStream_t stream)
+{
+    hipError_t e;
+    if (p->family == LORA_VARIANT_TILED && tiled_call_ok(y, ldy))
+        e = launch_expand_tiled(p, d, v, d_Bt_ptrs, y, ldy, beta, stream);
+    else if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED)
+        return LORA_ERR_UNSUPPORTED;
+    else if (!p->f32_expand_tiles.empty())
+        e = launch_expand_f32(p, d, v, d_Bt_ptrs, y, ldy, beta, stream);
+    else
+        e = launch_expand_general(p, d, v, d_Bt_ptrs, y, ldy, beta, stream);
+    return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+}
+
+// The three calls on one plan's own tiles; the entry points below add the second batch of a plan in mixture mode.
 static lora_status shrink_own(lora_plan* p, const void* x, int64_t ldx,
                               const void* const* d_At_ptrs, float* v, void* hip_stream, void* vb = nullptr,
                               bool* split_done = nullptr)
@@ -249,15 +290,7 @@ static lora_status shrink_own(lora_plan* p, const void* x, int64_t ldx,
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     lora_status st = ensure_uploaded(p, stream);
     if (st != LORA_OK) return st;
-    const lora_dev_tables d = tables_of(p);
-    hipError_t e;
-    if ((p->family == LORA_VARIANT_TILED || p->shrink_tiled_only) && tiled_call_ok(x, ldx))
-        e = launch_shrink_tiled(p, d, x, ldx, d_At_ptrs, v, stream, vb, split_done);
-    else if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED)
-        return LORA_ERR_UNSUPPORTED;                           // tiled kernels were demanded but x is not laid out for them
-    else
-        e = launch_shrink_general(p, d, x, ldx, d_At_ptrs, v, stream);
-    return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+    return run_shrink(p, tables_of(p), x, ldx, d_At_ptrs, v, stream, vb, split_done);
 }
 
 extern "C" lora_status lora_shrink(lora_plan* p, const void* x, int64_t ldx,
@@ -281,15 +314,7 @@ static lora_status expand_own(lora_plan* p, const float* v, const void* const* d
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     lora_status st = ensure_uploaded(p, stream);
     if (st != LORA_OK) return st;
-    const lora_dev_tables d = tables_of(p);
-    hipError_t e;
-    if (p->family == LORA_VARIANT_TILED && tiled_call_ok(y, ldy))
-        e = launch_expand_tiled(p, d, v, d_Bt_ptrs, y, ldy, beta, stream);
-    else if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED)
-        return LORA_ERR_UNSUPPORTED;
-    else
-        e = launch_expand_general(p, d, v, d_Bt_ptrs, y, ldy, beta, stream);
-    return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+    return run_expand(p, tables_of(p), v, d_Bt_ptrs, y, ldy, beta, stream);
 }
 
 extern "C" lora_status lora_expand(lora_plan* p, const float* v, const void* const* d_Bt_ptrs,
@@ -325,6 +350,14 @@ static lora_status delta_own(lora_plan* p, const void* x, int64_t ldx,
                                                       trace, trace_bytes);
         if (e == hipErrorInvalidValue && trace != nullptr) return LORA_ERR_WORKSPACE;   // the trace buffer is too small
         return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+    }
+    if (!p->f32_delta_tiles.empty()) {
+        if (misaligned(x, 4) || misaligned(y, 4) || misaligned(v, 16) || misaligned(d_At_ptrs, 8) || misaligned(d_Bt_ptrs, 8))
+            return LORA_ERR_INVALID_ARG;
+        hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+        const lora_status st = ensure_uploaded(p, stream);
+        if (st != LORA_OK) return st;
+        return launch_delta_f32(p, tables_of(p), x, ldx, d_At_ptrs, d_Bt_ptrs, y, ldy, beta, stream) == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
     }
     lora_status st = shrink_own(p, x, ldx, d_At_ptrs, v, hip_stream);
     if (st != LORA_OK) return st;
@@ -481,7 +514,6 @@ extern "C" lora_status lora_delta_static(lora_plan* p, const void* x, int64_t ld
     d.sync = base;
     const bool single = p->family == LORA_VARIANT_TILED && p->fused_ok && tiled_call_ok(x, ldx) && tiled_call_ok(y, ldy) &&
                         !misaligned(d_At_ptrs, 8) && !misaligned(d_Bt_ptrs, 8);
-    hipError_t e;
     if (single) {
         // the counters' launch arithmetic assumes one plan per slot: the array is shared by all plans, so they
         // start every call at zero
@@ -489,22 +521,15 @@ extern "C" lora_status lora_delta_static(lora_plan* p, const void* x, int64_t ld
         LORA_LAUNCH(LORA_K_CLEAR, clear_words_kernel, dim3((n16 + 255) / 256), dim3(256), 0, stream,
                     reinterpret_cast<uint4*>(base), n16);
         if (hipGetLastError() != hipSuccess) return LORA_ERR_DEVICE;
-        e = launch_delta_fused_small(p, d, x, ldx, d_At_ptrs, d_Bt_ptrs, v, y, ldy, beta, stream);
+        const hipError_t e = launch_delta_fused_small(p, d, x, ldx, d_At_ptrs, d_Bt_ptrs, v, y, ldy, beta, stream);
         return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
     }
     if (misaligned(x, elem_bytes(p->dtype)) || misaligned(y, elem_bytes(p->dtype)) || misaligned(d_At_ptrs, 8) ||
         misaligned(d_Bt_ptrs, 8))
         return LORA_ERR_INVALID_ARG;
-    if (p->family == LORA_VARIANT_TILED && tiled_call_ok(x, ldx) && tiled_call_ok(y, ldy)) {
-        e = launch_shrink_tiled(p, d, x, ldx, d_At_ptrs, v, stream);
-        if (e == hipSuccess) e = launch_expand_tiled(p, d, v, d_Bt_ptrs, y, ldy, beta, stream);
-    } else if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED) {
-        return LORA_ERR_UNSUPPORTED;
-    } else {
-        // (the same choice of shrink as lora_delta's: tiled also where only the expand is general)
-        if (p->shrink_tiled_only && tiled_call_ok(x, ldx)) e = launch_shrink_tiled(p, d, x, ldx, d_At_ptrs, v, stream);
-        else e = launch_shrink_general(p, d, x, ldx, d_At_ptrs, v, stream);
-        if (e == hipSuccess) e = launch_expand_general(p, d, v, d_Bt_ptrs, y, ldy, beta, stream);
-    }
-    return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+    if (!p->f32_delta_tiles.empty())
+        return launch_delta_f32(p, d, x, ldx, d_At_ptrs, d_Bt_ptrs, y, ldy, beta, stream) == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+    if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED && !tiled_call_ok(y, ldy)) return LORA_ERR_UNSUPPORTED;
+    st = run_shrink(p, d, x, ldx, d_At_ptrs, v, stream);
+    return st == LORA_OK ? run_expand(p, d, v, d_Bt_ptrs, y, ldy, beta, stream) : st;
 }

@@ -1,0 +1,311 @@
+// fp32 shrink / expand on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products and sums).
+//
+// Shrink: tiles of 16 FB rank rows x 16 TB tokens of one adapter, the contraction split over the eight wavefronts of a
+// workgroup (split_k.h) and over up to four workgroups.  It is bound by reading At and x; one token per workgroup, as
+// the VALU kernel has it, reads At once per token.  256 tokens on 16 adapters of rank 8..64, K = 4096: 267 -> 5 us.
+// Expand: 16 TB tokens x 64 features per wavefront, Bt and y straight from memory in operand order; bound by y and Bt.
+// Delta in one launch: see delta_f32_kernel.
+#include "kernels.h"
+#include "launch.h"
+#include "split_k.h"
+
+#include <atomic>
+#include <type_traits>
+
+namespace {
+
+// v[kpart][token][c0 ..] = s_a * (x A_a) over one K part
+template <int FB, int TB, int D, bool KTAIL, int SUMS>
+__global__ __launch_bounds__(512) void shrink_f32_kernel(
+    const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx,
+    const float* const* __restrict__ At_ptrs, int K, float* __restrict__ v, lora_vspec vsp)
+{
+    const lora_tile t = tiles[blockIdx.x];
+    const int kpart = (t.shape >> 8) & 15, kparts = (t.shape >> 12) & 15;
+    const float* At = At_ptrs[t.adapter] + (int64_t)t.c0 * K;
+    const int32_t* rows = perm + t.row0;
+    const float s_a = __int_as_float(t.reserved1);
+    float* const vp = v + kpart * vsp.part + t.c0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    using slice = split_k<float, FB, TB, D, KTAIL, SUMS>;
+    const int units = (K + slice::KUNIT - 1) / slice::KUNIT;
+    const int p_begin = units * kpart / kparts, p_end = units * (kpart + 1) / kparts;
+    if ((reinterpret_cast<uintptr_t>(At) & 15) != 0) {       // whole lines to LDS need 16-byte rows: a wavefront per value
+        const int k0 = p_begin * slice::KUNIT, k1 = min(K, p_end * slice::KUNIT);
+        for (int e = wave; e < t.nrows * t.cn; e += 8) {
+            const int tok = rows[e / t.cn], j = e % t.cn;
+            float acc = 0.f;
+            for (int k = k0 + lane; k < k1; k += 64) acc = fmaf(x[(int64_t)tok * ldx + k], At[(int64_t)j * K + k], acc);
+            acc = wave_sum(acc);
+            if (lane == 0) vp[(int64_t)tok * vsp.R + j] = s_a * acc;
+        }
+        return;
+    }
+    slice part(
+        K, At, x, wave, [&](int row) { return (int64_t)min(row, t.cn - 1) * K; },
+        [&](int row) { return (int64_t)rows[min(row, t.nrows - 1)] * ldx; });
+    part.run(p_begin + (p_end - p_begin) * wave / 8, p_begin + (p_end - p_begin) * (wave + 1) / 8);
+    part.park();
+    __syncthreads();
+    // a thread finishes F4 consecutive blocks (4 F4 consecutive rank rows) of one lane's token
+    constexpr int ITEMS = FB * TB * 64, F4 = ITEMS > 512 ? ITEMS / 512 : 1;
+    if (wave * F4 >= FB * TB) return;
+    const int b = wave * F4 / FB, f0 = wave * F4 % FB, row = 16 * b + (lane & 15);
+    if (row >= t.nrows) return;
+    float* const dst = vp + (int64_t)rows[row] * vsp.R;
+#pragma unroll
+    for (int f = 0; f < F4; ++f) {
+        const floatx4 sum = s_a * slice::total(f0 + f, b);
+        const int j = 4 * FB * (lane >> 4) + 4 * (f0 + f);
+        if (j + 4 <= t.cn) {
+            *reinterpret_cast<floatx4*>(dst + j) = sum;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (j + i < t.cn) dst[j + i] = sum[i];
+        }
+    }
+}
+
+// Four consecutive features of one token: y = beta y + d, rounded once.
+__device__ __forceinline__ void finish4(float* yp, floatx4 yin, floatx4 d, float beta, bool vec, int left)
+{
+    if (vec && left >= 4) {
+        if (beta != 0.f)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[i] = fmaf(beta, yin[i], d[i]);
+        *reinterpret_cast<floatx4*>(yp) = d;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < left) yp[i] = beta != 0.f ? fmaf(beta, yp[i], d[i]) : d[i];
+    }
+}
+
+// One wavefront: 16 TB tokens of one adapter x chunks of 64 features.  MFMA row 4 q + i of block b stands for feature
+// 16 q + 4 b + i of the chunk: a lane ends with 16 consecutive features of each of its tokens.
+template <int TB>
+__device__ __forceinline__ void expand_f32_tile(
+    const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ v, const lora_vspec& vsp,
+    const float* __restrict__ Bt, float* __restrict__ y, int64_t ldy, float beta, bool y_vec)
+{
+    constexpr int KS = TB == 1 ? 4 : 1;                      // steps of 16 ranks whose loads go out together
+    constexpr int SUMS = TB == 1 ? 4 : 1;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
+    const int r = t.reserved0, n_end = t.c0 + t.cn;
+    int tok[TB];
+#pragma unroll
+    for (int b = 0; b < TB; ++b) tok[b] = perm[t.row0 + min(16 * b + m, t.nrows - 1)];
+    for (int n0 = t.c0 + wave * 64; n0 < n_end; n0 += 256) {
+        const int n_lane = n0 + 16 * g;
+        floatx4 yin[TB][4], acc[TB][4][SUMS];
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                yin[b][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < SUMS; ++i) acc[b][q][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+                if (beta != 0.f && y_vec && n_lane + 4 * q + 4 <= n_end)
+                    yin[b][q] = *reinterpret_cast<const floatx4*>(y + (int64_t)tok[b] * ldy + n_lane + 4 * q);
+            }
+        for (int j0 = 0; j0 < r; j0 += 16 * KS) {
+            op16 bt[KS][4], vo[KS][TB], none;
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                if (j0 + 16 * s < r) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int n = n0 + 16 * (m >> 2) + 4 * q + (m & 3);
+                        bt[s][q] = row_chunk<float>(Bt + (int64_t)min(n, n_end - 1) * r, j0 + 16 * s + 4 * g, r);
+                    }
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) v_chunk<float>(v, vsp, tok[b], j0 + 16 * s + 4 * g, r, true, vo[s][b], none);
+                }
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                if (j0 + 16 * s < r) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int b = 0; b < TB; ++b) mma_apart(bt[s][q], vo[s][b], acc[b][q], 0);
+                }
+        }
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+            if (16 * b + m < t.nrows) {
+                float* yp = y + (int64_t)tok[b] * ldy + n_lane;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) finish4(yp + 4 * q, yin[b][q], folded(acc[b][q]), beta, y_vec, n_end - n_lane - 4 * q);
+            }
+    }
+}
+
+__global__ __launch_bounds__(256) void expand_f32_kernel(
+    const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const float* __restrict__ v, lora_vspec vsp,
+    const float* const* __restrict__ Bt_ptrs, float* __restrict__ y, int64_t ldy, float beta, bool y_vec)
+{
+    const lora_tile t = tiles[blockIdx.x];
+    const float* Bt = Bt_ptrs[t.adapter];
+    if (t.nrows > 16) expand_f32_tile<4>(t, perm, v, vsp, Bt, y, ldy, beta, y_vec);
+    else expand_f32_tile<1>(t, perm, v, vsp, Bt, y, ldy, beta, y_vec);
+}
+
+// Shrink and expand in one launch for problems so small that launches are what they cost: a workgroup owns 16 tokens of
+// one adapter x 128 features and computes the v of its tokens itself (K split over its eight wavefronts, added up in
+// LDS), once per 128 features instead of once.  Bt and y are requested before that.  Ranks up to 64.
+// 64 tokens, 256 -> 256, rank 8: kernels of 4.0 + 3.0 us -> one of 4.1, 11.4 -> 7.9 us per call.
+template <int JB>
+__device__ __forceinline__ void delta_f32_tile(
+    const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx, const float* __restrict__ At, int K,
+    const float* __restrict__ Bt, float* __restrict__ y, int64_t ldy, float beta, bool y_vec, floatx4* lds)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
+    const int r = t.reserved0, n_end = t.c0 + t.cn, tok = perm[t.row0 + min(m, t.nrows - 1)];
+    // Bt rows and y of this wavefront's 16 features
+    const int n0 = t.c0 + 16 * wave, n_lane = n0 + 4 * g;
+    float* const yp = y + (int64_t)tok * ldy + n_lane;
+    op16 bt[JB];
+    floatx4 yin = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < JB; ++s) bt[s] = row_chunk<float>(Bt + (int64_t)min(n0 + m, n_end - 1) * r, 16 * s + 4 * g, r);
+    if (beta != 0.f && y_vec && n_lane + 4 <= n_end) yin = *reinterpret_cast<const floatx4*>(yp);
+
+    constexpr int SUMS = JB <= 2 ? 8 : 4;
+    floatx4 acc[JB][SUMS];
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+        for (int i = 0; i < SUMS; ++i) acc[jb][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int steps = (K + 15) / 16;
+    const float* const xrow = x + (int64_t)tok * ldx;
+    const int s_end = steps * (wave + 1) / 8, whole = min(s_end, K / 16);
+    int s = steps * wave / 8;
+    const float* arow[JB];
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) arow[jb] = At + (int64_t)min(16 * jb + m, r - 1) * K;
+    auto add = [&](auto n_steps) {                           // whole steps: no chunk is cut, all their loads go out first
+        constexpr int U = decltype(n_steps)::value;
+        op16 xo[U], a[U][JB];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = 16 * (s + u) + 4 * g;
+            xo[u].u = ldg_unaligned(xrow + k);
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb) a[u][jb].u = ldg_unaligned(arow[jb] + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb) mma_apart(a[u][jb], xo[u], acc[jb], 4 * (u & 1));
+        s += U;
+    };
+    while (s + 4 <= whole) add(std::integral_constant<int, 4>{});
+    if (s + 2 <= whole) add(std::integral_constant<int, 2>{});
+    if (s < whole) add(std::integral_constant<int, 1>{});
+    if (s < s_end) {
+        const op16 xo = row_chunk<float>(xrow, 16 * s + 4 * g, K);
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) mma_apart(row_chunk<float>(arow[jb], 16 * s + 4 * g, K), xo, acc[jb], 0);
+    }
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) lds[(wave * JB + jb) * 64 + lane] = folded(acc[jb]);
+    __syncthreads();
+    floatx4* const vt = lds + 8 * JB * 64;                   // v as operands: [JB][64 lanes]
+    if (wave < JB) {
+        floatx4 part[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) part[q] = lds[(q * JB + wave) * 64 + lane];
+#pragma unroll
+        for (int st = 4; st > 0; st >>= 1)
+#pragma unroll
+            for (int q = 0; q < st; ++q) part[q] += part[q + st];
+        const float s_a = __int_as_float(t.reserved1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[0][i] = 16 * wave + 4 * g + i < r ? s_a * part[0][i] : 0.f;
+        vt[wave * 64 + lane] = part[0];
+    }
+    __syncthreads();
+    floatx4 d[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < JB; ++j) {
+        op16 vo;
+        vo.f = vt[j * 64 + lane];
+        mma_apart(bt[j], vo, d, 0);
+    }
+    if (m < t.nrows) finish4(yp, yin, folded(d), beta, y_vec, n_end - n_lane);
+}
+
+__global__ __launch_bounds__(512) void delta_f32_kernel(
+    const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx,
+    const float* const* __restrict__ At_ptrs, int K, const float* const* __restrict__ Bt_ptrs, float* __restrict__ y, int64_t ldy,
+    float beta, bool y_vec)
+{
+    __shared__ floatx4 lds[9 * 4 * 64];
+    const lora_tile t = tiles[blockIdx.x];
+    const float *At = At_ptrs[t.adapter], *Bt = Bt_ptrs[t.adapter];
+    if (t.reserved0 <= 16) delta_f32_tile<1>(t, perm, x, ldx, At, K, Bt, y, ldy, beta, y_vec, lds);
+    else if (t.reserved0 <= 32) delta_f32_tile<2>(t, perm, x, ldx, At, K, Bt, y, ldy, beta, y_vec, lds);
+    else delta_f32_tile<4>(t, perm, x, ldx, At, K, Bt, y, ldy, beta, y_vec, lds);
+}
+
+template <int FB, int TB, int D, int SUMS, bool KTAIL>
+hipError_t launch_shrink_shape(const lora_plan* p, const lora_dev_tables& d, const float* x, int64_t ldx, const void* const* At, float* v,
+                               hipStream_t stream)
+{
+    constexpr size_t lds_bytes = (size_t)8 * split_k<float, FB, TB, D, KTAIL, SUMS>::LDS_BYTES;
+    static_assert(D * (2 * FB + 2 * TB) >= FB * TB && lds_bytes <= 163840, "a wavefront's partial sums go where its operands were");
+    if (lds_bytes > 65536) {                                  // dynamic LDS above 64 KB has to be allowed once per kernel
+        static std::atomic<bool> attr_set{false};
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&shrink_f32_kernel<FB, TB, D, KTAIL, SUMS>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    LORA_LAUNCH(LORA_K_SHRINK_F32, (shrink_f32_kernel<FB, TB, D, KTAIL, SUMS>), dim3((unsigned)p->f32_shrink_tiles.size()), dim3(512), lds_bytes,
+                stream, d.f32_shrink_tiles, d.perm, x, ldx, (const float* const*)At, p->K, v, lora_vspec_of(p));
+    return hipGetLastError();
+}
+
+bool vec_rows(const void* y, int64_t ldy) { return ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0; }
+
+}  // namespace
+
+bool shrink_f32_supported(const lora_plan* p, const void* x, int64_t ldx)
+{
+    return !p->f32_shrink_tiles.empty() && ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 &&
+           (int64_t)p->T * ldx * 4 < (1ll << 32);            // 32-bit byte offsets
+}
+
+hipError_t launch_shrink_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
+                             hipStream_t stream)
+{
+#define SHRINK_F32(FB_, TB_, D_, SUMS_)                                                                                        \
+    if (p->f32_shrink_fb == FB_ && p->f32_shrink_tb == TB_)                                                             \
+        return p->K % 32 ? launch_shrink_shape<FB_, TB_, D_, SUMS_, true>(p, d, (const float*)x, ldx, At, v, stream)           \
+                         : launch_shrink_shape<FB_, TB_, D_, SUMS_, false>(p, d, (const float*)x, ldx, At, v, stream);
+    SHRINK_F32(1, 1, 2, 8) SHRINK_F32(2, 2, 1, 4)
+#undef SHRINK_F32
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_expand_f32(const lora_plan* p, const lora_dev_tables& d, const float* v, const void* const* Bt, void* y, int64_t ldy,
+                             float beta, hipStream_t stream)
+{
+    LORA_LAUNCH(LORA_K_EXPAND_F32, expand_f32_kernel, dim3((unsigned)p->f32_expand_tiles.size()), dim3(256), 0, stream,
+                d.f32_expand_tiles, d.perm, v, lora_vspec_of(p), (const float* const*)Bt, (float*)y, ldy, beta, vec_rows(y, ldy));
+    return hipGetLastError();
+}
+
+hipError_t launch_delta_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At,
+                            const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream)
+{
+    LORA_LAUNCH(LORA_K_DELTA_F32, delta_f32_kernel, dim3((unsigned)p->f32_delta_tiles.size()), dim3(512), 0, stream, d.f32_delta_tiles,
+                d.perm, (const float*)x, ldx, (const float* const*)At, p->K, (const float* const*)Bt, (float*)y, ldy, beta, vec_rows(y, ldy));
+    return hipGetLastError();
+}

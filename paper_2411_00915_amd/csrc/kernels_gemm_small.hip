@@ -22,53 +22,11 @@
 #include <algorithm>
 #include <atomic>
 
-#include "device_util.h"
 #include "kernels.h"
 #include "launch.h"
+#include "split_k.h"
 
 namespace {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-
-union op16 {            // 16 bytes of one row: 8 bf16 or 4 fp32 consecutive k
-    u32x4 u;
-    bf16x8 v;
-    floatx4 f;
-};
-
-// 16-byte loads from a wavefront-uniform base plus a 32-bit byte offset per lane
-__device__ __forceinline__ u32x4 ldg(const char* base, uint32_t off)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    return *(const __attribute__((address_space(1))) u32x4*)((const __attribute__((address_space(1))) char*)(uintptr_t)base + off);
-#else
-    return *reinterpret_cast<const u32x4*>(base + off);
-#endif
-}
-
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
-// lane i's 16 bytes at base + off -> LDS byte address lds_base + 16 i (base and lds_base wavefront-uniform); issued
-// from inline assembly, so the waits for it are written out
-__device__ __forceinline__ void load16_to_lds(const char* base, uint32_t off, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base) : "memory");
-}
-
-__device__ __forceinline__ floatx4 mma(const op16& a, const op16& b, floatx4 c, bf16_t)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
-}
-__device__ __forceinline__ floatx4 mma(const op16& a, const op16& b, floatx4 c, float)
-{
-    // lane group g supplies k = g of each 16x16x4 product; taking element i of every lane's chunk permutes k the same
-    // way on both sides
-#pragma unroll
-    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.f[i], b.f[i], c, 0, 0, 0);
-    return c;
-}
 
 struct small_delta_args {
     const int32_t* order;          // [T] tokens sorted by adapter, then tokens without adapter
@@ -84,70 +42,12 @@ struct small_delta_args {
 
 constexpr int KEY_NONE = LORA_UNMERGE_BIT - 1;
 
-// elements [j, j + 16 / sizeof(E)) of a row of r elements; those past the row's end are zero
-template <typename E>
-__device__ __forceinline__ op16 row_chunk(const E* row, int j, int r)
-{
-    constexpr int EPC = 16 / (int)sizeof(E);
-    op16 o;
-    o.u = u32x4{0, 0, 0, 0};
-    if (j >= r) return o;
-    if (r % EPC == 0) {                                      // uniform: the chunk is whole and aligned
-        o.u = ldg(reinterpret_cast<const char*>(row), (uint32_t)j * (uint32_t)sizeof(E));
-    } else if constexpr (sizeof(E) == 4) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (j + i < r) o.f[i] = row[j + i];
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (j + i < r) o.u[i >> 1] |= (uint32_t)row[j + i] << (16 * (i & 1));
-    }
-    return o;
-}
-
-// v[token][j ..] (sum of its K parts) as MFMA operands: bf16: two terms hi + lo; fp32: hi alone
-template <typename E>
-__device__ __forceinline__ void v_chunk(const float* v, const lora_vspec& vsp, int tok, int j, int r, bool mine, op16& hi, op16& lo)
-{
-    constexpr int EPC = 16 / (int)sizeof(E);
-    float f[EPC];
-#pragma unroll
-    for (int i = 0; i < EPC; ++i) f[i] = 0.f;
-    if (mine && j < r) {                                     // (rows are R floats apart, R % 8 == 0)
-        const float* p = v + (int64_t)tok * vsp.R + j;
-        floatx4 part[EPC / 4];
-#pragma unroll
-        for (int q = 0; q < EPC / 4; ++q) part[q] = *reinterpret_cast<const floatx4*>(p + 4 * q);
-        for (int s = 1; s < vsp.P; ++s)
-#pragma unroll
-            for (int q = 0; q < EPC / 4; ++q) part[q] += *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
-#pragma unroll
-        for (int i = 0; i < EPC; ++i) f[i] = j + i < r ? part[i >> 2][i & 3] : 0.f;      // past the rank: never written
-    }
-    if constexpr (sizeof(E) == 4) {
-        hi.f = floatx4{f[0], f[1], f[2], f[3]};
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bf16_t h0 = f32_to_bf16(f[2 * i]), h1 = f32_to_bf16(f[2 * i + 1]);
-            hi.u[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            lo.u[i] = (uint32_t)f32_to_bf16(f[2 * i] - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(f[2 * i + 1] - bf16_to_f32(h1)) << 16);
-        }
-    }
-}
-
-extern __shared__ floatx4 small_lds[];
-
-// Lane roles of the 16x16 MFMAs (rows = features, columns = tokens): lane l supplies row / column m = l % 16, chunk
-// g = l / 16 of a 64-byte step, and receives rows 4 g + i of column m.  Row 4 q + i of block f stands for feature
-// 4 FB q + 4 f + i of the tile, so over its FB blocks a lane holds 4 FB consecutive features of its token.
 template <typename E, int FB, int TB, int D, bool DELTA, bool KTAIL>
 __global__ __launch_bounds__(512) void gemm_small_kernel(
     int T, int K, int N, const E* __restrict__ x, int64_t ldx, const E* __restrict__ Wt, int64_t ldw,
     E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, small_delta_args da)
 {
-    constexpr int WAVES = 8, ES = (int)sizeof(E), EPC = 16 / ES, KSTEP = 4 * EPC, KUNIT = 2 * KSTEP;
+    constexpr int WAVES = 8;
     // workgroups are dealt round-robin to the 8 XCDs; the token tiles of one feature tile follow each other on one
     // XCD, so that its W rows come from memory once and are then in that XCD's L2
     const int q = (int)blockIdx.x >> 3, xcd = (int)blockIdx.x & 7;
@@ -157,107 +57,17 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
 
-    // Loads: an instruction brings 128 bytes of 8 rows (whole cache lines: a compute unit gets 100 - 120 GB/s that way,
-    // 38 GB/s as 64 bytes of 16 rows, the MFMA operand shape) straight into this wavefront's own part of LDS; lane l
-    // fetches the chunk that belongs in slot l % 8 of row l / 8.  (The launcher keeps N ldw and T ldx below 2^32
-    // bytes; rows past the end re-read the last one and are never stored.)
-    constexpr int NW = 2 * FB, NX = 2 * TB, NL = NW + NX;                // loads of a unit
-    const int lrow = lane >> 3, lslot = lane & 7;
-    auto swz_w = [](int row) { return (row & 3) | (((row / (4 * FB)) & 1) << 2); };   // eight values over the rows of eight lanes
-    auto swz_x = [](int row) { return row & 7; };
-    uint32_t off[NL];
-    uint32_t cut[NL];                                                    // KTAIL: what takes a chunk past K in the last unit back to its row's first
-    const int last_k = (K - 1) / KUNIT * KUNIT;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const bool is_w = i < NW;
-        const int row = (is_w ? i : i - NW) * 8 + lrow;
-        const int c = lslot ^ (is_w ? swz_w(row) : swz_x(row));
-        cut[i] = KTAIL && last_k + c * EPC >= K ? c * 16 : 0;
-        int64_t r = is_w ? n0 + row : t0 + row;
-        if (is_w) r = (r < N ? r : N - 1) * ldw;
-        else { r = r < T ? r : T - 1; r = (DELTA ? da.order[r] : r) * ldx; }
-        off[i] = (uint32_t)(r * ES) + c * 16;
-    }
-
-    floatx4 acc[FB][TB];
-#pragma unroll
-    for (int f = 0; f < FB; ++f)
-#pragma unroll
-        for (int b = 0; b < TB; ++b) acc[f][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    // this wavefront's units of 128 bytes per row, D of them in LDS
-    const int units = (K + KUNIT - 1) / KUNIT;
-    const int u_begin = (int)(((int64_t)units * wave) / WAVES), u_end = (int)(((int64_t)units * (wave + 1)) / WAVES);
-    char* const own_lds = reinterpret_cast<char*>(small_lds) + wave * (D * NL * 1024);
-    const uint32_t own_addr = lds_address(small_lds) + wave * (D * NL * 1024);
-    const char* const wb = reinterpret_cast<const char*>(Wt);
-    const char* const xb = reinterpret_cast<const char*>(x);
-    auto issue = [&](int u, int slot) {
-        const bool tail = KTAIL && u == units - 1;
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            load16_to_lds((i < NW ? wb : xb) + (int64_t)u * 128, tail ? off[i] - cut[i] : off[i], own_addr + slot * (NL * 1024) + i * 1024);
-        }
-    };
-    op16 w[2][FB], xr[2][TB];
-    auto read = [&](int slot) {
-        const char* p = own_lds + slot * (NL * 1024);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int c = 4 * s + g;
-#pragma unroll
-            for (int f = 0; f < FB; ++f) {
-                const int row = 4 * FB * (m >> 2) + 4 * f + (m & 3);
-                w[s][f].u = *reinterpret_cast<const u32x4*>(p + row * 128 + (c ^ swz_w(row)) * 16);
-            }
-#pragma unroll
-            for (int b = 0; b < TB; ++b) xr[s][b].u = *reinterpret_cast<const u32x4*>(p + NW * 1024 + (16 * b + m) * 128 + (c ^ swz_x(m)) * 16);
-        }
-    };
-    auto compute = [&](int u) {
-        if (KTAIL && u == units - 1) {
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-                if (last_k + s * KSTEP + g * EPC >= K) {
-#pragma unroll
-                    for (int f = 0; f < FB; ++f) w[s][f].u = u32x4{0, 0, 0, 0};
-#pragma unroll
-                    for (int b = 0; b < TB; ++b) xr[s][b].u = u32x4{0, 0, 0, 0};
-                }
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int f = 0; f < FB; ++f) acc[f][b] = mma(w[s][f], xr[s][b], acc[f][b], E{});
-    };
-    // waits until all but the youngest n units (n < D) have landed; loads return in order
-    auto landed = [&](int n) {
-        if (D >= 4 && n >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
-        else if (D >= 3 && n == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
-        else if (D >= 2 && n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    };
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (u_begin + d < u_end) issue(u_begin + d, d);
-    int slot = 0, u = u_begin;
-    for (; u + D < u_end; ++u) {
-        landed(D - 1);
-        read(slot);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                // the slot is in registers: refill it
-        issue(u + D, slot);
-        compute(u);
-        slot = slot + 1 == D ? 0 : slot + 1;
-    }
-    for (; u < u_end; ++u) {
-        landed(u_end - 1 - u);
-        read(slot);
-        compute(u);
-        slot = slot + 1 == D ? 0 : slot + 1;
-    }
+    // (the launcher keeps N ldw and T ldx below 2^32 bytes)
+    using slice = split_k<E, FB, TB, D, KTAIL>;
+    constexpr int ES = slice::ES, EPC = slice::EPC, KSTEP = slice::KSTEP;
+    slice part(
+        K, Wt, x, wave, [&](int row) { return (int64_t)min(n0 + row, N - 1) * ldw; },
+        [&](int row) {
+            const int r = min(t0 + row, T - 1);
+            return (int64_t)(DELTA ? da.order[r] : r) * ldx;
+        });
+    floatx4 (&acc)[FB][TB][1] = part.acc;
+    part.run((int)(((int64_t)part.units * wave) / WAVES), (int)(((int64_t)part.units * (wave + 1)) / WAVES));
 
     // ---- adapter deltas: the (adapter, rank step) pairs of the tile's tokens in turn to the wavefronts ------
     if constexpr (DELTA) {
@@ -290,8 +100,8 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
                     if (((members >> (16 * b)) & 0xffffull) == 0) continue;       // wavefront-uniform
 #pragma unroll
                     for (int f = 0; f < FB; ++f) {
-                        acc[f][b] = mma(bt[f], hi[b], acc[f][b], E{});
-                        if constexpr (ES == 2) acc[f][b] = mma(bt[f], lo[b], acc[f][b], E{});
+                        acc[f][b][0] = mma(bt[f], hi[b], acc[f][b][0], E{});
+                        if constexpr (ES == 2) acc[f][b][0] = mma(bt[f], lo[b], acc[f][b][0], E{});
                     }
                 }
             }
@@ -311,10 +121,7 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
     }
 
     // ---- partial sums meet in LDS, one rounding, store (rows go back to their tokens) ----
-#pragma unroll
-    for (int b = 0; b < TB; ++b)
-#pragma unroll
-        for (int f = 0; f < FB; ++f) reinterpret_cast<floatx4*>(own_lds)[(b * FB + f) * 64 + lane] = acc[f][b];
+    part.park();
     __syncthreads();
     // a thread finishes F4 consecutive blocks (4 F4 consecutive features) of one lane's token
     constexpr int ITEMS = FB * TB * 64, F4 = ITEMS > 512 ? ITEMS / 512 : 1;
@@ -322,16 +129,7 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
     const int b = wave * F4 / FB, f0 = wave * F4 % FB;
     floatx4 sum[F4];
 #pragma unroll
-    for (int f = 0; f < F4; ++f) {
-        floatx4 part[WAVES];
-#pragma unroll
-        for (int s = 0; s < WAVES; ++s) part[s] = small_lds[s * (D * NL * 64) + (b * FB + f0 + f) * 64 + lane];
-#pragma unroll
-        for (int st = WAVES / 2; st > 0; st >>= 1)
-#pragma unroll
-            for (int s = 0; s < st; ++s) part[s] += part[s + st];
-        sum[f] = part[0];
-    }
+    for (int f = 0; f < F4; ++f) sum[f] = slice::total(f0 + f, b);
     const int pos = t0 + 16 * b + m;
     if (pos >= T) return;
     const int n = n0 + 4 * FB * g + 4 * f0;

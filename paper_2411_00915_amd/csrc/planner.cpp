@@ -479,6 +479,88 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
     }
 }
 
+// Tiles of the fp32 matrix-core kernels.
+static void build_f32_tiles(lora_plan* p)
+{
+    const int G = (int)p->group_adapter.size();
+    if (G == 0) return;
+    auto rows_of = [&](int g) { return p->group_offset[g + 1] - p->group_offset[g]; };
+    auto rank_of = [&](int g) { return p->rank[p->group_adapter[g]]; };
+    auto tile_of = [&](int g, int32_t row, int32_t per) {
+        lora_tile t{};
+        t.adapter = p->group_adapter[g];
+        t.row0 = row;
+        t.nrows = std::min(per, p->group_offset[g + 1] - row);
+        t.reserved0 = rank_of(g);
+        std::memcpy(&t.reserved1, &p->scale[t.adapter], sizeof(float));
+        return t;
+    };
+    // ---- shrink (16-byte chunks of rows: K % 4 == 0).  A compute unit loads 16 (fb + tb) rows per workgroup at about
+    // 100 GB/s and multiplies at 256 flops/clk; the launch takes as long as the unit with the most workgroups; a K part
+    // costs its consumers another read of v.
+    if (p->K % 4 == 0) {
+        const int32_t units = (p->K + 31) / 32;
+        double best = 0;
+        for (int32_t s : {2, 1})
+            for (int32_t P = 1; P <= 4; P *= 2) {
+                // (lora_delta_static keeps v in an array of its own: parts must not be what outgrows it)
+                if (P > 1 && (units / P < 8 || (size_t)P * p->T * p->R * sizeof(float) > LORA_STATIC_V_BYTES)) break;
+                int64_t tiles = 0;
+                for (int g = 0; g < G; ++g) tiles += (int64_t)((rows_of(g) + 16 * s - 1) / (16 * s)) * ((rank_of(g) + 16 * s - 1) / (16 * s));
+                const double load = 2.0 * s * 64 / 100e9, math = s * s * 512.0 / 0.54e12;
+                const double cost = (double)((tiles * P + 255) / 256) * units * 32 / P * std::max(load, math) + (P - 1) * 0.3e-6;
+                if (best == 0 || cost < best) {
+                    best = cost;
+                    p->f32_shrink_fb = p->f32_shrink_tb = s;
+                    p->v_parts = P;
+                }
+            }
+        const int32_t s = p->f32_shrink_fb;
+        for (int g = 0; g < G; ++g)
+            for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16 * s)
+                for (int32_t j = 0; j < rank_of(g); j += 16 * s)
+                    for (int32_t q = 0; q < p->v_parts; ++q) {
+                        lora_tile t = tile_of(g, row, 16 * s);
+                        t.c0 = j;
+                        t.cn = std::min(16 * s, rank_of(g) - j);
+                        t.shape = (q << 8) | (p->v_parts << 12);
+                        p->f32_shrink_tiles.push_back(t);
+                    }
+    }
+    // ---- expand: 64-token tiles for groups of 64 tokens or more; four wavefronts of 64 features, walked further where
+    // that leaves more workgroups than the chip holds at a time
+    int64_t token_tiles = 0, token_tiles16 = 0;
+    int32_t max_rank = 0;
+    auto per_tile = [&](int g) { return rows_of(g) >= 64 ? 64 : 16; };
+    for (int g = 0; g < G; ++g) {
+        token_tiles += (rows_of(g) + per_tile(g) - 1) / per_tile(g);
+        token_tiles16 += (rows_of(g) + 15) / 16;
+        max_rank = std::max(max_rank, rank_of(g));
+    }
+    const int64_t blocks = (p->N + 255) / 256;
+    const int32_t n_tile = 256 * (int32_t)std::max<int64_t>(1, std::min(blocks, token_tiles * blocks / 1024));
+    for (int g = 0; g < G; ++g)
+        for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += per_tile(g))
+            for (int32_t n0 = 0; n0 < p->N; n0 += n_tile) {
+                lora_tile t = tile_of(g, row, per_tile(g));
+                t.c0 = n0;
+                t.cn = std::min(n_tile, p->N - n0);
+                p->f32_expand_tiles.push_back(t);
+            }
+    // ---- both in one launch: every 128 features read the tile's x and At again.  Microseconds per call, one launch /
+    // two, 64 tokens on 8 adapters: rank 8, K = N = 1024 7.7 / 10.8, 2048 8.4 / 10.8; ranks to 64, 512 8.5 / 11.1,
+    // 768 10.8 / 10.8, 1024 12.9 / 11.0
+    if (max_rank <= 64 && (int64_t)(16 + max_rank) * p->K * 4 <= 192 * 1024 && token_tiles16 * ((p->N + 127) / 128) <= 512)
+        for (int g = 0; g < G; ++g)
+            for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16)
+                for (int32_t n0 = 0; n0 < p->N; n0 += 128) {
+                    lora_tile t = tile_of(g, row, 16);
+                    t.c0 = n0;
+                    t.cn = std::min(128, p->N - n0);
+                    p->f32_delta_tiles.push_back(t);
+                }
+}
+
 // Tables of the fused GEMM: it walks the tokens in adapter-sorted order, so a tile of rows holds few
 // adapters, and folds each adapter's delta in (v_hi, v_lo against Bt_a; the register-staged kernels as extra
 // k-stages from the lists below, the ring kernel per wavefront from the row keys).  The full
@@ -615,6 +697,7 @@ static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_p
         else
             p->family = (n_active >= p->tuning.tiled_min_tokens) ? LORA_VARIANT_TILED : LORA_VARIANT_GENERAL;
         if (p->family == LORA_VARIANT_TILED) build_tiles(p);
+        if (p->dtype == LORA_F32 && p->variant_req != LORA_VARIANT_GENERAL) build_f32_tiles(p);
         // Ranks that only the expand kernels cannot take (not multiples of 8: rows of Bt_a would not be 16-byte
         // aligned; above 128): the shrink still runs on the MFMA kernels, which tile the rank axis in blocks of 16
         // rows of At_a and mask what they store.  That is also the path of task heads, whose widths are arbitrary.

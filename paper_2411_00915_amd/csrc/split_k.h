@@ -1,0 +1,281 @@
+// Pieces of the kernels that split the contraction over the wavefronts of a workgroup (gemm_small_kernel, the fp32 and
+// any-rank adapter kernels): 16-byte operands of bf16 or fp32 rows, their MFMA, and split_k, one wavefront's slice of
+// a tile's contraction.
+#pragma once
+#include "device_util.h"
+#include "kernels.h"
+
+namespace {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+
+union op16 {            // 16 bytes of one row: 8 bf16 or 4 fp32 consecutive k
+    u32x4 u;
+    bf16x8 v;
+    floatx4 f;
+};
+
+// 16 bytes at an address that is aligned to an element only (global loads take any address)
+template <typename E>
+__device__ __forceinline__ u32x4 ldg_unaligned(const E* p)
+{
+    typedef u32x4 unaligned_t __attribute__((aligned(2)));
+#if defined(__HIP_DEVICE_COMPILE__)
+    return *(const __attribute__((address_space(1))) unaligned_t*)(uintptr_t)p;
+#else
+    return *reinterpret_cast<const unaligned_t*>(p);
+#endif
+}
+
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
+// lane i's 16 bytes at base + off -> LDS byte address lds_base + 16 i (base and lds_base wavefront-uniform); issued
+// from inline assembly, so the waits for it are written out
+__device__ __forceinline__ void load16_to_lds(const char* base, uint32_t off, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base) : "memory");
+}
+
+__device__ __forceinline__ floatx4 mma(const op16& a, const op16& b, floatx4 c, bf16_t)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mma(const op16& a, const op16& b, floatx4 c, float)
+{
+    // lane group g supplies k = g of each 16x16x4 product; taking element i of every lane's chunk permutes k the same
+    // way on both sides
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.f[i], b.f[i], c, 0, 0, 0);
+    return c;
+}
+
+// fp32 with a sum of its own for every element of the chunks (those of index i go to c[i % N]): a chain of additions
+// is what loses digits, so it is cut in N; folded() adds the sums up as a tree
+template <int N>
+__device__ __forceinline__ void mma_apart(const op16& a, const op16& b, floatx4 (&c)[N], int first)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[(first + i) % N] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.f[i], b.f[i], c[(first + i) % N], 0, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ floatx4 folded(floatx4 (&c)[N])
+{
+#pragma unroll
+    for (int st = N / 2; st > 0; st >>= 1)
+#pragma unroll
+        for (int i = 0; i < st; ++i) c[i] += c[i + st];
+    return c[0];
+}
+
+// elements [j, j + 16 / sizeof(E)) of a row of r elements; those past the row's end are zero
+template <typename E>
+__device__ __forceinline__ op16 row_chunk(const E* row, int j, int r)
+{
+    constexpr int EPC = 16 / (int)sizeof(E);
+    op16 o;
+    o.u = u32x4{0, 0, 0, 0};
+    if (j >= r) return o;
+    if (j + EPC <= r) {                                      // whole; aligned to an element
+        o.u = ldg_unaligned(row + j);
+    } else if constexpr (sizeof(E) == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (j + i < r) o.f[i] = row[j + i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (j + i < r) o.u[i >> 1] |= (uint32_t)row[j + i] << (16 * (i & 1));
+    }
+    return o;
+}
+
+// v[token][j ..] (sum of its K parts) as MFMA operands: bf16: two terms hi + lo; fp32: hi alone
+template <typename E>
+__device__ __forceinline__ void v_chunk(const float* v, const lora_vspec& vsp, int tok, int j, int r, bool mine, op16& hi, op16& lo)
+{
+    constexpr int EPC = 16 / (int)sizeof(E);
+    float f[EPC];
+#pragma unroll
+    for (int i = 0; i < EPC; ++i) f[i] = 0.f;
+    if (mine && j < r) {                                     // (rows are R floats apart, R % 8 == 0)
+        const float* p = v + (int64_t)tok * vsp.R + j;
+        floatx4 part[EPC / 4];
+#pragma unroll
+        for (int q = 0; q < EPC / 4; ++q) part[q] = *reinterpret_cast<const floatx4*>(p + 4 * q);
+        for (int s = 1; s < vsp.P; ++s)
+#pragma unroll
+            for (int q = 0; q < EPC / 4; ++q) part[q] += *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
+#pragma unroll
+        for (int i = 0; i < EPC; ++i) f[i] = j + i < r ? part[i >> 2][i & 3] : 0.f;      // past the rank: never written
+    }
+    if constexpr (sizeof(E) == 4) {
+        hi.f = floatx4{f[0], f[1], f[2], f[3]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bf16_t h0 = f32_to_bf16(f[2 * i]), h1 = f32_to_bf16(f[2 * i + 1]);
+            hi.u[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+            lo.u[i] = (uint32_t)f32_to_bf16(f[2 * i] - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(f[2 * i + 1] - bf16_to_f32(h1)) << 16);
+        }
+    }
+}
+
+extern __shared__ floatx4 small_lds[];
+
+// One wavefront's slice of K of a tile of 16 FB rows of W (features, or rank rows of an adapter) x 16 TB tokens.
+//
+// Lane roles of the 16x16 MFMAs (rows = rows of W, columns = tokens): lane l supplies row / column m = l % 16, chunk
+// g = l / 16 of a 64-byte step, and receives rows 4 g + i of column m.  Row 4 q + i of block f stands for row
+// 4 FB q + 4 f + i of the tile, so over its FB blocks a lane holds 4 FB consecutive rows' results of its token.
+//
+// Loads: an instruction brings 128 bytes of 8 rows (whole cache lines: a compute unit gets 100 - 120 GB/s that way,
+// 38 GB/s as 64 bytes of 16 rows, the MFMA operand shape) straight into this wavefront's own part of LDS; lane l
+// fetches the chunk that belongs in slot l % 8 of row l / 8.  Nothing is shared between wavefronts, so the loop has no
+// barrier: D units of 128 bytes per row are in flight per wavefront.
+// SUMS (fp32): partial sums kept apart per result, see mma_apart.
+template <typename E, int FB, int TB, int D, bool KTAIL, int SUMS = 1>
+struct split_k {
+    static constexpr int ES = (int)sizeof(E), EPC = 16 / ES, KSTEP = 4 * EPC, KUNIT = 2 * KSTEP;
+    static constexpr int NW = 2 * FB, NX = 2 * TB, NL = NW + NX;         // loads of a unit
+    static constexpr int LDS_BYTES = D * NL * 1024;                      // of a wavefront
+    int K, last_k, units, m, g;
+    uint32_t off[NL];
+    uint32_t cut[NL];                                                    // KTAIL: what takes a chunk past K in the last unit back to its row's first
+    char* own_lds;
+    uint32_t own_addr;
+    const char *wb, *xb;
+    floatx4 acc[FB][TB][SUMS];
+    op16 w[2][FB], xr[2][TB];
+
+    static __device__ __forceinline__ int swz_w(int row) { return (row & 3) | (((row / (4 * FB)) & 1) << 2); }   // eight values over the rows of eight lanes
+    static __device__ __forceinline__ int swz_x(int row) { return row & 7; }
+
+    // w_row(row), x_row(row): element offsets of the tile's rows from W and x, below 2^32 bytes (rows that do not exist
+    // name one that does: what is computed for them is not stored)
+    template <typename RowW, typename RowX>
+    __device__ __forceinline__ split_k(int K_, const E* W, const E* x, int wave, RowW w_row, RowX x_row)
+        : K(K_), last_k((K_ - 1) / KUNIT * KUNIT), units((K_ + KUNIT - 1) / KUNIT), wb(reinterpret_cast<const char*>(W)), xb(reinterpret_cast<const char*>(x))
+    {
+        const int lane = threadIdx.x & 63;
+        m = lane & 15;
+        g = lane >> 4;
+        const int lrow = lane >> 3, lslot = lane & 7;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const bool is_w = i < NW;
+            const int row = (is_w ? i : i - NW) * 8 + lrow;
+            const int c = lslot ^ (is_w ? swz_w(row) : swz_x(row));
+            cut[i] = KTAIL && last_k + c * EPC >= K ? c * 16 : 0;
+            const int64_t r = is_w ? w_row(row) : x_row(row);
+            off[i] = (uint32_t)(r * ES) + c * 16;
+        }
+#pragma unroll
+        for (int f = 0; f < FB; ++f)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int i = 0; i < SUMS; ++i) acc[f][b][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        own_lds = reinterpret_cast<char*>(small_lds) + wave * LDS_BYTES;
+        own_addr = lds_address(small_lds) + wave * LDS_BYTES;
+    }
+    __device__ __forceinline__ void issue(int u, int slot)
+    {
+        const bool tail = KTAIL && u == units - 1;
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            load16_to_lds((i < NW ? wb : xb) + (int64_t)u * 128, tail ? off[i] - cut[i] : off[i], own_addr + slot * (NL * 1024) + i * 1024);
+    }
+    __device__ __forceinline__ void read(int slot)
+    {
+        const char* p = own_lds + slot * (NL * 1024);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int c = 4 * s + g;
+#pragma unroll
+            for (int f = 0; f < FB; ++f) {
+                const int row = 4 * FB * (m >> 2) + 4 * f + (m & 3);
+                w[s][f].u = *reinterpret_cast<const u32x4*>(p + row * 128 + (c ^ swz_w(row)) * 16);
+            }
+#pragma unroll
+            for (int b = 0; b < TB; ++b) xr[s][b].u = *reinterpret_cast<const u32x4*>(p + NW * 1024 + (16 * b + m) * 128 + (c ^ swz_x(m)) * 16);
+        }
+    }
+    __device__ __forceinline__ void compute(int u)
+    {
+        if (KTAIL && u == units - 1) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                if (last_k + s * KSTEP + g * EPC >= K) {
+#pragma unroll
+                    for (int f = 0; f < FB; ++f) w[s][f].u = u32x4{0, 0, 0, 0};
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) xr[s][b].u = u32x4{0, 0, 0, 0};
+                }
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int f = 0; f < FB; ++f) {
+                    if constexpr (SUMS > 1) mma_apart(w[s][f], xr[s][b], acc[f][b], 4 * s);
+                    else acc[f][b][0] = mma(w[s][f], xr[s][b], acc[f][b][0], E{});
+                }
+    }
+    // waits until all but the youngest n units (n < D) have landed; loads return in order
+    static __device__ __forceinline__ void landed(int n)
+    {
+        if (D >= 4 && n >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
+        else if (D >= 3 && n == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+        else if (D >= 2 && n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    // adds units [u_begin, u_end) of 128 bytes per row
+    __device__ __forceinline__ void run(int u_begin, int u_end)
+    {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (u_begin + d < u_end) issue(u_begin + d, d);
+        int slot = 0, u = u_begin;
+        for (; u + D < u_end; ++u) {
+            landed(D - 1);
+            read(slot);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the slot is in registers: refill it
+            issue(u + D, slot);
+            compute(u);
+            slot = slot + 1 == D ? 0 : slot + 1;
+        }
+        for (; u < u_end; ++u) {
+            landed(u_end - 1 - u);
+            read(slot);
+            compute(u);
+            slot = slot + 1 == D ? 0 : slot + 1;
+        }
+    }
+    // leaves this wavefront's partial sums where its operands were (a barrier, then the workgroup adds them up)
+    __device__ __forceinline__ void park()
+    {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int f = 0; f < FB; ++f) reinterpret_cast<floatx4*>(own_lds)[(b * FB + f) * 64 + lane] = folded(acc[f][b]);
+    }
+    // the sum over `waves` (8) wavefronts of block (f, b)
+    static __device__ __forceinline__ floatx4 total(int f, int b)
+    {
+        const int lane = threadIdx.x & 63;
+        floatx4 part[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) part[s] = small_lds[s * (LDS_BYTES / 16) + (b * FB + f) * 64 + lane];
+#pragma unroll
+        for (int st = 4; st > 0; st >>= 1)
+#pragma unroll
+            for (int s = 0; s < st; ++s) part[s] += part[s + st];
+        return part[0];
+    }
+};
+
+}  // namespace

@@ -277,6 +277,69 @@ def test_fp32_gemm_tiles_and_remainders(T, K, N):
     plan.destroy()
 
 
+def _check_f32_delta(w, ld_pad=0, shift=0):
+    """lora_shrink, lora_expand and lora_delta in fp32 against the oracle (bound: see
+    test_fp32_gemm_tiles_and_remainders).  shift: the factors lie `shift` elements past 16-byte boundaries."""
+    dl = device.to_device(w, DEV, with_w=False)
+    At, Bt, keep = dl.At_ptrs, dl.Bt_ptrs, []
+    if shift:
+        ptrs = []
+        for M in [a.T for a in w.A] + [b.T for b in w.B]:
+            buf = torch.empty(M.size + 8, dtype=torch.float32, device=DEV)
+            buf[shift:shift + M.size] = torch.from_numpy(np.ascontiguousarray(M).ravel()).to(DEV)
+            keep.append(buf)
+            ptrs.append(buf.data_ptr() + 4 * shift)
+        At, Bt = (torch.tensor(q, dtype=torch.int64, device=DEV) for q in (ptrs[:w.num_adapters], ptrs[w.num_adapters:]))
+    plan = device.make_plan(w)
+    R, v_bytes, _ = B.lora_plan_query(plan)
+    P = B.lora_plan_export(plan)["v_parts"]
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    tol = (1e-5, 5 * 2.0 ** -24 * 4 * np.sqrt((w.K + 256) / 3) / 1e-2)
+    x = torch.full((w.T, w.K + ld_pad), float("nan"), dtype=torch.float32, device=DEV)
+    x[:, :w.K] = torch.from_numpy(np.asarray(w.x, dtype=np.float32)).to(DEV)
+    v = torch.full((P, w.T, R), float("nan"), dtype=torch.float32, device=DEV)
+    assert v.numel() * 4 == v_bytes
+    y0 = torch.from_numpy(_y_in(w)).to(DEV)
+    y = torch.full((w.T + 1, w.N + ld_pad), 7.0, dtype=torch.float32, device=DEV)
+    ref = oracle.expand(w.x, tok, ad, w.N, y_in=_y_in(w).astype(np.float64))
+    none = torch.from_numpy(np.where(tok >= 0, w.adapter_rank[np.clip(tok, 0, None)], 0) == 0).to(DEV)
+    B.lora_shrink(plan, x, w.K + ld_pad, At, v)
+    rank_tok = np.where(tok >= 0, w.adapter_rank[np.clip(tok, 0, None)], 0)
+    valid = np.arange(R)[None, :] < rank_tok[:, None]
+    v_np = v.double().sum(0).cpu().numpy()
+    assert np.array_equal(~np.isnan(v_np), valid), "v written outside [0, r_a), or not inside"
+    _assert_close(np.where(valid, v_np, 0.0), oracle.shrink(w.x, tok, ad, apply_scale=True, R=R), tol, "v")
+    for call in ("expand", "delta"):
+        for beta in (1.0, 0.0):
+            y.fill_(7.0)
+            y[:w.T, :w.N] = y0
+            if call == "expand":
+                B.lora_expand(plan, v, Bt, y, w.N + ld_pad, beta)
+            else:
+                B.lora_delta(plan, x, w.K + ld_pad, At, Bt, v, y, w.N + ld_pad, beta)
+            torch.cuda.synchronize()
+            assert bool((y[:w.T, w.N:] == 7.0).all()) and bool((y[w.T] == 7.0).all()), "written outside y"
+            assert torch.equal(y[:w.T, :w.N][none], y0[none]), "rows without adapter must stay bit-identical"
+            got, want = _to_np(y)[:w.T, :w.N], ref - (0.0 if beta else _y_in(w).astype(np.float64))
+            active = ~none.cpu().numpy()
+            _assert_close(got[active], want[active], tol, f"{call} beta={beta}")
+    plan.destroy()
+
+
+@pytest.mark.parametrize("T,K,N,ranks,max_seg", [
+    (1, 4, 1, (1,), 1), (5, 64, 130, (8, 16), 2), (64, 256, 256, (8,), 16), (33, 252, 127, (64, 33, 1), 9), (40, 268, 513, (5, 48, 17), 30),
+    (257, 1024, 1000, (8, 64), 12), (300, 3208, 264, (8, 16, 100, 256), 150), (1000, 132, 520, (3, 20, 64, 128), 500),
+    (2100, 512, 256, (64, 128), 2100)])
+def test_fp32_adapter_kernels_tiles_and_remainders(T, K, N, ranks, max_seg):
+    """The fp32 matrix-core shrink (each of its tiles, K parts, K tails, ranks off 4 and 16), expand (16- and 64-token
+    tiles, ranks beyond a load group, N off 4 and 64) and the two in one launch, with padded and odd leading dimensions
+    (no 16-byte rows of y, the general shrink) and with factors that are aligned to an element only."""
+    w = wl.random_case(1700 + T + K, T, K, N, 5, ranks, dtype="f32", max_seg=max_seg, frac_none=0.15, scales=(0.5, 2.0, -1.0))
+    for ld_pad, shift in ((0, 0), (4, 1), (3, 0), (0, 3)):
+        _check_f32_delta(w, ld_pad, shift)
+
+
 @pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])
 def test_ring_gemm_shortest_rings_and_k_tails(K):
     """The 256 x 256 ring at its fewest stages (three of 64 k: prologue and drain only), one and two more, with and
