@@ -74,10 +74,12 @@
  * merged_adapter_plus1 naming an adapter of rank 0: same as 0.
  *
  * ALIGNMENT for the tuned bf16 kernels: base pointers 16 bytes; K, ldx, ldy,
- * ldw multiples of 8; ranks multiples of 8, at most 128.  Anything else (and
- * other layouts) runs through general kernels with no alignment demands, which are one
- * to two orders of magnitude slower per token; fp32 runs on matrix-core kernels of its own (any rank; the
- * shrink for K and ldx multiples of 4 and a 16-byte aligned x); padding an adapter's factors
+ * ldw multiples of 8; ranks multiples of 8, at most 128.  Other ranks up to
+ * LORA_MAX_RANK, and fp32, run on matrix-core kernels of their own, which take
+ * factors aligned to an element (the shrink: 16-byte rows of x and At, i.e. K
+ * and ldx multiples of 8, fp32 of 4).  Other layouts run through general kernels
+ * with no alignment demands, which are one to two orders of magnitude slower per
+ * token; padding an adapter's factors
  * with zero rank rows / columns to a multiple of 8 changes no result and moves
  * it onto the tuned kernels.  The rank demands are the expand's (rows of Bt_a
  * have r elements): lora_shrink alone runs on the tuned kernels for any rank

@@ -35,7 +35,7 @@ struct lora_dev_tables {
     const int32_t* shrink_rows;    // single-launch decode kernel: 16 tokens per shrink / expand tile, padded
     const int32_t* expand_rows;
     const lora_tile* f32_shrink_tiles;
-    const lora_tile* f32_expand_tiles;
+    const lora_tile* rows_expand_tiles;
     const lora_tile* f32_delta_tiles;
 };
 
@@ -49,10 +49,11 @@ hipError_t launch_expand_general(const lora_plan* p, const lora_dev_tables& d, c
 bool shrink_f32_supported(const lora_plan* p, const void* x, int64_t ldx);
 hipError_t launch_shrink_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
                              hipStream_t stream);
-hipError_t launch_expand_f32(const lora_plan* p, const lora_dev_tables& d, const float* v, const void* const* Bt, void* y, int64_t ldy,
-                             float beta, hipStream_t stream);
 hipError_t launch_delta_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At,
                             const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream);
+// fp32 or bf16, any rank, no alignment demands
+hipError_t launch_expand_rows(const lora_plan* p, const lora_dev_tables& d, const float* v, const void* const* Bt, void* y, int64_t ldy,
+                              float beta, hipStream_t stream);
 
 // tiled MFMA family (bf16; K, ranks, ldx, ldy multiples of 8; 16-byte aligned bases)
 // vb != nullptr: room for the split of v into two bf16 terms, [T][2][R]; *split_done tells whether the launch wrote it

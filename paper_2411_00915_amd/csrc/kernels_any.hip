@@ -1,9 +1,10 @@
-// fp32 shrink / expand on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products and sums).
+// fp32 shrink / expand on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products and sums), and the expand of small
+// bf16 batches whose ranks the tuned kernels do not take.
 //
 // Shrink: tiles of 16 FB rank rows x 16 TB tokens of one adapter, the contraction split over the eight wavefronts of a
 // workgroup (split_k.h) and over up to four workgroups.  It is bound by reading At and x; one token per workgroup, as
 // the VALU kernel has it, reads At once per token.  256 tokens on 16 adapters of rank 8..64, K = 4096: 267 -> 5 us.
-// Expand: 16 TB tokens x 64 features per wavefront, Bt and y straight from memory in operand order; bound by y and Bt.
+// Expand: 16 tokens x 64 features per wavefront; bound by y and Bt.
 // Delta in one launch: see delta_f32_kernel.
 #include "kernels.h"
 #include "launch.h"
@@ -83,73 +84,182 @@ __device__ __forceinline__ void finish4(float* yp, floatx4 yin, floatx4 d, float
     }
 }
 
-// One wavefront: 16 TB tokens of one adapter x chunks of 64 features.  MFMA row 4 q + i of block b stands for feature
-// 16 q + 4 b + i of the chunk: a lane ends with 16 consecutive features of each of its tokens.
-template <int TB>
-__device__ __forceinline__ void expand_f32_tile(
-    const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ v, const lora_vspec& vsp,
-    const float* __restrict__ Bt, float* __restrict__ y, int64_t ldy, float beta, bool y_vec)
+// Sixteen consecutive features of one token: y = beta y + d, rounded once.  `yin`: what was there, where `vec` (whole,
+// aligned 16-byte pieces); the others are read here.
+template <typename E>
+__device__ __forceinline__ void finish16(E* yp, const u32x4 (&yin)[sizeof(E)], const floatx4 (&d)[4], float beta, bool vec, int left)
 {
-    constexpr int KS = TB == 1 ? 4 : 1;                      // steps of 16 ranks whose loads go out together
-    constexpr int SUMS = TB == 1 ? 4 : 1;
+    if (vec && left >= 16) {
+        if constexpr (sizeof(E) == 4) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) finish4(yp + 4 * q, __builtin_bit_cast(floatx4, yin[q]), d[q], beta, true, 4);
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                u32x4 out;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float e0 = d[2 * h + q / 2][q % 2 * 2], e1 = d[2 * h + q / 2][q % 2 * 2 + 1];
+                    if (beta != 0.f) {
+                        e0 = fmaf(beta, bf16_to_f32((bf16_t)(yin[h][q] & 0xffffu)), e0);
+                        e1 = fmaf(beta, bf16_to_f32((bf16_t)(yin[h][q] >> 16)), e1);
+                    }
+                    out[q] = (uint32_t)f32_to_bf16(e0) | ((uint32_t)f32_to_bf16(e1) << 16);
+                }
+                *reinterpret_cast<u32x4*>(yp + 8 * h) = out;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (i < left) {
+                const float e = d[i >> 2][i & 3];
+                elem<E>::store(yp + i, beta != 0.f ? fmaf(beta, elem<E>::load(yp + i), e) : e);
+            }
+    }
+}
+
+// Expand, 16 TB tokens of one adapter per workgroup, chunks of 64 features per wavefront.  Bt and y come straight from
+// memory as each lane needs them (rows of any length, aligned to an element); v is common to the wavefronts and lies in
+// LDS as operands (bf16: two terms).  MFMA row 4 q + i of block f stands for feature 16 q + 4 f + i of the chunk: a lane
+// ends with 16 consecutive features of each of its tokens.
+//
+// Chunks of Bt are fetched whole from where they lie, into the next row if need be and, where they would reach past the
+// matrix, from before their place (N >= 8: there is a whole chunk); what is not theirs is shifted out and masked when
+// they are used.
+// 1000 tokens on 24 adapters of ranks 4 to 256, N = 4096: 123 us (one token per workgroup, Bt a row per thread) -> 15.
+template <typename E>
+__device__ __forceinline__ u32x4 own_elements(u32x4 b, uint32_t drop, int keep)
+{
+    if constexpr (sizeof(E) == 4) {
+        if (drop & 2) b = u32x4{b[2], b[3], 0, 0};
+        if (drop & 1) b = u32x4{b[1], b[2], b[3], 0};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = i < keep ? b[i] : 0u;
+    } else {
+        if (drop & 4) b = u32x4{b[2], b[3], 0, 0};
+        if (drop & 2) b = u32x4{b[1], b[2], b[3], 0};
+        if (drop & 1) b = u32x4{(b[0] >> 16) | (b[1] << 16), (b[1] >> 16) | (b[2] << 16), (b[2] >> 16) | (b[3] << 16), b[3] >> 16};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = 2 * i + 2 <= keep ? b[i] : (2 * i < keep ? b[i] & 0xffffu : 0u);
+    }
+    return b;
+}
+
+template <typename E, int TB>
+__device__ __forceinline__ void expand_rows_tile(
+    const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ v, const lora_vspec& vsp,
+    const E* __restrict__ Bt, E* __restrict__ y, int64_t ldy, int N, float beta, bool y_vec, op16* lds)
+{
+    constexpr int ES = (int)sizeof(E), EPC = 16 / ES, KSTEP = 4 * EPC, TERMS = ES == 2 ? 2 : 1;
+    constexpr int KS = TB == 1 ? 2 : 4;                      // steps of KSTEP ranks whose loads go out together (as many as registers hold)
+    constexpr int SUMS = ES == 4 ? 4 / TB : 1;               // (see mma_apart)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
-    const int r = t.reserved0, n_end = t.c0 + t.cn;
+    const int r = t.reserved0, n_end = t.c0 + t.cn, steps = (r + KSTEP - 1) / KSTEP;
     int tok[TB];
 #pragma unroll
     for (int b = 0; b < TB; ++b) tok[b] = perm[t.row0 + min(16 * b + m, t.nrows - 1)];
-    for (int n0 = t.c0 + wave * 64; n0 < n_end; n0 += 256) {
-        const int n_lane = n0 + 16 * g;
-        floatx4 yin[TB][4], acc[TB][4][SUMS];
+    int n0 = t.c0 + wave * 64;
+    op16 bt[KS][4];
+    u32x4 yin[TB][ES];
+    const uint32_t last = (uint32_t)N * (uint32_t)r - EPC;   // where the matrix's last whole chunk is (N r < 2^31)
+    const bool whole = r % EPC == 0;
+    auto place = [&](int s, int f) {                         // of the chunk of step s that this lane needs for block f
+        const int n = n0 + 16 * (m >> 2) + 4 * f + (m & 3);
+        return (uint32_t)min(n, n_end - 1) * (uint32_t)r + (uint32_t)(s * KSTEP + EPC * g);
+    };
+    auto load_b = [&](int s0) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            if (s0 + s < steps) {
+#pragma unroll
+                for (int f = 0; f < 4; ++f) bt[s][f].u = ldg_unaligned(Bt + min(place(s0 + s, f), last));
+            }
+    };
+    auto load_y = [&]() {
+        if (beta != 0.f && y_vec && n0 + 16 * g + 16 <= n_end) {
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int q = 0; q < ES; ++q) yin[b][q] = *reinterpret_cast<const u32x4*>(y + (int64_t)tok[b] * ldy + n0 + 16 * g + q * EPC);
+        }
+    };
+    if (n0 < n_end) {                                        // what does not depend on v goes out before it
+        load_y();
+        load_b(0);
+    }
+    for (int s = wave; s < steps; s += 4)
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            op16 hi, lo;
+            v_chunk<E>(v, vsp, tok[b], s * KSTEP + EPC * g, r, true, hi, lo);
+            lds[((s * TB + b) * TERMS) * 64 + lane] = hi;
+            if (ES == 2) lds[((s * TB + b) * TERMS + 1) * 64 + lane] = lo;
+        }
+    __syncthreads();
+    for (bool first = true; n0 < n_end; n0 += 256, first = false) {
+        if (!first) load_y();
+        floatx4 acc[TB][4][SUMS];
 #pragma unroll
         for (int b = 0; b < TB; ++b)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                yin[b][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int f = 0; f < 4; ++f)
 #pragma unroll
-                for (int i = 0; i < SUMS; ++i) acc[b][q][i] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (beta != 0.f && y_vec && n_lane + 4 * q + 4 <= n_end)
-                    yin[b][q] = *reinterpret_cast<const floatx4*>(y + (int64_t)tok[b] * ldy + n_lane + 4 * q);
-            }
-        for (int j0 = 0; j0 < r; j0 += 16 * KS) {
-            op16 bt[KS][4], vo[KS][TB], none;
+                for (int i = 0; i < SUMS; ++i) acc[b][f][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < steps; s0 += KS) {
+            if (!first || s0 > 0) load_b(s0);
 #pragma unroll
             for (int s = 0; s < KS; ++s)
-                if (j0 + 16 * s < r) {
+                if (s0 + s < steps) {
+                    const int left = r - (s0 + s) * KSTEP - EPC * g;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int n = n0 + 16 * (m >> 2) + 4 * q + (m & 3);
-                        bt[s][q] = row_chunk<float>(Bt + (int64_t)min(n, n_end - 1) * r, j0 + 16 * s + 4 * g, r);
+                    for (int f = 0; f < 4; ++f) {
+                        if (whole) {
+                            if (left <= 0) bt[s][f].u = u32x4{0, 0, 0, 0};
+                        } else {
+                            const uint32_t at = place(s0 + s, f);
+                            bt[s][f].u = own_elements<E>(bt[s][f].u, at > last ? at - last : 0u, left);
+                        }
                     }
 #pragma unroll
-                    for (int b = 0; b < TB; ++b) v_chunk<float>(v, vsp, tok[b], j0 + 16 * s + 4 * g, r, true, vo[s][b], none);
-                }
+                    for (int b = 0; b < TB; ++b) {
+                        const op16* vp = lds + (((s0 + s) * TB + b) * TERMS) * 64 + lane;
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
-                if (j0 + 16 * s < r) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int b = 0; b < TB; ++b) mma_apart(bt[s][q], vo[s][b], acc[b][q], 0);
+                        for (int f = 0; f < 4; ++f) {
+                            if constexpr (ES == 4) {
+                                mma_apart(bt[s][f], vp[0], acc[b][f], 0);
+                            } else {
+                                acc[b][f][0] = mma(bt[s][f], vp[0], acc[b][f][0], E{});
+                                acc[b][f][0] = mma(bt[s][f], vp[64], acc[b][f][0], E{});
+                            }
+                        }
+                    }
                 }
         }
 #pragma unroll
         for (int b = 0; b < TB; ++b)
             if (16 * b + m < t.nrows) {
-                float* yp = y + (int64_t)tok[b] * ldy + n_lane;
+                floatx4 d[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) finish4(yp + 4 * q, yin[b][q], folded(acc[b][q]), beta, y_vec, n_end - n_lane - 4 * q);
+                for (int f = 0; f < 4; ++f) d[f] = folded(acc[b][f]);
+                finish16<E>(y + (int64_t)tok[b] * ldy + n0 + 16 * g, yin[b], d, beta, y_vec, n_end - n0 - 16 * g);
             }
     }
 }
 
-__global__ __launch_bounds__(256) void expand_f32_kernel(
+extern __shared__ op16 expand_rows_lds[];
+
+// TBMAX: token blocks of the plan's largest tile (the kernel's register count is that of its widest case: small batches
+// get more wavefronts onto a compute unit)
+template <typename E, int TBMAX>
+__global__ __launch_bounds__(256, TBMAX == 1 ? 3 : 2) void expand_rows_kernel(
     const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const float* __restrict__ v, lora_vspec vsp,
-    const float* const* __restrict__ Bt_ptrs, float* __restrict__ y, int64_t ldy, float beta, bool y_vec)
+    const E* const* __restrict__ Bt_ptrs, E* __restrict__ y, int64_t ldy, int N, float beta, bool y_vec)
 {
     const lora_tile t = tiles[blockIdx.x];
-    const float* Bt = Bt_ptrs[t.adapter];
-    if (t.nrows > 16) expand_f32_tile<4>(t, perm, v, vsp, Bt, y, ldy, beta, y_vec);
-    else expand_f32_tile<1>(t, perm, v, vsp, Bt, y, ldy, beta, y_vec);
+    const E* Bt = Bt_ptrs[t.adapter];
+    if (TBMAX >= 2 && t.nrows > 16) expand_rows_tile<E, 2>(t, perm, v, vsp, Bt, y, ldy, N, beta, y_vec, expand_rows_lds);
+    else expand_rows_tile<E, 1>(t, perm, v, vsp, Bt, y, ldy, N, beta, y_vec, expand_rows_lds);
 }
 
 // Shrink and expand in one launch for problems so small that launches are what they cost: a workgroup owns 16 tokens of
@@ -272,7 +382,7 @@ hipError_t launch_shrink_shape(const lora_plan* p, const lora_dev_tables& d, con
     return hipGetLastError();
 }
 
-bool vec_rows(const void* y, int64_t ldy) { return ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0; }
+bool vec_rows(const void* y, int64_t ldy, int64_t es) { return ldy * es % 16 == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0; }
 
 }  // namespace
 
@@ -294,11 +404,21 @@ hipError_t launch_shrink_f32(const lora_plan* p, const lora_dev_tables& d, const
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_expand_f32(const lora_plan* p, const lora_dev_tables& d, const float* v, const void* const* Bt, void* y, int64_t ldy,
-                             float beta, hipStream_t stream)
+hipError_t launch_expand_rows(const lora_plan* p, const lora_dev_tables& d, const float* v, const void* const* Bt, void* y, int64_t ldy,
+                              float beta, hipStream_t stream)
 {
-    LORA_LAUNCH(LORA_K_EXPAND_F32, expand_f32_kernel, dim3((unsigned)p->f32_expand_tiles.size()), dim3(256), 0, stream,
-                d.f32_expand_tiles, d.perm, v, lora_vspec_of(p), (const float* const*)Bt, (float*)y, ldy, beta, vec_rows(y, ldy));
+#define EXPAND_ROWS(E_, TBMAX_)                                                                                              \
+    LORA_LAUNCH(LORA_K_EXPAND_ROWS, (expand_rows_kernel<E_, TBMAX_>), dim3((unsigned)p->rows_expand_tiles.size()), dim3(256), \
+                (size_t)p->rows_expand_lds, stream, d.rows_expand_tiles, d.perm, v, lora_vspec_of(p), (const E_* const*)Bt,   \
+                (E_*)y, ldy, p->N, beta, vec_rows(y, ldy, sizeof(E_)))
+    if (p->dtype == LORA_F32) {
+        if (p->rows_expand_tb == 1) EXPAND_ROWS(float, 1);
+        else EXPAND_ROWS(float, 2);
+    } else {
+        if (p->rows_expand_tb == 1) EXPAND_ROWS(bf16_t, 1);
+        else EXPAND_ROWS(bf16_t, 2);
+    }
+#undef EXPAND_ROWS
     return hipGetLastError();
 }
 
@@ -306,6 +426,6 @@ hipError_t launch_delta_f32(const lora_plan* p, const lora_dev_tables& d, const 
                             const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream)
 {
     LORA_LAUNCH(LORA_K_DELTA_F32, delta_f32_kernel, dim3((unsigned)p->f32_delta_tiles.size()), dim3(512), 0, stream, d.f32_delta_tiles,
-                d.perm, (const float*)x, ldx, (const float* const*)At, p->K, (const float* const*)Bt, (float*)y, ldy, beta, vec_rows(y, ldy));
+                d.perm, (const float*)x, ldx, (const float* const*)At, p->K, (const float* const*)Bt, (float*)y, ldy, beta, vec_rows(y, ldy, 4));
     return hipGetLastError();
 }

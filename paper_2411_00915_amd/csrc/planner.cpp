@@ -479,6 +479,43 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
     }
 }
 
+// Tiles of the expand that takes rows of any length: 16 tokens x 256 features; twice the tokens where that leaves more
+// than two workgroups per compute unit (microseconds of lora_delta, ranks 256, 32 / 16 tokens a tile: 64 tokens 18.7 /
+// 16.4, 300 tokens 29.3 / 29.6, 1000 tokens 54.8 / 76.5), more features where it leaves more than the chip holds at a
+// time; the heaviest first.
+static void build_rows_expand_tiles(lora_plan* p)
+{
+    if (p->N < 8 || (int64_t)p->N * LORA_MAX_RANK >= (1ll << 31)) return;   // the kernel fetches whole chunks, by 32-bit offsets
+    const int G = (int)p->group_adapter.size();
+    const int32_t kstep = p->dtype == LORA_F32 ? 16 : 32, terms = p->dtype == LORA_F32 ? 1 : 2;
+    auto token_tiles = [&](int32_t per) {
+        int64_t n = 0;
+        for (int g = 0; g < G; ++g) n += (p->group_offset[g + 1] - p->group_offset[g] + per - 1) / per;
+        return n;
+    };
+    const int64_t blocks = (p->N + 255) / 256;
+    const int32_t per = token_tiles(16) * blocks <= 512 ? 16 : 32;
+    const int32_t n_tile = 256 * (int32_t)std::max<int64_t>(1, std::min(blocks, token_tiles(per) * blocks / 1024));
+    for (int g = 0; g < G; ++g)
+        for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += per)
+            for (int32_t n0 = 0; n0 < p->N; n0 += n_tile) {
+                lora_tile t{};
+                t.adapter = p->group_adapter[g];
+                t.row0 = row;
+                t.nrows = std::min(per, p->group_offset[g + 1] - row);
+                t.c0 = n0;
+                t.cn = std::min(n_tile, p->N - n0);
+                t.reserved0 = p->rank[t.adapter];
+                const int32_t tb = t.nrows > 16 ? 2 : 1;
+                p->rows_expand_tb = std::max(p->rows_expand_tb, tb);
+                p->rows_expand_lds = std::max(p->rows_expand_lds, (t.reserved0 + kstep - 1) / kstep * tb * terms * 1024);
+                p->rows_expand_tiles.push_back(t);
+            }
+    auto weight = [](const lora_tile& t) { return (int64_t)t.cn * (t.reserved0 + 2 * t.nrows); };   // of Bt read, of y read and written
+    std::stable_sort(p->rows_expand_tiles.begin(), p->rows_expand_tiles.end(),
+                     [&](const lora_tile& x, const lora_tile& y) { return weight(x) > weight(y); });
+}
+
 // Tiles of the fp32 matrix-core kernels.
 static void build_f32_tiles(lora_plan* p)
 {
@@ -527,26 +564,13 @@ static void build_f32_tiles(lora_plan* p)
                         p->f32_shrink_tiles.push_back(t);
                     }
     }
-    // ---- expand: 64-token tiles for groups of 64 tokens or more; four wavefronts of 64 features, walked further where
-    // that leaves more workgroups than the chip holds at a time
-    int64_t token_tiles = 0, token_tiles16 = 0;
+    build_rows_expand_tiles(p);
+    int64_t token_tiles16 = 0;
     int32_t max_rank = 0;
-    auto per_tile = [&](int g) { return rows_of(g) >= 64 ? 64 : 16; };
     for (int g = 0; g < G; ++g) {
-        token_tiles += (rows_of(g) + per_tile(g) - 1) / per_tile(g);
         token_tiles16 += (rows_of(g) + 15) / 16;
         max_rank = std::max(max_rank, rank_of(g));
     }
-    const int64_t blocks = (p->N + 255) / 256;
-    const int32_t n_tile = 256 * (int32_t)std::max<int64_t>(1, std::min(blocks, token_tiles * blocks / 1024));
-    for (int g = 0; g < G; ++g)
-        for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += per_tile(g))
-            for (int32_t n0 = 0; n0 < p->N; n0 += n_tile) {
-                lora_tile t = tile_of(g, row, per_tile(g));
-                t.c0 = n0;
-                t.cn = std::min(n_tile, p->N - n0);
-                p->f32_expand_tiles.push_back(t);
-            }
     // ---- both in one launch: every 128 features read the tile's x and At again.  Microseconds per call, one launch /
     // two, 64 tokens on 8 adapters: rank 8, K = N = 1024 7.7 / 10.8, 2048 8.4 / 10.8; ranks to 64, 512 8.5 / 11.1,
     // 768 10.8 / 10.8, 1024 12.9 / 11.0
@@ -708,6 +732,10 @@ static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_p
             build_tiles(p, true);
             p->shrink_tiled_only = !p->shrink_tiles.empty();
         }
+        // ... and the expand on the kernel for rows of any length
+        if (p->family == LORA_VARIANT_GENERAL && !p->tiled_layout_ok && p->variant_req != LORA_VARIANT_GENERAL &&
+            p->dtype == LORA_BF16 && n_active > 0 && (p->variant_req == LORA_VARIANT_TILED || n_active >= p->tuning.tiled_min_tokens))
+            build_rows_expand_tiles(p);
         // (in mixture mode the removal's v must have the layout the GEMM's stages read, too)
         if (p->n_a < LORA_UNMERGE_BIT) build_gemm_tables(p, p->tiled_layout_ok && (!unmerge || unmerge->tiled_layout_ok));
     } catch (const std::bad_alloc&) {

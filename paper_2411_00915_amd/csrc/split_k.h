@@ -101,14 +101,21 @@ __device__ __forceinline__ void v_chunk(const float* v, const lora_vspec& vsp, i
     for (int i = 0; i < EPC; ++i) f[i] = 0.f;
     if (mine && j < r) {                                     // (rows are R floats apart, R % 8 == 0)
         const float* p = v + (int64_t)tok * vsp.R + j;
-        floatx4 part[EPC / 4];
+        floatx4 part[4][EPC / 4];
 #pragma unroll
-        for (int q = 0; q < EPC / 4; ++q) part[q] = *reinterpret_cast<const floatx4*>(p + 4 * q);
-        for (int s = 1; s < vsp.P; ++s)
+        for (int s = 0; s < 4; ++s)                          // all parts are requested before the first add
+            if (s < vsp.P) {
 #pragma unroll
-            for (int q = 0; q < EPC / 4; ++q) part[q] += *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
+                for (int q = 0; q < EPC / 4; ++q) part[s][q] = *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
+            }
 #pragma unroll
-        for (int i = 0; i < EPC; ++i) f[i] = j + i < r ? part[i >> 2][i & 3] : 0.f;      // past the rank: never written
+        for (int s = 1; s < 4; ++s)
+            if (s < vsp.P) {
+#pragma unroll
+                for (int q = 0; q < EPC / 4; ++q) part[0][q] += part[s][q];
+            }
+#pragma unroll
+        for (int i = 0; i < EPC; ++i) f[i] = j + i < r ? part[0][i >> 2][i & 3] : 0.f;   // past the rank: never written
     }
     if constexpr (sizeof(E) == 4) {
         hi.f = floatx4{f[0], f[1], f[2], f[3]};

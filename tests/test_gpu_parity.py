@@ -340,6 +340,52 @@ def test_fp32_adapter_kernels_tiles_and_remainders(T, K, N, ranks, max_seg):
         _check_f32_delta(w, ld_pad, shift)
 
 
+@pytest.mark.parametrize("T,N,ranks,max_seg", [
+    (1, 64, (1,), 1), (3, 64, (3, 256), 1), (20, 72, (1, 2, 5, 7), 3), (33, 204, (12, 100, 4), 9), (90, 1000, (9, 33, 65, 129), 30),
+    (150, 4100, (255, 31, 256), 60), (400, 520, (17, 63, 127, 8, 256), 200), (1200, 2056, (4, 100, 12, 256, 20, 48), 400)])
+def test_any_rank_expand(T, N, ranks, max_seg):
+    """The expand for ranks that are no multiple of 8 or above 128: rows of Bt that start and end inside 16-byte chunks,
+    the last rows of the matrix (whose chunks would reach past it), every number of token blocks, short feature ranges,
+    N off 8 and 64, and factors aligned to an element only; against the oracle and against the general kernel."""
+    w = wl.random_case(1800 + T + N, T, 128, N, 5, ranks, max_seg=max_seg, frac_none=0.15, scales=(0.5, 2.0, -1.0))
+    ldy = (N + 7) // 8 * 8 + 8
+    dl = device.to_device(w, DEV, with_w=False)
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    ref = oracle.expand(w.x, tok, ad, w.N, y_in=_y_in(w).astype(np.float64))
+    rank_tok = np.where(tok >= 0, w.adapter_rank[np.clip(tok, 0, None)], 0)
+    none = torch.from_numpy(rank_tok == 0).to(DEV)
+    y0 = torch.from_numpy(_y_in(w)).to(DEV, torch.bfloat16)
+    ptrs, keep = [], []
+    for i, b in enumerate(w.B):                       # Bt_a at 2, 4 .. bytes past a 16-byte boundary
+        buf = torch.empty(b.size + 8, dtype=torch.bfloat16, device=DEV)
+        buf[i % 7 + 1:i % 7 + 1 + b.size] = torch.from_numpy(np.ascontiguousarray(b.T).ravel()).to(DEV, torch.bfloat16)
+        keep.append(buf)
+        ptrs.append(buf.data_ptr() + 2 * (i % 7 + 1))
+    shifted = torch.tensor(ptrs, dtype=torch.int64, device=DEV)
+    out = {}
+    for variant in (B.LORA_VARIANT_AUTO, B.LORA_VARIANT_GENERAL):
+        plan = device.make_plan(w, variant)
+        _, v_bytes, _ = B.lora_plan_query(plan)
+        v = torch.full((v_bytes // 4,), float("nan"), dtype=torch.float32, device=DEV)
+        B.lora_shrink(plan, dl.x, w.K, dl.At_ptrs, v)
+        for beta in (1.0, 0.0):
+            for Bt in (dl.Bt_ptrs, shifted):
+                y = torch.full((w.T + 1, ldy), 7.0, dtype=torch.bfloat16, device=DEV)
+                y[:w.T, :w.N] = y0
+                B.lora_expand(plan, v, Bt, y, ldy, beta)
+                torch.cuda.synchronize()
+                assert bool((y[:w.T, w.N:] == 7.0).all()) and bool((y[w.T] == 7.0).all()), "written outside y"
+                assert torch.equal(y[:w.T, :w.N][none], y0[none]), "rows without adapter must stay bit-identical"
+                active = ~none.cpu().numpy()
+                got, want = _to_np(y)[:w.T, :w.N], ref - (0.0 if beta else _y_in(w).astype(np.float64))
+                _assert_close(got[active], want[active], BF16_TOL, f"variant {variant} beta {beta}")
+                out.setdefault(beta, y.clone())
+                # one rounding each of sums that differ by their order alone (and by v's split, 2^-16): a bf16 ulp apart at most
+                assert bool(((out[beta].float() - y.float()).abs() <= 2.0 ** -7 * y.float().abs() + 1e-4).all())
+        plan.destroy()
+
+
 @pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])
 def test_ring_gemm_shortest_rings_and_k_tails(K):
     """The 256 x 256 ring at its fewest stages (three of 64 k: prologue and drain only), one and two more, with and
