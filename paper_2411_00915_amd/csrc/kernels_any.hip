@@ -262,26 +262,19 @@ __global__ __launch_bounds__(256, TBMAX == 1 ? 3 : 2) void expand_rows_kernel(
     else expand_rows_tile<E, 1>(t, perm, v, vsp, Bt, y, ldy, N, beta, y_vec, expand_rows_lds);
 }
 
-// Shrink and expand in one launch for problems so small that launches are what they cost: a workgroup owns 16 tokens of
-// one adapter x 128 features and computes the v of its tokens itself (K split over its eight wavefronts, added up in
-// LDS), once per 128 features instead of once.  Bt and y are requested before that.  Ranks up to 64.
+// Problems so small that launches are what they cost: shrink and expand in one.  A workgroup owns 16 tokens of one adapter
+// x 128 features and computes the v of its tokens itself (K split over its eight wavefronts, added up in LDS), once per
+// 128 features instead of once.  Bt and y are requested before that.  Ranks up to 64.
 // 64 tokens, 256 -> 256, rank 8: kernels of 4.0 + 3.0 us -> one of 4.1, 11.4 -> 7.9 us per call.
-template <int JB>
-__device__ __forceinline__ void delta_f32_tile(
-    const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx, const float* __restrict__ At, int K,
-    const float* __restrict__ Bt, float* __restrict__ y, int64_t ldy, float beta, bool y_vec, floatx4* lds)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
-    const int r = t.reserved0, n_end = t.c0 + t.cn, tok = perm[t.row0 + min(m, t.nrows - 1)];
-    // Bt rows and y of this wavefront's 16 features
-    const int n0 = t.c0 + 16 * wave, n_lane = n0 + 4 * g;
-    float* const yp = y + (int64_t)tok * ldy + n_lane;
-    op16 bt[JB];
-    floatx4 yin = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < JB; ++s) bt[s] = row_chunk<float>(Bt + (int64_t)min(n0 + m, n_end - 1) * r, 16 * s + 4 * g, r);
-    if (beta != 0.f && y_vec && n_lane + 4 <= n_end) yin = *reinterpret_cast<const floatx4*>(yp);
+// Plans with such tiles run the shrink alone on the same arithmetic, so that both ways give the same bits.
 
+// s_a (x A_a) of the tile's 16 tokens: wavefront j < JB returns ranks 16 j + 4 g + i of token m (zero past the rank)
+template <int JB>
+__device__ __forceinline__ floatx4 small_v(const lora_tile& t, int tok, const float* __restrict__ x, int64_t ldx,
+                                           const float* __restrict__ At, int K, floatx4* lds)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), m = lane & 15, g = lane >> 4;
+    const int r = t.reserved0;
     constexpr int SUMS = JB <= 2 ? 8 : 4;
     floatx4 acc[JB][SUMS];
 #pragma unroll
@@ -322,20 +315,67 @@ __device__ __forceinline__ void delta_f32_tile(
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) lds[(wave * JB + jb) * 64 + lane] = folded(acc[jb]);
     __syncthreads();
+    floatx4 part[8];
+    if (wave >= JB) return floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) part[q] = lds[(q * JB + wave) * 64 + lane];
+#pragma unroll
+    for (int st = 4; st > 0; st >>= 1)
+#pragma unroll
+        for (int q = 0; q < st; ++q) part[q] += part[q + st];
+    const float s_a = __int_as_float(t.reserved1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) part[0][i] = 16 * wave + 4 * g + i < r ? s_a * part[0][i] : 0.f;
+    return part[0];
+}
+
+template <int JB>
+__device__ __forceinline__ void shrink_small_f32_tile(
+    const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx, const float* __restrict__ At, int K,
+    float* __restrict__ v, const lora_vspec& vsp, floatx4* lds)
+{
+    const int lane = threadIdx.x & 63, m = lane & 15, j = 16 * ((int)threadIdx.x >> 6) + 4 * (lane >> 4), r = t.reserved0;
+    const int tok = perm[t.row0 + min(m, t.nrows - 1)];
+    const floatx4 e = small_v<JB>(t, tok, x, ldx, At, K, lds);
+    if (m >= t.nrows) return;
+    float* const dst = v + (int64_t)tok * vsp.R + j;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (j + i < min(r, 16 * JB)) dst[i] = e[i];
+}
+
+// (tiles: 16 tokens x all ranks)
+__global__ __launch_bounds__(512) void shrink_small_f32_kernel(
+    const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx,
+    const float* const* __restrict__ At_ptrs, int K, float* __restrict__ v, lora_vspec vsp)
+{
+    __shared__ floatx4 lds[8 * 4 * 64];
+    const lora_tile t = tiles[blockIdx.x];
+    const float* At = At_ptrs[t.adapter];
+    if (t.reserved0 <= 16) shrink_small_f32_tile<1>(t, perm, x, ldx, At, K, v, vsp, lds);
+    else if (t.reserved0 <= 32) shrink_small_f32_tile<2>(t, perm, x, ldx, At, K, v, vsp, lds);
+    else shrink_small_f32_tile<4>(t, perm, x, ldx, At, K, v, vsp, lds);
+}
+
+template <int JB>
+__device__ __forceinline__ void delta_f32_tile(
+    const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx, const float* __restrict__ At, int K,
+    const float* __restrict__ Bt, float* __restrict__ y, int64_t ldy, float beta, bool y_vec, floatx4* lds)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
+    const int r = t.reserved0, n_end = t.c0 + t.cn, tok = perm[t.row0 + min(m, t.nrows - 1)];
+    // Bt rows and y of this wavefront's 16 features
+    const int n0 = t.c0 + 16 * wave, n_lane = n0 + 4 * g;
+    float* const yp = y + (int64_t)tok * ldy + n_lane;
+    op16 bt[JB];
+    floatx4 yin = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < JB; ++s) bt[s] = row_chunk<float>(Bt + (int64_t)min(n0 + m, n_end - 1) * r, 16 * s + 4 * g, r);
+    if (beta != 0.f && y_vec && n_lane + 4 <= n_end) yin = *reinterpret_cast<const floatx4*>(yp);
+
+    const floatx4 e = small_v<JB>(t, tok, x, ldx, At, K, lds);
     floatx4* const vt = lds + 8 * JB * 64;                   // v as operands: [JB][64 lanes]
-    if (wave < JB) {
-        floatx4 part[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) part[q] = lds[(q * JB + wave) * 64 + lane];
-#pragma unroll
-        for (int st = 4; st > 0; st >>= 1)
-#pragma unroll
-            for (int q = 0; q < st; ++q) part[q] += part[q + st];
-        const float s_a = __int_as_float(t.reserved1);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) part[0][i] = 16 * wave + 4 * g + i < r ? s_a * part[0][i] : 0.f;
-        vt[wave * 64 + lane] = part[0];
-    }
+    if (wave < JB) vt[wave * 64 + lane] = e;
     __syncthreads();
     floatx4 d[4];
 #pragma unroll
@@ -388,6 +428,7 @@ bool vec_rows(const void* y, int64_t ldy, int64_t es) { return ldy * es % 16 == 
 
 bool shrink_f32_supported(const lora_plan* p, const void* x, int64_t ldx)
 {
+    if (!p->f32_delta_tiles.empty()) return true;            // (no alignment demands)
     return !p->f32_shrink_tiles.empty() && ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 &&
            (int64_t)p->T * ldx * 4 < (1ll << 32);            // 32-bit byte offsets
 }
@@ -395,6 +436,11 @@ bool shrink_f32_supported(const lora_plan* p, const void* x, int64_t ldx)
 hipError_t launch_shrink_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
                              hipStream_t stream)
 {
+    if (!p->f32_delta_tiles.empty()) {
+        LORA_LAUNCH(LORA_K_SHRINK_F32, shrink_small_f32_kernel, dim3((unsigned)p->f32_shrink_tiles.size()), dim3(512), 0, stream,
+                    d.f32_shrink_tiles, d.perm, (const float*)x, ldx, (const float* const*)At, p->K, v, lora_vspec_of(p));
+        return hipGetLastError();
+    }
 #define SHRINK_F32(FB_, TB_, D_, SUMS_)                                                                                        \
     if (p->f32_shrink_fb == FB_ && p->f32_shrink_tb == TB_)                                                             \
         return p->K % 32 ? launch_shrink_shape<FB_, TB_, D_, SUMS_, true>(p, d, (const float*)x, ldx, At, v, stream)           \

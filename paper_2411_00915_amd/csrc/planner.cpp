@@ -483,7 +483,8 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
 // than two workgroups per compute unit (microseconds of lora_delta, ranks 256, 32 / 16 tokens a tile: 64 tokens 18.7 /
 // 16.4, 300 tokens 29.3 / 29.6, 1000 tokens 54.8 / 76.5), more features where it leaves more than the chip holds at a
 // time; the heaviest first.
-static void build_rows_expand_tiles(lora_plan* p)
+// per: tokens of a tile, 0: by that rule
+static void build_rows_expand_tiles(lora_plan* p, int32_t per)
 {
     if (p->N < 8 || (int64_t)p->N * LORA_MAX_RANK >= (1ll << 31)) return;   // the kernel fetches whole chunks, by 32-bit offsets
     const int G = (int)p->group_adapter.size();
@@ -494,7 +495,7 @@ static void build_rows_expand_tiles(lora_plan* p)
         return n;
     };
     const int64_t blocks = (p->N + 255) / 256;
-    const int32_t per = token_tiles(16) * blocks <= 512 ? 16 : 32;
+    if (per == 0) per = token_tiles(16) * blocks <= 512 ? 16 : 32;
     const int32_t n_tile = 256 * (int32_t)std::max<int64_t>(1, std::min(blocks, token_tiles(per) * blocks / 1024));
     for (int g = 0; g < G; ++g)
         for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += per)
@@ -532,6 +533,29 @@ static void build_f32_tiles(lora_plan* p)
         std::memcpy(&t.reserved1, &p->scale[t.adapter], sizeof(float));
         return t;
     };
+    // ---- shrink and expand in one launch, where every 128 features read the tile's x and At again.  Microseconds per
+    // call, one launch / two, 64 tokens on 8 adapters: rank 8, K = N = 1024 7.7 / 10.8, 2048 8.4 / 10.8; ranks to 64, 512
+    // 8.5 / 11.1, 768 10.8 / 10.8, 1024 12.9 / 11.0.  (The two steps alone then run on tiles of the same arithmetic.)
+    int64_t token_tiles16 = 0;
+    int32_t max_rank = 0;
+    for (int g = 0; g < G; ++g) {
+        token_tiles16 += (rows_of(g) + 15) / 16;
+        max_rank = std::max(max_rank, rank_of(g));
+    }
+    if (max_rank <= 64 && p->N >= 8 && (int64_t)(16 + max_rank) * p->K * 4 <= 192 * 1024 && token_tiles16 * ((p->N + 127) / 128) <= 512) {
+        for (int g = 0; g < G; ++g)
+            for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16) {
+                lora_tile t = tile_of(g, row, 16);
+                p->f32_shrink_tiles.push_back(t);
+                for (int32_t n0 = 0; n0 < p->N; n0 += 128) {
+                    t.c0 = n0;
+                    t.cn = std::min(128, p->N - n0);
+                    p->f32_delta_tiles.push_back(t);
+                }
+            }
+        build_rows_expand_tiles(p, 16);
+        return;
+    }
     // ---- shrink (16-byte chunks of rows: K % 4 == 0).  A compute unit loads 16 (fb + tb) rows per workgroup at about
     // 100 GB/s and multiplies at 256 flops/clk; the launch takes as long as the unit with the most workgroups; a K part
     // costs its consumers another read of v.
@@ -564,25 +588,7 @@ static void build_f32_tiles(lora_plan* p)
                         p->f32_shrink_tiles.push_back(t);
                     }
     }
-    build_rows_expand_tiles(p);
-    int64_t token_tiles16 = 0;
-    int32_t max_rank = 0;
-    for (int g = 0; g < G; ++g) {
-        token_tiles16 += (rows_of(g) + 15) / 16;
-        max_rank = std::max(max_rank, rank_of(g));
-    }
-    // ---- both in one launch: every 128 features read the tile's x and At again.  Microseconds per call, one launch /
-    // two, 64 tokens on 8 adapters: rank 8, K = N = 1024 7.7 / 10.8, 2048 8.4 / 10.8; ranks to 64, 512 8.5 / 11.1,
-    // 768 10.8 / 10.8, 1024 12.9 / 11.0
-    if (max_rank <= 64 && (int64_t)(16 + max_rank) * p->K * 4 <= 192 * 1024 && token_tiles16 * ((p->N + 127) / 128) <= 512)
-        for (int g = 0; g < G; ++g)
-            for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16)
-                for (int32_t n0 = 0; n0 < p->N; n0 += 128) {
-                    lora_tile t = tile_of(g, row, 16);
-                    t.c0 = n0;
-                    t.cn = std::min(128, p->N - n0);
-                    p->f32_delta_tiles.push_back(t);
-                }
+    build_rows_expand_tiles(p, 0);
 }
 
 // Tables of the fused GEMM: it walks the tokens in adapter-sorted order, so a tile of rows holds few
@@ -735,7 +741,7 @@ static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_p
         // ... and the expand on the kernel for rows of any length
         if (p->family == LORA_VARIANT_GENERAL && !p->tiled_layout_ok && p->variant_req != LORA_VARIANT_GENERAL &&
             p->dtype == LORA_BF16 && n_active > 0 && (p->variant_req == LORA_VARIANT_TILED || n_active >= p->tuning.tiled_min_tokens))
-            build_rows_expand_tiles(p);
+            build_rows_expand_tiles(p, 0);
         // (in mixture mode the removal's v must have the layout the GEMM's stages read, too)
         if (p->n_a < LORA_UNMERGE_BIT) build_gemm_tables(p, p->tiled_layout_ok && (!unmerge || unmerge->tiled_layout_ok));
     } catch (const std::bad_alloc&) {
