@@ -193,7 +193,7 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
                        (active >= tu.shrink_stream_min_tokens ||
                         (tu.shrink_stream_min_tokens < (1 << 30) && !small_tiles_only && (max_group >= 64 || active >= 128)));
     if (shrink_only) p->shrink_stream = false;
-    p->expand_stream = p->shrink_stream && p->N >= 64;
+    p->expand_stream = p->shrink_stream && p->N >= 64 && p->N % 8 == 0;       // it stores whole 16-byte pieces of a row
     p->expand_stream_ks = 1;
     p->expand_stream_lds = 0;
     int32_t stream_tokens = 128;

@@ -386,6 +386,12 @@ def test_any_rank_expand(T, N, ranks, max_seg):
         plan.destroy()
 
 
+def test_large_batch_expand_writes_nothing_past_an_n_off_eight():
+    """N no multiple of 8 under a padded leading dimension, a batch that would take the streaming kernels: the columns
+    between N and ldy stay as they are."""
+    run_delta_case(wl.random_case(1900, 1100, 1024, 204, 9, (16, 64), max_seg=200, frac_none=0.1, scales=(1.0, -0.5)), ld_pad=4)
+
+
 @pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])
 def test_ring_gemm_shortest_rings_and_k_tails(K):
     """The 256 x 256 ring at its fewest stages (three of 64 k: prologue and drain only), one and two more, with and
