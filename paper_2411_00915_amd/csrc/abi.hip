@@ -389,9 +389,14 @@ extern "C" lora_status lora_base_gemm(int32_t T, int32_t K, int32_t N, int32_t d
     if ((int64_t)(T + 15) / 16 > 65535) return LORA_ERR_UNSUPPORTED;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     hipError_t e;
-    if (gemm_small_wins(T, K, N, dtype) && gemm_small_supported(T, K, N, dtype, x, ldx, Wt, ldw, y, ldy))
+    const bool small_ok = gemm_small_supported(T, K, N, dtype, x, ldx, Wt, ldw, y, ldy);
+    const bool tiled_ok = gemm_tiled_supported(T, K, N, dtype, x, ldx, Wt, ldw, y, ldy);
+    const gemm_route_id route = tiled_ok ? gemm_route(T, K, N, ldx, ldw, true) : GEMM_SMALL;
+    if (route == GEMM_SMALL && small_ok)
         e = launch_gemm_small(T, K, N, dtype, x, ldx, Wt, ldw, y, ldy, nullptr, nullptr, nullptr, gemm_removal{}, nullptr, stream);
-    else if (gemm_tiled_supported(T, K, N, dtype, x, ldx, Wt, ldw, y, ldy))
+    else if (route == GEMM_MID_128 || route == GEMM_MID_192)
+        e = launch_gemm_mid(route, T, K, N, x, ldx, Wt, ldw, y, ldy, nullptr, nullptr, nullptr, gemm_removal{}, nullptr, stream);
+    else if (tiled_ok)
         e = launch_gemm_tiled(T, K, N, x, ldx, Wt, ldw, y, ldy, nullptr, nullptr, nullptr, nullptr, false, gemm_removal{}, nullptr, stream);
     else
         e = launch_gemm_general(T, K, N, dtype, x, ldx, Wt, ldw, y, ldy, nullptr, nullptr, nullptr, gemm_removal{}, nullptr, stream);
@@ -444,18 +449,20 @@ extern "C" lora_status lora_fused_forward(lora_plan* p, const void* x, int64_t l
     lora_plan_query(p, nullptr, &v_bytes, nullptr);
     char* vb = workspace ? static_cast<char*>(workspace) + align_up(v_bytes, 256) : nullptr;
     char* vb2 = vb ? vb + align_up((size_t)p->T * 2 * p->R * 2, 256) : nullptr;
-    // the GEMM of small batches (and of fp32) takes v as it is, with any rank; the others its split into two bf16 terms,
-    // which the streaming shrink writes itself, and 16-byte rows of Bt
+    // the GEMMs of small and medium batches (and of fp32) take v as it is, with any rank; the others its split into two
+    // bf16 terms, which the streaming shrink writes itself, and 16-byte rows of Bt
     const bool rows_ok = !has_delta || (int32_t)p->order.size() == p->T;
-    const bool tiled = rows_ok && gemm_tiled_supported(p->T, p->K, p->N, p->dtype, x, ldx, Wt, ldw, y, ldy) &&
-                       (!has_delta || !p->extra_ptr256.empty());
-    const bool small = rows_ok && !(p->dtype == LORA_F32 && p->variant_req == LORA_VARIANT_GENERAL) &&
-                       (!tiled || gemm_small_wins(p->T, p->K, p->N, p->dtype)) &&
+    const bool layout_ok = rows_ok && gemm_tiled_supported(p->T, p->K, p->N, p->dtype, x, ldx, Wt, ldw, y, ldy);
+    const bool stage_lists = !has_delta || !p->extra_ptr256.empty();
+    const gemm_route_id route = layout_ok ? gemm_route(p->T, p->K, p->N, ldx, ldw, stage_lists) : GEMM_SMALL;
+    const bool mid = route == GEMM_MID_128 || route == GEMM_MID_192, tiled = layout_ok && !mid && stage_lists;
+    const bool small = !mid && rows_ok && !(p->dtype == LORA_F32 && p->variant_req == LORA_VARIANT_GENERAL) && (!tiled || route == GEMM_SMALL) &&
                        gemm_small_supported(p->T, p->K, p->N, p->dtype, x, ldx, Wt, ldw, y, ldy);
+    char* const split = mid || small ? nullptr : vb;
     bool split_done = false, split2_done = false;
     if (has_delta) {
-        lora_status st = shrink_own(p, x, ldx, d_At_ptrs, v, hip_stream, small ? nullptr : vb, &split_done);
-        if (st == LORA_OK && u) st = shrink_own(p->unmerge, x, ldx, d_At_ptrs, removal_v(p, v), hip_stream, small ? nullptr : vb2, &split2_done);
+        lora_status st = shrink_own(p, x, ldx, d_At_ptrs, v, hip_stream, split, &split_done);
+        if (st == LORA_OK && u) st = shrink_own(p->unmerge, x, ldx, d_At_ptrs, removal_v(p, v), hip_stream, split ? vb2 : nullptr, &split2_done);
         if (st != LORA_OK) return st;
     }
     lora_status st = ensure_uploaded(p, stream);
@@ -467,6 +474,8 @@ extern "C" lora_status lora_fused_forward(lora_plan* p, const void* x, int64_t l
     hipError_t e;
     if (small)
         e = launch_gemm_small(p->T, p->K, p->N, p->dtype, x, ldx, Wt, ldw, y, ldy, p, &d, v, rm, d_Bt_ptrs, stream);
+    else if (mid)
+        e = launch_gemm_mid(route, p->T, p->K, p->N, x, ldx, Wt, ldw, y, ldy, p, &d, v, rm, d_Bt_ptrs, stream);
     else if (tiled)
         e = launch_gemm_tiled(p->T, p->K, p->N, x, ldx, Wt, ldw, y, ldy, p, &d, v, vb, split_done, rm, d_Bt_ptrs, stream);
     else

@@ -36,3 +36,21 @@ __device__ __forceinline__ float wave_sum(float v)
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
 }
+
+// Workgroups are dealt round-robin to the 8 XCDs; every XCD gets a contiguous run of tiles (so its L2 sees
+// neighbouring tiles).  Inside a run the tiles go in groups of GN feature tiles, token tile fastest over GN
+// feature tiles, so the 32 tiles an XCD works on at a time form an 8 x 4 block and share 8 x panels and 4 W
+// panels (instead of 32 x panels and one W panel) in its L2.
+__device__ __forceinline__ void tile_of_workgroup(int id, int tiles_n, int tiles_t, int& tile_n, int& tile_t)
+{
+    const int n_wg = tiles_n * tiles_t;
+    const int per = n_wg / 8, rem = n_wg % 8;
+    const int xcd = id & 7, q = id >> 3;
+    id = xcd * per + (xcd < rem ? xcd : rem) + q;       // XCD k owns per + (k < rem) tiles
+    constexpr int GN = 4;
+    const int group = id / (GN * tiles_t), first_n = group * GN;
+    const int group_n = min(tiles_n - first_n, GN);
+    const int in_group = id - group * (GN * tiles_t);
+    tile_n = first_n + in_group % group_n;
+    tile_t = in_group / group_n;
+}

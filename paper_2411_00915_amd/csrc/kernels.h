@@ -102,7 +102,13 @@ hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int
 // the contraction split over the wavefronts of a workgroup: small bf16 batches, every aligned fp32 batch
 bool gemm_small_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const void* x, int64_t ldx,
                           const void* Wt, int64_t ldw, const void* y, int64_t ldy);
-bool gemm_small_wins(int32_t T, int32_t K, int32_t N, int32_t dtype);       // the better kernel where the tiled ones could run, too
+double gemm_small_time(int32_t T, int32_t K, int32_t N);
+// which of them a bf16 problem that gemm_tiled_supported takes goes to; ring: whether launch_gemm_tiled may take it
+enum gemm_route_id { GEMM_SMALL = 1, GEMM_MID_128 = 2, GEMM_MID_192 = 3, GEMM_TILED = 4 };
+gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool ring);
+hipError_t launch_gemm_mid(gemm_route_id route, int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw,
+                           void* y, int64_t ldy, const lora_plan* p, const lora_dev_tables* d, const float* v,
+                           const gemm_removal& rm, const void* const* Bt, hipStream_t stream);
 hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, const void* x, int64_t ldx,
                              const void* Wt, int64_t ldw, void* y, int64_t ldy,
                              const lora_plan* p, const lora_dev_tables* d, const float* v, const gemm_removal& rm,

@@ -21,10 +21,11 @@
 //
 //   gemm_ring_kernel (further down): 256 x 256 tiles of large problems.  8 wavefronts, 16x16x32 MFMA,
 //     loads HBM -> LDS directly into a ring of quarter stages of 64 k.
-//   gemm_tiled_kernel: everything else.  Loads HBM -> registers -> LDS, double buffered (dynamic LDS,
+//   gemm_tiled_kernel: what neither that nor the kernels of smaller batches (kernels_gemm_small.hip,
+//     kernels_gemm_mid.hip; gemm_route chooses) take.  Loads HBM -> registers -> LDS, double buffered (dynamic LDS,
 //     2 x (BM + BT) x 128 bytes); workgroup tile = 4 wavefronts (2 x 2), each WB x WB MFMA blocks of 32 x 32:
-//     WB = 4: 256 features x 256 tokens x 64 k (large problems with K of at most 128)
-//     WB = 2: 128 x 128 x 64 (small problems, less padding waste)
+//     WB = 4: 256 features x 256 tokens x 64 k (large problems with K of at most 128, or past 32-bit offsets)
+//     WB = 2: 128 x 128 x 64 (operands past 32-bit offsets)
 //
 // Lane roles in v_mfma_f32_32x32x16_bf16 (D = A*B + C, A 32x16, B 16x32):
 //   lane l supplies A[row l%32][k 8*(l/32) .. +7], B[k 8*(l/32) .. +7][col l%32],
@@ -128,24 +129,6 @@ __device__ __forceinline__ const bf16_t* stage_v(const gemm_delta_args& da, int 
 {
     return (stage_id & STAGE_REMOVAL) ? da.vb2 + ((int64_t)token * 2 + part) * da.R2 + j
                                       : da.vb + ((int64_t)token * 2 + part) * da.R + j;
-}
-
-// Workgroups are dealt round-robin to the 8 XCDs; every XCD gets a contiguous run of tiles (so its L2 sees
-// neighbouring tiles).  Inside a run the tiles go in groups of GN feature tiles, token tile fastest over GN
-// feature tiles, so the 32 tiles an XCD works on at a time form an 8 x 4 block and share 8 x panels and 4 W
-// panels (instead of 32 x panels and one W panel) in its L2.
-__device__ __forceinline__ void tile_of_workgroup(int id, int tiles_n, int tiles_t, int& tile_n, int& tile_t)
-{
-    const int n_wg = tiles_n * tiles_t;
-    const int per = n_wg / 8, rem = n_wg % 8;
-    const int xcd = id & 7, q = id >> 3;
-    id = xcd * per + (xcd < rem ? xcd : rem) + q;       // XCD k owns per + (k < rem) tiles
-    constexpr int GN = 4;
-    const int group = id / (GN * tiles_t), first_n = group * GN;
-    const int group_n = min(tiles_n - first_n, GN);
-    const int in_group = id - group * (GN * tiles_t);
-    tile_n = first_n + in_group % group_n;
-    tile_t = in_group / group_n;
 }
 
 // KTAIL: K is not a multiple of 64, the last K stage's chunks beyond K are zero-filled
@@ -862,13 +845,13 @@ hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int
                              const lora_plan* p, const lora_dev_tables* d, const float* v, void* vb, bool split_done,
                              const gemm_removal& rm, const void* const* Bt, hipStream_t stream)
 {
-    // 256 x 256 tiles once there are enough of them to fill the 256 compute units
-    const bool big = (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192;
     const bool delta = p && (!p->perm.empty() || rm.plan);
     // the ring kernel: at least three stages of 64 k; rows of W and x addressed by 32-bit byte offsets, in its delta
-    // part also the split of v
-    const bool ring_ok = big && K > 2 * RK && (int64_t)N * ldw * 2 < (1ll << 32) && (int64_t)T * ldx * 2 < (1ll << 32) &&
+    // part also the split of v.  The register-staged kernel takes what it does not: 256 x 256 tiles once there are enough
+    // of them to fill the 256 compute units
+    const bool ring_ok = K > 2 * RK && (int64_t)N * ldw * 2 < (1ll << 32) && (int64_t)T * ldx * 2 < (1ll << 32) &&
                          (!delta || ((int64_t)T * p->R * 4 < (1ll << 32) && (!rm.plan || (int64_t)T * rm.plan->R * 4 < (1ll << 32))));
+    const bool big = (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192;
     gemm_delta_args da{};
     if (delta) {
         // the bf16 split of v, unless the shrink has written it already

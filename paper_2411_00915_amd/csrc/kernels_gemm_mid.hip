@@ -1,0 +1,389 @@
+// Base GEMM y = x W (+ adapter deltas) of batches of some hundred to a few thousand tokens (bf16): tiles of 128 tokens x
+// 128 or 192 features, for problems that are too few 256 x 256 tiles to give every compute unit one (or that leave a
+// last round nearly empty).
+//
+// A workgroup (8 wavefronts, two per SIMD) has the compute unit's LDS to itself: a ring of S stages of 64 k (whole
+// 128-byte lines of 64 WA rows of W and 128 rows of x), filled straight from memory S - 1 stages ahead.  A wavefront owns
+// 16 WA features x 64 tokens (WA x 4 blocks of v_mfma_f32_16x16x32_bf16).  What bounds the tile is LDS: per stage 8 (WA +
+// 4) 2 KB of operand reads and (64 WA + 128) 128 bytes of fills at 128 bytes/clk, 1216 clk for WA = 3 (1024 for WA = 2)
+// where the matrix cores need 768 (512).
+//
+// A phase is one k-step of 32: a memory part (the LDS reads of its operands; in a stage's second phase also the loads of
+// stage s + S - 1) and a matrix part (4 WA MFMAs), each closed by a barrier.  Wavefronts 4..7 run one part behind
+// wavefronts 0..3, with which they share the SIMDs, so one of the two reads LDS while the other issues MFMAs.
+//   RAW: stage s + 1 is first read in memory part 2 s + 2; every wavefront has waited for its own loads of it (vmcnt;
+//        loads return in order) at the end of its memory part 2 s + 1, one barrier earlier at least.
+//   WAR: stage s - 1, last read in memory part 2 s - 1, is overwritten by loads issued in memory part 2 s + 1; the LDS
+//        reads of the trailing wavefronts have returned before their MFMAs of phase 2 s - 1 issued, one barrier earlier.
+// The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
+//
+// DELTA: tokens in adapter-sorted order; after the K loop every wavefront adds the deltas of its own 64 tokens: per
+// adapter and 32 ranks, Bt_a[its features] and v (as the shrink left it, split into two bf16 terms) as MFMA operands.
+// (v read by every wavefront for itself, step by step behind Bt: lora_fused_forward of 1111 tokens in mixture mode, 5120 ->
+// 5120, 113 us; as operands in LDS, Bt a step ahead: 96.  It took 134 in the register-staged 128 x 128 tiles.)
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+
+#include "kernels.h"
+#include "launch.h"
+#include "split_k.h"
+
+namespace {
+
+constexpr int MID_TOKENS = 128;
+
+template <int WA, bool DELTA, bool KTAIL>
+__global__ __launch_bounds__(512) void gemm_mid_kernel(
+    int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
+    bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da)
+{
+    constexpr int BM = 64 * WA, NL = WA + 2, STAGE = (BM + MID_TOKENS) * 128, S = 163840 / STAGE, XOFF = BM * 128;
+    int tile_n, tile_t;
+    tile_of_workgroup(blockIdx.x, tiles_n, tiles_t, tile_n, tile_t);
+    const int n0 = tile_n * BM, t0 = tile_t * MID_TOKENS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
+    const int wn = (wave & 3) * 16 * WA, wt = (wave >> 2) * 64;      // the wavefront's origin in the tile
+
+    // Loads: 128 bytes of 8 rows each; lane l brings the chunk that belongs in slot l % 8 of row l / 8.  Of W's rows this
+    // wavefront brings 8 WA, of x's 16.  (The launcher keeps N ldw and T ldx below 2^32 bytes; rows past the end re-read
+    // the last one and are never stored.)  Chunk c of row r lies at slot c ^ f(r), f eight different values over the rows
+    // that eight consecutive lanes read.
+    uint32_t off[NL], cut[NL];                                       // cut (KTAIL): back from past K to the row's first chunk of the last stage
+    const int stages = (K + 63) / 64, last_k = (stages - 1) * 64;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const bool is_w = i < WA;
+        const int row = (is_w ? wave * WA + i : wave * 2 + i - WA) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ (is_w ? (row & 3) | (((row / (4 * WA)) & 1) << 2) : row & 7);
+        const int pos = min(t0 + row, T - 1);
+        const int64_t r = is_w ? min(n0 + row, N - 1) * ldw : (DELTA ? da.order[pos] : pos) * ldx;
+        off[i] = (uint32_t)(r * 2) + c * 16;
+        cut[i] = KTAIL && last_k + c * 8 >= K ? c * 16 : 0;
+    }
+    // DELTA: row wt + lane of the tile: its adapter (none: KEY_NONE), that adapter's rank and Bt, whether the removal applies;
+    // and row 16 wave + m, whose v this wavefront makes operands of
+    int my_own = KEY_NONE, my_rank = 0, v_tok = 0, v_rank = 0, v_removal = 0;
+    uint64_t my_bt = 0, removal = 0;
+    if constexpr (DELTA) {
+        const int pos = t0 + wt + lane, v_pos = t0 + 16 * wave + m;
+        const int key = pos < T ? da.row_key[da.order[pos]] : KEY_NONE;
+        v_tok = da.order[min(v_pos, T - 1)];
+        const int v_key = v_pos < T ? da.row_key[v_tok] : KEY_NONE, v_own = v_key & KEY_NONE;
+        my_own = key & KEY_NONE;
+        removal = __ballot((key & LORA_UNMERGE_BIT) != 0);
+        if (my_own != KEY_NONE) {
+            my_rank = da.rank[my_own];
+            my_bt = reinterpret_cast<uint64_t>(da.Bt_ptrs[my_own]);
+        }
+        v_rank = v_own != KEY_NONE ? da.rank[v_own] : 0;
+        v_removal = (v_key & LORA_UNMERGE_BIT) ? da.rank[da.merged] : 0;
+    }
+    const char *const wb = reinterpret_cast<const char*>(Wt), *const xb = reinterpret_cast<const char*>(x);
+    const uint32_t lds0 = lds_address(small_lds);
+    auto issue = [&](int st, uint32_t slot) {
+        const bool tail = KTAIL && st == stages - 1;
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            load16_to_lds((i < WA ? wb : xb) + (int64_t)st * 128, tail ? off[i] - cut[i] : off[i],
+                          lds0 + slot + (i < WA ? (wave * WA + i) * 1024 : XOFF + (wave * 2 + i - WA) * 1024));
+    };
+
+    floatx4 acc[WA][4];
+#pragma unroll
+    for (int a = 0; a < WA; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // operand addresses of k-step 0 (k-step 1: 64 bytes away by XOR); MFMA row 4 q + i of block a is feature 4 WA q + 4 a + i
+    const char* const lds_c = reinterpret_cast<const char*>(small_lds);
+    const uint32_t rw = (wn + 4 * WA * (m >> 2) + (m & 3)) * 128 + (g ^ (m & 7)) * 16;
+    const uint32_t rx = XOFF + (wt + m) * 128 + (g ^ (m & 7)) * 16;
+    op16 w[WA], xo[4];
+    auto read = [&](uint32_t slot, int ks, bool last) {
+#pragma unroll
+        for (int a = 0; a < WA; ++a) w[a].u = *reinterpret_cast<const u32x4*>(lds_c + (slot + (rw ^ (ks * 64))) + a * 512);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) xo[b].u = *reinterpret_cast<const u32x4*>(lds_c + (slot + (rx ^ (ks * 64))) + b * 2048);
+        if (KTAIL && last && last_k + (ks * 4 + g) * 8 >= K) {
+#pragma unroll
+            for (int a = 0; a < WA; ++a) w[a].u = u32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int b = 0; b < 4; ++b) xo[b].u = u32x4{0, 0, 0, 0};
+        }
+    };
+    auto multiply = [&]() {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int a = 0; a < WA; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[a].v, xo[b].v, acc[a][b], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+    };
+    auto barrier = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // waits until all but the youngest n stages' loads of this wavefront have landed
+    auto landed = [&](int n) {
+        if (S >= 5 && n >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
+        else if (n == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+        else if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    for (int st = 0; st < S - 1 && st < stages; ++st) issue(st, st * STAGE);
+    landed(min(S - 1, stages) - 1);
+    barrier();
+    if (wave >= 4) barrier();                                        // the trailing wavefronts: one part behind
+    auto next = [](uint32_t slot) { return slot + STAGE == S * STAGE ? 0u : slot + STAGE; };
+    uint32_t slot = 0, fill = (S - 1) * STAGE;
+    int s = 0;
+    for (; s < stages - (S - 1); ++s) {
+        read(slot, 0, false);
+        barrier();
+        multiply();
+        barrier();
+        read(slot, 1, false);
+        issue(s + S - 1, fill);
+        landed(S - 2);
+        barrier();
+        multiply();
+        barrier();
+        fill = slot;
+        slot = next(slot);
+    }
+    for (; s < stages; ++s) {                                        // nothing is left to be fetched
+        read(slot, 0, s == stages - 1);
+        barrier();
+        multiply();
+        barrier();
+        read(slot, 1, s == stages - 1);
+        landed(max(stages - 2 - s, 0));
+        barrier();
+        multiply();
+        barrier();
+        slot = next(slot);
+    }
+    if (wave < 4) barrier();
+
+    // ---- adapter deltas of this wavefront's 64 tokens: v of the tile's tokens as operands in LDS (a wavefront makes those
+    // of one block of 16 tokens), then (adapter, 32 ranks) by (adapter, 32 ranks), Bt one step ahead ----
+    if constexpr (DELTA) {
+        constexpr int VSTEPS = LORA_MAX_RANK / 32;
+        op16* const vops = reinterpret_cast<op16*>(small_lds);       // [8 token blocks][VSTEPS][hi, lo][64 lanes]
+        auto make_operands = [&](const float* v, const lora_vspec& vsp, int r) {
+            int rmax = r;
+#pragma unroll
+            for (int q = 1; q < 16; q *= 2) rmax = max(rmax, __shfl_xor(rmax, q));
+            const int steps = (__builtin_amdgcn_readfirstlane(rmax) + 31) / 32;
+            const float* const row = v + (int64_t)v_tok * vsp.R;
+            auto steps_of = [&](auto parts_t, int s0, int n) {       // n <= 2 steps, all loads first
+                constexpr int P = decltype(parts_t)::value;
+                floatx4 part[2][P][2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (q < n) {
+                        const float* p = row + min((s0 + q) * 32 + 8 * g, vsp.R - 8);
+#pragma unroll
+                        for (int i = 0; i < P; ++i)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) part[q][i][h] = *reinterpret_cast<const floatx4*>(p + i * vsp.part + 4 * h);
+                    }
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (q < n) {
+#pragma unroll
+                        for (int i = 1; i < P; ++i)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) part[q][0][h] += part[q][i][h];
+                        op16 hi, lo;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int j = (s0 + q) * 32 + 8 * g + 2 * i;                         // past the rank v holds nothing
+                            const float f0 = j < r ? part[q][0][i >> 1][2 * (i & 1)] : 0.f, f1 = j + 1 < r ? part[q][0][i >> 1][2 * (i & 1) + 1] : 0.f;
+                            const bf16_t h0 = f32_to_bf16(f0), h1 = f32_to_bf16(f1);
+                            hi.u[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+                            lo.u[i] = (uint32_t)f32_to_bf16(f0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(f1 - bf16_to_f32(h1)) << 16);
+                        }
+                        vops[((wave * VSTEPS + s0 + q) * 2) * 64 + lane] = hi;
+                        vops[((wave * VSTEPS + s0 + q) * 2 + 1) * 64 + lane] = lo;
+                    }
+            };
+            for (int s0 = 0; s0 < steps; s0 += 2) {
+                const int n = min(2, steps - s0);
+                if (vsp.P == 1) steps_of(std::integral_constant<int, 1>{}, s0, n);
+                else if (vsp.P == 2) steps_of(std::integral_constant<int, 2>{}, s0, n);
+                else steps_of(std::integral_constant<int, 4>{}, s0, n);
+            }
+        };
+        const int row = n0 + wn + 4 * WA * (m >> 2) + (m & 3);       // feature of MFMA row m in block 0
+        uint64_t todo, members;
+        int r, j0;
+        const bf16_t* Bt;
+        auto advance = [&]() {                                       // to the next (adapter, 32 ranks); everything wavefront-uniform
+            j0 += 32;
+            if (j0 < r) return true;
+            if (!todo) return false;
+            const int src = __ffsll((unsigned long long)todo) - 1, a = __builtin_amdgcn_readlane(my_own, src);
+            members = __ballot(my_own == a);
+            todo &= ~members;
+            r = __builtin_amdgcn_readlane(my_rank, src);
+            Bt = reinterpret_cast<const bf16_t*>((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_bt, src) |
+                                                 ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_bt >> 32), src) << 32));
+            j0 = 0;
+            return true;
+        };
+        auto load = [&](op16 (&bt)[WA]) {
+            const int j = j0 + 8 * g;
+            const bool whole = r % 8 == 0;
+#pragma unroll
+            for (int f = 0; f < WA; ++f) {
+                const bf16_t* p = Bt + (int64_t)min(row + 4 * f, N - 1) * r;
+                if (whole) bt[f].u = ldg_unaligned(p + (j < r ? j : 0));
+                else bt[f] = row_chunk<bf16_t>(p, j, r);
+            }
+        };
+        auto add = [&](op16 (&bt)[WA], uint64_t in, int j, int rank) {
+            if (j + 8 * g >= rank) {
+#pragma unroll
+                for (int f = 0; f < WA; ++f) bt[f].u = u32x4{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if (((in >> (16 * b)) & 0xffffull) == 0) continue;                 // wavefront-uniform
+                const op16* vp = vops + (((wt / 16 + b) * VSTEPS + j / 32) * 2) * 64 + lane;
+                op16 hi = vp[0], lo = vp[64];
+                if (!((in >> (16 * b + m)) & 1ull)) hi.u = lo.u = u32x4{0, 0, 0, 0};
+#pragma unroll
+                for (int f = 0; f < WA; ++f) {
+                    acc[f][b] = mma(bt[f], hi, acc[f][b], bf16_t{});
+                    acc[f][b] = mma(bt[f], lo, acc[f][b], bf16_t{});
+                }
+            }
+        };
+        auto run = [&]() {
+            op16 b0[WA], b1[WA];
+            bool more = advance();
+            if (more) load(b0);
+            while (more) {
+                uint64_t in = members;
+                int j = j0, rank = r;
+                more = advance();
+                if (more) load(b1);
+                add(b0, in, j, rank);
+                if (!more) break;
+                in = members; j = j0; rank = r;
+                more = advance();
+                if (more) load(b0);
+                add(b1, in, j, rank);
+            }
+        };
+        __syncthreads();
+        make_operands(da.v, da.vsp, v_rank);
+        __syncthreads();
+        todo = __ballot(my_own != KEY_NONE);
+        r = j0 = 0;
+        run();
+        if (da.merged >= 0) {                                        // mixture mode: the merged adapter, negated, where it applies
+            __syncthreads();
+            make_operands(da.v2, da.vsp2, v_removal);
+            __syncthreads();
+            todo = 0;
+            members = removal;
+            r = removal ? da.rank[da.merged] : 0;
+            Bt = reinterpret_cast<const bf16_t*>(da.Bt_ptrs[da.merged]);
+            j0 = -32;
+            run();
+        }
+    }
+
+    // ---- one rounding, store (rows go back to their tokens): a lane has 4 WA consecutive features of its tokens ----
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int pos = t0 + wt + 16 * b + m;
+        if (pos >= T) continue;
+        const int n = n0 + wn + 4 * WA * g;
+        bf16_t* yp = y + (int64_t)(DELTA ? da.order[pos] : pos) * ldy + n;
+#pragma unroll
+        for (int a = 0; a < WA; ++a) {
+            const floatx4 e = acc[a][b];
+            const uint2 o = {(uint32_t)f32_to_bf16(e[0]) | ((uint32_t)f32_to_bf16(e[1]) << 16),
+                             (uint32_t)f32_to_bf16(e[2]) | ((uint32_t)f32_to_bf16(e[3]) << 16)};
+            if (n + 4 * a + 4 <= N) {
+                *reinterpret_cast<uint2*>(yp + 4 * a) = o;           // (ldy % 8 == 0, y 16-byte aligned)
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (n + 4 * a + i < N) yp[4 * a + i] = f32_to_bf16(e[i]);
+            }
+        }
+    }
+}
+
+template <int WA, bool DELTA, bool KTAIL>
+hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
+                      const row_delta_args& da, hipStream_t stream)
+{
+    const int tiles_n = (N + 64 * WA - 1) / (64 * WA), tiles_t = (T + MID_TOKENS - 1) / MID_TOKENS;
+    constexpr size_t lds_bytes = 163840;
+    static std::atomic<bool> attr_set{false};                 // dynamic LDS above 64 KB has to be allowed once per kernel
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_mid_kernel<WA, DELTA, KTAIL>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    LORA_LAUNCH(DELTA ? LORA_K_GEMM_MID_DELTA : LORA_K_GEMM_MID, (gemm_mid_kernel<WA, DELTA, KTAIL>), dim3((unsigned)(tiles_n * tiles_t)),
+                dim3(512), lds_bytes, stream, T, K, N, (const bf16_t*)x, ldx, (const bf16_t*)Wt, ldw, (bf16_t*)y, ldy, tiles_n, tiles_t, da);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// The kernel a problem takes least time on.  Each is modelled as rounds of tiles over the 256 compute units; a round
+// takes a fixed part (first loads, last stores) and per stage of 64 k a time that grows from an almost idle chip to a
+// full one.  Measured, cold weights, microseconds (small / 128 / 192 / 256 x 256 ring / what it was before):
+//   4096 -> 4096,  256 tokens 16 / 31 / 35 / 64 / 16,  640: 42 / 33 / 36 / 63 / 45,  1280: 79 / 64 / 44 / 68 / 70,
+//                  1536: - / 67 / 79 / 69 / 75,  2048: - / 68 / 80 / 72 / 77,  3072: - / 111 / 128 / 85 / 85
+//   5120 -> 5120,  1024 tokens 91 / 79 / 53 / 84 / 85,  2048: - / 116 / 99 / 84 / 137
+//   4096 -> 11008, 256 tokens 42 / 34 / 38 / 65 / 42,  512: 80 / 64 / 45 / - / 71,  1024: 157 / 98 / 84 / 73 / 115
+//   5120 -> 13824, 320 tokens 108 / 87 / 66 / - / 86,  640: 180 / 128 / 116 / 95 / 138
+gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool ring)
+{
+    if ((int64_t)N * ldw * 2 >= (1ll << 32) || (int64_t)T * ldx * 2 >= (1ll << 32)) return GEMM_TILED;   // 32-bit byte offsets
+    const double stages = (K + 63) / 64;
+    auto rounds = [&](int32_t bm, int32_t bt, double fixed, double idle, double more, int power) {
+        const int64_t tiles = (int64_t)((N + bm - 1) / bm) * ((T + bt - 1) / bt);
+        const int64_t full = tiles / 256;
+        const double left = (double)(tiles % 256) / 256;
+        double us = full * (fixed + stages * (idle + more));
+        if (left > 0) us += fixed + stages * (idle + more * (power == 2 ? left * left : left));
+        return us;
+    };
+    const bool ring_ok = ring && K > 128;                     // (its fewest stages: three)
+    if (ring && !ring_ok && (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192) return GEMM_TILED;
+    gemm_route_id best = GEMM_SMALL;
+    double us = gemm_small_time(T, K, N);
+    auto take = [&](gemm_route_id id, double t) {
+        if (t < us) { us = t; best = id; }
+    };
+    take(GEMM_MID_128, rounds(128, 128, 2.5, 0.43, 0.10, 1));
+    take(GEMM_MID_192, rounds(192, 128, 2.5, 0.51, 0.19, 1));
+    if (ring_ok) take(GEMM_TILED, rounds(256, 256, 4.0, 0.95, 0.55, 2));
+    return best;
+}
+
+// p != nullptr: fold the adapter delta in; v holds the shrink's output
+hipError_t launch_gemm_mid(gemm_route_id route, int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw,
+                           void* y, int64_t ldy, const lora_plan* p, const lora_dev_tables* d, const float* v,
+                           const gemm_removal& rm, const void* const* Bt, hipStream_t stream)
+{
+    const bool delta = p && (!p->perm.empty() || rm.plan);
+    const row_delta_args da = delta ? row_deltas_of(p, d, v, rm, Bt) : row_delta_args{};
+#define MID_LAUNCH(WA_, D_, KT_) launch_one<WA_, D_, KT_>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
+#define MID_DISPATCH(D_, KT_) (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, KT_) : MID_LAUNCH(3, D_, KT_))
+    if (delta) return K % 64 ? MID_DISPATCH(true, true) : MID_DISPATCH(true, false);
+    return K % 64 ? MID_DISPATCH(false, true) : MID_DISPATCH(false, false);
+#undef MID_DISPATCH
+#undef MID_LAUNCH
+}

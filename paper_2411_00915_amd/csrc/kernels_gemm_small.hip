@@ -28,24 +28,10 @@
 
 namespace {
 
-struct small_delta_args {
-    const int32_t* order;          // [T] tokens sorted by adapter, then tokens without adapter
-    const int32_t* row_key;        // [T] adapter of the token (bits 0..22; all ones: none) | removal bit
-    const int32_t* rank;
-    const float* v;
-    lora_vspec vsp;
-    const void* const* Bt_ptrs;
-    const float* v2;               // mixture mode: the removal's v
-    lora_vspec vsp2;
-    int merged;                    // the merged adapter, or -1
-};
-
-constexpr int KEY_NONE = LORA_UNMERGE_BIT - 1;
-
 template <typename E, int FB, int TB, int D, bool DELTA, bool KTAIL>
 __global__ __launch_bounds__(512) void gemm_small_kernel(
     int T, int K, int N, const E* __restrict__ x, int64_t ldx, const E* __restrict__ Wt, int64_t ldw,
-    E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, small_delta_args da)
+    E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, row_delta_args da)
 {
     constexpr int WAVES = 8;
     // workgroups are dealt round-robin to the 8 XCDs; the token tiles of one feature tile follow each other on one
@@ -161,7 +147,7 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
 
 template <typename E, int FB, int TB, int D, bool DELTA, bool KTAIL>
 hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
-                      const small_delta_args& da, hipStream_t stream)
+                      const row_delta_args& da, hipStream_t stream)
 {
     const int tiles_n = (N + 16 * FB - 1) / (16 * FB), tiles_t = (T + 16 * TB - 1) / (16 * TB);
     constexpr size_t lds_bytes = (size_t)8 * D * (2 * FB + 2 * TB) * 1024;
@@ -209,7 +195,7 @@ small_tile choose_small_tile(int32_t T, int32_t K, int32_t N, int32_t dtype)
 
 template <typename E, bool DELTA, bool KTAIL>
 hipError_t launch_tile(const small_tile& t, int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw,
-                       void* y, int64_t ldy, const small_delta_args& da, hipStream_t stream)
+                       void* y, int64_t ldy, const row_delta_args& da, hipStream_t stream)
 {
 #define SMALL_TILE(FB_, TB_, D_) \
     if (t.fb == FB_ && t.tb == TB_) return launch_one<E, FB_, TB_, D_, DELTA, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream);
@@ -231,10 +217,12 @@ bool gemm_small_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const 
     return (int64_t)((N + 15) / 16 + 8) * ((T + 15) / 16) < (1ll << 31);
 }
 
-// (bf16: measured at 512 tokens, N = K = 4096: 35 us here, 104 us in 128 x 128 tiles; 1024 tokens: 69 and 100 us)
-bool gemm_small_wins(int32_t T, int32_t K, int32_t N, int32_t dtype)
+// microseconds (measured: 1.35 times the bound, and a start for every workgroup a compute unit gets)
+double gemm_small_time(int32_t T, int32_t K, int32_t N)
 {
-    return dtype == LORA_F32 || T <= 512;
+    const small_tile t = choose_small_tile(T, K, N, LORA_BF16);
+    const int64_t wgs = (int64_t)((N + 16 * t.fb - 1) / (16 * t.fb)) * ((T + 16 * t.tb - 1) / (16 * t.tb));
+    return 1.35e6 * small_cost(t, T, K, N, LORA_BF16) + 2.0 + (wgs + 255) / 256;
 }
 
 // p != nullptr: fold the adapter delta in; v holds the shrink's output.  rm: likewise for the removal of the merged
@@ -246,10 +234,7 @@ hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, con
     const bool delta = p && (!p->perm.empty() || rm.plan);
     const bool ktail = K % (dtype == LORA_F32 ? 32 : 64) != 0;
     const small_tile t = choose_small_tile(T, K, N, dtype);
-    small_delta_args da{};
-    if (delta)
-        da = small_delta_args{d->order, d->row_key, d->rank, v, lora_vspec_of(p), Bt, rm.v, rm.plan ? lora_vspec_of(rm.plan) : lora_vspec{0, 1, 0},
-                              rm.plan ? p->merged : -1};
+    const row_delta_args da = delta ? row_deltas_of(p, d, v, rm, Bt) : row_delta_args{};
 #define SMALL_LAUNCH(E_, D_, KT_) launch_tile<E_, D_, KT_>(t, T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
     if (dtype == LORA_F32) {
         if (delta) return ktail ? SMALL_LAUNCH(float, true, true) : SMALL_LAUNCH(float, true, false);

@@ -26,6 +26,8 @@ enum lora_kernel_id {
     LORA_K_CLEAR,
     LORA_K_GEMM_SMALL,
     LORA_K_GEMM_SMALL_DELTA,
+    LORA_K_GEMM_MID,
+    LORA_K_GEMM_MID_DELTA,
     LORA_K_SHRINK_F32,
     LORA_K_EXPAND_ROWS,
     LORA_K_DELTA_F32,

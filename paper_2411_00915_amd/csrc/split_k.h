@@ -129,6 +129,26 @@ __device__ __forceinline__ void v_chunk(const float* v, const lora_vspec& vsp, i
     }
 }
 
+// adapter deltas of kernels whose rows are the tokens in the plan's order
+struct row_delta_args {
+    const int32_t* order;          // [T] tokens sorted by adapter, then tokens without adapter
+    const int32_t* row_key;        // [T] adapter of the token (bits 0..22; all ones: none) | removal bit
+    const int32_t* rank;
+    const float* v;
+    lora_vspec vsp;
+    const void* const* Bt_ptrs;
+    const float* v2;               // mixture mode: the removal's v
+    lora_vspec vsp2;
+    int merged;                    // the merged adapter, or -1
+};
+constexpr int KEY_NONE = LORA_UNMERGE_BIT - 1;
+
+inline row_delta_args row_deltas_of(const lora_plan* p, const lora_dev_tables* d, const float* v, const gemm_removal& rm, const void* const* Bt)
+{
+    return row_delta_args{d->order, d->row_key, d->rank, v, lora_vspec_of(p), Bt, rm.v, rm.plan ? lora_vspec_of(rm.plan) : lora_vspec{0, 1, 0},
+                          rm.plan ? p->merged : -1};
+}
+
 extern __shared__ floatx4 small_lds[];
 
 // One wavefront's slice of K of a tile of 16 FB rows of W (features, or rank rows of an adapter) x 16 TB tokens.

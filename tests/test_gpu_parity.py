@@ -392,6 +392,20 @@ def test_large_batch_expand_writes_nothing_past_an_n_off_eight():
     run_delta_case(wl.random_case(1900, 1100, 1024, 204, 9, (16, 64), max_seg=200, frac_none=0.1, scales=(1.0, -0.5)), ld_pad=4)
 
 
+@pytest.mark.parametrize("T,K,N,ranks", [
+    (600, 8, 1000, (8, 16)), (513, 72, 4104, (8, 16, 64)), (640, 264, 2000, (24, 128)), (1025, 328, 1160, (1, 5, 20, 100, 256)),
+    (777, 136, 5000, (8, 64)), (777, 200, 5000, (16, 128)), (700, 264, 5000, (3, 8, 100)), (777, 1160, 5000, (8, 64, 128)),
+    (1111, 640, 5120, (16, 64)), (1300, 200, 776, (8, 12, 64)), (2049, 1032, 520, (64,)), (1400, 328, 1544, (16, 32))])
+def test_medium_batch_gemm_stages_and_remainders(T, K, N, ranks):
+    """The GEMM of 128-token tiles in both widths: fewer stages than its ring holds, as many, one more, K tails of one
+    chunk and of all but one; remainders of tokens and features; any rank; tokens without adapter, mixture mode."""
+    # (scales of one magnitude s: rounding W' costs u sqrt(1 + s_m^2) and y itself u sqrt(1 + s_own^2), so mixture mode
+    # stays within u sqrt(2) = 2.4e-3 of plain inference, under run_mixture_case's bound, only where s_m is not the larger)
+    w = wl.random_case(1600 + T + K, T, K, N, 12, ranks, max_seg=60, frac_none=0.15, scales=(1.0, -1.0))
+    run_forward_case(w, n_sample=256)
+    run_mixture_case(w, 2, n_sample=256)
+
+
 @pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])
 def test_ring_gemm_shortest_rings_and_k_tails(K):
     """The 256 x 256 ring at its fewest stages (three of 64 k: prologue and drain only), one and two more, with and
