@@ -47,7 +47,7 @@ KERNEL_KEYS = {"shrink_tiled_kernel": "shrink", "expand_tiled_kernel": "expand",
                "gemm_ring_kernel": "gemm", "gemm_ring_kernel<delta>": "gemm_delta",
                "gemm_small_kernel": "gemm", "gemm_small_kernel<delta>": "gemm_delta",
                "gemm_mid_kernel": "gemm", "gemm_mid_kernel<delta>": "gemm_delta",
-               "shrink_f32_kernel": "shrink", "expand_rows_kernel": "expand", "delta_f32_kernel": "delta",
+               "shrink_rows_kernel": "shrink", "expand_rows_kernel": "expand", "delta_f32_kernel": "delta",
                "shrink_general_kernel": "shrink", "expand_general_kernel": "expand", "gemm_general_kernel": "gemm"}
 WORKLOADS = ["cfg2", "cfg3", "cfg4", "cfg4d", "cfg5", "cfg5mlp"]
 

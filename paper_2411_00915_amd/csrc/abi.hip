@@ -64,7 +64,7 @@ bool misaligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p
 struct table_layout {
     size_t perm, token_adapter, row_key, rank, scale, shrink_tiles, expand_tiles, sync, sync_bytes, total;
     size_t order, extra_ptr128, extra128, extra_ptr256, extra256, zeros, shrink_rows, expand_rows;
-    size_t f32_shrink, rows_expand, f32_delta;
+    size_t rows_shrink, rows_expand, f32_delta;
 };
 
 table_layout layout_of(const lora_plan* p)
@@ -87,7 +87,7 @@ table_layout layout_of(const lora_plan* p)
     L.zeros = take(256);
     L.shrink_rows = take(p->shrink_rows.size() * sizeof(int32_t));
     L.expand_rows = take(p->expand_rows.size() * sizeof(int32_t));
-    L.f32_shrink = take(p->f32_shrink_tiles.size() * sizeof(lora_tile));
+    L.rows_shrink = take(p->rows_shrink_tiles.size() * sizeof(lora_tile));
     L.rows_expand = take(p->rows_expand_tiles.size() * sizeof(lora_tile));
     L.f32_delta = take(p->f32_delta_tiles.size() * sizeof(lora_tile));
     L.sync_bytes = p->fused_ok ? p->group_adapter.size() * 128 : 0;
@@ -153,7 +153,7 @@ lora_status ensure_uploaded(lora_plan* p, hipStream_t stream)
     std::memset(h + L.zeros, 0, 256);
     put(L.shrink_rows, p->shrink_rows.data(), p->shrink_rows.size() * sizeof(int32_t));
     put(L.expand_rows, p->expand_rows.data(), p->expand_rows.size() * sizeof(int32_t));
-    put(L.f32_shrink, p->f32_shrink_tiles.data(), p->f32_shrink_tiles.size() * sizeof(lora_tile));
+    put(L.rows_shrink, p->rows_shrink_tiles.data(), p->rows_shrink_tiles.size() * sizeof(lora_tile));
     put(L.rows_expand, p->rows_expand_tiles.data(), p->rows_expand_tiles.size() * sizeof(lora_tile));
     put(L.f32_delta, p->f32_delta_tiles.data(), p->f32_delta_tiles.size() * sizeof(lora_tile));
     std::memset(h + L.sync, 0, L.sync_bytes);                    // hand-off counters start at zero
@@ -184,7 +184,7 @@ lora_status ensure_uploaded(lora_plan* p, hipStream_t stream)
     p->d_extra256 = reinterpret_cast<int32_t*>(d + L.extra256);
     p->d_shrink_rows = reinterpret_cast<int32_t*>(d + L.shrink_rows);
     p->d_expand_rows = reinterpret_cast<int32_t*>(d + L.expand_rows);
-    p->d_f32_shrink_tiles = reinterpret_cast<lora_tile*>(d + L.f32_shrink);
+    p->d_rows_shrink_tiles = reinterpret_cast<lora_tile*>(d + L.rows_shrink);
     p->d_rows_expand_tiles = reinterpret_cast<lora_tile*>(d + L.rows_expand);
     p->d_f32_delta_tiles = reinterpret_cast<lora_tile*>(d + L.f32_delta);
     return LORA_OK;
@@ -194,7 +194,7 @@ lora_dev_tables tables_of(const lora_plan* p)
 {
     return lora_dev_tables{p->d_perm, p->d_token_adapter, p->d_row_key, p->d_rank, p->d_scale, p->d_shrink_tiles, p->d_expand_tiles,
                            p->d_sync, p->d_order, p->d_extra_ptr128, p->d_extra128, p->d_extra_ptr256, p->d_extra256, p->d_zeros,
-                           p->d_shrink_rows, p->d_expand_rows, p->d_f32_shrink_tiles, p->d_rows_expand_tiles, p->d_f32_delta_tiles};
+                           p->d_shrink_rows, p->d_expand_rows, p->d_rows_shrink_tiles, p->d_rows_expand_tiles, p->d_f32_delta_tiles};
 }
 
 size_t elem_bytes(int32_t dtype) { return dtype == LORA_F32 ? 4 : 2; }
@@ -251,12 +251,14 @@ static lora_status run_shrink(lora_plan* p, const lora_dev_tables& d, const void
                               hipStream_t stream, void* vb = nullptr, bool* split_done = nullptr)
 {
     hipError_t e;
-    if ((p->family == LORA_VARIANT_TILED || p->shrink_tiled_only) && tiled_call_ok(x, ldx))
+    if (p->shrink_tiled_only && tiled_call_ok(x, ldx) && shrink_rows_supported(p, x, ldx))
+        e = launch_shrink_rows(p, d, x, ldx, d_At_ptrs, v, stream);
+    else if ((p->family == LORA_VARIANT_TILED || p->shrink_tiled_only) && tiled_call_ok(x, ldx))
         e = launch_shrink_tiled(p, d, x, ldx, d_At_ptrs, v, stream, vb, split_done);
     else if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED)
         return LORA_ERR_UNSUPPORTED;                           // tiled kernels were demanded but x is not laid out for them
-    else if (shrink_f32_supported(p, x, ldx))
-        e = launch_shrink_f32(p, d, x, ldx, d_At_ptrs, v, stream);
+    else if (p->dtype == LORA_F32 && shrink_rows_supported(p, x, ldx))
+        e = launch_shrink_rows(p, d, x, ldx, d_At_ptrs, v, stream);
     else
         e = launch_shrink_general(p, d, x, ldx, d_At_ptrs, v, stream);
     return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
@@ -282,7 +284,7 @@ static lora_status shrink_own(lora_plan* p, const void* x, int64_t ldx,
                               const void* const* d_At_ptrs, float* v, void* hip_stream, void* vb = nullptr,
                               bool* split_done = nullptr)
 {
-    if (split_done) *split_done = false;
+    if (split_done) *split_done = false;                       // (only the streaming shrink writes it)
     if (p->perm.empty()) return LORA_OK;                       // no token has an adapter: nothing to do
     if (!x || !d_At_ptrs || !v) return LORA_ERR_INVALID_ARG;
     if (ldx < p->K) return LORA_ERR_INVALID_ARG;

@@ -34,7 +34,7 @@ struct lora_dev_tables {
     const void* zeros;             // 256 zero bytes
     const int32_t* shrink_rows;    // single-launch decode kernel: 16 tokens per shrink / expand tile, padded
     const int32_t* expand_rows;
-    const lora_tile* f32_shrink_tiles;
+    const lora_tile* rows_shrink_tiles;
     const lora_tile* rows_expand_tiles;
     const lora_tile* f32_delta_tiles;
 };
@@ -46,8 +46,8 @@ hipError_t launch_expand_general(const lora_plan* p, const lora_dev_tables& d, c
                                  const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream);
 
 // fp32 on the matrix cores (plans that have the tiles); the delta in one launch: v stays inside
-bool shrink_f32_supported(const lora_plan* p, const void* x, int64_t ldx);
-hipError_t launch_shrink_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
+bool shrink_rows_supported(const lora_plan* p, const void* x, int64_t ldx);
+hipError_t launch_shrink_rows(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
                              hipStream_t stream);
 hipError_t launch_delta_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At,
                             const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream);

@@ -1,10 +1,12 @@
-// fp32 shrink / expand on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 products and sums), and the expand of small
-// bf16 batches whose ranks the tuned kernels do not take.
+// Shrink and expand for fp32 (v_mfma_f32_16x16x4_f32: fp32 products and sums) and for bf16 batches whose ranks the tuned
+// kernels do not take.
 //
 // Shrink: tiles of 16 FB rank rows x 16 TB tokens of one adapter, the contraction split over the eight wavefronts of a
-// workgroup (split_k.h) and over up to four workgroups.  It is bound by reading At and x; one token per workgroup, as
-// the VALU kernel has it, reads At once per token.  256 tokens on 16 adapters of rank 8..64, K = 4096: 267 -> 5 us.
-// Expand: 16 tokens x 64 features per wavefront; bound by y and Bt.
+// workgroup (split_k.h) and over up to four workgroups.  It is bound by reading At and x.  fp32, 256 tokens on 16 adapters
+// of rank 8..64, K = 4096: 267 us (one token per workgroup, At read once per token) -> 5.  bf16, K = 4096, lora_shrink
+// against 64-byte pieces of 16 rows straight into registers: 256 tokens on 64 adapters of rank 2..256 11.7 -> 10.0 us, 1024
+// tokens 19.2 -> 12.4; lora_delta of 1000 single tokens on 24 adapters of rank 256 73 -> 52.
+// Expand: 16 or 32 tokens x 64 features per wavefront; bound by y and Bt.
 // Delta in one launch: see delta_f32_kernel.
 #include "kernels.h"
 #include "launch.h"
@@ -16,20 +18,20 @@
 namespace {
 
 // v[kpart][token][c0 ..] = s_a * (x A_a) over one K part
-template <int FB, int TB, int D, bool KTAIL, int SUMS>
-__global__ __launch_bounds__(512) void shrink_f32_kernel(
-    const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx,
-    const float* const* __restrict__ At_ptrs, int K, float* __restrict__ v, lora_vspec vsp)
+template <typename E, int FB, int TB, int D, bool KTAIL, int SUMS>
+__global__ __launch_bounds__(512) void shrink_rows_kernel(
+    const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const E* __restrict__ x, int64_t ldx,
+    const E* const* __restrict__ At_ptrs, int K, float* __restrict__ v, lora_vspec vsp)
 {
     const lora_tile t = tiles[blockIdx.x];
     const int kpart = (t.shape >> 8) & 15, kparts = (t.shape >> 12) & 15;
-    const float* At = At_ptrs[t.adapter] + (int64_t)t.c0 * K;
+    const E* At = At_ptrs[t.adapter] + (int64_t)t.c0 * K;
     const int32_t* rows = perm + t.row0;
     const float s_a = __int_as_float(t.reserved1);
     float* const vp = v + kpart * vsp.part + t.c0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    using slice = split_k<float, FB, TB, D, KTAIL, SUMS>;
+    using slice = split_k<E, FB, TB, D, KTAIL, SUMS>;
     const int units = (K + slice::KUNIT - 1) / slice::KUNIT;
     const int p_begin = units * kpart / kparts, p_end = units * (kpart + 1) / kparts;
     if ((reinterpret_cast<uintptr_t>(At) & 15) != 0) {       // whole lines to LDS need 16-byte rows: a wavefront per value
@@ -37,7 +39,7 @@ __global__ __launch_bounds__(512) void shrink_f32_kernel(
         for (int e = wave; e < t.nrows * t.cn; e += 8) {
             const int tok = rows[e / t.cn], j = e % t.cn;
             float acc = 0.f;
-            for (int k = k0 + lane; k < k1; k += 64) acc = fmaf(x[(int64_t)tok * ldx + k], At[(int64_t)j * K + k], acc);
+            for (int k = k0 + lane; k < k1; k += 64) acc = fmaf(elem<E>::load(x + (int64_t)tok * ldx + k), elem<E>::load(At + (int64_t)j * K + k), acc);
             acc = wave_sum(acc);
             if (lane == 0) vp[(int64_t)tok * vsp.R + j] = s_a * acc;
         }
@@ -402,23 +404,23 @@ __global__ __launch_bounds__(512) void delta_f32_kernel(
     else delta_f32_tile<4>(t, perm, x, ldx, At, K, Bt, y, ldy, beta, y_vec, lds);
 }
 
-template <int FB, int TB, int D, int SUMS, bool KTAIL>
-hipError_t launch_shrink_shape(const lora_plan* p, const lora_dev_tables& d, const float* x, int64_t ldx, const void* const* At, float* v,
+template <typename E, int FB, int TB, int D, int SUMS, bool KTAIL>
+hipError_t launch_shrink_shape(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
                                hipStream_t stream)
 {
-    constexpr size_t lds_bytes = (size_t)8 * split_k<float, FB, TB, D, KTAIL, SUMS>::LDS_BYTES;
+    constexpr size_t lds_bytes = (size_t)8 * split_k<E, FB, TB, D, KTAIL, SUMS>::LDS_BYTES;
     static_assert(D * (2 * FB + 2 * TB) >= FB * TB && lds_bytes <= 163840, "a wavefront's partial sums go where its operands were");
     if (lds_bytes > 65536) {                                  // dynamic LDS above 64 KB has to be allowed once per kernel
         static std::atomic<bool> attr_set{false};
         if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&shrink_f32_kernel<FB, TB, D, KTAIL, SUMS>),
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&shrink_rows_kernel<E, FB, TB, D, KTAIL, SUMS>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
             if (e != hipSuccess) return e;
             attr_set = true;
         }
     }
-    LORA_LAUNCH(LORA_K_SHRINK_F32, (shrink_f32_kernel<FB, TB, D, KTAIL, SUMS>), dim3((unsigned)p->f32_shrink_tiles.size()), dim3(512), lds_bytes,
-                stream, d.f32_shrink_tiles, d.perm, x, ldx, (const float* const*)At, p->K, v, lora_vspec_of(p));
+    LORA_LAUNCH(LORA_K_SHRINK_ROWS, (shrink_rows_kernel<E, FB, TB, D, KTAIL, SUMS>), dim3((unsigned)p->rows_shrink_tiles.size()), dim3(512),
+                lds_bytes, stream, d.rows_shrink_tiles, d.perm, (const E*)x, ldx, (const E* const*)At, p->K, v, lora_vspec_of(p));
     return hipGetLastError();
 }
 
@@ -426,27 +428,33 @@ bool vec_rows(const void* y, int64_t ldy, int64_t es) { return ldy * es % 16 == 
 
 }  // namespace
 
-bool shrink_f32_supported(const lora_plan* p, const void* x, int64_t ldx)
+bool shrink_rows_supported(const lora_plan* p, const void* x, int64_t ldx)
 {
     if (!p->f32_delta_tiles.empty()) return true;            // (no alignment demands)
-    return !p->f32_shrink_tiles.empty() && ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 &&
-           (int64_t)p->T * ldx * 4 < (1ll << 32);            // 32-bit byte offsets
+    const int64_t es = p->dtype == LORA_F32 ? 4 : 2;
+    return !p->rows_shrink_tiles.empty() && ldx * es % 16 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 &&
+           (int64_t)p->T * ldx * es < (1ll << 32);           // 32-bit byte offsets
 }
 
-hipError_t launch_shrink_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
-                             hipStream_t stream)
+hipError_t launch_shrink_rows(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
+                              hipStream_t stream)
 {
     if (!p->f32_delta_tiles.empty()) {
-        LORA_LAUNCH(LORA_K_SHRINK_F32, shrink_small_f32_kernel, dim3((unsigned)p->f32_shrink_tiles.size()), dim3(512), 0, stream,
-                    d.f32_shrink_tiles, d.perm, (const float*)x, ldx, (const float* const*)At, p->K, v, lora_vspec_of(p));
+        LORA_LAUNCH(LORA_K_SHRINK_ROWS, shrink_small_f32_kernel, dim3((unsigned)p->rows_shrink_tiles.size()), dim3(512), 0, stream,
+                    d.rows_shrink_tiles, d.perm, (const float*)x, ldx, (const float* const*)At, p->K, v, lora_vspec_of(p));
         return hipGetLastError();
     }
-#define SHRINK_F32(FB_, TB_, D_, SUMS_)                                                                                        \
-    if (p->f32_shrink_fb == FB_ && p->f32_shrink_tb == TB_)                                                             \
-        return p->K % 32 ? launch_shrink_shape<FB_, TB_, D_, SUMS_, true>(p, d, (const float*)x, ldx, At, v, stream)           \
-                         : launch_shrink_shape<FB_, TB_, D_, SUMS_, false>(p, d, (const float*)x, ldx, At, v, stream);
-    SHRINK_F32(1, 1, 2, 8) SHRINK_F32(2, 2, 1, 4)
-#undef SHRINK_F32
+#define SHRINK_ROWS(E_, FB_, TB_, D_, SUMS_)                                                                            \
+    if (p->rows_shrink_fb == FB_ && p->rows_shrink_tb == TB_)                                                           \
+        return p->K % (128 / (int)sizeof(E_)) ? launch_shrink_shape<E_, FB_, TB_, D_, SUMS_, true>(p, d, x, ldx, At, v, stream)  \
+                                              : launch_shrink_shape<E_, FB_, TB_, D_, SUMS_, false>(p, d, x, ldx, At, v, stream);
+    if (p->dtype == LORA_F32) {
+        SHRINK_ROWS(float, 1, 1, 2, 8) SHRINK_ROWS(float, 2, 2, 1, 4)
+    } else {
+        SHRINK_ROWS(bf16_t, 1, 1, 2, 1) SHRINK_ROWS(bf16_t, 2, 1, 1, 1) SHRINK_ROWS(bf16_t, 4, 1, 1, 1)
+        SHRINK_ROWS(bf16_t, 2, 2, 1, 1) SHRINK_ROWS(bf16_t, 4, 2, 1, 1) SHRINK_ROWS(bf16_t, 4, 4, 1, 1)
+    }
+#undef SHRINK_ROWS
     return hipErrorInvalidValue;
 }
 

@@ -28,7 +28,7 @@ enum lora_kernel_id {
     LORA_K_GEMM_SMALL_DELTA,
     LORA_K_GEMM_MID,
     LORA_K_GEMM_MID_DELTA,
-    LORA_K_SHRINK_F32,
+    LORA_K_SHRINK_ROWS,
     LORA_K_EXPAND_ROWS,
     LORA_K_DELTA_F32,
     LORA_K_PROBE_EMPTY,

@@ -69,13 +69,14 @@ struct lora_plan {
     bool tiled_layout_ok = false;  // K and all active ranks multiples of 8
     bool shrink_tiled_only = false; // family GENERAL, but the shrink has tiles and runs on the MFMA kernels (ranks that
                                     // only the expand cannot take: not multiples of 8, or above 128)
-    // fp32 on the matrix cores: tiles of the shrink (16 fb rank rows x 16 tb tokens x a K part) and, for the smallest
-    // problems, of shrink and expand in one launch (16 tokens x 128 features)
-    std::vector<lora_tile> f32_shrink_tiles, f32_delta_tiles;
+    // shrink tiles (16 fb rank rows x 16 tb tokens x a K part) of the kernel that splits K over its wavefronts: fp32, and
+    // bf16 where only the expand's ranks keep a batch off the tuned kernels; for the smallest fp32 problems (16 tokens x
+    // all ranks) next to those of shrink and expand in one launch (16 tokens x 128 features)
+    std::vector<lora_tile> rows_shrink_tiles, f32_delta_tiles;
     // expand tiles of the kernel that takes rows of any length: fp32, and bf16 with ranks the tuned kernels do not take
     std::vector<lora_tile> rows_expand_tiles;
     int32_t rows_expand_lds = 0, rows_expand_tb = 1;   // of its launch: dynamic LDS bytes, token blocks of the largest tile
-    int32_t f32_shrink_fb = 1, f32_shrink_tb = 1;
+    int32_t rows_shrink_fb = 1, rows_shrink_tb = 1;
     // fused GEMM: what a row is matched against an adapter stage by: its adapter in bits 0..22 (all ones: none),
     // bit 23 set when the removal of the merged adapter applies to it
     std::vector<int32_t> row_key;
@@ -105,7 +106,7 @@ struct lora_plan {
     int32_t* d_extra256 = nullptr;
     int32_t* d_shrink_rows = nullptr;
     int32_t* d_expand_rows = nullptr;
-    lora_tile* d_f32_shrink_tiles = nullptr;
+    lora_tile* d_rows_shrink_tiles = nullptr;
     lora_tile* d_rows_expand_tiles = nullptr;
     lora_tile* d_f32_delta_tiles = nullptr;
     void* d_zeros = nullptr;          // 256 zero bytes (source of masked chunks in the fused GEMM)

@@ -517,6 +517,57 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
                      [&](const lora_tile& x, const lora_tile& y) { return weight(x) > weight(y); });
 }
 
+// Tiles of the shrink that splits K over its wavefronts.  A compute unit loads 16 (fb + tb) rows per workgroup at about
+// 100 GB/s and multiplies at 256 (bf16: 4096) flops/clk; the launch takes as long as the unit with the most workgroups;
+// a K part costs the consumers of v another read of it.  parts: K parts, 0: by the same rule
+static void build_rows_shrink_tiles(lora_plan* p, int32_t parts)
+{
+    struct shape { int32_t fb, tb; };
+    static const shape f32_shapes[] = {{2, 2}, {1, 1}}, bf16_shapes[] = {{4, 4}, {4, 2}, {2, 2}, {4, 1}, {2, 1}, {1, 1}};
+    const bool f32 = p->dtype == LORA_F32;
+    const shape* shapes = f32 ? f32_shapes : bf16_shapes;
+    const int n_shapes = f32 ? 2 : 6, G = (int)p->group_adapter.size();
+    const int32_t kunit = f32 ? 32 : 64, units = (p->K + kunit - 1) / kunit;
+    double best = 0;
+    for (int i = 0; i < n_shapes; ++i) {
+        const int32_t fb = shapes[i].fb, tb = shapes[i].tb;
+        int64_t tiles = 0;
+        for (int g = 0; g < G; ++g)
+            tiles += (int64_t)((p->group_offset[g + 1] - p->group_offset[g] + 16 * tb - 1) / (16 * tb)) *
+                     ((p->rank[p->group_adapter[g]] + 16 * fb - 1) / (16 * fb));
+        for (int32_t P = parts ? parts : 1; P <= (parts ? parts : 4); P *= 2) {
+            // (lora_delta_static keeps v in an array of its own: parts must not be what outgrows it)
+            if (!parts && P > 1 && (units / P < 8 || (size_t)P * p->T * p->R * sizeof(float) > LORA_STATIC_V_BYTES)) break;
+            const double load = (fb + tb) * 16.0 * (f32 ? 4 : 2) / 100e9, math = fb * tb * 512.0 / (f32 ? 0.54e12 : 8.6e12);
+            const double cost = (double)((tiles * P + 255) / 256) * ((double)units * kunit / P * std::max(load, math) + 0.5e-6) + (P - 1) * 0.3e-6;
+            if (best == 0 || cost < best) {
+                best = cost;
+                p->rows_shrink_fb = fb;
+                p->rows_shrink_tb = tb;
+                p->v_parts = P;
+            }
+        }
+    }
+    const int32_t fb = p->rows_shrink_fb, tb = p->rows_shrink_tb;
+    for (int g = 0; g < G; ++g) {
+        const int32_t a = p->group_adapter[g], r = p->rank[a];
+        for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16 * tb)
+            for (int32_t j = 0; j < r; j += 16 * fb)
+                for (int32_t q = 0; q < p->v_parts; ++q) {
+                    lora_tile t{};
+                    t.adapter = a;
+                    t.row0 = row;
+                    t.nrows = std::min(16 * tb, p->group_offset[g + 1] - row);
+                    t.c0 = j;
+                    t.cn = std::min(16 * fb, r - j);
+                    t.shape = (q << 8) | (p->v_parts << 12);
+                    t.reserved0 = r;
+                    std::memcpy(&t.reserved1, &p->scale[a], sizeof(float));
+                    p->rows_shrink_tiles.push_back(t);
+                }
+    }
+}
+
 // Tiles of the fp32 matrix-core kernels.
 static void build_f32_tiles(lora_plan* p)
 {
@@ -546,7 +597,7 @@ static void build_f32_tiles(lora_plan* p)
         for (int g = 0; g < G; ++g)
             for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16) {
                 lora_tile t = tile_of(g, row, 16);
-                p->f32_shrink_tiles.push_back(t);
+                p->rows_shrink_tiles.push_back(t);
                 for (int32_t n0 = 0; n0 < p->N; n0 += 128) {
                     t.c0 = n0;
                     t.cn = std::min(128, p->N - n0);
@@ -556,38 +607,7 @@ static void build_f32_tiles(lora_plan* p)
         build_rows_expand_tiles(p, 16);
         return;
     }
-    // ---- shrink (16-byte chunks of rows: K % 4 == 0).  A compute unit loads 16 (fb + tb) rows per workgroup at about
-    // 100 GB/s and multiplies at 256 flops/clk; the launch takes as long as the unit with the most workgroups; a K part
-    // costs its consumers another read of v.
-    if (p->K % 4 == 0) {
-        const int32_t units = (p->K + 31) / 32;
-        double best = 0;
-        for (int32_t s : {2, 1})
-            for (int32_t P = 1; P <= 4; P *= 2) {
-                // (lora_delta_static keeps v in an array of its own: parts must not be what outgrows it)
-                if (P > 1 && (units / P < 8 || (size_t)P * p->T * p->R * sizeof(float) > LORA_STATIC_V_BYTES)) break;
-                int64_t tiles = 0;
-                for (int g = 0; g < G; ++g) tiles += (int64_t)((rows_of(g) + 16 * s - 1) / (16 * s)) * ((rank_of(g) + 16 * s - 1) / (16 * s));
-                const double load = 2.0 * s * 64 / 100e9, math = s * s * 512.0 / 0.54e12;
-                const double cost = (double)((tiles * P + 255) / 256) * units * 32 / P * std::max(load, math) + (P - 1) * 0.3e-6;
-                if (best == 0 || cost < best) {
-                    best = cost;
-                    p->f32_shrink_fb = p->f32_shrink_tb = s;
-                    p->v_parts = P;
-                }
-            }
-        const int32_t s = p->f32_shrink_fb;
-        for (int g = 0; g < G; ++g)
-            for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16 * s)
-                for (int32_t j = 0; j < rank_of(g); j += 16 * s)
-                    for (int32_t q = 0; q < p->v_parts; ++q) {
-                        lora_tile t = tile_of(g, row, 16 * s);
-                        t.c0 = j;
-                        t.cn = std::min(16 * s, rank_of(g) - j);
-                        t.shape = (q << 8) | (p->v_parts << 12);
-                        p->f32_shrink_tiles.push_back(t);
-                    }
-    }
+    if (p->K % 4 == 0) build_rows_shrink_tiles(p, 0);        // (16-byte chunks of rows)
     build_rows_expand_tiles(p, 0);
 }
 
@@ -737,6 +757,7 @@ static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_p
             (p->variant_req == LORA_VARIANT_TILED || n_active >= p->tuning.tiled_min_tokens)) {
             build_tiles(p, true);
             p->shrink_tiled_only = !p->shrink_tiles.empty();
+            if (p->shrink_tiled_only) build_rows_shrink_tiles(p, p->v_parts);
         }
         // ... and the expand on the kernel for rows of any length
         if (p->family == LORA_VARIANT_GENERAL && !p->tiled_layout_ok && p->variant_req != LORA_VARIANT_GENERAL &&

@@ -20,7 +20,7 @@ const char* kNames[LORA_K_COUNT] = {"shrink_general_kernel", "expand_general_ker
                                     "shrink_stream_kernel", "expand_stream_kernel", "merge_kernel",
                                     "gemm_ring_kernel", "gemm_ring_kernel<delta>", "clear_words_kernel",
                                     "gemm_small_kernel", "gemm_small_kernel<delta>", "gemm_mid_kernel",
-                                    "gemm_mid_kernel<delta>", "shrink_f32_kernel", "expand_rows_kernel",
+                                    "gemm_mid_kernel<delta>", "shrink_rows_kernel", "expand_rows_kernel",
                                     "delta_f32_kernel", "probe_empty_kernel", "probe_read_kernel", "probe_mfma_kernel"};
 long long* g_trace = nullptr;
 size_t g_trace_bytes = 0;

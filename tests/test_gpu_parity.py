@@ -340,6 +340,41 @@ def test_fp32_adapter_kernels_tiles_and_remainders(T, K, N, ranks, max_seg):
         _check_f32_delta(w, ld_pad, shift)
 
 
+@pytest.mark.parametrize("T,K,ranks,max_seg", [
+    (1, 8, (1,), 1), (3, 72, (2, 5), 1), (20, 1000, (10, 101, 256), 2), (50, 520, (1, 17, 33), 20), (64, 4096, (174, 2), 4),
+    (200, 648, (256, 130), 60), (300, 136, (9,), 300), (900, 2120, (4, 100, 255), 200), (3000, 264, (129, 256), 900)])
+def test_any_rank_shrink_tiles_and_remainders(T, K, ranks, max_seg):
+    """The shrink of bf16 batches with ranks off the tuned kernels: tiles from 16 x 16 to 64 x 64, K parts, fewer units of
+    64 k than wavefronts, K tails, remainders of tokens and ranks; factors on 16-byte boundaries and off them (the
+    kernel's own general path)."""
+    w = wl.random_case(2000 + T + K, T, K, 64, 7, ranks, max_seg=max_seg, frac_none=0.15, scales=(0.5, 2.0, -1.0))
+    dl = device.to_device(w, DEV, with_w=False)
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    ptrs, keep = [], []
+    for i, a in enumerate(w.A):
+        buf = torch.empty(a.size + 8, dtype=torch.bfloat16, device=DEV)
+        buf[i % 7 + 1:i % 7 + 1 + a.size] = torch.from_numpy(np.ascontiguousarray(a.T).ravel()).to(DEV, torch.bfloat16)
+        keep.append(buf)
+        ptrs.append(buf.data_ptr() + 2 * (i % 7 + 1))
+    plan = device.make_plan(w)
+    R, v_bytes, _ = B.lora_plan_query(plan)
+    P = B.lora_plan_export(plan)["v_parts"]
+    x = torch.full((w.T, w.K + 8), float("nan"), dtype=torch.bfloat16, device=DEV)
+    x[:, :w.K] = dl.x
+    valid = np.arange(R)[None, :] < np.where(tok >= 0, w.adapter_rank[np.clip(tok, 0, None)], 0)[:, None]
+    ref = oracle.shrink(w.x, tok, ad, apply_scale=True, R=R)
+    for At in (dl.At_ptrs, torch.tensor(ptrs, dtype=torch.int64, device=DEV)):
+        v = torch.full((P, w.T, R), float("nan"), dtype=torch.float32, device=DEV)
+        B.lora_shrink(plan, x, w.K + 8, At, v)
+        torch.cuda.synchronize()
+        v_np = v.double().sum(0).cpu().numpy()
+        assert np.array_equal(~np.isnan(v_np), valid), "v written outside [0, r_a), or not inside"
+        if valid.any():
+            _assert_close(np.where(valid, v_np, 0.0), ref, V_TOL, "v")
+    plan.destroy()
+
+
 @pytest.mark.parametrize("T,N,ranks,max_seg", [
     (1, 64, (1,), 1), (3, 64, (3, 256), 1), (20, 72, (1, 2, 5, 7), 3), (33, 204, (12, 100, 4), 9), (90, 1000, (9, 33, 65, 129), 30),
     (150, 4100, (255, 31, 256), 60), (400, 520, (17, 63, 127, 8, 256), 200), (1200, 2056, (4, 100, 12, 256, 20, 48), 400)])
