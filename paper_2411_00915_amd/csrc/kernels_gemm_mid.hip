@@ -252,12 +252,13 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
             for (int b = 0; b < 4; ++b) {
                 if (((in >> (16 * b)) & 0xffffull) == 0) continue;                 // wavefront-uniform
                 const op16* vp = vops + (((wt / 16 + b) * VSTEPS + j / 32) * 2) * 64 + lane;
-                op16 hi = vp[0], lo = vp[64];
-                if (!((in >> (16 * b + m)) & 1ull)) hi.u = lo.u = u32x4{0, 0, 0, 0};
+                const op16 hi = vp[0], lo = vp[64];
+                const bool mine = (in >> (16 * b + m)) & 1ull;       // (a product with zeros would carry the adapter's infinities over)
 #pragma unroll
                 for (int f = 0; f < WA; ++f) {
-                    acc[f][b] = mma(bt[f], hi, acc[f][b], bf16_t{});
-                    acc[f][b] = mma(bt[f], lo, acc[f][b], bf16_t{});
+                    const floatx4 e = mma(bt[f], lo, mma(bt[f], hi, acc[f][b], bf16_t{}), bf16_t{});
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[f][b][i] = mine ? e[i] : acc[f][b][i];
                 }
             }
         };

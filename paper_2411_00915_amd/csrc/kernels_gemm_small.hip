@@ -86,8 +86,11 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
                     if (((members >> (16 * b)) & 0xffffull) == 0) continue;       // wavefront-uniform
 #pragma unroll
                     for (int f = 0; f < FB; ++f) {
-                        acc[f][b][0] = mma(bt[f], hi[b], acc[f][b][0], E{});
-                        if constexpr (ES == 2) acc[f][b][0] = mma(bt[f], lo[b], acc[f][b][0], E{});
+                        floatx4 e = mma(bt[f], hi[b], acc[f][b][0], E{});
+                        if constexpr (ES == 2) e = mma(bt[f], lo[b], e, E{});
+                        // (a product with zeros would carry the adapter's infinities over to other tokens)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[f][b][0][i] = (members >> (16 * b + m)) & 1ull ? e[i] : acc[f][b][0][i];
                     }
                 }
             }

@@ -427,6 +427,36 @@ def test_large_batch_expand_writes_nothing_past_an_n_off_eight():
     run_delta_case(wl.random_case(1900, 1100, 1024, 204, 9, (16, 64), max_seg=200, frac_none=0.1, scales=(1.0, -0.5)), ld_pad=4)
 
 
+@pytest.mark.parametrize("T,dtype,ranks", [(90, "f32", (8, 20)), (90, "bf16", (8, 16)), (90, "bf16", (5, 100)), (700, "bf16", (8, 16)), (700, "bf16", (5, 100))])
+def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, dtype, ranks):
+    """One adapter's factors hold infinities and NaN: the tokens of all other adapters, and of none, come out bit for bit
+    as with that adapter's factors finite (small and medium GEMM, fp32 and any rank)."""
+    w = wl.random_case(2300 + T + ranks[0], T, 264, 520 if T < 512 else 2000, 6, ranks, dtype=dtype, max_seg=7, frac_none=0.2)
+    dl = device.to_device(w, DEV, with_w=True)
+    tdt = device.torch_dtype(w)
+    plan = device.make_plan(w)
+    ws = torch.empty(max(B.lora_plan_query(plan)[2], 256), dtype=torch.uint8, device=DEV)
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    bad = int(tok[tok >= 0][0])
+    out, keep = [], []
+    for fill in (None, float("inf"), float("nan")):
+        Bt = dl.Bt_ptrs
+        if fill is not None:
+            keep.append(torch.full((w.N, int(w.adapter_rank[bad])), fill, dtype=tdt, device=DEV))
+            Bt = Bt.clone()
+            Bt[bad] = keep[-1].data_ptr()
+        y = torch.empty((w.T, w.N), dtype=tdt, device=DEV)
+        B.lora_fused_forward(plan, dl.x, w.K, dl.Wt, w.K, dl.At_ptrs, Bt, y, w.N, ws, ws.numel())
+        torch.cuda.synchronize()
+        out.append(y)
+    others = torch.from_numpy(tok != bad).to(DEV)
+    assert bool(others.any()) and bool(torch.isfinite(out[0]).all())
+    for y in out[1:]:
+        assert torch.equal(y[others], out[0][others])
+        assert not bool(torch.isfinite(y[~others]).any())
+    plan.destroy()
+
+
 @pytest.mark.parametrize("T,K,N,ranks", [
     (600, 8, 1000, (8, 16)), (513, 72, 4104, (8, 16, 64)), (640, 264, 2000, (24, 128)), (1025, 328, 1160, (1, 5, 20, 100, 256)),
     (777, 136, 5000, (8, 64)), (777, 200, 5000, (16, 128)), (700, 264, 5000, (3, 8, 100)), (777, 1160, 5000, (8, 64, 128)),
