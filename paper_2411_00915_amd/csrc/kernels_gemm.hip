@@ -474,8 +474,10 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(
 // one of the two wavefronts of a SIMD issues its 16 MFMAs back to back, the other does its memory part.
 //   RAW: granule k + 2 is read in memory part k + 1; every wavefront has waited for its own loads of it (vmcnt; loads
 //        return in order) at the end of its memory part k, one barrier earlier at least.
-//   WAR: granule g, read in memory part g - 1, is overwritten by loads issued in memory part g + 1; the LDS reads of
-//        the trailing wavefronts have returned before their MFMAs of phase g - 1 issued, one barrier earlier.
+//   WAR: granule g, read in memory part g - 1, is overwritten by loads issued in memory part g + 1, when the trailing
+//        wavefronts are in matrix part g; every wavefront's LDS reads of it have returned at the end of its matrix part
+//        g - 1, one barrier earlier: its MFMAs use XL, XH and WH in that part; WL, first used in the part after it, is
+//        waited for (by then its reads are a matrix part old and long back: the wait costs nothing).
 // The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
 //
 // Measured against the version with stages of 32 k (same process, cold operands, bf16, T x K x N): 16384 x 5120 x 5120
@@ -625,6 +627,7 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
 #define RING_BARRIER() do { __builtin_amdgcn_sched_barrier(0); asm volatile("s_barrier" ::: "memory"); __builtin_amdgcn_sched_barrier(0); } while (0)
 #define RING_WAIT_(N_) asm volatile("s_waitcnt vmcnt(" #N_ ")" ::: "memory")
 #define RING_WAIT(N_) RING_WAIT_(N_)
+#define RING_READS_RETURNED() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
 
     // prologue: granules 0..8 on their way, granule 0 (WL of stage 0) into registers, granule 1 landed
 #pragma unroll
@@ -633,6 +636,7 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
     RING_BARRIER();
     read_w(wl, 0);
     RING_WAIT(14);
+    RING_READS_RETURNED();
     RING_BARRIER();
     if (wave >= 4) RING_BARRIER();                                   // the trailing wavefronts: one part behind
 
@@ -670,6 +674,7 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
         RING_WAIT(W3);                                                                                                 \
         RING_BARRIER();                                                                                                \
         mma(wh, xl, 4, 0);                                                                                             \
+        RING_READS_RETURNED();                                                                                         \
         RING_BARRIER();                                                                                                \
         q = q4;                                                                                                        \
         ++s;                                                                                                           \
@@ -684,6 +689,7 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
 #undef RING_BARRIER
 #undef RING_WAIT
 #undef RING_WAIT_
+#undef RING_READS_RETURNED
 
     // ---- adapter deltas of this wavefront's 64 tokens -----------------------
     if constexpr (DELTA) {
