@@ -34,7 +34,8 @@ __global__ __launch_bounds__(512) void shrink_rows_kernel(
     using slice = split_k<E, FB, TB, D, KTAIL, SUMS>;
     const int units = (K + slice::KUNIT - 1) / slice::KUNIT;
     const int p_begin = units * kpart / kparts, p_end = units * (kpart + 1) / kparts;
-    if ((reinterpret_cast<uintptr_t>(At) & 15) != 0) {       // whole lines to LDS need 16-byte rows: a wavefront per value
+    // whole lines to LDS need 16-byte rows, and 32-bit offsets a tile of less than 4 GB: else a wavefront per value
+    if ((reinterpret_cast<uintptr_t>(At) & 15) != 0 || (int64_t)t.cn * K * (int64_t)sizeof(E) > (1ll << 32)) {
         const int k0 = p_begin * slice::KUNIT, k1 = min(K, p_end * slice::KUNIT);
         for (int e = wave; e < t.nrows * t.cn; e += 8) {
             const int tok = rows[e / t.cn], j = e % t.cn;

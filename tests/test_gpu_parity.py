@@ -375,6 +375,26 @@ def test_any_rank_shrink_tiles_and_remainders(T, K, ranks, max_seg):
     plan.destroy()
 
 
+@pytest.mark.parametrize("dtype,rank,K", [("f32", 16, 71582792), ("bf16", 17, 143165584)])
+def test_shrink_of_factors_past_four_gigabytes(dtype, rank, K):
+    """The last row of an adapter's At starts past 2^32 bytes behind its first.  Row j of At is one at 100 + j places
+    (sums of ones are exact) and zero elsewhere, so a row taken from another place of the matrix shows."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    At = torch.zeros((rank, K), dtype=tdt, device=DEV)
+    assert (rank - 1) * K * At.element_size() > 2 ** 32
+    for j in range(rank):
+        At[j, 1000 * j:1000 * j + 100 + j] = 1.0
+    x = torch.ones((1, K), dtype=tdt, device=DEV)
+    plan = B.lora_plan(1, np.array([0, 1], np.int32), np.array([0], np.int32), np.array([rank], np.int32), np.array([2.0], np.float32),
+                       K, 8, B.LORA_F32 if dtype == "f32" else B.LORA_BF16)
+    R, v_bytes, _ = B.lora_plan_query(plan)
+    v = torch.zeros((v_bytes // (4 * R), R), dtype=torch.float32, device=DEV)
+    B.lora_shrink(plan, x, K, torch.tensor([At.data_ptr()], dtype=torch.int64, device=DEV), v)
+    torch.cuda.synchronize()
+    assert v.sum(0)[:rank].tolist() == [2.0 * (100 + j) for j in range(rank)]
+    plan.destroy()
+
+
 @pytest.mark.parametrize("T,N,ranks,max_seg", [
     (1, 64, (1,), 1), (3, 64, (3, 256), 1), (20, 72, (1, 2, 5, 7), 3), (33, 204, (12, 100, 4), 9), (90, 1000, (9, 33, 65, 129), 30),
     (150, 4100, (255, 31, 256), 60), (400, 520, (17, 63, 127, 8, 256), 200), (1200, 2056, (4, 100, 12, 256, 20, 48), 400)])
