@@ -359,7 +359,7 @@ static lora_status delta_own(lora_plan* p, const void* x, int64_t ldx,
         hipStream_t stream = static_cast<hipStream_t>(hip_stream);
         const lora_status st = ensure_uploaded(p, stream);
         if (st != LORA_OK) return st;
-        return launch_delta_f32(p, tables_of(p), x, ldx, d_At_ptrs, d_Bt_ptrs, y, ldy, beta, stream) == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+        return launch_delta_f32(p, tables_of(p), x, ldx, d_At_ptrs, d_Bt_ptrs, v, y, ldy, beta, stream) == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
     }
     lora_status st = shrink_own(p, x, ldx, d_At_ptrs, v, hip_stream);
     if (st != LORA_OK) return st;
@@ -539,7 +539,7 @@ extern "C" lora_status lora_delta_static(lora_plan* p, const void* x, int64_t ld
         misaligned(d_Bt_ptrs, 8))
         return LORA_ERR_INVALID_ARG;
     if (!p->f32_delta_tiles.empty())
-        return launch_delta_f32(p, d, x, ldx, d_At_ptrs, d_Bt_ptrs, y, ldy, beta, stream) == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+        return launch_delta_f32(p, d, x, ldx, d_At_ptrs, d_Bt_ptrs, nullptr, y, ldy, beta, stream) == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
     if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED && !tiled_call_ok(y, ldy)) return LORA_ERR_UNSUPPORTED;
     st = run_shrink(p, d, x, ldx, d_At_ptrs, v, stream);
     return st == LORA_OK ? run_expand(p, d, v, d_Bt_ptrs, y, ldy, beta, stream) : st;

@@ -45,13 +45,14 @@ hipError_t launch_shrink_general(const lora_plan* p, const lora_dev_tables& d, c
 hipError_t launch_expand_general(const lora_plan* p, const lora_dev_tables& d, const float* v,
                                  const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream);
 
-// fp32 on the matrix cores (plans that have the tiles); the delta in one launch: v stays inside
+// any rank on the matrix cores (plans that have the tiles): fp32, and bf16 with ranks the tuned kernels do not take
 bool shrink_rows_supported(const lora_plan* p, const void* x, int64_t ldx);
 hipError_t launch_shrink_rows(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At, float* v,
                              hipStream_t stream);
+// shrink and expand of small fp32 plans in one launch; v may be null
 hipError_t launch_delta_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At,
-                            const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream);
-// fp32 or bf16, any rank, no alignment demands
+                            const void* const* Bt, float* v, void* y, int64_t ldy, float beta, hipStream_t stream);
+// (no alignment demands)
 hipError_t launch_expand_rows(const lora_plan* p, const lora_dev_tables& d, const float* v, const void* const* Bt, void* y, int64_t ldy,
                               float beta, hipStream_t stream);
 

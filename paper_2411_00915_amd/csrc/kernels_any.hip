@@ -332,19 +332,25 @@ __device__ __forceinline__ floatx4 small_v(const lora_tile& t, int tok, const fl
     return part[0];
 }
 
+// ... to the rows of v
+template <int JB>
+__device__ __forceinline__ void store_small_v(const lora_tile& t, int tok, floatx4 e, float* __restrict__ v, const lora_vspec& vsp)
+{
+    const int lane = threadIdx.x & 63, j = 16 * ((int)threadIdx.x >> 6) + 4 * (lane >> 4);
+    if ((lane & 15) >= t.nrows) return;
+    float* const dst = v + (int64_t)tok * vsp.R + j;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (j + i < min(t.reserved0, 16 * JB)) dst[i] = e[i];
+}
+
 template <int JB>
 __device__ __forceinline__ void shrink_small_f32_tile(
     const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx, const float* __restrict__ At, int K,
     float* __restrict__ v, const lora_vspec& vsp, floatx4* lds)
 {
-    const int lane = threadIdx.x & 63, m = lane & 15, j = 16 * ((int)threadIdx.x >> 6) + 4 * (lane >> 4), r = t.reserved0;
-    const int tok = perm[t.row0 + min(m, t.nrows - 1)];
-    const floatx4 e = small_v<JB>(t, tok, x, ldx, At, K, lds);
-    if (m >= t.nrows) return;
-    float* const dst = v + (int64_t)tok * vsp.R + j;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (j + i < min(r, 16 * JB)) dst[i] = e[i];
+    const int tok = perm[t.row0 + min((int)threadIdx.x & 15, t.nrows - 1)];
+    store_small_v<JB>(t, tok, small_v<JB>(t, tok, x, ldx, At, K, lds), v, vsp);
 }
 
 // (tiles: 16 tokens x all ranks)
@@ -363,7 +369,8 @@ __global__ __launch_bounds__(512) void shrink_small_f32_kernel(
 template <int JB>
 __device__ __forceinline__ void delta_f32_tile(
     const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx, const float* __restrict__ At, int K,
-    const float* __restrict__ Bt, float* __restrict__ y, int64_t ldy, float beta, bool y_vec, floatx4* lds)
+    const float* __restrict__ Bt, float* __restrict__ v, const lora_vspec& vsp, float* __restrict__ y, int64_t ldy, float beta, bool y_vec,
+    floatx4* lds)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
     const int r = t.reserved0, n_end = t.c0 + t.cn, tok = perm[t.row0 + min(m, t.nrows - 1)];
@@ -379,6 +386,7 @@ __device__ __forceinline__ void delta_f32_tile(
     const floatx4 e = small_v<JB>(t, tok, x, ldx, At, K, lds);
     floatx4* const vt = lds + 8 * JB * 64;                   // v as operands: [JB][64 lanes]
     if (wave < JB) vt[wave * 64 + lane] = e;
+    if (v && t.c0 == 0) store_small_v<JB>(t, tok, e, v, vsp);
     __syncthreads();
     floatx4 d[4];
 #pragma unroll
@@ -394,15 +402,15 @@ __device__ __forceinline__ void delta_f32_tile(
 
 __global__ __launch_bounds__(512) void delta_f32_kernel(
     const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const float* __restrict__ x, int64_t ldx,
-    const float* const* __restrict__ At_ptrs, int K, const float* const* __restrict__ Bt_ptrs, float* __restrict__ y, int64_t ldy,
-    float beta, bool y_vec)
+    const float* const* __restrict__ At_ptrs, int K, const float* const* __restrict__ Bt_ptrs, float* __restrict__ v, lora_vspec vsp,
+    float* __restrict__ y, int64_t ldy, float beta, bool y_vec)
 {
     __shared__ floatx4 lds[9 * 4 * 64];
     const lora_tile t = tiles[blockIdx.x];
     const float *At = At_ptrs[t.adapter], *Bt = Bt_ptrs[t.adapter];
-    if (t.reserved0 <= 16) delta_f32_tile<1>(t, perm, x, ldx, At, K, Bt, y, ldy, beta, y_vec, lds);
-    else if (t.reserved0 <= 32) delta_f32_tile<2>(t, perm, x, ldx, At, K, Bt, y, ldy, beta, y_vec, lds);
-    else delta_f32_tile<4>(t, perm, x, ldx, At, K, Bt, y, ldy, beta, y_vec, lds);
+    if (t.reserved0 <= 16) delta_f32_tile<1>(t, perm, x, ldx, At, K, Bt, v, vsp, y, ldy, beta, y_vec, lds);
+    else if (t.reserved0 <= 32) delta_f32_tile<2>(t, perm, x, ldx, At, K, Bt, v, vsp, y, ldy, beta, y_vec, lds);
+    else delta_f32_tile<4>(t, perm, x, ldx, At, K, Bt, v, vsp, y, ldy, beta, y_vec, lds);
 }
 
 template <typename E, int FB, int TB, int D, int SUMS, bool KTAIL>
@@ -478,9 +486,9 @@ hipError_t launch_expand_rows(const lora_plan* p, const lora_dev_tables& d, cons
 }
 
 hipError_t launch_delta_f32(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx, const void* const* At,
-                            const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream)
+                            const void* const* Bt, float* v, void* y, int64_t ldy, float beta, hipStream_t stream)
 {
     LORA_LAUNCH(LORA_K_DELTA_F32, delta_f32_kernel, dim3((unsigned)p->f32_delta_tiles.size()), dim3(512), 0, stream, d.f32_delta_tiles,
-                d.perm, (const float*)x, ldx, (const float* const*)At, p->K, (const float* const*)Bt, (float*)y, ldy, beta, vec_rows(y, ldy, 4));
+                d.perm, (const float*)x, ldx, (const float* const*)At, p->K, (const float* const*)Bt, v, lora_vspec_of(p), (float*)y, ldy, beta, vec_rows(y, ldy, 4));
     return hipGetLastError();
 }

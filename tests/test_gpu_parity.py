@@ -340,6 +340,22 @@ def test_fp32_adapter_kernels_tiles_and_remainders(T, K, N, ranks, max_seg):
         _check_f32_delta(w, ld_pad, shift)
 
 
+@pytest.mark.parametrize("T,K,N,ranks", [(64, 256, 256, (8,)), (33, 252, 127, (64, 33, 1)), (90, 512, 4096, (17, 40)), (40, 4096, 264, (64, 16))])
+def test_fp32_delta_leaves_the_v_of_shrink(T, K, N, ranks):
+    """lora_delta writes the caller's v as lora_shrink does, bit for bit, in one launch (the first three) as in two."""
+    w = wl.random_case(1750 + T + K, T, K, N, 5, ranks, dtype="f32", max_seg=9, frac_none=0.15, scales=(0.5, 2.0, -1.0))
+    dl = device.to_device(w, DEV, with_w=False)
+    plan = device.make_plan(w)
+    n = B.lora_plan_query(plan)[1] // 4
+    v = [torch.full((n,), 777.0, dtype=torch.float32, device=DEV) for _ in range(2)]
+    y = torch.zeros((T, N), dtype=torch.float32, device=DEV)
+    B.lora_shrink(plan, dl.x, K, dl.At_ptrs, v[0])
+    B.lora_delta(plan, dl.x, K, dl.At_ptrs, dl.Bt_ptrs, v[1], y, N, 0.0)
+    torch.cuda.synchronize()
+    assert bool((v[0] != 777.0).any()) and torch.equal(v[0], v[1])
+    plan.destroy()
+
+
 @pytest.mark.parametrize("T,K,ranks,max_seg", [
     (1, 8, (1,), 1), (3, 72, (2, 5), 1), (20, 1000, (10, 101, 256), 2), (50, 520, (1, 17, 33), 20), (64, 4096, (174, 2), 4),
     (200, 648, (256, 130), 60), (300, 136, (9,), 300), (900, 2120, (4, 100, 255), 200), (3000, 264, (129, 256), 900)])
