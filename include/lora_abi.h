@@ -319,7 +319,7 @@ lora_status lora_delta_static(lora_plan* plan, const void* x, int64_t ldx,
  * lora_base_gemm -- the base-model product shared by all requests of the batch
  * (section 1 / section 2, unmerged inference):  y = x W, Wt [N,K] with ldw.
  * MFMA with fp32 accumulation.  Used for the
- * "separate" path base GEMM + shrink + expand.
+ * "separate" path base GEMM + shrink + expand.  y must not share memory with x or Wt (nor in lora_fused_forward).
  */
 lora_status lora_base_gemm(int32_t num_tokens, int32_t k, int32_t n, int32_t dtype,
                            const void* x, int64_t ldx, const void* Wt, int64_t ldw,

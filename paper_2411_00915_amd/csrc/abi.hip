@@ -209,6 +209,18 @@ const float* removal_v(const lora_plan* p, const float* v) { return removal_v(p,
 // layout the tiled kernels need at call time
 bool tiled_call_ok(const void* base, int64_t ld) { return !misaligned(base, 16) && ld % 8 == 0; }
 
+// Whether x [T, K] and y [T, N] have bytes in common.  (One launch would then read x while it writes y.)  Columns of one
+// buffer, x and y side by side in each of its rows, have not.
+bool share_memory(const lora_plan* p, const void* x, int64_t ldx, const void* y, int64_t ldy)
+{
+    const int64_t es = (int64_t)elem_bytes(p->dtype), x0 = (int64_t)reinterpret_cast<uintptr_t>(x), y0 = (int64_t)reinterpret_cast<uintptr_t>(y);
+    const int64_t x_row = p->K * es, y_row = p->N * es, x1 = x0 + (p->T - 1) * ldx * es + x_row, y1 = y0 + (p->T - 1) * ldy * es + y_row;
+    if (x1 <= y0 || y1 <= x0) return false;
+    if (ldx != ldy) return true;
+    const int64_t pitch = ldx * es, ahead = ((y0 - x0) % pitch + pitch) % pitch;      // of y's rows, from x's
+    return !(ahead >= x_row && ahead + y_row <= pitch);
+}
+
 }  // namespace
 
 // Releases a plan's device tables (called by lora_plan_destroy, planner.cpp, through lora_plan_device_release).
@@ -341,7 +353,8 @@ static lora_status delta_own(lora_plan* p, const void* x, int64_t ldx,
     if (p->perm.empty()) return LORA_OK;
     if (!x || !d_At_ptrs || !d_Bt_ptrs || !v || !y) return LORA_ERR_INVALID_ARG;
     if (ldx < p->K || ldy < p->N) return LORA_ERR_INVALID_ARG;
-    if (p->family == LORA_VARIANT_TILED && p->fused_ok && tiled_call_ok(x, ldx) && tiled_call_ok(y, ldy) &&
+    const bool one_launch = (p->fused_ok || !p->f32_delta_tiles.empty()) && !share_memory(p, x, ldx, y, ldy);
+    if (one_launch && p->family == LORA_VARIANT_TILED && tiled_call_ok(x, ldx) && tiled_call_ok(y, ldy) &&
         !misaligned(v, 16) && !misaligned(d_At_ptrs, 8) && !misaligned(d_Bt_ptrs, 8)) {
         hipStream_t stream = static_cast<hipStream_t>(hip_stream);
         lora_status st = ensure_uploaded(p, stream);
@@ -353,7 +366,7 @@ static lora_status delta_own(lora_plan* p, const void* x, int64_t ldx,
         if (e == hipErrorInvalidValue && trace != nullptr) return LORA_ERR_WORKSPACE;   // the trace buffer is too small
         return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
     }
-    if (!p->f32_delta_tiles.empty()) {
+    if (one_launch && !p->f32_delta_tiles.empty()) {
         if (misaligned(x, 4) || misaligned(y, 4) || misaligned(v, 16) || misaligned(d_At_ptrs, 8) || misaligned(d_Bt_ptrs, 8))
             return LORA_ERR_INVALID_ARG;
         hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -373,6 +386,10 @@ extern "C" lora_status lora_delta(lora_plan* p, const void* x, int64_t ldx,
     if (!p) return LORA_ERR_INVALID_ARG;
     if (!(beta == 0.f || beta == 1.f)) return LORA_ERR_INVALID_ARG;
     if (p->unmerge && !p->unmerge->perm.empty()) {             // mixture mode: removal first, see lora_expand
+        if (x && y && ldx >= p->K && ldy >= p->N && share_memory(p, x, ldx, y, ldy)) {   // all of x is read before any of y is written
+            const lora_status st = lora_shrink(p, x, ldx, d_At_ptrs, v, hip_stream);
+            return st == LORA_OK ? lora_expand(p, v, d_Bt_ptrs, y, ldy, beta, hip_stream) : st;
+        }
         const lora_status st = delta_own(p->unmerge, x, ldx, d_At_ptrs, d_Bt_ptrs, removal_v(p, v), y, ldy, beta, hip_stream);
         if (st != LORA_OK) return st;
         beta = 1.f;
@@ -523,7 +540,8 @@ extern "C" lora_status lora_delta_static(lora_plan* p, const void* x, int64_t ld
     float* v = reinterpret_cast<float*>(base + kStaticSyncBytes);
     lora_dev_tables d = tables_of(p);
     d.sync = base;
-    const bool single = p->family == LORA_VARIANT_TILED && p->fused_ok && tiled_call_ok(x, ldx) && tiled_call_ok(y, ldy) &&
+    const bool one_launch = (p->fused_ok || !p->f32_delta_tiles.empty()) && !share_memory(p, x, ldx, y, ldy);
+    const bool single = one_launch && p->family == LORA_VARIANT_TILED && tiled_call_ok(x, ldx) && tiled_call_ok(y, ldy) &&
                         !misaligned(d_At_ptrs, 8) && !misaligned(d_Bt_ptrs, 8);
     if (single) {
         // the counters' launch arithmetic assumes one plan per slot: the array is shared by all plans, so they
@@ -538,7 +556,7 @@ extern "C" lora_status lora_delta_static(lora_plan* p, const void* x, int64_t ld
     if (misaligned(x, elem_bytes(p->dtype)) || misaligned(y, elem_bytes(p->dtype)) || misaligned(d_At_ptrs, 8) ||
         misaligned(d_Bt_ptrs, 8))
         return LORA_ERR_INVALID_ARG;
-    if (!p->f32_delta_tiles.empty())
+    if (one_launch && !p->f32_delta_tiles.empty())
         return launch_delta_f32(p, d, x, ldx, d_At_ptrs, d_Bt_ptrs, nullptr, y, ldy, beta, stream) == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
     if (p->family == LORA_VARIANT_TILED && p->variant_req == LORA_VARIANT_TILED && !tiled_call_ok(y, ldy)) return LORA_ERR_UNSUPPORTED;
     st = run_shrink(p, d, x, ldx, d_At_ptrs, v, stream);

@@ -356,6 +356,51 @@ def test_fp32_delta_leaves_the_v_of_shrink(T, K, N, ranks):
     plan.destroy()
 
 
+@pytest.mark.parametrize("T,K,ranks,dtype,merged", [
+    (64, 256, (8,), "f32", None), (33, 512, (64, 16), "f32", None), (60, 512, (8, 64), "bf16", None), (200, 1024, (8, 12, 200), "bf16", None),
+    (64, 256, (8,), "f32", 1), (60, 512, (8, 64), "bf16", 1)])
+def test_delta_in_place_and_side_by_side(T, K, ranks, dtype, merged):
+    """lora_delta with y = x (K = N), or y a few rows behind x in one buffer, gives the bits of lora_shrink followed by
+    lora_expand on buffers of their own; x and y as columns of one buffer those of lora_delta on buffers of their own.  Also
+    lora_delta_static."""
+    w = wl.random_case(1770 + T + K, T, K, K, 5, ranks, dtype=dtype, max_seg=9, frac_none=0.15, scales=(0.5, 1.0, -1.0))
+    dl = device.to_device(w, DEV, with_w=False)
+    tdt = device.torch_dtype(w)
+    plan = B.lora_plan(T, w.seg_indptr, w.seg_adapter, w.adapter_rank, w.adapter_scale, K, K, dl.dtype, merged_adapter=merged)
+    v = torch.zeros(B.lora_plan_query(plan)[1] // 4, dtype=torch.float32, device=DEV)
+    B.lora_plan_upload(plan)
+    x = dl.x[:, :K].contiguous()
+
+    def apart(x, y, beta):
+        y = y.clone()
+        B.lora_shrink(plan, x, K, dl.At_ptrs, v)
+        B.lora_expand(plan, v, dl.Bt_ptrs, y, K, beta)
+        return y
+
+    def call(static, x, ldx, y, ldy, beta):
+        if static:
+            B.lora_delta_static(plan, x, ldx, dl.At_ptrs, dl.Bt_ptrs, y, ldy, beta)
+        else:
+            B.lora_delta(plan, x, ldx, dl.At_ptrs, dl.Bt_ptrs, v, y, ldy, beta)
+
+    for static in (False, True) if merged is None else (False,):
+        for beta in (1.0, 0.0):
+            both = x.clone()
+            call(static, both, K, both, K, beta)
+            assert torch.equal(both, apart(x, x, beta)), "in place"
+            rows = torch.randn((T + 8, K), device=DEV).to(tdt)
+            want = apart(rows[:T].clone(), rows[8:].clone(), beta)
+            call(static, rows, K, rows[8:], K, beta)
+            assert torch.equal(rows[8:], want), "rows of one buffer"
+            columns = torch.randn((T, 2 * K + 8), device=DEV).to(tdt)
+            columns[:, :K] = x
+            want = columns[:, K:2 * K].contiguous()
+            call(static, x, K, want, K, beta)
+            call(static, columns, 2 * K + 8, columns[:, K:], 2 * K + 8, beta)
+            assert torch.equal(columns[:, K:2 * K], want) and torch.equal(columns[:, :K], x), "columns of one buffer"
+    plan.destroy()
+
+
 @pytest.mark.parametrize("T,K,ranks,max_seg", [
     (1, 8, (1,), 1), (3, 72, (2, 5), 1), (20, 1000, (10, 101, 256), 2), (50, 520, (1, 17, 33), 20), (64, 4096, (174, 2), 4),
     (200, 648, (256, 130), 60), (300, 136, (9,), 300), (900, 2120, (4, 100, 255), 200), (3000, 264, (129, 256), 900)])
