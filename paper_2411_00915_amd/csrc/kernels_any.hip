@@ -124,7 +124,7 @@ __device__ __forceinline__ void finish16(E* yp, const u32x4 (&yin)[sizeof(E)], c
 
 // Expand, 16 TB tokens of one adapter per workgroup, chunks of 64 features per wavefront.  Bt and y come straight from
 // memory as each lane needs them (rows of any length, aligned to an element); v is common to the wavefronts and lies in
-// LDS as operands (bf16: two terms).  MFMA row 4 q + i of block f stands for feature 16 q + 4 f + i of the chunk: a lane
+// LDS as operands (bf16: three terms, all of its 24 bits; with two, lora_delta took 2 to 5 % less).  MFMA row 4 q + i of block f stands for feature 16 q + 4 f + i of the chunk: a lane
 // ends with 16 consecutive features of each of its tokens.
 //
 // Chunks of Bt are fetched whole from where they lie, into the next row if need be and, where they would reach past the
@@ -149,12 +149,31 @@ __device__ __forceinline__ u32x4 own_elements(u32x4 b, uint32_t drop, int keep)
     return b;
 }
 
+// Sixteen features of one token by fp32 products, rank after rank.  The terms of an infinite v, and their products with an
+// infinite Bt, add up to NaN also where v Bt is an infinity or a number: sums that came out as NaN are done again.
+template <typename E>
+__device__ __forceinline__ void plain_tile_row(int tok, const float* __restrict__ v, const lora_vspec& vsp, const E* __restrict__ Bt, int r,
+                                               E* __restrict__ y, int64_t ldy, int n, int n_end, float beta)
+{
+    v += (int64_t)tok * vsp.R;
+    y += (int64_t)tok * ldy;
+    for (int i = n; i < min(n + 16, n_end); ++i) {
+        float d = 0.f;
+        for (int j = 0; j < r; ++j) {
+            float vj = v[j];
+            for (int p = 1; p < vsp.P; ++p) vj += v[p * vsp.part + j];
+            d = fmaf(vj, elem<E>::load(Bt + (int64_t)i * r + j), d);
+        }
+        elem<E>::store(y + i, beta != 0.f ? fmaf(beta, elem<E>::load(y + i), d) : d);
+    }
+}
+
 template <typename E, int TB>
 __device__ __forceinline__ void expand_rows_tile(
     const lora_tile& t, const int32_t* __restrict__ perm, const float* __restrict__ v, const lora_vspec& vsp,
     const E* __restrict__ Bt, E* __restrict__ y, int64_t ldy, int N, float beta, bool y_vec, op16* lds)
 {
-    constexpr int ES = (int)sizeof(E), EPC = 16 / ES, KSTEP = 4 * EPC, TERMS = ES == 2 ? 2 : 1;
+    constexpr int ES = (int)sizeof(E), EPC = 16 / ES, KSTEP = 4 * EPC, TERMS = ES == 2 ? 3 : 1;
     constexpr int KS = TB == 1 ? 2 : 4;                      // steps of KSTEP ranks whose loads go out together (as many as registers hold)
     constexpr int SUMS = ES == 4 ? 4 / TB : 1;               // (see mma_apart)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
@@ -194,10 +213,13 @@ __device__ __forceinline__ void expand_rows_tile(
     for (int s = wave; s < steps; s += 4)
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
-            op16 hi, lo;
-            v_chunk<E>(v, vsp, tok[b], s * KSTEP + EPC * g, r, true, hi, lo);
-            lds[((s * TB + b) * TERMS) * 64 + lane] = hi;
-            if (ES == 2) lds[((s * TB + b) * TERMS + 1) * 64 + lane] = lo;
+            float f[EPC];
+            op16 o[TERMS];
+            v_values<EPC>(v, vsp, tok[b], s * KSTEP + EPC * g, r, true, f);
+            if constexpr (ES == 4) o[0].f = floatx4{f[0], f[1], f[2], f[3]};
+            else bf16_terms<TERMS>(f, o);
+#pragma unroll
+            for (int t = 0; t < TERMS; ++t) lds[((s * TB + b) * TERMS + t) * 64 + lane] = o[t];
         }
     __syncthreads();
     for (bool first = true; n0 < n_end; n0 += 256, first = false) {
@@ -232,21 +254,33 @@ __device__ __forceinline__ void expand_rows_tile(
                             if constexpr (ES == 4) {
                                 mma_apart(bt[s][f], vp[0], acc[b][f], 0);
                             } else {
-                                acc[b][f][0] = mma(bt[s][f], vp[0], acc[b][f][0], E{});
-                                acc[b][f][0] = mma(bt[s][f], vp[64], acc[b][f][0], E{});
+#pragma unroll
+                                for (int t = 0; t < TERMS; ++t) acc[b][f][0] = mma(bt[s][f], vp[t * 64], acc[b][f][0], E{});
                             }
                         }
                     }
                 }
         }
+        int again = 0;
 #pragma unroll
         for (int b = 0; b < TB; ++b)
             if (16 * b + m < t.nrows) {
                 floatx4 d[4];
 #pragma unroll
                 for (int f = 0; f < 4; ++f) d[f] = folded(acc[b][f]);
-                finish16<E>(y + (int64_t)tok[b] * ldy + n0 + 16 * g, yin[b], d, beta, y_vec, n_end - n0 - 16 * g);
+                bool nan = false;                            // (of features that are not there, too: their sums are a neighbour's)
+                if (ES == 2) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) nan |= d[i >> 2][i & 3] != d[i >> 2][i & 3];
+                }
+                if (nan) again |= 1 << b;
+                else finish16<E>(y + (int64_t)tok[b] * ldy + n0 + 16 * g, yin[b], d, beta, y_vec, n_end - n0 - 16 * g);
             }
+        if (ES == 2 && again) {
+#pragma unroll 1
+            for (int b = 0; b < TB; ++b)
+                if ((again >> b) & 1) plain_tile_row(perm[t.row0 + 16 * b + m], v, vsp, Bt, r, y, ldy, n0 + 16 * g, n_end, beta);
+        }
     }
 }
 

@@ -488,7 +488,7 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
 {
     if (p->N < 8 || (int64_t)p->N * LORA_MAX_RANK >= (1ll << 31)) return;   // the kernel fetches whole chunks, by 32-bit offsets
     const int G = (int)p->group_adapter.size();
-    const int32_t kstep = p->dtype == LORA_F32 ? 16 : 32, terms = p->dtype == LORA_F32 ? 1 : 2;
+    const int32_t kstep = p->dtype == LORA_F32 ? 16 : 32, terms = p->dtype == LORA_F32 ? 1 : 3;
     auto token_tiles = [&](int32_t per) {
         int64_t n = 0;
         for (int g = 0; g < G; ++g) n += (p->group_offset[g + 1] - p->group_offset[g] + per - 1) / per;

@@ -91,41 +91,64 @@ __device__ __forceinline__ op16 row_chunk(const E* row, int j, int r)
     return o;
 }
 
-// v[token][j ..] (sum of its K parts) as MFMA operands: bf16: two terms hi + lo; fp32: hi alone
-template <typename E>
-__device__ __forceinline__ void v_chunk(const float* v, const lora_vspec& vsp, int tok, int j, int r, bool mine, op16& hi, op16& lo)
+// v[token][j ..] (sum of its K parts); past the rank, and for tokens that are not `mine`, zero
+template <int N>
+__device__ __forceinline__ void v_values(const float* v, const lora_vspec& vsp, int tok, int j, int r, bool mine, float (&f)[N])
 {
-    constexpr int EPC = 16 / (int)sizeof(E);
-    float f[EPC];
 #pragma unroll
-    for (int i = 0; i < EPC; ++i) f[i] = 0.f;
+    for (int i = 0; i < N; ++i) f[i] = 0.f;
     if (mine && j < r) {                                     // (rows are R floats apart, R % 8 == 0)
         const float* p = v + (int64_t)tok * vsp.R + j;
-        floatx4 part[4][EPC / 4];
+        floatx4 part[4][N / 4];
 #pragma unroll
         for (int s = 0; s < 4; ++s)                          // all parts are requested before the first add
             if (s < vsp.P) {
 #pragma unroll
-                for (int q = 0; q < EPC / 4; ++q) part[s][q] = *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
+                for (int q = 0; q < N / 4; ++q) part[s][q] = *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
             }
 #pragma unroll
         for (int s = 1; s < 4; ++s)
             if (s < vsp.P) {
 #pragma unroll
-                for (int q = 0; q < EPC / 4; ++q) part[0][q] += part[s][q];
+                for (int q = 0; q < N / 4; ++q) part[0][q] += part[s][q];
             }
 #pragma unroll
-        for (int i = 0; i < EPC; ++i) f[i] = j + i < r ? part[0][i >> 2][i & 3] : 0.f;   // past the rank: never written
+        for (int i = 0; i < N; ++i) f[i] = j + i < r ? part[0][i >> 2][i & 3] : 0.f;     // past the rank: never written
     }
+}
+
+// f as the sum of TERMS bf16 operands, each the rounded rest of those before it: two terms keep 16 bits of the
+// significand, three all 24.  Infinities, and what rounds to one, give NaN in the last term.
+template <int TERMS>
+__device__ __forceinline__ void bf16_terms(const float (&f)[8], op16 (&o)[TERMS])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float f0 = f[2 * i], f1 = f[2 * i + 1];
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t) {
+            const bf16_t h0 = f32_to_bf16(f0), h1 = f32_to_bf16(f1);
+            o[t].u[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+            f0 -= bf16_to_f32(h0);
+            f1 -= bf16_to_f32(h1);
+        }
+    }
+}
+
+// v[token][j ..] as MFMA operands: bf16: two terms hi + lo; fp32: hi alone
+template <typename E>
+__device__ __forceinline__ void v_chunk(const float* v, const lora_vspec& vsp, int tok, int j, int r, bool mine, op16& hi, op16& lo)
+{
+    constexpr int EPC = 16 / (int)sizeof(E);
+    float f[EPC];
+    v_values<EPC>(v, vsp, tok, j, r, mine, f);
     if constexpr (sizeof(E) == 4) {
         hi.f = floatx4{f[0], f[1], f[2], f[3]};
     } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bf16_t h0 = f32_to_bf16(f[2 * i]), h1 = f32_to_bf16(f[2 * i + 1]);
-            hi.u[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            lo.u[i] = (uint32_t)f32_to_bf16(f[2 * i] - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(f[2 * i + 1] - bf16_to_f32(h1)) << 16);
-        }
+        op16 o[2];
+        bf16_terms<2>(f, o);
+        hi = o[0];
+        lo = o[1];
     }
 }
 

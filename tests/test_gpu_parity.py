@@ -502,6 +502,70 @@ def test_any_rank_expand(T, N, ranks, max_seg):
         plan.destroy()
 
 
+def _one_adapter_plan(T, K, N, rank, variant=B.LORA_VARIANT_AUTO):
+    return B.lora_plan(T, np.array([0, T], np.int32), np.array([0], np.int32), np.array([rank], np.int32), np.array([1.0], np.float32),
+                       K, N, B.LORA_BF16, variant)
+
+
+@pytest.mark.parametrize("rank", [2, 12, 100, 256])
+def test_any_rank_expand_uses_all_bits_of_v(rank):
+    """v holds 1 + 2^-10 + 2^-23 and 1 + 2^-10, Bt the same power of two with opposite signs: in fp32 every product and sum
+    is exact and 2^-23 of it is left; with less than the 24 bits of v, nothing."""
+    T, N = 37, 200
+    plan = _one_adapter_plan(T, 64, N, rank)
+    R, v_bytes, _ = B.lora_plan_query(plan)
+    v = torch.zeros((v_bytes // (4 * T * R), T, R), dtype=torch.float32, device=DEV)
+    Bt = torch.zeros((N, rank), dtype=torch.bfloat16, device=DEV)
+    b = 2.0 ** (torch.arange(N, device=DEV) % 7).float()
+    j0, j1 = 0, rank - 1
+    v[0, :, j0], v[0, :, j1] = 1 + 2.0 ** -10 + 2.0 ** -23, 1 + 2.0 ** -10
+    Bt[:, j0], Bt[:, j1] = b.bfloat16(), -b.bfloat16()
+    y = torch.full((T, N), 5.0, dtype=torch.bfloat16, device=DEV)
+    B.lora_expand(plan, v, torch.tensor([Bt.data_ptr()], dtype=torch.int64, device=DEV), y, N, 0.0)
+    torch.cuda.synchronize()
+    assert torch.equal(y.float(), (b * 2.0 ** -23).expand(T, N))
+    plan.destroy()
+
+
+def _non_finite_rows(T, R, N, rank):
+    """v rows and a Bt whose products are infinities, NaN and numbers that a v beyond bf16's largest value leads to"""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rank)
+    v = torch.randn((T, R), generator=gen, device=DEV)
+    Bt = torch.randn((N, rank), generator=gen, device=DEV).abs().clamp_min(0.1).bfloat16()
+    inf, top = float("inf"), float(np.float32(3.4e38))                 # (bf16 rounds 3.4e38 to infinity)
+    v[0, 0], v[1, rank - 1], v[2, 0], v[3, 0] = inf, -inf, float("nan"), top
+    v[4, 0], v[4, rank - 1] = inf, -inf
+    v[5, :] = 1.0                                                      # one bf16 term, the others zero
+    Bt[:, 0] = torch.where(torch.arange(N, device=DEV) % 5 == 0, 0.0, 2.0 ** -10).bfloat16()      # (row 0 of v: infinity times zero)
+    Bt[7, rank // 2], Bt[8, rank // 2] = inf, -inf
+    return v, Bt
+
+
+@pytest.mark.parametrize("rank", [2, 12, 100, 256])
+def test_any_rank_expand_of_infinities(rank):
+    """Infinities and NaN in v and Bt come out as from fp32 products: against the general kernel."""
+    T, N = 21, 203
+    out = []
+    for variant in (B.LORA_VARIANT_AUTO, B.LORA_VARIANT_GENERAL):
+        plan = _one_adapter_plan(T, 64, N, rank, variant)
+        R, v_bytes, _ = B.lora_plan_query(plan)
+        rows, Bt = _non_finite_rows(T, R, N, rank)
+        v = torch.zeros((v_bytes // (4 * T * R), T, R), dtype=torch.float32, device=DEV)
+        v[0] = rows
+        y = torch.ones((T, N), dtype=torch.bfloat16, device=DEV)
+        B.lora_expand(plan, v, torch.tensor([Bt.data_ptr()], dtype=torch.int64, device=DEV), y, N, 1.0)
+        torch.cuda.synchronize()
+        out.append(y.float())
+        plan.destroy()
+    got, want = out
+    assert bool(torch.isinf(want[0]).any()) and bool(torch.isfinite(want[3]).any()) and bool(torch.isinf(want[6:, 7]).all())
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(got[torch.isinf(want)], want[torch.isinf(want)]) and torch.equal(torch.isinf(got), torch.isinf(want))
+    f = torch.isfinite(want)
+    assert bool(((got[f] - want[f]).abs() <= 2.0 ** -7 * want[f].abs() + 1e-4).all())
+
+
 def test_large_batch_expand_writes_nothing_past_an_n_off_eight():
     """N no multiple of 8 under a padded leading dimension, a batch that would take the streaming kernels: the columns
     between N and ldy stay as they are."""
