@@ -115,7 +115,8 @@ typedef enum { LORA_F32 = 0, LORA_BF16 = 1 } lora_dtype;
  * family over the same inputs. */
 typedef enum {
     LORA_VARIANT_AUTO = 0,      /* planner decides per batch */
-    LORA_VARIANT_GENERAL = 1,   /* general VALU kernels only */
+    LORA_VARIANT_GENERAL = 1,   /* general VALU kernels only (but bf16 plans with ranks the tuned kernels take, or
+                                   without adapters, have lora_fused_forward's product on MFMA kernels) */
     LORA_VARIANT_TILED = 2      /* tiled MFMA kernels wherever the layout allows */
 } lora_variant;
 

@@ -473,9 +473,11 @@ extern "C" lora_status lora_fused_forward(lora_plan* p, const void* x, int64_t l
     const bool rows_ok = !has_delta || (int32_t)p->order.size() == p->T;
     const bool layout_ok = rows_ok && gemm_tiled_supported(p->T, p->K, p->N, p->dtype, x, ldx, Wt, ldw, y, ldy);
     const bool stage_lists = !has_delta || !p->extra_ptr256.empty();
-    const gemm_route_id route = layout_ok ? gemm_route(p->T, p->K, p->N, ldx, ldw, stage_lists) : GEMM_SMALL;
+    // (plans that asked for the general kernels: fp32 and other ranks than the tuned kernels' stay on them)
+    const bool any_rank_ok = p->variant_req != LORA_VARIANT_GENERAL || (p->dtype == LORA_BF16 && stage_lists);
+    const gemm_route_id route = layout_ok && any_rank_ok ? gemm_route(p->T, p->K, p->N, ldx, ldw, stage_lists) : GEMM_SMALL;
     const bool mid = route == GEMM_MID_128 || route == GEMM_MID_192, tiled = layout_ok && !mid && stage_lists;
-    const bool small = !mid && rows_ok && !(p->dtype == LORA_F32 && p->variant_req == LORA_VARIANT_GENERAL) && (!tiled || route == GEMM_SMALL) &&
+    const bool small = !mid && rows_ok && any_rank_ok && (!tiled || route == GEMM_SMALL) &&
                        gemm_small_supported(p->T, p->K, p->N, p->dtype, x, ldx, Wt, ldw, y, ldy);
     char* const split = mid || small ? nullptr : vb;
     bool split_done = false, split2_done = false;

@@ -572,6 +572,32 @@ def test_large_batch_expand_writes_nothing_past_an_n_off_eight():
     run_delta_case(wl.random_case(1900, 1100, 1024, 204, 9, (16, 64), max_seg=200, frac_none=0.1, scales=(1.0, -0.5)), ld_pad=4)
 
 
+def _launched(call):
+    """names of the library's kernels that call() launches"""
+    B.lora_timing_begin()
+    try:
+        call()
+    finally:
+        names = set(B.lora_timing_end())
+    return names
+
+
+@pytest.mark.parametrize("T,dtype,ranks", [(90, "f32", (8, 20)), (90, "bf16", (5, 100)), (700, "bf16", (5, 100))])
+def test_general_variant_runs_the_general_kernels(T, dtype, ranks):
+    """A plan made with LORA_VARIANT_GENERAL, in fp32 or with ranks off the tuned kernels: no matrix-core kernel runs."""
+    w = wl.random_case(2400 + T, T, 264, 520, 6, ranks, dtype=dtype, max_seg=7, frac_none=0.2)
+    dl = device.to_device(w, DEV, with_w=True)
+    plan = device.make_plan(w, B.LORA_VARIANT_GENERAL)
+    ws = torch.empty(max(B.lora_plan_query(plan)[2], 256), dtype=torch.uint8, device=DEV)
+    y = torch.empty((T, w.N), dtype=device.torch_dtype(w), device=DEV)
+    names = _launched(lambda: B.lora_fused_forward(plan, dl.x, w.K, dl.Wt, w.K, dl.At_ptrs, dl.Bt_ptrs, y, w.N, ws, ws.numel()))
+    assert names == {"shrink_general_kernel", "gemm_general_kernel"}
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    _assert_close(_to_np(y), oracle.forward(w.x, w.W, tok, ad), _tol(w), "fused forward")
+    plan.destroy()
+
+
 @pytest.mark.parametrize("T,dtype,ranks", [(90, "f32", (8, 20)), (90, "bf16", (8, 16)), (90, "bf16", (5, 100)), (700, "bf16", (8, 16)), (700, "bf16", (5, 100))])
 def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, dtype, ranks):
     """One adapter's factors hold infinities and NaN: the tokens of all other adapters, and of none, come out bit for bit
