@@ -18,7 +18,8 @@
 // The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
 //
 // DELTA: tokens in adapter-sorted order; after the K loop every wavefront adds the deltas of its own 64 tokens: per
-// adapter and 32 ranks, Bt_a[its features] and v (as the shrink left it, split into two bf16 terms) as MFMA operands.
+// adapter and 32 ranks, Bt_a[its features] and v (as the shrink left it, split into two bf16 terms, or, for ranks off the
+// tuned kernels, in fp32 products: 1111 tokens of ranks 100 and 20, 5120 -> 5120, 109 us, with two terms 99) as MFMA operands.
 // (v read by every wavefront for itself, step by step behind Bt: lora_fused_forward of 1111 tokens in mixture mode, 5120 ->
 // 5120, 113 us; as operands in LDS, Bt a step ahead: 96.  It took 134 in the register-staged 128 x 128 tiles.)
 #include <algorithm>
@@ -33,7 +34,7 @@ namespace {
 
 constexpr int MID_TOKENS = 128;
 
-template <int WA, bool DELTA, bool KTAIL>
+template <int WA, row_delta DELTA, bool KTAIL>
 __global__ __launch_bounds__(512) void gemm_mid_kernel(
     int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
     bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da)
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
         const int row = (is_w ? wave * WA + i : wave * 2 + i - WA) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ (is_w ? (row & 3) | (((row / (4 * WA)) & 1) << 2) : row & 7);
         const int pos = min(t0 + row, T - 1);
-        const int64_t r = is_w ? min(n0 + row, N - 1) * ldw : (DELTA ? da.order[pos] : pos) * ldx;
+        const int64_t r = is_w ? min(n0 + row, N - 1) * ldw : (DELTA != NO_DELTA ? da.order[pos] : pos) * ldx;
         off[i] = (uint32_t)(r * 2) + c * 16;
         cut[i] = KTAIL && last_k + c * 8 >= K ? c * 16 : 0;
     }
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
     // and row 16 wave + m, whose v this wavefront makes operands of
     int my_own = KEY_NONE, my_rank = 0, v_tok = 0, v_rank = 0, v_removal = 0;
     uint64_t my_bt = 0, removal = 0;
-    if constexpr (DELTA) {
+    if constexpr (DELTA != NO_DELTA) {
         const int pos = t0 + wt + lane, v_pos = t0 + 16 * wave + m;
         const int key = pos < T ? da.row_key[da.order[pos]] : KEY_NONE;
         v_tok = da.order[min(v_pos, T - 1)];
@@ -168,9 +169,9 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
 
     // ---- adapter deltas of this wavefront's 64 tokens: v of the tile's tokens as operands in LDS (a wavefront makes those
     // of one block of 16 tokens), then (adapter, 32 ranks) by (adapter, 32 ranks), Bt one step ahead ----
-    if constexpr (DELTA) {
+    if constexpr (DELTA != NO_DELTA) {
         constexpr int VSTEPS = LORA_MAX_RANK / 32;
-        op16* const vops = reinterpret_cast<op16*>(small_lds);       // [8 token blocks][VSTEPS][hi, lo][64 lanes]
+        op16* const vops = reinterpret_cast<op16*>(small_lds);       // [8 token blocks][VSTEPS][two bf16 terms, or two halves in fp32][64 lanes]
         auto make_operands = [&](const float* v, const lora_vspec& vsp, int r) {
             int rmax = r;
 #pragma unroll
@@ -196,17 +197,18 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
                         for (int i = 1; i < P; ++i)
 #pragma unroll
                             for (int h = 0; h < 2; ++h) part[q][0][h] += part[q][i][h];
-                        op16 hi, lo;
+                        float f[8];
+                        op16 o[2];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int j = (s0 + q) * 32 + 8 * g + 2 * i;                         // past the rank v holds nothing
-                            const float f0 = j < r ? part[q][0][i >> 1][2 * (i & 1)] : 0.f, f1 = j + 1 < r ? part[q][0][i >> 1][2 * (i & 1) + 1] : 0.f;
-                            const bf16_t h0 = f32_to_bf16(f0), h1 = f32_to_bf16(f1);
-                            hi.u[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-                            lo.u[i] = (uint32_t)f32_to_bf16(f0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(f1 - bf16_to_f32(h1)) << 16);
+                        for (int i = 0; i < 8; ++i) f[i] = (s0 + q) * 32 + 8 * g + i < r ? part[q][0][i >> 2][i & 3] : 0.f;   // past the rank v holds nothing
+                        if constexpr (DELTA == PLAIN_DELTA) {
+                            o[0].f = floatx4{f[0], f[1], f[2], f[3]};
+                            o[1].f = floatx4{f[4], f[5], f[6], f[7]};
+                        } else {
+                            bf16_terms<2>(f, o);
                         }
-                        vops[((wave * VSTEPS + s0 + q) * 2) * 64 + lane] = hi;
-                        vops[((wave * VSTEPS + s0 + q) * 2 + 1) * 64 + lane] = lo;
+                        vops[((wave * VSTEPS + s0 + q) * 2) * 64 + lane] = o[0];
+                        vops[((wave * VSTEPS + s0 + q) * 2 + 1) * 64 + lane] = o[1];
                     }
             };
             for (int s0 = 0; s0 < steps; s0 += 2) {
@@ -252,13 +254,21 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
             for (int b = 0; b < 4; ++b) {
                 if (((in >> (16 * b)) & 0xffffull) == 0) continue;                 // wavefront-uniform
                 const op16* vp = vops + (((wt / 16 + b) * VSTEPS + j / 32) * 2) * 64 + lane;
-                const op16 hi = vp[0], lo = vp[64];
+                const op16 v0 = vp[0], v1 = vp[64];
                 const bool mine = (in >> (16 * b + m)) & 1ull;       // (a product with zeros would carry the adapter's infinities over)
+                auto take = [&](auto product) {
 #pragma unroll
-                for (int f = 0; f < WA; ++f) {
-                    const floatx4 e = mma(bt[f], lo, mma(bt[f], hi, acc[f][b], bf16_t{}), bf16_t{});
+                    for (int f = 0; f < WA; ++f) {
+                        const floatx4 e = product(bt[f], acc[f][b]);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[f][b][i] = mine ? e[i] : acc[f][b][i];
+                        for (int i = 0; i < 4; ++i) acc[f][b][i] = mine ? e[i] : acc[f][b][i];
+                    }
+                };
+                if constexpr (DELTA == PLAIN_DELTA) {
+                    const float f8[8] = {v0.f[0], v0.f[1], v0.f[2], v0.f[3], v1.f[0], v1.f[1], v1.f[2], v1.f[3]};
+                    take([&](const op16& w, floatx4 c) { return mma_plain(w, f8, c); });
+                } else {
+                    take([&](const op16& w, floatx4 c) { return mma(w, v1, mma(w, v0, c, bf16_t{}), bf16_t{}); });
                 }
             }
         };
@@ -304,7 +314,7 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
         const int pos = t0 + wt + 16 * b + m;
         if (pos >= T) continue;
         const int n = n0 + wn + 4 * WA * g;
-        bf16_t* yp = y + (int64_t)(DELTA ? da.order[pos] : pos) * ldy + n;
+        bf16_t* yp = y + (int64_t)(DELTA != NO_DELTA ? da.order[pos] : pos) * ldy + n;
 #pragma unroll
         for (int a = 0; a < WA; ++a) {
             const floatx4 e = acc[a][b];
@@ -321,7 +331,7 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
     }
 }
 
-template <int WA, bool DELTA, bool KTAIL>
+template <int WA, row_delta DELTA, bool KTAIL>
 hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
                       const row_delta_args& da, hipStream_t stream)
 {
@@ -334,7 +344,7 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    LORA_LAUNCH(DELTA ? LORA_K_GEMM_MID_DELTA : LORA_K_GEMM_MID, (gemm_mid_kernel<WA, DELTA, KTAIL>), dim3((unsigned)(tiles_n * tiles_t)),
+    LORA_LAUNCH(DELTA != NO_DELTA ? LORA_K_GEMM_MID_DELTA : LORA_K_GEMM_MID, (gemm_mid_kernel<WA, DELTA, KTAIL>), dim3((unsigned)(tiles_n * tiles_t)),
                 dim3(512), lds_bytes, stream, T, K, N, (const bf16_t*)x, ldx, (const bf16_t*)Wt, ldw, (bf16_t*)y, ldy, tiles_n, tiles_t, da);
     return hipGetLastError();
 }
@@ -383,8 +393,9 @@ hipError_t launch_gemm_mid(gemm_route_id route, int32_t T, int32_t K, int32_t N,
     const row_delta_args da = delta ? row_deltas_of(p, d, v, rm, Bt) : row_delta_args{};
 #define MID_LAUNCH(WA_, D_, KT_) launch_one<WA_, D_, KT_>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
 #define MID_DISPATCH(D_, KT_) (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, KT_) : MID_LAUNCH(3, D_, KT_))
-    if (delta) return K % 64 ? MID_DISPATCH(true, true) : MID_DISPATCH(true, false);
-    return K % 64 ? MID_DISPATCH(false, true) : MID_DISPATCH(false, false);
+    if (!delta) return K % 64 ? MID_DISPATCH(NO_DELTA, true) : MID_DISPATCH(NO_DELTA, false);
+    if (p->extra_ptr256.empty()) return K % 64 ? MID_DISPATCH(PLAIN_DELTA, true) : MID_DISPATCH(PLAIN_DELTA, false);
+    return K % 64 ? MID_DISPATCH(TERMS_DELTA, true) : MID_DISPATCH(TERMS_DELTA, false);
 #undef MID_DISPATCH
 #undef MID_LAUNCH
 }

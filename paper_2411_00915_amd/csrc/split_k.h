@@ -69,6 +69,15 @@ __device__ __forceinline__ floatx4 folded(floatx4 (&c)[N])
     return c[0];
 }
 
+// eight bf16 by eight fp32 values of every lane, as fp32 products
+__device__ __forceinline__ floatx4 mma_plain(const op16& a, const float (&f)[8], floatx4 c)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(i & 1 ? a.u[i >> 1] & 0xffff0000u : a.u[i >> 1] << 16), f[i], c, 0, 0, 0);
+    return c;
+}
+
 // elements [j, j + 16 / sizeof(E)) of a row of r elements; those past the row's end are zero
 template <typename E>
 __device__ __forceinline__ op16 row_chunk(const E* row, int j, int r)
@@ -135,24 +144,9 @@ __device__ __forceinline__ void bf16_terms(const float (&f)[8], op16 (&o)[TERMS]
     }
 }
 
-// v[token][j ..] as MFMA operands: bf16: two terms hi + lo; fp32: hi alone
-template <typename E>
-__device__ __forceinline__ void v_chunk(const float* v, const lora_vspec& vsp, int tok, int j, int r, bool mine, op16& hi, op16& lo)
-{
-    constexpr int EPC = 16 / (int)sizeof(E);
-    float f[EPC];
-    v_values<EPC>(v, vsp, tok, j, r, mine, f);
-    if constexpr (sizeof(E) == 4) {
-        hi.f = floatx4{f[0], f[1], f[2], f[3]};
-    } else {
-        op16 o[2];
-        bf16_terms<2>(f, o);
-        hi = o[0];
-        lo = o[1];
-    }
-}
-
-// adapter deltas of kernels whose rows are the tokens in the plan's order
+// Adapter deltas of kernels whose rows are the tokens in the plan's order: none, with v as two bf16 terms, or with v in
+// fp32 products (fp32, and bf16 with ranks off the tuned kernels, whose v was always taken whole)
+enum row_delta { NO_DELTA, TERMS_DELTA, PLAIN_DELTA };
 struct row_delta_args {
     const int32_t* order;          // [T] tokens sorted by adapter, then tokens without adapter
     const int32_t* row_key;        // [T] adapter of the token (bits 0..22; all ones: none) | removal bit

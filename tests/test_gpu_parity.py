@@ -598,6 +598,71 @@ def test_general_variant_runs_the_general_kernels(T, dtype, ranks):
     plan.destroy()
 
 
+ANY_RANK_FUSED = [(40, 520, 12, "gemm_small_kernel<delta>"), (100, 1000, 100, "gemm_small_kernel<delta>"),
+                  (700, 5000, 12, "gemm_mid_kernel<delta>"), (520, 2000, 256, "gemm_mid_kernel<delta>")]
+
+
+def _fused_one_adapter(x, W, At, Bt, variant=B.LORA_VARIANT_AUTO):
+    """lora_fused_forward of one adapter on every second request of three tokens; (output, kernels)"""
+    (T, K), (N, r) = x.shape, Bt.shape
+    offsets = np.append(np.arange(0, T, 3), T).astype(np.int32)
+    plan = B.lora_plan(T, offsets, (np.arange(len(offsets) - 1) % 2 - 1).astype(np.int32), np.array([r], np.int32), np.array([1.0], np.float32),
+                       K, N, B.LORA_BF16, variant)
+    ws = torch.empty(max(B.lora_plan_query(plan)[2], 256), dtype=torch.uint8, device=DEV)
+    y = torch.full((T, N), 7.0, dtype=torch.bfloat16, device=DEV)
+    A, Bp = (torch.tensor([m.data_ptr()], dtype=torch.int64, device=DEV) for m in (At, Bt))
+    names = _launched(lambda: B.lora_fused_forward(plan, x, K, W, K, A, Bp, y, N, ws, ws.numel()))
+    plan.destroy()
+    return y.float(), names, torch.arange(T, device=DEV) // 3 % 2 == 1
+
+
+@pytest.mark.parametrize("T,N,rank,kernel", ANY_RANK_FUSED)
+def test_any_rank_fused_forward_uses_all_bits_of_v(T, N, rank, kernel):
+    """v is 1 + 2^-10 + 2^-23 and 1 + 2^-10 (exact sums of At), Bt the same power of two with opposite signs, W zero: in
+    fp32 2^-23 of it is left; with less than the 24 bits of v, nothing."""
+    K = 264
+    x, W = torch.ones((T, K), device=DEV).bfloat16(), torch.zeros((N, K), dtype=torch.bfloat16, device=DEV)
+    At, Bt = torch.zeros((rank, K), dtype=torch.bfloat16, device=DEV), torch.zeros((N, rank), dtype=torch.bfloat16, device=DEV)
+    At[0, 0], At[0, 100], At[0, 200] = 1.0, 2.0 ** -10, 2.0 ** -23
+    At[rank - 1, 0], At[rank - 1, 100] = 1.0, 2.0 ** -10
+    b = 2.0 ** (torch.arange(N, device=DEV) % 7).float()
+    Bt[:, 0], Bt[:, rank - 1] = b.bfloat16(), -b.bfloat16()
+    y, names, on = _fused_one_adapter(x, W, At, Bt)
+    assert kernel in names
+    assert torch.equal(y, torch.where(on[:, None], b * 2.0 ** -23, 0.0))
+
+
+@pytest.mark.parametrize("T,N,rank,kernel", ANY_RANK_FUSED)
+def test_any_rank_fused_forward_of_infinities(T, N, rank, kernel):
+    """An infinite v, one beyond bf16's largest value, and infinities in Bt come out as from fp32 products: against the
+    general kernel.  (v overflows in its sum; x itself is finite.)"""
+    K = 264
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T)
+    x, W = torch.randn((T, K), generator=gen, device=DEV).bfloat16(), (torch.randn((N, K), generator=gen, device=DEV) / 16).bfloat16()
+    x[:, :40] = 0.0
+    At = (torch.randn((rank, K), generator=gen, device=DEV) / 16).bfloat16()
+    Bt = torch.randn((N, rank), generator=gen, device=DEV).abs().clamp_min(0.1).bfloat16()
+    At[:, :40] = 0.0
+    At[0, 0], At[rank - 1, 1], At[:, 2] = 2.0 ** 100, -2.0 ** 100, 1.0
+    for i in range(10):
+        At[0, 20 + i] = 2.0 ** (127 - i)                               # their sum: beyond bf16's largest value, below fp32's
+    Bt[:, 0] = torch.where(torch.arange(N, device=DEV) % 5 == 0, 0.0, 2.0 ** -10).bfloat16()
+    Bt[7, rank // 2], Bt[8, rank // 2] = float("inf"), -float("inf")
+    x[3, 0] = x[4, 1] = x[5, 0] = x[5, 1] = 2.0 ** 100                 # (requests of three tokens, the second and fourth on the adapter)
+    x[9, 20:30] = 1.0
+    x[10, 40:], x[10, 2] = 0.0, 1.0                                    # v = 1 everywhere: one bf16 term, the others zero
+    got, names, on = _fused_one_adapter(x, W, At, Bt)
+    want, general, _ = _fused_one_adapter(x, W, At, Bt, B.LORA_VARIANT_GENERAL)
+    assert kernel in names and "gemm_general_kernel" in general
+    assert bool(torch.isinf(want[3]).any()) and bool(torch.isnan(want[3]).any()) and bool(torch.isfinite(want[9, 9:]).all())
+    assert bool(torch.isinf(want[10, 7])) and bool(torch.isfinite(want[~on]).all())
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(got[torch.isinf(want)], want[torch.isinf(want)]) and torch.equal(torch.isinf(got), torch.isinf(want))
+    f = torch.isfinite(want)
+    assert bool(((got[f] - want[f]).abs() <= 2.0 ** -7 * want[f].abs() + 1e-3).all())
+
+
 @pytest.mark.parametrize("T,dtype,ranks", [(90, "f32", (8, 20)), (90, "bf16", (8, 16)), (90, "bf16", (5, 100)), (700, "bf16", (8, 16)), (700, "bf16", (5, 100))])
 def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, dtype, ranks):
     """One adapter's factors hold infinities and NaN: the tokens of all other adapters, and of none, come out bit for bit
