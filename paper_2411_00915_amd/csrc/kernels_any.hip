@@ -34,22 +34,13 @@ __global__ __launch_bounds__(512) void shrink_rows_kernel(
     using slice = split_k<E, FB, TB, D, KTAIL, SUMS>;
     const int units = (K + slice::KUNIT - 1) / slice::KUNIT;
     const int p_begin = units * kpart / kparts, p_end = units * (kpart + 1) / kparts;
-    // whole lines to LDS need 16-byte rows, and 32-bit offsets a tile of less than 4 GB: else a wavefront per value
-    if ((reinterpret_cast<uintptr_t>(At) & 15) != 0 || (int64_t)t.cn * K * (int64_t)sizeof(E) > (1ll << 32)) {
-        const int k0 = p_begin * slice::KUNIT, k1 = min(K, p_end * slice::KUNIT);
-        for (int e = wave; e < t.nrows * t.cn; e += 8) {
-            const int tok = rows[e / t.cn], j = e % t.cn;
-            float acc = 0.f;
-            for (int k = k0 + lane; k < k1; k += 64) acc = fmaf(elem<E>::load(x + (int64_t)tok * ldx + k), elem<E>::load(At + (int64_t)j * K + k), acc);
-            acc = wave_sum(acc);
-            if (lane == 0) vp[(int64_t)tok * vsp.R + j] = s_a * acc;
-        }
-        return;
-    }
-    slice part(
-        K, At, x, wave, [&](int row) { return (int64_t)min(row, t.cn - 1) * K; },
-        [&](int row) { return (int64_t)rows[min(row, t.nrows - 1)] * ldx; });
-    part.run(p_begin + (p_end - p_begin) * wave / 8, p_begin + (p_end - p_begin) * (wave + 1) / 8);
+    const auto w_row = [&](int row) { return (int64_t)min(row, t.cn - 1) * K; };
+    const auto x_row = [&](int row) { return (int64_t)rows[min(row, t.nrows - 1)] * ldx; };
+    slice part(K, At, x, wave, w_row, x_row);
+    const int u_begin = p_begin + (p_end - p_begin) * wave / 8, u_end = p_begin + (p_end - p_begin) * (wave + 1) / 8;
+    // whole lines to LDS need 16-byte rows, and 32-bit offsets a tile of less than 4 GB
+    if ((reinterpret_cast<uintptr_t>(At) & 15) == 0 && (int64_t)t.cn * K * (int64_t)sizeof(E) <= (1ll << 32)) part.run(u_begin, u_end);
+    else part.run_anywhere(At, x, w_row, x_row, u_begin, u_end);
     part.park();
     __syncthreads();
     // a thread finishes F4 consecutive blocks (4 F4 consecutive rank rows) of one lane's token

@@ -298,6 +298,43 @@ struct split_k {
             slot = slot + 1 == D ? 0 : slot + 1;
         }
     }
+    // The same for rows of W at any address, 64 bits of it: 64-byte pieces straight to registers.  bf16 off a dword is
+    // fetched as the dwords that hold it (what they hold beside it is shifted out): lora_shrink of 256 tokens on 64 adapters
+    // of rank 2 to 256, K = 4096, 18.5 us, by loads at its own address 31.4, a wavefront per value 171; W aligned 10.
+    template <typename RowW, typename RowX>
+    __device__ __forceinline__ void run_anywhere(const E* W, const E* x, RowW w_row, RowX x_row, int u_begin, int u_end)
+    {
+        const bool odd = ES == 2 && (reinterpret_cast<uintptr_t>(W) & 3) != 0;         // every row of W (K % EPC == 0)
+        const E *wr[FB], *xp[TB];
+#pragma unroll
+        for (int f = 0; f < FB; ++f) wr[f] = W + w_row(4 * FB * (m >> 2) + 4 * f + (m & 3)) - (odd ? 1 : 0);
+#pragma unroll
+        for (int b = 0; b < TB; ++b) xp[b] = x + x_row(16 * b + m);
+        for (int u = u_begin; u < u_end; ++u) {
+            uint32_t fifth[2][FB];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int k = min(u * KUNIT + s * KSTEP + g * EPC, K - EPC);           // (past K: zeroed by compute)
+#pragma unroll
+                for (int f = 0; f < FB; ++f) {
+                    w[s][f].u = ldg_unaligned(wr[f] + k);
+                    if (odd) fifth[s][f] = *reinterpret_cast<const uint32_t*>(wr[f] + k + EPC);
+                }
+#pragma unroll
+                for (int b = 0; b < TB; ++b) xr[s][b].u = ldg_unaligned(xp[b] + k);
+            }
+            if (odd) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int f = 0; f < FB; ++f) {
+                        u32x4& q = w[s][f].u;
+                        q = u32x4{(q[0] >> 16) | (q[1] << 16), (q[1] >> 16) | (q[2] << 16), (q[2] >> 16) | (q[3] << 16), (q[3] >> 16) | (fifth[s][f] << 16)};
+                    }
+            }
+            compute(u);
+        }
+    }
     // leaves this wavefront's partial sums where its operands were (a barrier, then the workgroup adds them up)
     __device__ __forceinline__ void park()
     {
