@@ -35,11 +35,11 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
     E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, row_delta_args da)
 {
     constexpr int WAVES = 8;
-    // workgroups are dealt round-robin to the 8 XCDs; the token tiles of one feature tile follow each other on one
-    // XCD, so that its W rows come from memory once and are then in that XCD's L2
-    const int q = (int)blockIdx.x >> 3, xcd = (int)blockIdx.x & 7;
-    const int tile_t = q % tiles_t, tile_n = (q / tiles_t) * 8 + xcd;
-    if (tile_n >= tiles_n) return;
+    // workgroups are dealt round-robin to the 8 XCDs; every XCD gets an eighth of the tiles, the token tiles of one feature
+    // tile next to each other, so that its W rows come from memory once and are then in that XCD's L2
+    const int n_wg = tiles_n * tiles_t, xcd = (int)blockIdx.x & 7;
+    const int tile = xcd * (n_wg / 8) + min(xcd, n_wg % 8) + ((int)blockIdx.x >> 3);
+    const int tile_n = tile / tiles_t, tile_t = tile % tiles_t;
     const int n0 = tile_n * 16 * FB, t0 = tile_t * 16 * TB;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
@@ -179,7 +179,7 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
         }
     }
     LORA_LAUNCH(DELTA != NO_DELTA ? LORA_K_GEMM_SMALL_DELTA : LORA_K_GEMM_SMALL, (gemm_small_kernel<E, FB, TB, D, DELTA, KTAIL>),
-                dim3((unsigned)((tiles_n + 7) / 8 * 8 * tiles_t)), dim3(512), lds_bytes, stream, T, K, N, (const E*)x, ldx, (const E*)Wt, ldw,
+                dim3((unsigned)(tiles_n * tiles_t)), dim3(512), lds_bytes, stream, T, K, N, (const E*)x, ldx, (const E*)Wt, ldw,
                 (E*)y, ldy, tiles_n, tiles_t, ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0, da);
     return hipGetLastError();
 }
@@ -231,7 +231,7 @@ bool gemm_small_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const 
     if (T < 1 || N < 1 || K % epc || ldx % epc || ldw % epc || mis(x) || mis(Wt)) return false;
     if (dtype == LORA_BF16 && (ldy % 8 || mis(y))) return false;
     if ((int64_t)N * ldw * es >= (1ll << 32) || (int64_t)T * ldx * es >= (1ll << 32)) return false;      // 32-bit byte offsets
-    return (int64_t)((N + 15) / 16 + 8) * ((T + 15) / 16) < (1ll << 31);
+    return (int64_t)((N + 15) / 16) * ((T + 15) / 16) < (1ll << 31);
 }
 
 // microseconds (measured: 1.35 times the bound, and a start for every workgroup a compute unit gets)
