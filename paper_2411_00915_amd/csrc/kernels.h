@@ -88,6 +88,11 @@ struct gemm_removal {
     bool split_done = false;       // the shrink has written the split already
 };
 
+// which of the GEMMs below a bf16 problem that gemm_tiled_supported takes goes to; tiled: whether launch_gemm_tiled may take it;
+// GEMM_TILED_128: launch_gemm_tiled with its 128 x 128 tiles
+enum gemm_route_id { GEMM_SMALL = 1, GEMM_MID_128 = 2, GEMM_MID_192 = 3, GEMM_TILED = 4, GEMM_TILED_128 = 5 };
+gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool delta, bool tiled);
+
 // base GEMM  y = x Wt^T  (+ optional adapter delta in the epilogue when p != nullptr)
 hipError_t launch_gemm_general(int32_t T, int32_t K, int32_t N, int32_t dtype, const void* x, int64_t ldx,
                                const void* Wt, int64_t ldw, void* y, int64_t ldy,
@@ -98,15 +103,12 @@ bool gemm_tiled_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const 
 hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx,
                              const void* Wt, int64_t ldw, void* y, int64_t ldy,
                              const lora_plan* p, const lora_dev_tables* d, const float* v, void* vb, bool split_done,
-                             const gemm_removal& rm, const void* const* Bt, hipStream_t stream);
+                             const gemm_removal& rm, const void* const* Bt, hipStream_t stream, gemm_route_id route);
 
 // the contraction split over the wavefronts of a workgroup: small bf16 batches, every aligned fp32 batch
 bool gemm_small_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const void* x, int64_t ldx,
                           const void* Wt, int64_t ldw, const void* y, int64_t ldy);
 double gemm_small_time(int32_t T, int32_t K, int32_t N);
-// which of them a bf16 problem that gemm_tiled_supported takes goes to; ring: whether launch_gemm_tiled may take it
-enum gemm_route_id { GEMM_SMALL = 1, GEMM_MID_128 = 2, GEMM_MID_192 = 3, GEMM_TILED = 4 };
-gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool ring);
 hipError_t launch_gemm_mid(gemm_route_id route, int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw,
                            void* y, int64_t ldy, const lora_plan* p, const lora_dev_tables* d, const float* v,
                            const gemm_removal& rm, const void* const* Bt, hipStream_t stream);

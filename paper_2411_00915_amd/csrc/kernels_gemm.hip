@@ -24,8 +24,8 @@
 //   gemm_tiled_kernel: what neither that nor the kernels of smaller batches (kernels_gemm_small.hip,
 //     kernels_gemm_mid.hip; gemm_route chooses) take.  Loads HBM -> registers -> LDS, double buffered (dynamic LDS,
 //     2 x (BM + BT) x 128 bytes); workgroup tile = 4 wavefronts (2 x 2), each WB x WB MFMA blocks of 32 x 32:
-//     WB = 4: 256 features x 256 tokens x 64 k (large problems with K of at most 128, or past 32-bit offsets)
-//     WB = 2: 128 x 128 x 64 (operands past 32-bit offsets)
+//     WB = 4: 256 features x 256 tokens x 64 k (large problems with adapters and K of at most 128, or past 32-bit offsets)
+//     WB = 2: 128 x 128 x 64 (products of few stages without adapters, and operands past 32-bit offsets)
 //
 // Lane roles in v_mfma_f32_32x32x16_bf16 (D = A*B + C, A 32x16, B 16x32):
 //   lane l supplies A[row l%32][k 8*(l/32) .. +7], B[k 8*(l/32) .. +7][col l%32],
@@ -849,15 +849,15 @@ bool gemm_tiled_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const 
 hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx,
                              const void* Wt, int64_t ldw, void* y, int64_t ldy,
                              const lora_plan* p, const lora_dev_tables* d, const float* v, void* vb, bool split_done,
-                             const gemm_removal& rm, const void* const* Bt, hipStream_t stream)
+                             const gemm_removal& rm, const void* const* Bt, hipStream_t stream, gemm_route_id route)
 {
     const bool delta = p && (!p->perm.empty() || rm.plan);
     // the ring kernel: at least three stages of 64 k; rows of W and x addressed by 32-bit byte offsets, in its delta
     // part also the split of v.  The register-staged kernel takes what it does not: 256 x 256 tiles once there are enough
     // of them to fill the 256 compute units
-    const bool ring_ok = K > 2 * RK && (int64_t)N * ldw * 2 < (1ll << 32) && (int64_t)T * ldx * 2 < (1ll << 32) &&
+    const bool ring_ok = route == GEMM_TILED && K > 2 * RK && (int64_t)N * ldw * 2 < (1ll << 32) && (int64_t)T * ldx * 2 < (1ll << 32) &&
                          (!delta || ((int64_t)T * p->R * 4 < (1ll << 32) && (!rm.plan || (int64_t)T * rm.plan->R * 4 < (1ll << 32))));
-    const bool big = (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192;
+    const bool big = route == GEMM_TILED && (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192;
     gemm_delta_args da{};
     if (delta) {
         // the bf16 split of v, unless the shrink has written it already

@@ -359,28 +359,36 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
 //   5120 -> 5120,  1024 tokens 91 / 79 / 53 / 84 / 85,  2048: - / 116 / 99 / 84 / 137
 //   4096 -> 11008, 256 tokens 42 / 34 / 38 / 65 / 42,  512: 80 / 64 / 45 / - / 71,  1024: 157 / 98 / 84 / 73 / 115
 //   5120 -> 13824, 320 tokens 108 / 87 / 66 / - / 86,  640: 180 / 128 / 116 / 95 / 138
-gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool ring)
+// Products of few stages are the register-staged 128 x 128 tiles' (two on a compute unit, so that one's stores and first
+// loads run beside the other's stages; without adapters, whose infinities they do not keep apart).  Kernel times, small /
+// 128 / 192 / ring / register-staged: 2944 tokens, 32 -> 2568, 24.6 / 11.1 / 12.7 / - / 8.8;  4944, 128 -> 3496: 48.8 / 24.1 /
+// 21.7 / - / 18.6;  9901, 256 -> 1568: 53.4 / 24.5 / 24.6 / 23.4 / 18.1;  1452, 1024 -> 4096: 34.6 / 25.7 / 29.3 / 24.4 / 22.9.
+// The constants are fitted to such times of 2000 problems (8 to 16384 tokens, K 8 to 13824, N 64 to 13824): the choice takes
+// 0.4 % longer than the best of the five on average, 1.24 times at worst.
+gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool delta, bool tiled)
 {
     if ((int64_t)N * ldw * 2 >= (1ll << 32) || (int64_t)T * ldx * 2 >= (1ll << 32)) return GEMM_TILED;   // 32-bit byte offsets
     const double stages = (K + 63) / 64;
-    auto rounds = [&](int32_t bm, int32_t bt, double fixed, double idle, double more, int power) {
+    // slots: tiles the chip holds at a time
+    auto rounds = [&](int32_t bm, int32_t bt, double slots, double fixed, double idle, double more, int power) {
         const int64_t tiles = (int64_t)((N + bm - 1) / bm) * ((T + bt - 1) / bt);
-        const int64_t full = tiles / 256;
-        const double left = (double)(tiles % 256) / 256;
+        const int64_t full = tiles / (int64_t)slots;
+        const double left = (double)(tiles % (int64_t)slots) / slots;
         double us = full * (fixed + stages * (idle + more));
         if (left > 0) us += fixed + stages * (idle + more * (power == 2 ? left * left : left));
         return us;
     };
-    const bool ring_ok = ring && K > 128;                     // (its fewest stages: three)
-    if (ring && !ring_ok && (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192) return GEMM_TILED;
+    const bool ring = tiled && K > 128;                       // (its fewest stages: three)
+    if (tiled && !ring && delta && (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192) return GEMM_TILED;
     gemm_route_id best = GEMM_SMALL;
     double us = gemm_small_time(T, K, N);
     auto take = [&](gemm_route_id id, double t) {
         if (t < us) { us = t; best = id; }
     };
-    take(GEMM_MID_128, rounds(128, 128, 2.5, 0.43, 0.10, 1));
-    take(GEMM_MID_192, rounds(192, 128, 2.5, 0.51, 0.19, 1));
-    if (ring_ok) take(GEMM_TILED, rounds(256, 256, 4.0, 0.95, 0.55, 2));
+    take(GEMM_MID_128, rounds(128, 128, 256, 2.0, 0.43, 0.10, 1));
+    take(GEMM_MID_192, rounds(192, 128, 256, 3.1, 0.51, 0.19, 1));
+    if (ring) take(GEMM_TILED, rounds(256, 256, 256, 4.4, 0.95, 0.55, 2));
+    if (!delta) take(GEMM_TILED_128, 0.3 + rounds(128, 128, 512, 1.7, 0.585, 0.56, 1));
     return best;
 }
 

@@ -234,12 +234,12 @@ bool gemm_small_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const 
     return (int64_t)((N + 15) / 16) * ((T + 15) / 16) < (1ll << 31);
 }
 
-// microseconds (measured: 1.35 times the bound, and a start for every workgroup a compute unit gets)
+// microseconds (measured: 1.35 times the bound, and a start for every workgroup a compute unit gets; see gemm_route)
 double gemm_small_time(int32_t T, int32_t K, int32_t N)
 {
     const small_tile t = choose_small_tile(T, K, N, LORA_BF16);
     const int64_t wgs = (int64_t)((N + 16 * t.fb - 1) / (16 * t.fb)) * ((T + 16 * t.tb - 1) / (16 * t.tb));
-    return 1.35e6 * small_cost(t, T, K, N, LORA_BF16) + 2.0 + (wgs + 255) / 256;
+    return 1.35e6 * small_cost(t, T, K, N, LORA_BF16) + 1.0 + 0.75 * ((wgs + 255) / 256);
 }
 
 // p != nullptr: fold the adapter delta in; v holds the shrink's output.  rm: likewise for the removal of the merged
