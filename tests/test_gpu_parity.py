@@ -47,6 +47,16 @@ def _y_in(w, seed=99):
     return wl.round_to_bf16(y) if w.dtype == "bf16" else y
 
 
+def _launched(call):
+    """names of the library's kernels that call() launches"""
+    B.lora_timing_begin()
+    try:
+        call()
+    finally:
+        names = set(B.lora_timing_end())
+    return names
+
+
 def run_delta_case(w, variant=B.LORA_VARIANT_AUTO, ld_pad=0, check_beta0=True, rows=None):
     """shrink + expand through the ABI vs the oracle.  `rows` limits the oracle
     comparison of y to a sample of tokens (v is always checked in full)."""
@@ -290,7 +300,7 @@ def _check_f32_delta(w, ld_pad=0, shift=0):
             keep.append(buf)
             ptrs.append(buf.data_ptr() + 4 * shift)
         At, Bt = (torch.tensor(q, dtype=torch.int64, device=DEV) for q in (ptrs[:w.num_adapters], ptrs[w.num_adapters:]))
-    plan = device.make_plan(w)
+    plan = device.make_plan(w, B.LORA_VARIANT_TILED)                   # (small problems would take the general expand)
     R, v_bytes, _ = B.lora_plan_query(plan)
     P = B.lora_plan_export(plan)["v_parts"]
     tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
@@ -480,7 +490,7 @@ def test_any_rank_expand(T, N, ranks, max_seg):
         ptrs.append(buf.data_ptr() + 2 * (i % 7 + 1))
     shifted = torch.tensor(ptrs, dtype=torch.int64, device=DEV)
     out = {}
-    for variant in (B.LORA_VARIANT_AUTO, B.LORA_VARIANT_GENERAL):
+    for variant in (B.LORA_VARIANT_TILED, B.LORA_VARIANT_GENERAL):
         plan = device.make_plan(w, variant)
         _, v_bytes, _ = B.lora_plan_query(plan)
         v = torch.full((v_bytes // 4,), float("nan"), dtype=torch.float32, device=DEV)
@@ -502,7 +512,19 @@ def test_any_rank_expand(T, N, ranks, max_seg):
         plan.destroy()
 
 
-def _one_adapter_plan(T, K, N, rank, variant=B.LORA_VARIANT_AUTO):
+@pytest.mark.parametrize("T,N,ranks,dtype,kernel", [
+    (16, 4100, (91, 92), "bf16", "expand_rows_kernel"), (16, 4040, (91, 92), "bf16", "expand_general_kernel"),
+    (700, 1240, (7, 8), "f32", "expand_rows_kernel"), (700, 1060, (7, 8), "f32", "expand_general_kernel"), (700, 40, (17, 20), "f32", "expand_rows_kernel")])
+def test_expand_takes_the_general_kernel_below_six_million_products(T, N, ranks, dtype, kernel):
+    """Either side of the line between the general and the any-rank expand; both against the oracle."""
+    w = wl.random_case(1850 + T + N, T, 2304, N, 3, ranks, dtype=dtype, max_seg=60, scales=(0.5, -1.0))
+    products = int(w.adapter_rank[oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)].sum()) * N
+    assert (products >= 6000000) == (kernel == "expand_rows_kernel") or ranks == (17, 20), products
+    names = _launched(lambda: run_delta_case(w))
+    assert kernel in names and len([n for n in names if "expand" in n]) == 1, names
+
+
+def _one_adapter_plan(T, K, N, rank, variant=B.LORA_VARIANT_TILED):
     return B.lora_plan(T, np.array([0, T], np.int32), np.array([0], np.int32), np.array([rank], np.int32), np.array([1.0], np.float32),
                        K, N, B.LORA_BF16, variant)
 
@@ -547,7 +569,7 @@ def test_any_rank_expand_of_infinities(rank):
     """Infinities and NaN in v and Bt come out as from fp32 products: against the general kernel."""
     T, N = 21, 203
     out = []
-    for variant in (B.LORA_VARIANT_AUTO, B.LORA_VARIANT_GENERAL):
+    for variant in (B.LORA_VARIANT_TILED, B.LORA_VARIANT_GENERAL):
         plan = _one_adapter_plan(T, 64, N, rank, variant)
         R, v_bytes, _ = B.lora_plan_query(plan)
         rows, Bt = _non_finite_rows(T, R, N, rank)
@@ -570,16 +592,6 @@ def test_large_batch_expand_writes_nothing_past_an_n_off_eight():
     """N no multiple of 8 under a padded leading dimension, a batch that would take the streaming kernels: the columns
     between N and ldy stay as they are."""
     run_delta_case(wl.random_case(1900, 1100, 1024, 204, 9, (16, 64), max_seg=200, frac_none=0.1, scales=(1.0, -0.5)), ld_pad=4)
-
-
-def _launched(call):
-    """names of the library's kernels that call() launches"""
-    B.lora_timing_begin()
-    try:
-        call()
-    finally:
-        names = set(B.lora_timing_end())
-    return names
 
 
 @pytest.mark.parametrize("T,dtype,ranks", [(90, "f32", (8, 20)), (90, "bf16", (5, 100)), (700, "bf16", (5, 100))])
