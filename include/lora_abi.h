@@ -336,7 +336,10 @@ lora_status lora_base_gemm(int32_t num_tokens, int32_t k, int32_t n, int32_t dty
  * adapter-sorted order and adds each adapter's v B_a to the accumulators of
  * the rows that carry it (as extra k-stages of its pipeline, or wavefront by
  * wavefront after the K loop, depending on the kernel).  LORA_ERR_WORKSPACE if
- * the workspace is too small.
+ * the workspace is too small.  Infinities and NaN in one adapter's factors reach
+ * that adapter's tokens only -- except with bf16, K <= 128 and 192 tiles of 256 x
+ * 256 or more, or with x or W of 4 GB and more: there they also reach the tokens
+ * that share a tile of 256 rows with them.
  */
 lora_status lora_fused_forward(lora_plan* plan, const void* x, int64_t ldx,
                                const void* Wt, int64_t ldw,

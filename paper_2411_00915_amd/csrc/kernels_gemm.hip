@@ -722,12 +722,18 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
                 }
 #pragma unroll
                 for (int b = 0; b < WX; ++b) {
-                    if (((members >> (16 * b)) & 0xffffull) == 0) continue;      // wavefront-uniform
+                    const uint64_t in16 = (members >> (16 * b)) & 0xffffull;      // wavefront-uniform
+                    if (in16 == 0) continue;
+                    const bool mine = (in16 >> l16) & 1ull;
 #pragma unroll
                     for (int blk = 0; blk < WA; ++blk) {
-                        acc[blk][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb[blk].v, vh[b].v, acc[blk][b], 0, 0, 0);
-                        acc[blk][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb[blk].v, vl[b].v, acc[blk][b], 0, 0, 0);
+                        floatx4 e = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb[blk].v, vh[b].v, acc[blk][b], 0, 0, 0);
+                        e = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb[blk].v, vl[b].v, e, 0, 0, 0);
+                        // (a product with zeros would carry the adapter's infinities over to other tokens)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[blk][b][i] = mine ? e[i] : acc[blk][b][i];
                     }
+                    __builtin_amdgcn_sched_barrier(0);               // (one block of tokens at a time, or registers spill)
                 }
             }
         };

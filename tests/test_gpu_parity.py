@@ -675,11 +675,13 @@ def test_any_rank_fused_forward_of_infinities(T, N, rank, kernel):
     assert bool(((got[f] - want[f]).abs() <= 2.0 ** -7 * want[f].abs() + 1e-3).all())
 
 
-@pytest.mark.parametrize("T,dtype,ranks", [(90, "f32", (8, 20)), (90, "bf16", (8, 16)), (90, "bf16", (5, 100)), (700, "bf16", (8, 16)), (700, "bf16", (5, 100))])
-def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, dtype, ranks):
+@pytest.mark.parametrize("T,N,dtype,ranks,kernel", [
+    (90, 520, "f32", (8, 20), "small"), (90, 520, "bf16", (8, 16), "small"), (90, 520, "bf16", (5, 100), "small"),
+    (700, 5000, "bf16", (8, 16), "mid"), (700, 5000, "bf16", (5, 100), "mid"), (3585, 3600, "bf16", (8, 16), "ring")])
+def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, N, dtype, ranks, kernel):
     """One adapter's factors hold infinities and NaN: the tokens of all other adapters, and of none, come out bit for bit
-    as with that adapter's factors finite (small and medium GEMM, fp32 and any rank)."""
-    w = wl.random_case(2300 + T + ranks[0], T, 264, 520 if T < 512 else 2000, 6, ranks, dtype=dtype, max_seg=7, frac_none=0.2)
+    as with that adapter's factors finite (small, medium and ring GEMM, fp32 and any rank)."""
+    w = wl.random_case(2300 + T + ranks[0], T, 264, N, 6, ranks, dtype=dtype, max_seg=7, frac_none=0.2)
     dl = device.to_device(w, DEV, with_w=True)
     tdt = device.torch_dtype(w)
     plan = device.make_plan(w)
@@ -694,8 +696,8 @@ def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, dtype, rank
             Bt = Bt.clone()
             Bt[bad] = keep[-1].data_ptr()
         y = torch.empty((w.T, w.N), dtype=tdt, device=DEV)
-        B.lora_fused_forward(plan, dl.x, w.K, dl.Wt, w.K, dl.At_ptrs, Bt, y, w.N, ws, ws.numel())
-        torch.cuda.synchronize()
+        names = _launched(lambda: B.lora_fused_forward(plan, dl.x, w.K, dl.Wt, w.K, dl.At_ptrs, Bt, y, w.N, ws, ws.numel()))
+        assert f"gemm_{kernel}_kernel<delta>" in names
         out.append(y)
     others = torch.from_numpy(tok != bad).to(DEV)
     assert bool(others.any()) and bool(torch.isfinite(out[0]).all())
