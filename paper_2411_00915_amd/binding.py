@@ -216,6 +216,13 @@ def lora_tuning_table_get() -> list:
             for i in range(n)]
 
 
+def lora_gemm_choice(tokens: int, k: int, n: int, dtype: int, delta: bool):
+    """(kernel, feature blocks, token blocks): what an aligned product takes; kernel 1 small, 2 and 3 medium, 4 ring (or
+    register-staged), 5 register-staged 128 x 128; the blocks of 16 are the small kernel's tile."""
+    c = int(_lib.lora_gemm_choice(int(tokens), int(k), int(n), int(dtype), int(delta)))
+    return c >> 16, c >> 8 & 255, c & 255
+
+
 LORA_PROBE_EMPTY, LORA_PROBE_READ, LORA_PROBE_MFMA = 0, 1, 2
 
 

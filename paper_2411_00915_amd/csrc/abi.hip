@@ -422,6 +422,14 @@ extern "C" lora_status lora_base_gemm(int32_t T, int32_t K, int32_t N, int32_t d
     return e == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
 }
 
+// Not part of the ABI: which kernel and which tile of it an aligned product of below 4 GB takes, so that tests can tell
+// what their shapes cover: gemm_route_id << 16 | gemm_small_tile (of the small GEMM; else 0)
+extern "C" int32_t lora_gemm_choice(int32_t T, int32_t K, int32_t N, int32_t dtype, int32_t delta)
+{
+    const gemm_route_id route = dtype == LORA_F32 ? GEMM_SMALL : gemm_route(T, K, N, K, K, delta != 0, true);
+    return (int32_t)route << 16 | (route == GEMM_SMALL ? gemm_small_tile(T, K, N, dtype) : 0);
+}
+
 extern "C" lora_status lora_merge(int32_t L, int32_t N, int32_t K, int32_t r, float scale, int32_t dtype,
                                   int32_t variant, void* const* d_Wt_ptrs, int64_t ldw,
                                   const void* const* d_At_ptrs, const void* const* d_Bt_ptrs, void* hip_stream)

@@ -109,6 +109,7 @@ hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int
 bool gemm_small_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const void* x, int64_t ldx,
                           const void* Wt, int64_t ldw, const void* y, int64_t ldy);
 double gemm_small_time(int32_t T, int32_t K, int32_t N);
+int32_t gemm_small_tile(int32_t T, int32_t K, int32_t N, int32_t dtype);   // 16-feature blocks << 8 | 16-token blocks
 hipError_t launch_gemm_mid(gemm_route_id route, int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw,
                            void* y, int64_t ldy, const lora_plan* p, const lora_dev_tables* d, const float* v,
                            const gemm_removal& rm, const void* const* Bt, hipStream_t stream);

@@ -245,6 +245,12 @@ double gemm_small_time(int32_t T, int32_t K, int32_t N)
     return 1.35e6 * small_cost(t, T, K, N, LORA_BF16) + 1.0 + 0.75 * ((wgs + 255) / 256);
 }
 
+int32_t gemm_small_tile(int32_t T, int32_t K, int32_t N, int32_t dtype)
+{
+    const small_tile t = choose_small_tile(T, K, N, dtype);
+    return t.fb << 8 | t.tb;
+}
+
 // p != nullptr: fold the adapter delta in; v holds the shrink's output.  rm: likewise for the removal of the merged
 // adapter (mixture mode).  The plan has its row order (p->order) where there is any delta.
 hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, const void* x, int64_t ldx, const void* Wt, int64_t ldw,

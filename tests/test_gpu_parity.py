@@ -233,17 +233,63 @@ def test_cfg5_large(shape):
     run_forward_case(w, n_sample=128)
 
 
-@pytest.mark.parametrize("T,K,N", [(3585, 128, 3600), (3600, 160, 3585), (3585, 200, 3600)])
-def test_large_tile_gemm_ragged_shapes(T, K, N):
-    """The 256 x 256 tile kernels on ragged T and N with few stages: the shortest ring (four stages of 32 k), an odd
-    number of stages, and a K that is no multiple of 32 (staged through registers, with a K tail); base GEMM and
-    fused forward, with mixed ranks, tokens without adapter and several adapters per tile."""
+@pytest.mark.parametrize("T,K,N,kernel", [(3585, 128, 3600, "tiled"), (3585, 120, 3600, "tiled"), (3600, 72, 3592, "tiled"),
+                                           (3600, 160, 3592, "ring"), (3585, 200, 3600, "ring")])
+def test_large_tile_gemm_ragged_shapes(T, K, N, kernel):
+    """The 256 x 256 tile kernels on ragged T and N with few stages: register-staged with two of 64 k, whole, with one chunk
+    missing and with one chunk only in the last; the ring with three and four.  Base GEMM and fused forward, with mixed
+    ranks, tokens without adapter and several adapters per tile."""
     w = wl.random_case(700 + K, T, K, N, 40, (8, 16, 24, 32, 64, 128), max_seg=90, frac_none=0.15, scales=(0.5, 2.0))
-    run_forward_case(w, n_sample=160)
+    assert f"gemm_{kernel}_kernel<delta>" in _launched(lambda: run_forward_case(w, n_sample=160))
 
 
+@pytest.mark.parametrize("T,K,N,ldx,ranks,kernel", [
+    (300, 264, 520, 7200000, (8, 64), "gemm_tiled_kernel<delta>"), (300, 256, 520, 7200000, (128,), "gemm_tiled_kernel<delta>"),
+    (3600, 264, 3600, 600000, (8, 64), "gemm_tiled_kernel<delta>"), (3600, 256, 3600, 600000, (16, 128), "gemm_tiled_kernel<delta>"),
+    (40, 264, 136, 54000000, (12, 100), "gemm_general_kernel")])
+def test_gemm_of_operands_past_four_gigabytes(T, K, N, ldx, ranks, kernel):
+    """x with rows so far apart that its last ones start past 2^32 bytes: the register-staged kernel in both tile sizes with
+    more than two stages, with and without a K tail, and the general kernel for other ranks; base GEMM and fused forward."""
+    w = wl.random_case(720 + T + K, T, K, N, 9, ranks, max_seg=40, frac_none=0.15, scales=(0.5, 2.0))
+    dl = device.to_device(w, DEV, with_w=True)
+    assert 2 ** 32 <= 2 * T * ldx < 2 ** 32 + 2 ** 26
+    x = torch.empty((T, ldx), dtype=torch.bfloat16, device=DEV)
+    x[:, :K] = dl.x
+    plan = device.make_plan(w)
+    ws = torch.empty(max(B.lora_plan_query(plan)[2], 256), dtype=torch.uint8, device=DEV)
+    y = torch.full((T, N), 9.0, dtype=torch.bfloat16, device=DEV)
+    rows = np.unique(np.concatenate([np.arange(0, T, max(1, T // 150)), [T - 1]]))
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    B.lora_base_gemm(T, K, N, dl.dtype, x, ldx, dl.Wt, K, y, N)
+    torch.cuda.synchronize()
+    _assert_close(_to_np(y)[rows], oracle.base(w.x, w.W, rows=rows), BF16_TOL, "base gemm")
+    y.fill_(9.0)
+    assert kernel in _launched(lambda: B.lora_fused_forward(plan, x, ldx, dl.Wt, K, dl.At_ptrs, dl.Bt_ptrs, y, N, ws, ws.numel()))
+    _assert_close(_to_np(y)[rows], oracle.forward(w.x, w.W, tok, ad, rows=rows), BF16_TOL, "fused forward")
+    plan.destroy()
+
+
+@pytest.mark.parametrize("T,K,N", [(2900, 32, 2568), (3000, 72, 1544), (5000, 128, 1160), (1400, 264, 5000), (700, 200, 9000)])
+def test_products_of_few_stages(T, K, N):
+    """Base products that the register-staged 128 x 128 tiles take: one stage to five, with and without a K tail, ragged T
+    and N; against the oracle on a sample of rows."""
+    w = wl.random_case(760 + K, T, K, N, 1, (8,), max_seg=T, frac_none=1.0)
+    dl = device.to_device(w, DEV, with_w=True)
+    y = torch.full((T + 1, N), 9.0, dtype=torch.bfloat16, device=DEV)
+    names = _launched(lambda: B.lora_base_gemm(T, K, N, dl.dtype, dl.x, K, dl.Wt, K, y, N))
+    assert names == {"gemm_tiled_kernel"}
+    rows = np.unique(np.concatenate([np.arange(0, T, max(1, T // 200)), [T - 1]]))
+    _assert_close(_to_np(y)[rows], oracle.base(w.x, w.W, rows=rows), BF16_TOL, "base gemm")
+    assert bool((y[T] == 9.0).all()) and bool((y[:T] != 9.0).any(dim=1).all())
+
+
+# every tile of the small GEMM for bf16 (ranks of the tuned kernels and others) and for fp32: see
+# test_planner.test_small_gemm_shapes_cover_every_tile
 SMALL_GEMM_SHAPES = [(1, 8, 8), (1, 4096, 4096), (15, 72, 40), (17, 1000, 1096), (33, 64, 16), (47, 520, 4104), (65, 128, 2056),
-                     (100, 3208, 1000), (129, 584, 4096), (257, 72, 4104), (500, 640, 1480), (511, 136, 72)]
+                     (100, 3208, 1000), (129, 584, 4096), (257, 72, 1000), (500, 640, 1480), (511, 136, 72), (16, 1000, 1096),
+                     (34, 200, 2056), (45, 520, 6008), (46, 264, 6008), (47, 520, 1480), (48, 200, 4104), (90, 264, 5000), (91, 200, 5000),
+                     (131, 520, 2504), (190, 264, 5000), (191, 264, 5000)]
 
 
 def _small_gemm_case(T, K, N, dtype):
@@ -257,7 +303,8 @@ def test_small_batch_gemm_tiles_and_remainders(T, K, N):
     """The GEMM that splits K over the wavefronts of a workgroup: every tile shape its rule picks, remainders of
     tokens and features, fewer units of K than wavefronts, K tails of one chunk, tokens without adapter, mixture mode."""
     w = _small_gemm_case(T, K, N, "bf16")
-    run_forward_case(w)
+    names = _launched(lambda: run_forward_case(w))
+    assert ("gemm_small_kernel<delta>" in names) == (B.lora_gemm_choice(T, K, N, B.LORA_BF16, True)[0] == 1)
     if T > 16:
         run_mixture_case(w, 2)
 
@@ -708,16 +755,16 @@ def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, N, dtype, r
 
 
 @pytest.mark.parametrize("T,K,N,ranks", [
-    (600, 8, 1000, (8, 16)), (513, 72, 4104, (8, 16, 64)), (640, 264, 2000, (24, 128)), (1025, 328, 1160, (1, 5, 20, 100, 256)),
+    (600, 8, 3000, (8, 16)), (513, 72, 4104, (8, 16, 64)), (640, 264, 2000, (24, 128)), (1025, 328, 2056, (1, 5, 20, 100, 256)),
     (777, 136, 5000, (8, 64)), (777, 200, 5000, (16, 128)), (700, 264, 5000, (3, 8, 100)), (777, 1160, 5000, (8, 64, 128)),
-    (1111, 640, 5120, (16, 64)), (1300, 200, 776, (8, 12, 64)), (2049, 1032, 520, (64,)), (1400, 328, 1544, (16, 32))])
+    (1111, 640, 5120, (16, 64)), (1111, 264, 5120, (16, 64)), (1300, 200, 776, (8, 12, 64)), (2049, 1032, 1032, (64,)), (1400, 328, 1544, (16, 32))])
 def test_medium_batch_gemm_stages_and_remainders(T, K, N, ranks):
     """The GEMM of 128-token tiles in both widths: fewer stages than its ring holds, as many, one more, K tails of one
     chunk and of all but one; remainders of tokens and features; any rank; tokens without adapter, mixture mode."""
     # (scales of one magnitude s: rounding W' costs u sqrt(1 + s_m^2) and y itself u sqrt(1 + s_own^2), so mixture mode
     # stays within u sqrt(2) = 2.4e-3 of plain inference, under run_mixture_case's bound, only where s_m is not the larger)
     w = wl.random_case(1600 + T + K, T, K, N, 12, ranks, max_seg=60, frac_none=0.15, scales=(1.0, -1.0))
-    run_forward_case(w, n_sample=256)
+    assert "gemm_mid_kernel<delta>" in _launched(lambda: run_forward_case(w, n_sample=256))
     run_mixture_case(w, 2, n_sample=256)
 
 
@@ -731,14 +778,13 @@ def test_ring_gemm_shortest_rings_and_k_tails(K):
     run_mixture_case(w, 3, n_sample=96)
 
 
-@pytest.mark.parametrize("K", [256, 200])
-def test_large_tile_gemm_with_hundreds_of_adapters_per_tile(K):
-    """Single-token segments of 400 adapters: a 256-row tile carries about 250 adapters.  K = 256: the ring kernel,
-    whose wavefronts then walk about 60 adapters each for their 64 rows.  K = 200 (no multiple of 32): the
-    register-staged kernel with far more adapter stages than it caches per tile (256), so that it reads the stages
-    beyond its list from memory."""
+@pytest.mark.parametrize("K,kernel", [(256, "ring"), (120, "tiled")])
+def test_large_tile_gemm_with_hundreds_of_adapters_per_tile(K, kernel):
+    """Single-token segments of 400 adapters: a 256-row tile carries about 250 adapters.  The ring kernel's wavefronts then
+    walk about 60 adapters each for their 64 rows; the register-staged kernel has far more adapter stages than it caches
+    per tile (256), so that it reads the stages beyond its list from memory."""
     w = wl.random_case(811, 3840, K, 3328, 400, (32, 64), max_seg=1, frac_none=0.05)
-    run_forward_case(w, n_sample=160)
+    assert f"gemm_{kernel}_kernel<delta>" in _launched(lambda: run_forward_case(w, n_sample=160))
 
 
 @pytest.mark.parametrize("shape", ["decode", "prefill"])
@@ -809,12 +855,16 @@ def test_ragged_small_cases(variant):
 def test_fused_forward_with_a_single_k_stage():
     # K of at most 64 is one stage of the register-staged GEMM: the first stage fetched ahead is then already an
     # adapter stage, whose descriptors every thread reads from LDS (a missing barrier there once let a workgroup read
-    # them before they were written; found by a random sweep).  Several row tiles, many adapters per tile, plain and
-    # mixture mode, different batches back to back.
-    for seed, (T, K, N, n_a, ranks) in enumerate([(700, 64, 200, 9, (64,)), (300, 40, 328, 30, (8, 16, 32)),
-                                                  (520, 64, 136, 5, (128,)), (130, 32, 72, 12, (8, 64))]):
+    # them before they were written; found by a random sweep).  Many adapters per tile, plain and mixture mode, different
+    # batches back to back; batches so large that this kernel takes them, and small ones, which the small and medium
+    # GEMMs take.
+    for seed, (T, K, N, n_a, ranks, large) in enumerate([(3700, 64, 3400, 9, (64,), True), (3585, 40, 3600, 300, (8, 16, 32), True),
+                                                         (3600, 64, 3592, 5, (128,), True), (3850, 32, 3336, 120, (8, 64), True),
+                                                         (700, 64, 200, 9, (64,), False), (300, 40, 328, 30, (8, 16, 32), False),
+                                                         (520, 64, 136, 5, (128,), False), (130, 32, 72, 12, (8, 64), False)]):
         w = wl.random_case(600 + seed, T, K, N, n_a, ranks, max_seg=3, frac_none=0.1, scales=(1.0, 2.0, -0.5))
-        run_forward_case(w, n_sample=min(T, 160), variant=B.LORA_VARIANT_TILED)
+        names = _launched(lambda: run_forward_case(w, n_sample=min(T, 160), variant=B.LORA_VARIANT_TILED))
+        assert ("gemm_tiled_kernel<delta>" in names) == large, names
         run_mixture_case(w, seed % n_a, n_sample=min(T, 96))
 
 

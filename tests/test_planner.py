@@ -424,3 +424,14 @@ def test_streaming_tiles_for_small_batches_with_long_groups():
     assert shrink_rows(256, 16, 64)[0] == 16 and shrink_rows(256, 16, 64)[1] <= 32   # short groups, ranks <= 64: 16-token tiles of the decode launch
     assert shrink_rows(48, 4, 128)[1] <= 64                     # 48 tokens in groups of 12: too small for the streaming kernels
     assert shrink_rows(256, 1, 128, shrink_stream_min_tokens=1 << 30)[1] <= 64       # streaming switched off
+
+
+def test_small_gemm_shapes_cover_every_tile():
+    """The shapes of the GPU tests of the GEMM that splits K over its wavefronts pick every tile it has: in bf16 with
+    ranks of the tuned kernels (even token counts) and with others (odd ones), and in fp32."""
+    from test_gpu_parity import SMALL_GEMM_SHAPES
+    tiles = {(4, 4), (2, 4), (4, 2), (2, 2), (4, 1), (1, 2), (1, 1)}
+    for odd in (0, 1):
+        picked = [B.lora_gemm_choice(T, K, N, B.LORA_BF16, True) for T, K, N in SMALL_GEMM_SHAPES if T % 2 == odd]
+        assert {c[1:] for c in picked if c[0] == 1} == tiles, odd
+    assert {B.lora_gemm_choice(T, K, N, B.LORA_F32, True)[1:] for T, K, N in SMALL_GEMM_SHAPES if K >= 32} == tiles
