@@ -4,6 +4,9 @@
 #include <stdint.h>
 
 typedef unsigned short bf16_t;   // raw bfloat16 bits
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
@@ -35,6 +38,16 @@ __device__ __forceinline__ float wave_sum(float v)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
+}
+
+// Loads straight to LDS: lane i's 16 bytes at base + off -> LDS byte address lds_base + 16 i (base and lds_base
+// wavefront-uniform).  Issued from inline assembly, so the waits for them are written out.  M0 carries the LDS address;
+// nothing else in the kernels that use this uses M0 (LDS instructions of gfx9 and later do not read it).
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
+__device__ __forceinline__ void load16_to_lds(const char* base, uint32_t off, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base) : "memory");
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs; every XCD gets a contiguous run of tiles (so its L2 sees

@@ -34,18 +34,11 @@
 // block stands for feature 16h + 4q + p, so a lane (h = l/32) ends up with the
 // 16 consecutive features 16h .. 16h+15 of its token: 32-byte stores of y.
 #include <atomic>
-#include "device_util.h"
 #include "kernels.h"
 #include "launch.h"
+#include "mfma_tile.h"
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-
-union op16 {
-    uint4 u;
-    bf16x8 v;
-};
 
 namespace {
 
@@ -58,44 +51,17 @@ constexpr int BK = 64;    // k per stage; a tile row is 128 bytes = 8 chunks of 
 __device__ __forceinline__ int lds_slot(int row, int chunk) { return row * 8 + (chunk ^ ((row >> 1) & 7)); }
 __device__ __forceinline__ int lds_slot_w(int row, int chunk) { return row * 8 + (chunk ^ (((row >> 1) & 3) | ((row >> 2) & 4))); }
 
-// 16-byte loads through pointers that come out of a table or are computed from one: the address space is stated,
-// or they would be flat loads (which also count as LDS traffic, so that waits on them are coarse)
-__device__ __forceinline__ uint4 ldg16(const void* p)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-    const u32x4 r = *(const __attribute__((address_space(1))) u32x4*)(uintptr_t)p;
-    return uint4{r[0], r[1], r[2], r[3]};
-#else       // the host pass only parses device functions
-    return *reinterpret_cast<const uint4*>(p);
-#endif
-}
-
-// the same from a wavefront-uniform base plus a 32-bit byte offset per lane (one address register per lane for any
-// number of loads that share the offset)
+// 16-byte load from a wavefront-uniform base plus a 32-bit byte offset per lane (one address register per lane for any
+// number of loads that share the offset); the base comes out of a table: the address space is stated, as in ld16
 __device__ __forceinline__ uint4 ldg16_off(const void* uniform_base, uint32_t byte_off)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
     const __attribute__((address_space(1))) char* b = (const __attribute__((address_space(1))) char*)(uintptr_t)uniform_base;
     const u32x4 r = *(const __attribute__((address_space(1))) u32x4*)(b + byte_off);
     return uint4{r[0], r[1], r[2], r[3]};
 #else
     return *reinterpret_cast<const uint4*>(static_cast<const char*>(uniform_base) + byte_off);
 #endif
-}
-
-__device__ __forceinline__ void split_bf16(const float* f, op16& hi, op16& lo)
-{
-    uint32_t h[8], l[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const bf16_t hb = f32_to_bf16(f[i]);
-        h[i] = hb;
-        l[i] = f32_to_bf16(f[i] - bf16_to_f32(hb));
-    }
-    hi.u = uint4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-    lo.u = uint4{l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16)};
 }
 
 extern __shared__ uint4 gemm_lds[];
@@ -493,22 +459,6 @@ constexpr int GRANULE = 16384;          // bytes: 128 rows x 128 bytes
 // permutation); each f takes eight different values over the rows that eight consecutive lanes read.
 __device__ __forceinline__ int ring_f_x(int row) { return row & 7; }
 __device__ __forceinline__ int ring_f_w(int row) { return (row & 3) | ((row >> 2) & 4); }
-
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
-
-// lane i's 16 bytes at base + off -> LDS byte address lds_base + 16 i (base and lds_base wavefront-uniform).  M0
-// carries the LDS address; nothing else in these kernels uses M0 (LDS instructions of gfx9 and later do not read it).
-__device__ __forceinline__ void load16_to_lds(const char* base, uint32_t off, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base) : "memory");
-}
-__device__ __forceinline__ const char* uniform_ptr(const char* p)
-{
-    const uint64_t u = reinterpret_cast<uint64_t>(p);
-    return reinterpret_cast<const char*>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u) |
-                                         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32)) << 32));
-}
 
 // KTAIL: K is no multiple of 64.  The last stage's chunks past K are fetched from the row's first chunk of that stage
 // (in bounds) and zeroed in the registers.

@@ -7,9 +7,6 @@
 #pragma once
 #include "device_util.h"
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-
 union op16 {            // one 16-byte MFMA operand
     uint4 u;
     bf16x8 v;
@@ -21,7 +18,6 @@ union op16 {            // one 16-byte MFMA operand
 __device__ __forceinline__ uint4 ld16(const bf16_t* p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
     const u32x4 r = *(const __attribute__((address_space(1))) u32x4*)(uintptr_t)p;
     return uint4{r[0], r[1], r[2], r[3]};
 #else       // the host pass only parses device functions
@@ -35,7 +31,6 @@ __device__ __forceinline__ uint4 ld16_global(const bf16_t* p) { return ld16(p); 
 __device__ __forceinline__ uint4 ld16_stream(const bf16_t* p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
     const u32x4 r = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4*)(uintptr_t)p);
     return uint4{r[0], r[1], r[2], r[3]};
 #else
@@ -45,7 +40,6 @@ __device__ __forceinline__ uint4 ld16_stream(const bf16_t* p)
 __device__ __forceinline__ void st16_stream(bf16_t* p, uint4 val)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
     const u32x4 r = {val.x, val.y, val.z, val.w};
     __builtin_nontemporal_store(r, (__attribute__((address_space(1))) u32x4*)(uintptr_t)p);
 #else

@@ -7,10 +7,6 @@
 
 namespace {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-
 union op16 {            // 16 bytes of one row: 8 bf16 or 4 fp32 consecutive k
     u32x4 u;
     bf16x8 v;
@@ -27,15 +23,6 @@ __device__ __forceinline__ u32x4 ldg_unaligned(const E* p)
 #else
     return *reinterpret_cast<const unaligned_t*>(p);
 #endif
-}
-
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
-// lane i's 16 bytes at base + off -> LDS byte address lds_base + 16 i (base and lds_base wavefront-uniform); issued
-// from inline assembly, so the waits for it are written out
-__device__ __forceinline__ void load16_to_lds(const char* base, uint32_t off, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base) : "memory");
 }
 
 __device__ __forceinline__ floatx4 mma(const op16& a, const op16& b, floatx4 c, bf16_t)
@@ -271,9 +258,8 @@ struct split_k {
     // waits until all but the youngest n units (n < D) have landed; loads return in order
     static __device__ __forceinline__ void landed(int n)
     {
-        if (D >= 4 && n >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
-        else if (D >= 3 && n == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
-        else if (D >= 2 && n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+        static_assert(D <= 2, "as many waits as units in flight");
+        if (D >= 2 && n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     // adds units [u_begin, u_end) of 128 bytes per row
