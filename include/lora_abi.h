@@ -77,7 +77,8 @@
  * ldw multiples of 8; ranks multiples of 8, at most 128.  Other ranks up to
  * LORA_MAX_RANK, and fp32, run on matrix-core kernels of their own, which take
  * factors aligned to an element (the shrink: K and ldx multiples of 8, fp32 of
- * 4, and a 16-byte aligned x; it is fastest with At aligned so, too).  Other layouts run through general kernels
+ * 4, and a 16-byte aligned x; it is fastest with At aligned so, too); small
+ * expands of theirs run on the general kernel, which is faster there.  Other layouts run through general kernels
  * with no alignment demands, which are one to two orders of magnitude slower per
  * token; padding an adapter's factors
  * with zero rank rows / columns to a multiple of 8 changes no result and moves

@@ -424,10 +424,11 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(
 // 256 x 256 tiles of large problems.  Tiles go HBM -> LDS directly (global_load_lds_dwordx4: no staging registers, no
 // LDS write instructions) into a ring of ten granules of 16 KB, two stages of 64 k ahead of their use.
 //
-// What bounds a compute unit's loads is the number of cache lines its requests touch, not their bytes: fetched as
-// 16 rows x 64 bytes per instruction, L2-resident data arrives at 38 GB/s per compute unit however many loads are in
-// flight; as 8 rows x 128 bytes (whole lines) at 100 - 120 GB/s.  A 256 x 256 tile at 1.2 PFLOP/s of the chip takes
-// 36 GB/s per compute unit, so stages of 32 k (64 bytes of a row) end there; hence stages of 64 k.
+// What bounds a compute unit's loads is the number of cache lines its requests touch, not their bytes: L2-resident rows
+// arrive at 100 - 108 GB/s per compute unit as 8 rows x 128 bytes (whole lines) per instruction, at 59 - 65 GB/s as 16 rows x
+// 64 bytes whose other halves are asked for when they have left the 32 KB L1 (with eight loads in flight per wavefront).  A
+// 256 x 256 tile at 1.45 PFLOP/s of the chip takes 44 GB/s per compute unit next to its LDS reads and barriers, so stages
+// of 32 k (64 bytes of a row) came near their end; hence stages of 64 k.
 //
 // Eight wavefronts, two per SIMD, each 128 features x 64 tokens (8 x 4 blocks of v_mfma_f32_16x16x32_bf16, 128
 // accumulator registers).  A stage is four phases of 16 MFMAs, one per quadrant of the wavefront's tile:
@@ -456,7 +457,7 @@ constexpr int GRANULE = 16384;          // bytes: 128 rows x 128 bytes
 
 // Chunk c of granule row r lives at slot 8 r + (c ^ f(r)).  An operand read (ds_read_b128) has lane l take chunk
 // 4 ks + l / 16 of one of 16 rows: x rows r0 + l % 16, W rows r0 + 16 (l % 16 / 4) + l % 4 (the MFMA row
-// permutation); each f takes eight different values over the rows that eight consecutive lanes read.
+// permutation); each f takes eight different values over the rows that eight consecutive lanes read (SQ_LDS_BANK_CONFLICT: 0).
 __device__ __forceinline__ int ring_f_x(int row) { return row & 7; }
 __device__ __forceinline__ int ring_f_w(int row) { return (row & 3) | ((row >> 2) & 4); }
 

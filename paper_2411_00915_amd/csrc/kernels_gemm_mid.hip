@@ -4,9 +4,10 @@
 //
 // A workgroup (8 wavefronts, two per SIMD) has the compute unit's LDS to itself: a ring of S stages of 64 k (whole
 // 128-byte lines of 64 WA rows of W and 128 rows of x), filled straight from memory S - 1 stages ahead.  A wavefront owns
-// 16 WA features x 64 tokens (WA x 4 blocks of v_mfma_f32_16x16x32_bf16).  What bounds the tile is LDS: per stage 8 (WA +
-// 4) 2 KB of operand reads and (64 WA + 128) 128 bytes of fills at 128 bytes/clk, 1216 clk for WA = 3 (1024 for WA = 2)
-// where the matrix cores need 768 (512).
+// 16 WA features x 64 tokens (WA x 4 blocks of v_mfma_f32_16x16x32_bf16).  A stage takes 0.51 us for WA = 3 (0.43 for WA = 2)
+// with few compute units at work and 0.70 (0.53) with all of them, where the matrix cores need 768 clk (512), 0.37 us at 2.1
+// GHz, the 40 KB (32 KB) of fills 0.38 us at 105 GB/s, and the LDS reads 448 clk (no bank conflicts, by counter): none of
+// them alone; matrix part and memory part alternate, and the fills share the L2 with the other tiles'.
 //
 // A phase is one k-step of 32: a memory part (the LDS reads of its operands; in a stage's second phase also the loads of
 // stage s + S - 1) and a matrix part (4 WA MFMAs), each closed by a barrier.  Wavefronts 4..7 run one part behind

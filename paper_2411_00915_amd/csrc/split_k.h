@@ -161,8 +161,8 @@ extern __shared__ floatx4 small_lds[];
 // g = l / 16 of a 64-byte step, and receives rows 4 g + i of column m.  Row 4 q + i of block f stands for row
 // 4 FB q + 4 f + i of the tile, so over its FB blocks a lane holds 4 FB consecutive rows' results of its token.
 //
-// Loads: an instruction brings 128 bytes of 8 rows (whole cache lines: a compute unit gets 100 - 120 GB/s that way,
-// 38 GB/s as 64 bytes of 16 rows, the MFMA operand shape) straight into this wavefront's own part of LDS; lane l
+// Loads: an instruction brings 128 bytes of 8 rows (whole cache lines: a compute unit gets 100 - 108 GB/s that way,
+// 59 - 65 GB/s as 64 bytes of 16 rows, the MFMA operand shape) straight into this wavefront's own part of LDS; lane l
 // fetches the chunk that belongs in slot l % 8 of row l / 8.  Nothing is shared between wavefronts, so the loop has no
 // barrier: D units of 128 bytes per row are in flight per wavefront.
 // SUMS (fp32): partial sums kept apart per result, see mma_apart.
