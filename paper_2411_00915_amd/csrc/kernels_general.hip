@@ -58,8 +58,13 @@ __global__ __launch_bounds__(256) void expand_general_kernel(
     const T* B = Bt[a];
     for (int n = blockIdx.y * 256 + threadIdx.x; n < N; n += gridDim.y * 256) {
         const T* Bn = B + (int64_t)n * r;
-        float acc = 0.f;
-        for (int j = 0; j < r; ++j) acc = fmaf(vs[j], elem<T>::load(Bn + j), acc);
+        float part[4] = {0.f, 0.f, 0.f, 0.f};                // (a chain of additions is what loses digits: cut in four)
+        int j = 0;
+        for (; j + 4 <= r; j += 4)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[i] = fmaf(vs[j + i], elem<T>::load(Bn + j + i), part[i]);
+        for (; j < r; ++j) part[0] = fmaf(vs[j], elem<T>::load(Bn + j), part[0]);
+        float acc = (part[0] + part[1]) + (part[2] + part[3]);
         T* yp = y + (int64_t)t * ldy + n;
         if (beta != 0.f) acc = fmaf(beta, elem<T>::load(yp), acc);
         elem<T>::store(yp, acc);

@@ -484,9 +484,10 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
 // 16.4, 300 tokens 29.3 / 29.6, 1000 tokens 54.8 / 76.5), more features where it leaves more than the chip holds at a
 // time; the heaviest first.
 // per: tokens of a tile, 0: by that rule, and no tiles at all for problems so small that a tile's chain of loads is what
-// they cost: below 6 million products the general kernel, which has a thread per value, takes less (kernel times, this /
-// general, by products: 0.3 - 1 million 5.9 / 4.9 us, 2 - 4 6.9 / 6.9, 8 - 16 7.8 / 10.8, 16 - 32 7.8 / 17.1; fp32 0.3 - 1
-// million 6.7 / 4.7, 4 - 8 9.1 / 7.5, 8 - 16 8.9 / 10.8: there only up to rank 16, whose sums are as exact either way).
+// they cost: below 12 million products, y's way through a value counted as eight of them, the general kernel, which has a
+// thread per value, takes less (kernel times, this / general, by products alone: 0.3 - 1 million 5.9 / 4.8 us, 2 - 4 7.0 /
+// 6.0, 4 - 8 7.5 / 6.7, 8 - 16 7.8 / 8.5, 16 - 32 7.8 / 11.8; 505 tokens of rank 1, N = 13768, 7 million, 16.4 / 22.5; fp32 up
+// to rank 16, whose sums are as exact either way: 0.3 - 1 million 5.1 / 4.3, 2 - 4 6.6 / 5.5, 8 - 16 9.7 / 10.0).
 static void build_rows_expand_tiles(lora_plan* p, int32_t per)
 {
     if (p->N < 8 || (int64_t)p->N * LORA_MAX_RANK >= (1ll << 31)) return;   // the kernel fetches whole chunks, by 32-bit offsets
@@ -497,9 +498,9 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
         for (int g = 0; g < G; ++g) {
             const int32_t r = p->rank[p->group_adapter[g]];
             max_rank = std::max(max_rank, r);
-            products += (int64_t)(p->group_offset[g + 1] - p->group_offset[g]) * r * p->N;
+            products += (int64_t)(p->group_offset[g + 1] - p->group_offset[g]) * (r + 8) * p->N;
         }
-        if (products < 6000000 && (p->dtype == LORA_BF16 || max_rank <= 16)) return;
+        if (products < 12000000 && (p->dtype == LORA_BF16 || max_rank <= 16)) return;
     }
     const int32_t kstep = p->dtype == LORA_F32 ? 16 : 32, terms = p->dtype == LORA_F32 ? 1 : 3;
     auto token_tiles = [&](int32_t per) {
