@@ -115,8 +115,8 @@ __device__ __forceinline__ void finish16(E* yp, const u32x4 (&yin)[sizeof(E)], c
 
 // Expand, 16 TB tokens of one adapter per workgroup, chunks of 64 features per wavefront.  Bt and y come straight from
 // memory as each lane needs them (rows of any length, aligned to an element); v is common to the wavefronts and lies in
-// LDS as operands (bf16: three terms, all of its 24 bits; with two, lora_delta took 2 to 5 % less).  MFMA row 4 q + i of block f stands for feature 16 q + 4 f + i of the chunk: a lane
-// ends with 16 consecutive features of each of its tokens.
+// LDS as operands (bf16: three terms, all of its 24 bits; with two, lora_delta took 2 to 5 % less).  MFMA row 4 q + i of
+// block f stands for feature 16 q + 4 f + i of the chunk: a lane ends with 16 consecutive features of each of its tokens.
 //
 // Chunks of Bt are fetched whole from where they lie, into the next row if need be and, where they would reach past the
 // matrix, from before their place (N >= 8: there is a whole chunk); what is not theirs is shifted out and masked when

@@ -315,7 +315,8 @@ struct split_k {
 #pragma unroll
                     for (int f = 0; f < FB; ++f) {
                         u32x4& q = w[s][f].u;
-                        q = u32x4{(q[0] >> 16) | (q[1] << 16), (q[1] >> 16) | (q[2] << 16), (q[2] >> 16) | (q[3] << 16), (q[3] >> 16) | (fifth[s][f] << 16)};
+                        q = u32x4{(q[0] >> 16) | (q[1] << 16), (q[1] >> 16) | (q[2] << 16), (q[2] >> 16) | (q[3] << 16),
+                                  (q[3] >> 16) | (fifth[s][f] << 16)};
                     }
             }
             compute(u);
