@@ -20,7 +20,7 @@ static inline lora_vspec lora_vspec_of(const lora_plan* p)
 struct lora_dev_tables {
     const int32_t* perm;
     const int32_t* token_adapter;
-    const int32_t* row_key;        // fused GEMM: adapter of the token (bits 0..22 all ones: none) | removal bit
+    const int32_t* row_key;        // fused GEMM, in its row order: adapter of the token (bits 0..22 all ones: none) | removal bit
     const int32_t* rank;
     const float* scale;
     const lora_tile* shrink_tiles;

@@ -69,7 +69,7 @@ constexpr int META_MAX = 256;      // adapter stages of a tile whose metadata is
 
 struct gemm_delta_args {
     const int32_t* order;          // [T] tokens sorted by adapter, then tokens without adapter; nullptr = identity
-    const int32_t* row_key;        // [T] the token's adapter (bits 0..22; all ones: none) | removal bit
+    const int32_t* row_key;        // [T] in the order above: the token's adapter (bits 0..22; all ones: none) | removal bit
     const int32_t* rank;
     const int32_t* extra_ptr;      // [token tiles + 1]
     const int32_t* extra;          // stage id (adapter, | removal bit) | rank block << 24
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(
         gx[i] = x + (int64_t)tok * ldx + c * 8;
         slot[i] = lds_slot(row, c);
         slot_w[i] = lds_slot_w(row, c);
-        if constexpr (DELTA) lds_rows[i * 256 + tid] = make_int2(tok, pos_ok ? da.row_key[tok] : KEY_NONE);
+        if constexpr (DELTA) lds_rows[i * 256 + tid] = make_int2(tok, pos_ok ? da.row_key[pos] : KEY_NONE);
     }
 
     floatx16 acc[WB][WB];
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
     if constexpr (DELTA) {
         const int pos = t0 + wt + lane;
         my_tok = da.order[pos < T ? pos : T - 1];
-        my_key = pos < T ? da.row_key[my_tok] : KEY_NONE;
+        my_key = pos < T ? da.row_key[pos] : KEY_NONE;
     }
 
     const int stages = (K + RK - 1) / RK;                            // at least 3 (checked by the launcher)

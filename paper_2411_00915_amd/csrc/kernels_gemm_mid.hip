@@ -69,9 +69,9 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
     uint64_t my_bt = 0, removal = 0;
     if constexpr (DELTA != NO_DELTA) {
         const int pos = t0 + wt + lane, v_pos = t0 + 16 * wave + m;
-        const int key = pos < T ? da.row_key[da.order[pos]] : KEY_NONE;
+        const int key = pos < T ? da.row_key[pos] : KEY_NONE;
         v_tok = da.order[min(v_pos, T - 1)];
-        const int v_key = v_pos < T ? da.row_key[v_tok] : KEY_NONE, v_own = v_key & KEY_NONE;
+        const int v_key = v_pos < T ? da.row_key[v_pos] : KEY_NONE, v_own = v_key & KEY_NONE;
         my_own = key & KEY_NONE;
         removal = __ballot((key & LORA_UNMERGE_BIT) != 0);
         if (my_own != KEY_NONE) {

@@ -15,11 +15,13 @@
 // Measured (whole lora_fused_forward, cold weights): 64 single-token requests on 32 adapters, 4096 -> 4096, 104 -> 21 us;
 // fp32, 256 tokens, 4096 -> 4096: this kernel 600 -> 73 us (the matrix cores' share of that at 2.1 GHz is 64 us).
 //
-// DELTA: tokens in adapter-sorted order; before the partial sums are added up, the wavefronts share out the (adapter,
-// rank step) pairs of the tile's tokens and add v B_a of theirs to their own partial sums, so the delta is spread over
-// the workgroup and joins the same fp32 sum.  v is read as the shrink left it (fp32, K parts added in order); with bf16
-// it is split into two bf16 terms in registers, or, for ranks off the tuned kernels, multiplied as it is (fp32 products:
-// 64 tokens on 32 adapters of ranks 4 to 100, 4096 -> 4096, 25.3 us, with two terms 24.1).
+// DELTA: tokens in adapter-sorted order; before the partial sums are added up, the wavefronts share out the items
+// (16-token block, adapter in it, rank step) of the tile's tokens and add v B_a of theirs to their own partial sums, so the
+// delta is spread over the workgroup and joins the same fp32 sum.  It costs trips to memory: an item's operands are requested
+// one item ahead, the first item's beside the K loop (32 tokens on 32 adapters, 4096 -> 11008: kernel 32.5 -> 30.0 us; 64
+// tokens, 5120 -> 13824: 52.1 -> 45.8; the product alone takes 21 and 35).  v is read as the shrink left it (fp32, K parts
+// added in order); with bf16 it is split into two bf16 terms in registers, or, for ranks off the tuned kernels, multiplied as
+// it is (fp32 products: 64 tokens on 32 adapters of ranks 4 to 100, 4096 -> 4096, 25.3 us, with two terms 24.1).
 #include <algorithm>
 #include <atomic>
 
@@ -44,6 +46,17 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
 
+    // DELTA: row `lane` of the tile, its adapter (none: KEY_NONE), that adapter's rank and Bt: two rounds of loads that run
+    // beside the K loop's first
+    int my_tok = 0, my_key = KEY_NONE, my_rank = 0;
+    uint64_t my_bt = 0;
+    if constexpr (DELTA != NO_DELTA) {
+        const int pos = t0 + lane;
+        const bool row_in = lane < 16 * TB && pos < T;
+        my_tok = da.order[row_in ? pos : T - 1];
+        my_key = row_in ? da.row_key[pos] : KEY_NONE;
+    }
+    const int own = my_key & KEY_NONE;
     // (the launcher keeps N ldw and T ldx below 2^32 bytes)
     using slice = split_k<E, FB, TB, D, KTAIL>;
     constexpr int ES = slice::ES, EPC = slice::EPC, KSTEP = slice::KSTEP;
@@ -54,73 +67,167 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
             return (int64_t)(DELTA != NO_DELTA ? da.order[r] : r) * ldx;
         });
     floatx4 (&acc)[FB][TB][1] = part.acc;
-    part.run((int)(((int64_t)part.units * wave) / WAVES), (int)(((int64_t)part.units * (wave + 1)) / WAVES));
+    const int u_begin = (int)(((int64_t)part.units * wave) / WAVES), u_end = (int)(((int64_t)part.units * (wave + 1)) / WAVES);
+    if (DELTA != NO_DELTA && own != KEY_NONE) {
+        my_rank = da.rank[own];
+        my_bt = reinterpret_cast<uint64_t>(da.Bt_ptrs[own]);
+    }
+    part.start(u_begin, u_end);
 
-    // ---- adapter deltas: the (adapter, rank step) pairs of the tile's tokens in turn to the wavefronts ------
-    if constexpr (DELTA != NO_DELTA) {
-        const int pos = t0 + lane;
-        const bool row_in = lane < 16 * TB && pos < T;
-        const int my_tok = da.order[row_in ? pos : T - 1];
-        const int my_key = row_in ? da.row_key[my_tok] : KEY_NONE;
-        const int own = my_key & KEY_NONE;
-        const int my_rank = own != KEY_NONE ? da.rank[own] : 0;
-        const uint64_t my_bt = own != KEY_NONE ? reinterpret_cast<uint64_t>(da.Bt_ptrs[own]) : 0;
-        int tokb[TB];
+    if constexpr (DELTA == NO_DELTA) {
+        part.drain(u_begin, u_end, [] {}, [] {});
+    } else {
+        // ---- adapter deltas, in items of (16-token block, adapter in it, KSTEP ranks), in turn to the wavefronts; an item's
+        // operands are requested before the item before it is multiplied, the first item's inside the K loop ----
+        int my_steps = 0, my_end = 0, items = 0, rm_rank = 0, rm_steps = 0;
+        uint64_t removal = 0, rm_bt = 0;
+        auto share_out = [&]() {
+            // the first row of an adapter in its block leads: items [my_end - my_steps, my_end) are its
+            const int before = __shfl_up(own, 1);
+            const bool leads = own != KEY_NONE && (m == 0 || before != own);
+            my_end = my_steps = leads ? (my_rank + KSTEP - 1) / KSTEP : 0;
 #pragma unroll
-        for (int b = 0; b < TB; ++b) tokb[b] = __shfl(my_tok, 16 * b + m);
-        int turn = 0;
-        auto apply = [&](const E* Bt, int r, uint64_t members, const float* v, const lora_vspec& vsp) {
-            for (int j0 = 0; j0 < r; j0 += KSTEP) {
-                if ((turn++ & (WAVES - 1)) != wave) continue;
-                const int j = j0 + EPC * g;
-                op16 bt[FB];
-                float vf[TB][EPC];
+            for (int q = 1; q < 64; q *= 2) {
+                const int up = __shfl_up(my_end, q);
+                my_end += lane >= q ? up : 0;
+            }
+            items = __builtin_amdgcn_readlane(my_end, 63);
+            // mixture mode: the merged adapter's on every block, masked to the rows that the removal applies to
+            removal = __ballot((my_key & LORA_UNMERGE_BIT) != 0);
+            if (removal) {
+                rm_rank = da.rank[da.merged];
+                rm_steps = (rm_rank + KSTEP - 1) / KSTEP;
+                rm_bt = reinterpret_cast<uint64_t>(da.Bt_ptrs[da.merged]);
+            }
+        };
+        struct item {                                        // (wavefront-uniform)
+            const E* Bt;
+            int r, j0, block;
+            uint32_t rows;                                   // of the block that are the adapter's
+            bool rm;
+        };
+        auto find = [&](int i, item& it) {
+            if (i < items) {
+                const int src = __ffsll((unsigned long long)__ballot(my_end > i)) - 1, a = __builtin_amdgcn_readlane(own, src);
+                it.block = src >> 4;
+                it.rows = (uint32_t)(__ballot(own == a) >> (src & 48)) & 0xffffu;
+                it.r = __builtin_amdgcn_readlane(my_rank, src);
+                it.j0 = (i - __builtin_amdgcn_readlane(my_end, src) + __builtin_amdgcn_readlane(my_steps, src)) * KSTEP;
+                it.Bt = reinterpret_cast<const E*>((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_bt, src) |
+                                                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_bt >> 32), src) << 32));
+                it.rm = false;
+                return true;
+            }
+            i -= items;
+            if (i >= TB * rm_steps) return false;
+            it.block = i / rm_steps;
+            it.rows = (uint32_t)(removal >> (16 * it.block)) & 0xffffu;
+            it.r = rm_rank;
+            it.j0 = (i - it.block * rm_steps) * KSTEP;
+            it.Bt = reinterpret_cast<const E*>(rm_bt);
+            it.rm = true;
+            return true;
+        };
+        // K parts of v that are requested ahead (as many as registers hold; the others when they are used)
+        constexpr int AHEAD = ES == 4 || FB * TB >= 8 ? 4 : 1;
+        struct operands {
+            op16 bt[FB];
+            floatx4 v[AHEAD][EPC / 4];
+        };
+        // (past a rank's end v and Bt are read where there is something; `add` masks it)
+        auto v_at = [&](const item& it) {
+            const lora_vspec& vsp = it.rm ? da.vsp2 : da.vsp;
+            return (it.rm ? da.v2 : da.v) + (int64_t)__shfl(my_tok, 16 * it.block + m) * vsp.R + min(it.j0 + EPC * g, vsp.R - EPC);
+        };
+        auto load = [&](const item& it, operands& o) {
 #pragma unroll
-                for (int f = 0; f < FB; ++f) {
-                    const int n = n0 + 4 * FB * (m >> 2) + 4 * f + (m & 3);
-                    bt[f] = row_chunk<E>(Bt + (int64_t)(n < N ? n : N - 1) * r, j, r);
+            for (int f = 0; f < FB; ++f) {
+                const int n = n0 + 4 * FB * (m >> 2) + 4 * f + (m & 3);
+                o.bt[f] = row_chunk<E>(it.Bt + (int64_t)(n < N ? n : N - 1) * it.r, it.j0 + EPC * g, it.r);
+            }
+            const lora_vspec& vsp = it.rm ? da.vsp2 : da.vsp;
+            const float* const p = v_at(it);
+#pragma unroll
+            for (int s = 0; s < AHEAD; ++s)
+                if (s < vsp.P) {
+#pragma unroll
+                    for (int q = 0; q < EPC / 4; ++q) o.v[s][q] = *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
                 }
+        };
+        auto add = [&](const item& it, operands& o) {
+            const lora_vspec& vsp = it.rm ? da.vsp2 : da.vsp;
+            if constexpr (AHEAD > 1) {
 #pragma unroll
-                for (int b = 0; b < TB; ++b) v_values<EPC>(v, vsp, tokb[b], j, r, (members >> (16 * b + m)) & 1ull, vf[b]);
+                for (int s = 1; s < 4; ++s)
+                    if (s < vsp.P) {
 #pragma unroll
-                for (int b = 0; b < TB; ++b) {
-                    if (((members >> (16 * b)) & 0xffffull) == 0) continue;       // wavefront-uniform
-                    const bool mine = (members >> (16 * b + m)) & 1ull;
-                    auto add = [&](auto product) {
-#pragma unroll
-                        for (int f = 0; f < FB; ++f) {
-                            const floatx4 e = product(bt[f], acc[f][b][0]);
-                            // (a product with zeros would carry the adapter's infinities over to other tokens)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) acc[f][b][0][i] = mine ? e[i] : acc[f][b][0][i];
-                        }
-                    };
-                    if constexpr (ES == 4) {
-                        op16 vo;
-                        vo.f = floatx4{vf[b][0], vf[b][1], vf[b][2], vf[b][3]};
-                        add([&](const op16& w, floatx4 c) { return mma(w, vo, c, E{}); });
-                    } else if constexpr (DELTA == PLAIN_DELTA) {
-                        add([&](const op16& w, floatx4 c) { return mma_plain(w, vf[b], c); });
-                    } else {
-                        op16 vo[2];
-                        bf16_terms<2>(vf[b], vo);
-                        add([&](const op16& w, floatx4 c) { return mma(w, vo[1], mma(w, vo[0], c, E{}), E{}); });
+                        for (int q = 0; q < EPC / 4; ++q) o.v[0][q] += o.v[s][q];
                     }
+            } else if (vsp.P > 1) {
+                const float* const p = v_at(it);
+                floatx4 rest[3][EPC / 4];
+#pragma unroll
+                for (int s = 1; s < 4; ++s)
+                    if (s < vsp.P) {
+#pragma unroll
+                        for (int q = 0; q < EPC / 4; ++q) rest[s - 1][q] = *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
+                    }
+#pragma unroll
+                for (int s = 1; s < 4; ++s)
+                    if (s < vsp.P) {
+#pragma unroll
+                        for (int q = 0; q < EPC / 4; ++q) o.v[0][q] += rest[s - 1][q];
+                    }
+            }
+            const bool mine = (it.rows >> m) & 1u;
+            float f[EPC];
+#pragma unroll
+            for (int i = 0; i < EPC; ++i) f[i] = mine && it.j0 + EPC * g + i < it.r ? o.v[0][i >> 2][i & 3] : 0.f;
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                if (b != it.block) continue;
+                auto take = [&](auto product) {
+#pragma unroll
+                    for (int w = 0; w < FB; ++w) {
+                        const floatx4 e = product(o.bt[w], acc[w][b][0]);
+                        // (a product with zeros would carry the adapter's infinities over to other tokens)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[w][b][0][i] = mine ? e[i] : acc[w][b][0][i];
+                    }
+                };
+                if constexpr (ES == 4) {
+                    op16 vo;
+                    vo.f = floatx4{f[0], f[1], f[2], f[3]};
+                    take([&](const op16& w, floatx4 c) { return mma(w, vo, c, E{}); });
+                } else if constexpr (DELTA == PLAIN_DELTA) {
+                    take([&](const op16& w, floatx4 c) { return mma_plain(w, f, c); });
+                } else {
+                    op16 vo[2];
+                    bf16_terms<2>(f, vo);
+                    take([&](const op16& w, floatx4 c) { return mma(w, vo[1], mma(w, vo[0], c, E{}), E{}); });
                 }
             }
         };
-        uint64_t todo = __ballot(own != KEY_NONE);
-        while (todo) {
-            const int src = __ffsll((unsigned long long)todo) - 1;
-            const int a = __builtin_amdgcn_readlane(own, src), r = __builtin_amdgcn_readlane(my_rank, src);
-            const uint64_t bt = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_bt, src) |
-                                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_bt >> 32), src) << 32);
-            const uint64_t members = __ballot(own == a);
-            todo &= ~members;
-            apply(reinterpret_cast<const E*>(bt), r, members, da.v, da.vsp);
+        item i0, i1;
+        operands o0, o1;
+        int i = wave;
+        bool more = false;
+        const auto first = [&] {
+            share_out();
+            more = find(i, i0);
+            if (more) load(i0, o0);
+        };
+        if constexpr (ES == 4) part.drain(u_begin, u_end, [] {}, first);  // (a branch in its loop costs the matrix cores more than it hides)
+        else part.drain(u_begin, u_end, first, [] {});
+        while (more) {
+            more = find(i += WAVES, i1);
+            if (more) load(i1, o1);
+            add(i0, o0);
+            if (!more) break;
+            more = find(i += WAVES, i0);
+            if (more) load(i0, o0);
+            add(i1, o1);
         }
-        const uint64_t removal = __ballot((my_key & LORA_UNMERGE_BIT) != 0);
-        if (removal) apply(reinterpret_cast<const E*>(da.Bt_ptrs[da.merged]), da.rank[da.merged], removal, da.v2, da.vsp2);
     }
 
     // ---- partial sums meet in LDS, one rounding, store (rows go back to their tokens) ----

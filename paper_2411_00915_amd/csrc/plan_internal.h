@@ -77,8 +77,8 @@ struct lora_plan {
     std::vector<lora_tile> rows_expand_tiles;
     int32_t rows_expand_lds = 0, rows_expand_tb = 1;   // of its launch: dynamic LDS bytes, token blocks of the largest tile
     int32_t rows_shrink_fb = 1, rows_shrink_tb = 1;
-    // fused GEMM: what a row is matched against an adapter stage by: its adapter in bits 0..22 (all ones: none),
-    // bit 23 set when the removal of the merged adapter applies to it
+    // fused GEMM: what a row (in the order above, so that both come with one round of loads) is matched against an adapter
+    // stage by: its adapter in bits 0..22 (all ones: none), bit 23 set when the removal of the merged adapter applies to it
     std::vector<int32_t> row_key;
 
     // Mixture mode: adapter `merged` is folded into the base weight.  This plan then holds the tokens' own branches

@@ -638,16 +638,16 @@ static void build_f32_tiles(lora_plan* p)
 static void build_gemm_tables(lora_plan* p, bool stage_lists)
 {
     const lora_plan* u = p->unmerge;
-    p->row_key.resize((size_t)p->T);
+    std::vector<int32_t> key((size_t)p->T);                   // by token
     for (int32_t t = 0; t < p->T; ++t) {
         const int32_t a = p->token_adapter[t];
-        p->row_key[t] = (a < 0 ? LORA_UNMERGE_BIT - 1 : a) | (u && u->token_adapter[t] >= 0 ? LORA_UNMERGE_BIT : 0);
+        key[t] = (a < 0 ? LORA_UNMERGE_BIT - 1 : a) | (u && u->token_adapter[t] >= 0 ? LORA_UNMERGE_BIT : 0);
     }
     std::vector<int32_t> sorted = p->perm;
     sorted.reserve((size_t)p->T);
     for (int pass = 0; pass < 2; ++pass)
         for (int32_t t = 0; t < p->T; ++t)
-            if (p->token_adapter[t] < 0 && ((p->row_key[t] & LORA_UNMERGE_BIT) != 0) == (pass == 0)) sorted.push_back(t);
+            if (p->token_adapter[t] < 0 && ((key[t] & LORA_UNMERGE_BIT) != 0) == (pass == 0)) sorted.push_back(t);
 
     // adapter stages of the rows [p0, p1) of `rows`: one per `cols` columns of [v_hi | v_lo] (2 r columns) and
     // adapter; the rows of one adapter are adjacent
@@ -655,7 +655,7 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
         int32_t n = 0, last = -1;
         bool removal = false;
         for (int32_t q = p0; q < p1; ++q) {
-            removal = removal || (p->row_key[rows[q]] & LORA_UNMERGE_BIT);
+            removal = removal || (key[rows[q]] & LORA_UNMERGE_BIT);
             const int32_t a = p->token_adapter[rows[q]];
             if (a < 0 || a == last) continue;
             last = a;
@@ -680,6 +680,8 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
         std::copy(sorted.begin() + (size_t)blocks[b] * 256, sorted.begin() + (size_t)blocks[b] * 256 + 256,
                   p->order.begin() + (size_t)b * 256);
     std::copy(sorted.begin() + (size_t)full * 256, sorted.end(), p->order.begin() + (size_t)full * 256);
+    p->row_key.resize((size_t)p->T);
+    for (int32_t q = 0; q < p->T; ++q) p->row_key[q] = key[p->order[q]];
 
     if (!stage_lists) return;
     for (int h = 0; h < 2; ++h) {

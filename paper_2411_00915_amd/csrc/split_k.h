@@ -136,7 +136,7 @@ __device__ __forceinline__ void bf16_terms(const float (&f)[8], op16 (&o)[TERMS]
 enum row_delta { NO_DELTA, TERMS_DELTA, PLAIN_DELTA };
 struct row_delta_args {
     const int32_t* order;          // [T] tokens sorted by adapter, then tokens without adapter
-    const int32_t* row_key;        // [T] adapter of the token (bits 0..22; all ones: none) | removal bit
+    const int32_t* row_key;        // [T] in that order: adapter of the token (bits 0..22; all ones: none) | removal bit
     const int32_t* rank;
     const float* v;
     lora_vspec vsp;
@@ -262,24 +262,39 @@ struct split_k {
         if (D >= 2 && n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    // adds units [u_begin, u_end) of 128 bytes per row
-    __device__ __forceinline__ void run(int u_begin, int u_end)
+    // adds units [u_begin, u_end) of 128 bytes per row: `start` requests the first D, `drain` goes through them all.  For
+    // loads of the caller's that its own code after the loop needs: `early` is called when the second round of requests is
+    // out, `late` before the last unit is multiplied (where there are too few units, both before the first wait).
+    __device__ __forceinline__ void start(int u_begin, int u_end)
     {
 #pragma unroll
         for (int d = 0; d < D; ++d)
             if (u_begin + d < u_end) issue(u_begin + d, d);
+    }
+    __device__ __forceinline__ void run(int u_begin, int u_end)
+    {
+        start(u_begin, u_end);
+        drain(u_begin, u_end, [] {}, [] {});
+    }
+    template <typename Early, typename Late>
+    __device__ __forceinline__ void drain(int u_begin, int u_end, Early early, Late late)
+    {
+        if (u_begin + D >= u_end) early();
+        if (u_begin >= u_end) late();
         int slot = 0, u = u_begin;
         for (; u + D < u_end; ++u) {
             landed(D - 1);
             read(slot);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the slot is in registers: refill it
             issue(u + D, slot);
+            if (u == u_begin) early();
             compute(u);
             slot = slot + 1 == D ? 0 : slot + 1;
         }
         for (; u < u_end; ++u) {
             landed(u_end - 1 - u);
             read(slot);
+            if (u == u_end - 1) late();
             compute(u);
             slot = slot + 1 == D ? 0 : slot + 1;
         }
