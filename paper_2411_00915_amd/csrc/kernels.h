@@ -65,9 +65,17 @@ hipError_t launch_expand_tiled(const lora_plan* p, const lora_dev_tables& d, con
                                const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream);
 
 // streaming kernels for prefill-sized batches (plans with shrink_stream / expand_stream; called by the two above)
+// second: another plan's tiles (also of the streaming shrink, over the same x) in the same launch
+struct shrink_second {
+    const lora_plan* plan = nullptr;
+    const lora_dev_tables* tables = nullptr;
+    float* v = nullptr;
+    void* vb = nullptr;
+    bool* split_done = nullptr;
+};
 hipError_t launch_shrink_stream(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx,
                                 const void* const* At, float* v, hipStream_t stream, void* vb = nullptr,
-                                bool* split_done = nullptr);
+                                bool* split_done = nullptr, const shrink_second& second = {});
 hipError_t launch_expand_stream(const lora_plan* p, const lora_dev_tables& d, const float* v,
                                 const void* const* Bt, void* y, int64_t ldy, float beta, hipStream_t stream);
 

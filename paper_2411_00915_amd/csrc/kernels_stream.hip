@@ -2,6 +2,7 @@
 // What is common to the wavefronts of a tile (the adapter matrix) goes through LDS; the big stream (x, y, W)
 // stays private to a wavefront, is fetched as whole cache lines several stages ahead, and reaches the MFMA
 // operand layout through a small LDS patch of the wavefront's own.
+#include <algorithm>
 #include <atomic>
 #include "mfma_tile.h"
 #include "kernels.h"
@@ -196,15 +197,31 @@ __device__ __forceinline__ void shrink_stream_tile(
 
 extern __shared__ uint4 shrink_stream_lds[];
 
+// one batch of a launch: its tiles and where its v goes
+struct shrink_batch {
+    const lora_tile* tiles;
+    const int32_t* perm;
+    float* v;
+    lora_vspec vsp;
+    bf16_t* vb;
+};
+
 // JBMAX: the largest rank-block count among the plan's tiles (the kernel's register count is that
-// of its widest case, so plans without ranks above 64 get a leaner build)
+// of its widest case, so plans without ranks above 64 get a leaner build).
+// Workgroups [0, n_first) take the tiles of `first`, the others those of `second`: mixture mode's two batches over the
+// same x in one launch.  Each alone is a round of workgroups that mostly starts up and drains.
 template <int JBMAX>
 __global__ __launch_bounds__(512) void shrink_stream_kernel(
-    const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm,
-    const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* const* __restrict__ At_ptrs, int K,
-    float* __restrict__ v, lora_vspec R, const bf16_t* __restrict__ zeros, bf16_t* __restrict__ vb)
+    const shrink_batch first, const shrink_batch second, int n_first,
+    const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* const* __restrict__ At_ptrs, int K, const bf16_t* __restrict__ zeros)
 {
-    const lora_tile tile = tiles[blockIdx.x];
+    const int b = (int)blockIdx.x;
+    const bool is_first = b < n_first;
+    const lora_tile tile = is_first ? first.tiles[b] : second.tiles[b - n_first];
+    const int32_t* const perm = is_first ? first.perm : second.perm;
+    float* const v = is_first ? first.v : second.v;
+    bf16_t* const vb = is_first ? first.vb : second.vb;
+    const lora_vspec R{is_first ? first.vsp.R : second.vsp.R, is_first ? first.vsp.P : second.vsp.P, is_first ? first.vsp.part : second.vsp.part};
     const bf16_t* At = At_ptrs[tile.adapter];
     const int nb = tile.shape & 15, jb = (tile.shape >> 4) & 15;
 #define STREAM_CASE(JB_, KW_) \
@@ -217,20 +234,31 @@ __global__ __launch_bounds__(512) void shrink_stream_kernel(
 }
 
 hipError_t launch_shrink_stream(const lora_plan* p, const lora_dev_tables& d, const void* x, int64_t ldx,
-                                const void* const* At, float* v, hipStream_t stream, void* vb, bool* split_done)
+                                const void* const* At, float* v, hipStream_t stream, void* vb, bool* split_done, const shrink_second& second)
 {
-    const int n_tiles = (int)p->shrink_tiles.size();
-    if (p->v_parts != 1) vb = nullptr;            // partial sums: the split is of their sum, a pass of its own
-    if (split_done) *split_done = vb != nullptr;
+    // (partial sums: the split is of their sum, a pass of its own)
+    auto batch_of = [](const lora_plan* q, const lora_dev_tables& t, float* qv, void* qvb) {
+        return shrink_batch{t.shrink_tiles, t.perm, qv, lora_vspec_of(q), q->v_parts == 1 ? (bf16_t*)qvb : nullptr};
+    };
+    const shrink_batch b0 = batch_of(p, d, v, vb);
+    if (split_done) *split_done = b0.vb != nullptr;
+    const int n_first = (int)p->shrink_tiles.size();
+    int n_tiles = n_first, max_blocks = p->shrink_max_blocks;
+    shrink_batch b1 = b0;
+    if (second.plan) {
+        b1 = batch_of(second.plan, *second.tables, second.v, second.vb);
+        if (second.split_done) *second.split_done = b1.vb != nullptr;
+        n_tiles += (int)second.plan->shrink_tiles.size();
+        max_blocks = std::max(max_blocks, second.plan->shrink_max_blocks);
+    }
     // two slabs of 16 JB rows x 256 bytes (the final cross-wavefront sum needs the same 8 JB KB), and a
     // 4 KB patch per wavefront
-    const size_t stream_lds = (size_t)p->shrink_max_blocks * 8192 + 32768;
+    const size_t stream_lds = (size_t)max_blocks * 8192 + 32768;
 #define STREAM_LAUNCH(JBMAX_)                                                                                          \
     LORA_LAUNCH(LORA_K_SHRINK_STREAM, shrink_stream_kernel<JBMAX_>, dim3(n_tiles), dim3(512), stream_lds, stream,      \
-                d.shrink_tiles, d.perm, (const bf16_t*)x, ldx, (const bf16_t* const*)At, p->K, v, lora_vspec_of(p),    \
-                (const bf16_t*)d.zeros, (bf16_t*)vb)
-    if (p->shrink_max_blocks <= 2) STREAM_LAUNCH(2);
-    else if (p->shrink_max_blocks <= 4) STREAM_LAUNCH(4);
+                b0, b1, n_first, (const bf16_t*)x, ldx, (const bf16_t* const*)At, p->K, (const bf16_t*)d.zeros)
+    if (max_blocks <= 2) STREAM_LAUNCH(2);
+    else if (max_blocks <= 4) STREAM_LAUNCH(4);
     else STREAM_LAUNCH(8);
 #undef STREAM_LAUNCH
     return hipGetLastError();

@@ -1291,6 +1291,24 @@ def test_mixture_mode_cfg4_mixed():
     run_mixture_case(w, int(np.argmax(counts)), n_sample=160)      # the most popular adapter is the merged one
 
 
+@pytest.mark.parametrize("T,K,N,ranks,merged_rank,max_seg", [
+    (130, 1024, 264, (8, 128), 8, 140), (257, 1160, 192, (8, 128), 128, 70), (1100, 4096, 328, (16, 64), 64, 300),
+    (1500, 1032, 200, (64, 24), 24, 5)])
+def test_mixture_mode_shrinks_of_both_batches_in_one_launch(T, K, N, ranks, merged_rank, max_seg):
+    # widths of the two batches that differ either way, K parts of their own, K off the 128 of a stage
+    w = wl.random_case(433 + T, T, K, N, 5, ranks, max_seg=max_seg, frac_none=0.1)
+    m = int(np.argmax(w.adapter_rank == merged_rank))
+    dl = device.to_device(w, DEV, with_w=False)
+    plan = device.make_plan(w, merged_adapter=m)
+    v = torch.zeros(B.lora_plan_query(plan)[1] // 4, dtype=torch.float32, device=DEV)
+    B.lora_timing_begin()
+    B.lora_shrink(plan, dl.x, w.K, dl.At_ptrs, v)
+    torch.cuda.synchronize()
+    assert {name: r["count"] for name, r in B.lora_timing_end().items()} == {"shrink_stream_kernel": 1}
+    plan.destroy()
+    run_mixture_case(w, m)
+
+
 # ---------------------------------------------------------------- mode switch (merge / unmerge)
 def _merge_case(L, N, K, r, scale, dtype="bf16", variant=B.LORA_VARIANT_AUTO, ld_pad=0, seed=0, check_layers=None):
     print(f"  merge case L={L} N={N} K={K} r={r} s={scale} {dtype} variant={variant} ld_pad={ld_pad}", flush=True)
