@@ -62,7 +62,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 bool misaligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
 
 struct table_layout {
-    size_t perm, token_adapter, row_key, rank, scale, shrink_tiles, expand_tiles, sync, sync_bytes, total;
+    size_t perm, token_adapter, row_key, rank, scale, shrink_tiles, expand_tiles, sync, sync_bytes, layer_sync, layer_sync_bytes, total;
     size_t order, extra_ptr128, extra128, extra_ptr256, extra256, zeros, shrink_rows, expand_rows;
     size_t rows_shrink, rows_expand, f32_delta;
 };
@@ -92,6 +92,8 @@ table_layout layout_of(const lora_plan* p)
     L.f32_delta = take(p->f32_delta_tiles.size() * sizeof(lora_tile));
     L.sync_bytes = p->fused_ok ? p->group_adapter.size() * 128 : 0;
     L.sync = take(L.sync_bytes);
+    L.layer_sync_bytes = layer_small_planned(p) ? LORA_LAYER_SYNC_BYTES : 0;
+    L.layer_sync = take(L.layer_sync_bytes);
     L.total = std::max<size_t>(off, 256);
     return L;
 }
@@ -157,6 +159,7 @@ lora_status ensure_uploaded(lora_plan* p, hipStream_t stream)
     put(L.rows_expand, p->rows_expand_tiles.data(), p->rows_expand_tiles.size() * sizeof(lora_tile));
     put(L.f32_delta, p->f32_delta_tiles.data(), p->f32_delta_tiles.size() * sizeof(lora_tile));
     std::memset(h + L.sync, 0, L.sync_bytes);                    // hand-off counters start at zero
+    std::memset(h + L.layer_sync, 0, L.layer_sync_bytes);
     if (hipMemcpyAsync(dbuf, hbuf, L.total, hipMemcpyHostToDevice, stream) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(dbuf);
@@ -176,6 +179,7 @@ lora_status ensure_uploaded(lora_plan* p, hipStream_t stream)
     p->d_shrink_tiles = reinterpret_cast<lora_tile*>(d + L.shrink_tiles);
     p->d_expand_tiles = reinterpret_cast<lora_tile*>(d + L.expand_tiles);
     p->d_sync = d + L.sync;
+    p->d_layer_sync = L.layer_sync_bytes ? d + L.layer_sync : nullptr;
     p->d_zeros = d + L.zeros;
     p->d_order = reinterpret_cast<int32_t*>(d + L.order);
     p->d_extra_ptr128 = reinterpret_cast<int32_t*>(d + L.extra_ptr128);
@@ -194,7 +198,8 @@ lora_dev_tables tables_of(const lora_plan* p)
 {
     return lora_dev_tables{p->d_perm, p->d_token_adapter, p->d_row_key, p->d_rank, p->d_scale, p->d_shrink_tiles, p->d_expand_tiles,
                            p->d_sync, p->d_order, p->d_extra_ptr128, p->d_extra128, p->d_extra_ptr256, p->d_extra256, p->d_zeros,
-                           p->d_shrink_rows, p->d_expand_rows, p->d_rows_shrink_tiles, p->d_rows_expand_tiles, p->d_f32_delta_tiles};
+                           p->d_shrink_rows, p->d_expand_rows, p->d_rows_shrink_tiles, p->d_rows_expand_tiles, p->d_f32_delta_tiles,
+                           p->d_layer_sync};
 }
 
 size_t elem_bytes(int32_t dtype) { return dtype == LORA_F32 ? 4 : 2; }
@@ -512,6 +517,12 @@ extern "C" lora_status lora_fused_forward(lora_plan* p, const void* x, int64_t l
                        gemm_small_supported(p->T, p->K, p->N, p->dtype, x, ldx, Wt, ldw, y, ldy);
     char* const split = mid || small ? nullptr : vb;
     bool split_done = false, split2_done = false;
+    if (small && has_delta && layer_small_planned(p) && !misaligned(d_At_ptrs, 8)) {      // the shrink goes in the product's launch
+        const lora_status st = ensure_uploaded(p, stream);
+        if (st != LORA_OK) return st;
+        const lora_dev_tables d = tables_of(p);
+        return launch_layer_small(p->T, p->K, p->N, x, ldx, Wt, ldw, y, ldy, p, &d, v, d_At_ptrs, d_Bt_ptrs, stream) == hipSuccess ? LORA_OK : LORA_ERR_DEVICE;
+    }
     if (has_delta) {
         const lora_status st = u ? shrink_both(p, x, ldx, d_At_ptrs, v, hip_stream, split, &split_done, split ? vb2 : nullptr, &split2_done)
                                  : shrink_own(p, x, ldx, d_At_ptrs, v, hip_stream, split, &split_done);

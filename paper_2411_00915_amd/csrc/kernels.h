@@ -37,6 +37,7 @@ struct lora_dev_tables {
     const lora_tile* rows_shrink_tiles;
     const lora_tile* rows_expand_tiles;
     const lora_tile* f32_delta_tiles;
+    void* layer_sync;              // hand-off counters of launch_layer_small; null: the plan has none
 };
 
 // general VALU family (any dtype, any alignment)
@@ -125,6 +126,12 @@ hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, con
                              const void* Wt, int64_t ldw, void* y, int64_t ldy,
                              const lora_plan* p, const lora_dev_tables* d, const float* v, const gemm_removal& rm,
                              const void* const* Bt, hipStream_t stream);
+
+// shrink and small GEMM in one launch: plans of layer_small_planned, problems of gemm_small_supported
+bool layer_small_planned(const lora_plan* p);
+hipError_t launch_layer_small(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
+                              const lora_plan* p, const lora_dev_tables* d, float* v, const void* const* At, const void* const* Bt,
+                              hipStream_t stream);
 
 // mode switch: Wt_l += s Bt_l At_l for L layers in one launch (device arrays of L pointers each)
 hipError_t launch_merge_tiled(int32_t L, int32_t N, int32_t K, int32_t r, float s, void* const* Wt, int64_t ldw,

@@ -12,12 +12,13 @@
 // fp32 runs on v_mfma_f32_16x16x4_f32 the same way (fp32 products and sums); there the matrix cores bind (256
 // flops/clk per compute unit) and the same tiles serve every batch size.
 //
-// Measured (whole lora_fused_forward, cold weights): 64 single-token requests on 32 adapters, 4096 -> 4096, 104 -> 21 us;
+// Measured (whole lora_fused_forward, cold weights): 64 single-token requests on 32 adapters, 4096 -> 4096, 104 -> 15 us;
 // fp32, 256 tokens, 4096 -> 4096: this kernel 600 -> 73 us (the matrix cores' share of that at 2.1 GHz is 64 us).
 //
 // DELTA: tokens in adapter-sorted order; before the partial sums are added up, the wavefronts share out the items
 // (16-token block, adapter in it, rank step) of the tile's tokens and add v B_a of theirs to their own partial sums, so the
-// delta is spread over the workgroup and joins the same fp32 sum.  It costs trips to memory: an item's operands are requested
+// delta is spread over the workgroup and joins the same fp32 sum.  The shrink goes in the same launch where its batch is
+// decode-shaped (layer_small_kernel).  The delta costs trips to memory: an item's operands are requested
 // one item ahead, the first item's beside the K loop (32 tokens on 32 adapters, 4096 -> 11008: kernel 32.5 -> 30.0 us; 64
 // tokens, 5120 -> 13824: 52.1 -> 45.8; the product alone takes 21 and 35).  v is read as the shrink left it (fp32, K parts
 // added in order); with bf16 it is split into two bf16 terms in registers, or, for ranks off the tuned kernels, multiplied as
@@ -31,16 +32,46 @@
 
 namespace {
 
-template <typename E, int FB, int TB, int D, row_delta DELTA, bool KTAIL>
-__global__ __launch_bounds__(512) void gemm_small_kernel(
-    int T, int K, int N, const E* __restrict__ x, int64_t ldx, const E* __restrict__ Wt, int64_t ldw,
-    E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, row_delta_args da)
+// Hand-off of v inside a launch (layer_small_kernel).  Shrink workgroup b counts itself in slot b % 16 of `done` when its
+// part of v is published, product workgroup b in slot b % 16 of `through` when it has no more use for v; neither is ever
+// reset.  A product workgroup that is not through itself divides its slot of `through` by that slot's workgroups and has
+// the number of launches before this one, so it knows what every slot of `done` will read when all of v is there.
+// Shrink workgroups wait for nothing and start first.  The wait for them is bounded in time: after wait_ticks of the
+// device's wall clock a wavefront computes the rows of v that it needs itself, from x and At.
+constexpr int kSyncSlots = 16;
+struct layer_sync_slot {         // a cache line of its own
+    unsigned long long done, through;
+    unsigned long long pad[14];
+};
+static_assert(sizeof(layer_sync_slot) * kSyncSlots == LORA_LAYER_SYNC_BYTES, "size of the slots in a plan's device tables");
+__host__ __device__ constexpr int workgroups_of_slot(int n, int slot) { return (n + kSyncSlots - 1 - slot) / kSyncSlots; }
+
+struct shrink_args {
+    const lora_tile* tiles;      // list_parts K parts each, next to each other; here `parts` of them
+    const int32_t* perm;
+    const float* scale;
+    const bf16_t* const* At_ptrs;
+    layer_sync_slot* sync;
+    int n_wg, parts, list_parts;
+    long long wait_ticks;
+};
+
+__device__ __forceinline__ unsigned long long ld_agent(const void* p)
+{
+    return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One tile of features x tokens.  HANDOFF: v is published during this launch (see above)
+template <typename E, int FB, int TB, int D, row_delta DELTA, bool KTAIL, bool HANDOFF>
+__device__ __forceinline__ void gemm_small_tile_of(
+    const int wg, int T, int K, int N, const E* __restrict__ x, int64_t ldx, const E* __restrict__ Wt, int64_t ldw,
+    E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, const row_delta_args& da, const shrink_args& sh)
 {
     constexpr int WAVES = 8;
     // workgroups are dealt round-robin to the 8 XCDs; every XCD gets an eighth of the tiles, the token tiles of one feature
     // tile next to each other, so that its W rows come from memory once and are then in that XCD's L2
-    const int n_wg = tiles_n * tiles_t, xcd = (int)blockIdx.x & 7;
-    const int tile = xcd * (n_wg / 8) + min(xcd, n_wg % 8) + ((int)blockIdx.x >> 3);
+    const int n_wg = tiles_n * tiles_t, xcd = wg & 7;
+    const int tile = xcd * (n_wg / 8) + min(xcd, n_wg % 8) + (wg >> 3);
     const int tile_n = tile / tiles_t, tile_t = tile % tiles_t;
     const int n0 = tile_n * 16 * FB, t0 = tile_t * 16 * TB;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -93,7 +124,7 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
             }
             items = __builtin_amdgcn_readlane(my_end, 63);
             // mixture mode: the merged adapter's on every block, masked to the rows that the removal applies to
-            removal = __ballot((my_key & LORA_UNMERGE_BIT) != 0);
+            removal = HANDOFF ? 0 : __ballot((my_key & LORA_UNMERGE_BIT) != 0);
             if (removal) {
                 rm_rank = da.rank[da.merged];
                 rm_steps = (rm_rank + KSTEP - 1) / KSTEP;
@@ -102,7 +133,7 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
         };
         struct item {                                        // (wavefront-uniform)
             const E* Bt;
-            int r, j0, block;
+            int a, r, j0, block;
             uint32_t rows;                                   // of the block that are the adapter's
             bool rm;
         };
@@ -111,6 +142,7 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
                 const int src = __ffsll((unsigned long long)__ballot(my_end > i)) - 1, a = __builtin_amdgcn_readlane(own, src);
                 it.block = src >> 4;
                 it.rows = (uint32_t)(__ballot(own == a) >> (src & 48)) & 0xffffu;
+                it.a = a;
                 it.r = __builtin_amdgcn_readlane(my_rank, src);
                 it.j0 = (i - __builtin_amdgcn_readlane(my_end, src) + __builtin_amdgcn_readlane(my_steps, src)) * KSTEP;
                 it.Bt = reinterpret_cast<const E*>((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_bt, src) |
@@ -119,9 +151,10 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
                 return true;
             }
             i -= items;
-            if (i >= TB * rm_steps) return false;
+            if (HANDOFF || i >= TB * rm_steps) return false;
             it.block = i / rm_steps;
             it.rows = (uint32_t)(removal >> (16 * it.block)) & 0xffffu;
+            it.a = da.merged;
             it.r = rm_rank;
             it.j0 = (i - it.block * rm_steps) * KSTEP;
             it.Bt = reinterpret_cast<const E*>(rm_bt);
@@ -129,34 +162,80 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
             return true;
         };
         // K parts of v that are requested ahead (as many as registers hold; the others when they are used)
-        constexpr int AHEAD = ES == 4 || FB * TB >= 8 ? 4 : 1;
+        constexpr int AHEAD = ES == 4 || (FB * TB >= 8 && !HANDOFF) ? 4 : 1;
         struct operands {
             op16 bt[FB];
             floatx4 v[AHEAD][EPC / 4];
         };
         // (past a rank's end v and Bt are read where there is something; `add` masks it)
         auto v_at = [&](const item& it) {
-            const lora_vspec& vsp = it.rm ? da.vsp2 : da.vsp;
-            return (it.rm ? da.v2 : da.v) + (int64_t)__shfl(my_tok, 16 * it.block + m) * vsp.R + min(it.j0 + EPC * g, vsp.R - EPC);
+            const lora_vspec& vsp = !HANDOFF && it.rm ? da.vsp2 : da.vsp;
+            return (!HANDOFF && it.rm ? da.v2 : da.v) + (int64_t)__shfl(my_tok, 16 * it.block + m) * vsp.R + min(it.j0 + EPC * g, vsp.R - EPC);
         };
-        auto load = [&](const item& it, operands& o) {
+        auto v_chunk = [&](const float* p) {
+            if constexpr (HANDOFF) {
+                // (past the caches of this XCD, which may hold what an earlier launch left there)
+                const unsigned long long q[2] = {ld_agent(p), ld_agent(p + 2)};
+                return floatx4{__uint_as_float((uint32_t)q[0]), __uint_as_float((uint32_t)(q[0] >> 32)),
+                               __uint_as_float((uint32_t)q[1]), __uint_as_float((uint32_t)(q[1] >> 32))};
+            } else {
+                return *reinterpret_cast<const floatx4*>(p);
+            }
+        };
+        bool published = true;                               // (wavefront-uniform)
+        auto load_bt = [&](const item& it, operands& o) {
 #pragma unroll
             for (int f = 0; f < FB; ++f) {
                 const int n = n0 + 4 * FB * (m >> 2) + 4 * f + (m & 3);
                 o.bt[f] = row_chunk<E>(it.Bt + (int64_t)(n < N ? n : N - 1) * it.r, it.j0 + EPC * g, it.r);
             }
-            const lora_vspec& vsp = it.rm ? da.vsp2 : da.vsp;
+        };
+        auto load_v = [&](const item& it, operands& o) {
+            if constexpr (HANDOFF) {
+                if (!published) {                            // not seen in time: this lane's ranks of its token, from x and At
+                    const float s_a = sh.scale[it.a];
+                    const bf16_t* const xr = x + (int64_t)__shfl(my_tok, 16 * it.block + m) * ldx;
+                    const bf16_t* const At = sh.At_ptrs[it.a];
+#pragma unroll
+                    for (int q = 0; q < EPC / 4; ++q) o.v[0][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (int i = 0; i < EPC; ++i) {
+                        const bf16_t* const ar = At + (int64_t)min(it.j0 + EPC * g + i, it.r - 1) * K;
+                        float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                        for (int k = 0; k < K; k += 8) {
+                            const u32x4 xa = ldg_unaligned(xr + k), aa = ldg_unaligned(ar + k);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                sum[q] = fmaf(bf16_to_f32((bf16_t)(xa[q] & 0xffffu)), bf16_to_f32((bf16_t)(aa[q] & 0xffffu)), sum[q]);
+                                sum[q] = fmaf(bf16_to_f32((bf16_t)(xa[q] >> 16)), bf16_to_f32((bf16_t)(aa[q] >> 16)), sum[q]);
+                            }
+                        }
+                        const float f = s_a * ((sum[0] + sum[1]) + (sum[2] + sum[3]));
+#pragma unroll
+                        for (int q = 0; q < EPC; ++q) o.v[0][q >> 2][q & 3] = q == i ? f : o.v[0][q >> 2][q & 3];
+                    }
+                    return;
+                }
+            }
+            const lora_vspec& vsp = !HANDOFF && it.rm ? da.vsp2 : da.vsp;
             const float* const p = v_at(it);
 #pragma unroll
             for (int s = 0; s < AHEAD; ++s)
                 if (s < vsp.P) {
 #pragma unroll
-                    for (int q = 0; q < EPC / 4; ++q) o.v[s][q] = *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
+                    for (int q = 0; q < EPC / 4; ++q) o.v[s][q] = v_chunk(p + s * vsp.part + 4 * q);
                 }
         };
+        auto load = [&](const item& it, operands& o) {
+            load_bt(it, o);
+            load_v(it, o);
+        };
         auto add = [&](const item& it, operands& o) {
-            const lora_vspec& vsp = it.rm ? da.vsp2 : da.vsp;
-            if constexpr (AHEAD > 1) {
+            const lora_vspec& vsp = !HANDOFF && it.rm ? da.vsp2 : da.vsp;
+            if (HANDOFF && !published) {
+                // (the sum itself)
+            } else if constexpr (AHEAD > 1) {
 #pragma unroll
                 for (int s = 1; s < 4; ++s)
                     if (s < vsp.P) {
@@ -170,7 +249,7 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
                 for (int s = 1; s < 4; ++s)
                     if (s < vsp.P) {
 #pragma unroll
-                        for (int q = 0; q < EPC / 4; ++q) rest[s - 1][q] = *reinterpret_cast<const floatx4*>(p + s * vsp.part + 4 * q);
+                        for (int q = 0; q < EPC / 4; ++q) rest[s - 1][q] = v_chunk(p + s * vsp.part + 4 * q);
                     }
 #pragma unroll
                 for (int s = 1; s < 4; ++s)
@@ -212,12 +291,42 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
         operands o0, o1;
         int i = wave;
         bool more = false;
+        // HANDOFF: lane l < 16 looks after slot l of `done`
+        unsigned long long before = 0, seen = 0;
+        const layer_sync_slot* slot = nullptr;
+        const int own_slot = wg & (kSyncSlots - 1);
         const auto first = [&] {
             share_out();
             more = find(i, i0);
-            if (more) load(i0, o0);
+            if (!more) return;
+            if constexpr (HANDOFF) {
+                load_bt(i0, o0);
+                before = ld_agent(&sh.sync[own_slot].through);
+                slot = sh.sync + (lane & (kSyncSlots - 1));
+            } else {
+                load(i0, o0);
+            }
         };
-        if constexpr (ES == 4) part.drain(u_begin, u_end, [] {}, first);  // (a branch in its loop costs the matrix cores more than it hides)
+        if constexpr (HANDOFF) {
+            part.drain(u_begin, u_end, first, [&] { if (more) seen = ld_agent(&slot->done); });
+            if (more) {
+                const unsigned long long target =
+                    (before / (unsigned)workgroups_of_slot(n_wg, own_slot) + 1) * (unsigned)workgroups_of_slot(sh.n_wg, lane & (kSyncSlots - 1));
+                if (__ballot(seen < target) != 0) {
+                    const long long t0 = (long long)wall_clock64();
+                    for (;;) {
+                        seen = ld_agent(&slot->done);
+                        published = __ballot(seen < target) == 0;
+                        if (published || (long long)wall_clock64() - t0 >= sh.wait_ticks) break;
+                        __builtin_amdgcn_s_sleep(2);
+                    }
+                }
+                // the counts have been seen, so every store of v was acknowledged before; the fence keeps the compiler from
+                // moving loads of v up
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                load_v(i0, o0);
+            }
+        } else if constexpr (ES == 4) part.drain(u_begin, u_end, [] {}, first);  // (a branch in its loop costs the matrix cores more than it hides)
         else part.drain(u_begin, u_end, first, [] {});
         while (more) {
             more = find(i += WAVES, i1);
@@ -233,6 +342,8 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
     // ---- partial sums meet in LDS, one rounding, store (rows go back to their tokens) ----
     part.park();
     __syncthreads();
+    if (HANDOFF && tid == 0)
+        __hip_atomic_fetch_add(&sh.sync[wg & (kSyncSlots - 1)].through, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // a thread finishes F4 consecutive blocks (4 F4 consecutive features) of one lane's token
     constexpr int ITEMS = FB * TB * 64, F4 = ITEMS > 512 ? ITEMS / 512 : 1;
     if (wave * F4 >= FB * TB) return;
@@ -270,21 +381,92 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
 }
 
 template <typename E, int FB, int TB, int D, row_delta DELTA, bool KTAIL>
+__global__ __launch_bounds__(512) void gemm_small_kernel(
+    int T, int K, int N, const E* __restrict__ x, int64_t ldx, const E* __restrict__ Wt, int64_t ldw,
+    E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, row_delta_args da)
+{
+    gemm_small_tile_of<E, FB, TB, D, DELTA, KTAIL, false>((int)blockIdx.x, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, y_vec, da, shrink_args{});
+}
+
+// A tile of the shrink (16 FB rank rows x 16 tokens x a K part) in a launch that reads v: stored past this XCD's caches,
+// counted when the stores are acknowledged.
+template <int FB, int D, bool KTAIL>
+__device__ __forceinline__ void publish_shrink(const lora_tile& t, int wg, int K, const bf16_t* __restrict__ x, int64_t ldx, float* v,
+                                               const lora_vspec& vsp, const shrink_args& sh)
+{
+    const uint64_t at = reinterpret_cast<uint64_t>(sh.At_ptrs[t.adapter] + (int64_t)t.c0 * K);
+    const bf16_t* const At = reinterpret_cast<const bf16_t*>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at) |
+                                                            ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32));
+    const int32_t* rows = sh.perm + t.row0;
+    const float s_a = __int_as_float(t.reserved1);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kpart = wg % sh.parts;
+    using slice = split_k<bf16_t, FB, 1, D, KTAIL>;
+    const int units = (K + slice::KUNIT - 1) / slice::KUNIT;
+    const int p_begin = units * kpart / sh.parts, p_end = units * (kpart + 1) / sh.parts;
+    const auto w_row = [&](int row) { return (int64_t)min(row, t.cn - 1) * K; };
+    const auto x_row = [&](int row) { return (int64_t)rows[min(row, t.nrows - 1)] * ldx; };
+    slice part(K, At, x, wave, w_row, x_row);
+    const int u_begin = p_begin + (p_end - p_begin) * wave / 8, u_end = p_begin + (p_end - p_begin) * (wave + 1) / 8;
+    // whole lines to LDS need 16-byte rows, and 32-bit offsets a tile of less than 4 GB
+    if ((reinterpret_cast<uintptr_t>(At) & 15) == 0 && (int64_t)t.cn * K * 2 <= (1ll << 32)) part.run(u_begin, u_end);
+    else part.run_anywhere(At, x, w_row, x_row, u_begin, u_end);
+    part.park();
+    __syncthreads();
+    const int m = lane & 15, j = 4 * FB * (lane >> 4) + 4 * wave;
+    if (wave < FB && m < t.nrows && j < t.cn) {              // (ranks are multiples of 8)
+        const floatx4 sum = s_a * slice::total(wave, 0);
+        float* const dst = v + kpart * vsp.part + (int64_t)rows[m] * vsp.R + t.c0 + j;
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+            const unsigned long long two = (unsigned long long)__float_as_uint(sum[i]) | ((unsigned long long)__float_as_uint(sum[i + 1]) << 32);
+            __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst + i), two, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // every storing thread waits for its stores' acknowledgement, then one adds the workgroup to the count
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) __hip_atomic_fetch_add(&sh.sync[wg & (kSyncSlots - 1)].done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Shrink and product of a small batch in one launch: workgroups [0, n_wg) of the shrink, then those of the product, which
+// need v only behind their K loop.  The shrink alone is a launch of 4 to 7 us that leaves most of the memory rate unused;
+// here it runs beside the product's first loads of W (what that gave: layer_small_planned).
+template <int FB, int TB, int D, bool KTAIL>
+__global__ __launch_bounds__(512) void layer_small_kernel(
+    int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
+    bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da, float* v, shrink_args sh)
+{
+    const int wg = (int)blockIdx.x;
+    if (wg < sh.n_wg) {
+        const lora_tile t = sh.tiles[wg / sh.parts * sh.list_parts];
+        if (((t.shape >> 4) & 15) == 1) publish_shrink<1, 2, KTAIL>(t, wg, K, x, ldx, v, da.vsp, sh);
+        else publish_shrink<2, 1, KTAIL>(t, wg, K, x, ldx, v, da.vsp, sh);
+    } else {
+        gemm_small_tile_of<bf16_t, FB, TB, D, TERMS_DELTA, KTAIL, true>(wg - sh.n_wg, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, true, da, sh);
+    }
+}
+
+// dynamic LDS above 64 KB has to be allowed once per kernel
+template <typename Kernel>
+hipError_t allow_lds(Kernel kernel, size_t bytes, std::atomic<bool>& done)
+{
+    if (bytes <= 65536 || done) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) done = true;
+    return e;
+}
+
+template <typename E, int FB, int TB, int D, row_delta DELTA, bool KTAIL>
 hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
                       const row_delta_args& da, hipStream_t stream)
 {
     const int tiles_n = (N + 16 * FB - 1) / (16 * FB), tiles_t = (T + 16 * TB - 1) / (16 * TB);
     constexpr size_t lds_bytes = (size_t)8 * D * (2 * FB + 2 * TB) * 1024;
     static_assert(D * (2 * FB + 2 * TB) >= FB * TB && lds_bytes <= 163840, "a wavefront's partial sums go where its operands were");
-    if (lds_bytes > 65536) {                                  // dynamic LDS above 64 KB has to be allowed once per kernel
-        static std::atomic<bool> attr_set{false};
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_small_kernel<E, FB, TB, D, DELTA, KTAIL>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-            if (e != hipSuccess) return e;
-            attr_set = true;
-        }
-    }
+    static std::atomic<bool> allowed{false};
+    const hipError_t e = allow_lds(&gemm_small_kernel<E, FB, TB, D, DELTA, KTAIL>, lds_bytes, allowed);
+    if (e != hipSuccess) return e;
     LORA_LAUNCH(DELTA != NO_DELTA ? LORA_K_GEMM_SMALL_DELTA : LORA_K_GEMM_SMALL, (gemm_small_kernel<E, FB, TB, D, DELTA, KTAIL>),
                 dim3((unsigned)(tiles_n * tiles_t)), dim3(512), lds_bytes, stream, T, K, N, (const E*)x, ldx, (const E*)Wt, ldw,
                 (E*)y, ldy, tiles_n, tiles_t, ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0, da);
@@ -375,4 +557,69 @@ hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, con
     return p->extra_ptr256.empty() ? SMALL_DISPATCH(bf16_t, PLAIN_DELTA) : SMALL_DISPATCH(bf16_t, TERMS_DELTA);
 #undef SMALL_DISPATCH
 #undef SMALL_LAUNCH
+}
+
+// Whether launch_layer_small takes the plan's product: decode-shaped batches (16-token tiles of the shrink).  Microseconds of
+// lora_fused_forward, two launches / one: 64 tokens on 32 adapters, 4096 -> 4096, 18.7 / 15.3; one token 12.0 / 9.2; 16
+// tokens, 4096 -> 11008, 28.1 / 23.6; 12 tokens, 13824 -> 5120, 44.8 / 35.9; 90 tokens on 64 adapters, 4096 -> 11008, 72.4 /
+// 63.0; 160 tokens, 4096 -> 4096, 23.9 / 17.8.  Not on the 32 x 64 tiles: of those a compute unit holds one workgroup, and they
+// come where there is one for each, so some start only behind the shrink (100 tokens on 100 adapters of rank 8, 22.5 / 23.2; on
+// 64 of rank 64 35.5 / 34.4).
+bool layer_small_planned(const lora_plan* p)
+{
+    if (p->dtype != LORA_BF16 || p->family != LORA_VARIANT_TILED || !p->shrink_small || p->shrink_tiles.empty() || p->unmerge ||
+        p->extra_ptr256.empty() || (int32_t)p->order.size() != p->T)
+        return false;
+    const small_tile t = choose_small_tile(p->T, p->K, p->N, LORA_BF16);
+    return !(t.fb == 2 && t.tb == 4);
+}
+
+namespace {
+template <int FB, int TB, int D, bool KTAIL>
+hipError_t launch_layer_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
+                            const row_delta_args& da, float* v, const shrink_args& sh, hipStream_t stream)
+{
+    const int tiles_n = (N + 16 * FB - 1) / (16 * FB), tiles_t = (T + 16 * TB - 1) / (16 * TB);
+    // (the shrink's widest: 8 KB a wavefront)
+    constexpr size_t lds_bytes = std::max<size_t>((size_t)8 * D * (2 * FB + 2 * TB) * 1024, 65536);
+    static std::atomic<bool> allowed{false};
+    const hipError_t e = allow_lds(&layer_small_kernel<FB, TB, D, KTAIL>, lds_bytes, allowed);
+    if (e != hipSuccess) return e;
+    LORA_LAUNCH(LORA_K_GEMM_SMALL_DELTA, (layer_small_kernel<FB, TB, D, KTAIL>), dim3((unsigned)(sh.n_wg + tiles_n * tiles_t)), dim3(512), lds_bytes,
+                stream, T, K, N, (const bf16_t*)x, ldx, (const bf16_t*)Wt, ldw, (bf16_t*)y, ldy, tiles_n, tiles_t, da, v, sh);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_layer_small(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
+                              const lora_plan* p, const lora_dev_tables* d, float* v, const void* const* At, const void* const* Bt,
+                              hipStream_t stream)
+{
+    static std::atomic<int> wall_khz[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (wall_khz[dev] == 0) {
+        int khz = 0;
+        if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0) khz = 100000;
+        wall_khz[dev] = khz;
+    }
+    const small_tile t = choose_small_tile(T, K, N, LORA_BF16);
+    // K parts: few tiles are a long chain each, many take compute units from the product, and a second part is another trip to
+    // memory for each of its items.  Microseconds with 1 / 2 / 4 parts, 4096 -> 4096: 4 tiles (one token) 10.9 / 9.9 / 9.2, 16
+    // (8 tokens) 12.3 / 11.8 / 12.3, 60 (32 tokens) 16.5 / 16.1 / 23.3; 30 tiles, 4096 -> 11008, 24.6 / 26.4 / 30.3
+    const int tiles = (int)p->shrink_tiles.size() / p->v_parts;
+    int parts = 1;
+    while (parts < p->v_parts && 2 * parts * tiles <= 32) parts *= 2;
+    row_delta_args da = row_deltas_of(p, d, v, gemm_removal{}, Bt);
+    da.vsp.P = parts;
+    const shrink_args sh{d->shrink_tiles, d->perm, d->scale, (const bf16_t* const*)At, (layer_sync_slot*)d->layer_sync, tiles * parts, parts,
+                         p->v_parts, (long long)p->fused_wait_us * wall_khz[dev] / 1000};
+    const bool ktail = K % 64 != 0;
+#define LAYER_TILE(FB_, TB_, D_)                                                                                                           \
+    if (t.fb == FB_ && t.tb == TB_)                                                                                                        \
+        return ktail ? launch_layer_one<FB_, TB_, D_, true>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, v, sh, stream)                            \
+                     : launch_layer_one<FB_, TB_, D_, false>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, v, sh, stream);
+    LAYER_TILE(4, 4, 1) LAYER_TILE(4, 2, 1) LAYER_TILE(2, 2, 1) LAYER_TILE(4, 1, 1) LAYER_TILE(1, 2, 1) LAYER_TILE(1, 1, 2)
+#undef LAYER_TILE
+    return hipErrorInvalidValue;
 }

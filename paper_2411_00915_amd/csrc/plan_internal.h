@@ -110,12 +110,15 @@ struct lora_plan {
     lora_tile* d_rows_expand_tiles = nullptr;
     lora_tile* d_f32_delta_tiles = nullptr;
     void* d_zeros = nullptr;          // 256 zero bytes (source of masked chunks in the fused GEMM)
+    void* d_layer_sync = nullptr;     // hand-off counters of shrink and product in one launch (only where layer_small_planned)
     void* d_sync = nullptr;           // hand-off counters, 128 bytes per adapter group (only when fused_ok)
 };
 
 // How a plan's device tables are released: set by the translation unit that owns them (abi.hip) when the library
 // is loaded; stays null in host-only builds of the planner, where no plan ever has device tables.
 extern void (*lora_plan_device_release)(lora_plan*);
+
+constexpr size_t LORA_LAYER_SYNC_BYTES = 16 * 128;
 
 // stage ids and row keys of the fused GEMM: bit 23 marks the stages / the rows of the merged adapter's removal
 constexpr int32_t LORA_UNMERGE_BIT = 1 << 23;

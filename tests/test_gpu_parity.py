@@ -309,6 +309,38 @@ def test_small_batch_gemm_tiles_and_remainders(T, K, N):
         run_mixture_case(w, 2)
 
 
+@pytest.mark.parametrize("wait", [True, False])
+@pytest.mark.parametrize("T,K,N,tile", [
+    (1, 1024, 1000, (1, 1)), (7, 72, 264, (1, 1)), (25, 1096, 3992, (1, 2)), (37, 584, 4096, (2, 2)), (16, 520, 11008, (4, 1)),
+    (20, 512, 13824, (4, 2)), (40, 520, 13816, (4, 4)), (200, 264, 4104, (4, 2))])
+def test_small_batch_shrink_and_gemm_in_one_launch(T, K, N, tile, wait):
+    """Every tile that takes the shrink into its launch, K tails, one K part and more, remainders of tokens and features,
+    tokens without adapter, factors on 16-byte boundaries and off them.  Every call has another x: v of the call before
+    would show.  wait=False: the product never waits for the shrink and computes v itself."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, True)[1:] == tile
+    w = wl.random_case(1700 + T + K, T, K, N, 9 if T < 100 else 40, (8, 16, 40, 64), max_seg=5, frac_none=0.15 if T > 1 else 0.0, scales=(0.5, 2.0, -1.0))
+    dl = device.to_device(w, DEV, with_w=True)
+    plan = device.make_plan(w, tuning=None if wait else {"fused_wait_us": 1})
+    _, _, ws_bytes = B.lora_plan_query(plan)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    keep = [torch.empty(a.size + 8, dtype=torch.bfloat16, device=DEV) for a in w.A]
+    for i, (buf, a) in enumerate(zip(keep, w.A)):
+        buf[i % 8:i % 8 + a.size] = torch.from_numpy(np.ascontiguousarray(a.T).ravel()).to(DEV, torch.bfloat16)
+    odd = torch.tensor([buf.data_ptr() + 2 * (i % 8) for i, buf in enumerate(keep)], dtype=torch.int64, device=DEV)
+    ws = torch.full((ws_bytes,), 255, dtype=torch.uint8, device=DEV)          # (fp32: NaN)
+    y = torch.full((T + 1, N), 9.0, dtype=torch.bfloat16, device=DEV)
+    for call, At in enumerate((dl.At_ptrs, odd, dl.At_ptrs)):
+        x = wl.round_to_bf16(np.random.default_rng(call).standard_normal((T, K)).astype(np.float32))
+        xd = torch.from_numpy(x).to(DEV, torch.bfloat16)
+        names = _launched(lambda: B.lora_fused_forward(plan, xd, K, dl.Wt, K, At, dl.Bt_ptrs, y, N, ws, ws.numel()))
+        torch.cuda.synchronize()
+        assert names == {"gemm_small_kernel<delta>"}, "one launch"
+        _assert_close(_to_np(y)[:T], oracle.forward(x, w.W, tok, ad), BF16_TOL, f"fused forward, call {call}")
+    assert bool((y[T] == 9.0).all()), "written beyond the last token"
+    plan.destroy()
+
+
 @pytest.mark.parametrize("T,K,N", SMALL_GEMM_SHAPES + [(70, 100, 77)])
 def test_fp32_gemm_tiles_and_remainders(T, K, N):
     """The same kernel in fp32, also with an N that is no multiple of 4.  A sum of n = K + rank fp32 additions whose
