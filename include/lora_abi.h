@@ -336,7 +336,7 @@ lora_status lora_base_gemm(int32_t num_tokens, int32_t k, int32_t n, int32_t dty
  * 256-byte aligned), then one GEMM kernel that walks the tokens in
  * adapter-sorted order and adds each adapter's v B_a to the accumulators of
  * the rows that carry it (as extra k-stages of its pipeline, or wavefront by
- * wavefront after the K loop, depending on the kernel).  Decode-shaped batches run
+ * wavefront after the K loop, depending on the kernel).  Small bf16 batches run
  * as one launch: the product's workgroups need v only behind their K loop and wait
  * (bounded) for the shrink's through counters in the plan's device tables; if those
  * are not seen in time they compute v themselves.  LORA_ERR_WORKSPACE if

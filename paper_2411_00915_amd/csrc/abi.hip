@@ -64,7 +64,7 @@ bool misaligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p
 struct table_layout {
     size_t perm, token_adapter, row_key, rank, scale, shrink_tiles, expand_tiles, sync, sync_bytes, layer_sync, layer_sync_bytes, total;
     size_t order, extra_ptr128, extra128, extra_ptr256, extra256, zeros, shrink_rows, expand_rows;
-    size_t rows_shrink, rows_expand, f32_delta;
+    size_t rows_shrink, rows_expand, f32_delta, layer_shrink;
 };
 
 table_layout layout_of(const lora_plan* p)
@@ -90,6 +90,7 @@ table_layout layout_of(const lora_plan* p)
     L.rows_shrink = take(p->rows_shrink_tiles.size() * sizeof(lora_tile));
     L.rows_expand = take(p->rows_expand_tiles.size() * sizeof(lora_tile));
     L.f32_delta = take(p->f32_delta_tiles.size() * sizeof(lora_tile));
+    L.layer_shrink = take(p->layer_shrink_tiles.size() * sizeof(lora_tile));
     L.sync_bytes = p->fused_ok ? p->group_adapter.size() * 128 : 0;
     L.sync = take(L.sync_bytes);
     L.layer_sync_bytes = layer_small_planned(p) ? LORA_LAYER_SYNC_BYTES : 0;
@@ -158,6 +159,7 @@ lora_status ensure_uploaded(lora_plan* p, hipStream_t stream)
     put(L.rows_shrink, p->rows_shrink_tiles.data(), p->rows_shrink_tiles.size() * sizeof(lora_tile));
     put(L.rows_expand, p->rows_expand_tiles.data(), p->rows_expand_tiles.size() * sizeof(lora_tile));
     put(L.f32_delta, p->f32_delta_tiles.data(), p->f32_delta_tiles.size() * sizeof(lora_tile));
+    put(L.layer_shrink, p->layer_shrink_tiles.data(), p->layer_shrink_tiles.size() * sizeof(lora_tile));
     std::memset(h + L.sync, 0, L.sync_bytes);                    // hand-off counters start at zero
     std::memset(h + L.layer_sync, 0, L.layer_sync_bytes);
     if (hipMemcpyAsync(dbuf, hbuf, L.total, hipMemcpyHostToDevice, stream) != hipSuccess) {
@@ -191,6 +193,7 @@ lora_status ensure_uploaded(lora_plan* p, hipStream_t stream)
     p->d_rows_shrink_tiles = reinterpret_cast<lora_tile*>(d + L.rows_shrink);
     p->d_rows_expand_tiles = reinterpret_cast<lora_tile*>(d + L.rows_expand);
     p->d_f32_delta_tiles = reinterpret_cast<lora_tile*>(d + L.f32_delta);
+    p->d_layer_shrink_tiles = reinterpret_cast<lora_tile*>(d + L.layer_shrink);
     return LORA_OK;
 }
 
@@ -199,7 +202,7 @@ lora_dev_tables tables_of(const lora_plan* p)
     return lora_dev_tables{p->d_perm, p->d_token_adapter, p->d_row_key, p->d_rank, p->d_scale, p->d_shrink_tiles, p->d_expand_tiles,
                            p->d_sync, p->d_order, p->d_extra_ptr128, p->d_extra128, p->d_extra_ptr256, p->d_extra256, p->d_zeros,
                            p->d_shrink_rows, p->d_expand_rows, p->d_rows_shrink_tiles, p->d_rows_expand_tiles, p->d_f32_delta_tiles,
-                           p->d_layer_sync};
+                           p->d_layer_shrink_tiles, p->d_layer_sync};
 }
 
 size_t elem_bytes(int32_t dtype) { return dtype == LORA_F32 ? 4 : 2; }

@@ -37,6 +37,7 @@ struct lora_dev_tables {
     const lora_tile* rows_shrink_tiles;
     const lora_tile* rows_expand_tiles;
     const lora_tile* f32_delta_tiles;
+    const lora_tile* layer_shrink_tiles;
     void* layer_sync;              // hand-off counters of launch_layer_small; null: the plan has none
 };
 

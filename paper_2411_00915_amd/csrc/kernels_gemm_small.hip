@@ -17,8 +17,7 @@
 //
 // DELTA: tokens in adapter-sorted order; before the partial sums are added up, the wavefronts share out the items
 // (16-token block, adapter in it, rank step) of the tile's tokens and add v B_a of theirs to their own partial sums, so the
-// delta is spread over the workgroup and joins the same fp32 sum.  The shrink goes in the same launch where its batch is
-// decode-shaped (layer_small_kernel).  The delta costs trips to memory: an item's operands are requested
+// delta is spread over the workgroup and joins the same fp32 sum.  The shrink goes in the same launch (layer_small_kernel).  The delta costs trips to memory: an item's operands are requested
 // one item ahead, the first item's beside the K loop (32 tokens on 32 adapters, 4096 -> 11008: kernel 32.5 -> 30.0 us; 64
 // tokens, 5120 -> 13824: 52.1 -> 45.8; the product alone takes 21 and 35).  v is read as the shrink left it (fp32, K parts
 // added in order); with bf16 it is split into two bf16 terms in registers, or, for ranks off the tuned kernels, multiplied as
@@ -559,15 +558,15 @@ hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, con
 #undef SMALL_LAUNCH
 }
 
-// Whether launch_layer_small takes the plan's product: decode-shaped batches (16-token tiles of the shrink).  Microseconds of
-// lora_fused_forward, two launches / one: 64 tokens on 32 adapters, 4096 -> 4096, 18.7 / 15.3; one token 12.0 / 9.2; 16
-// tokens, 4096 -> 11008, 28.1 / 23.6; 12 tokens, 13824 -> 5120, 44.8 / 35.9; 90 tokens on 64 adapters, 4096 -> 11008, 72.4 /
-// 63.0; 160 tokens, 4096 -> 4096, 23.9 / 17.8.  Not on the 32 x 64 tiles: of those a compute unit holds one workgroup, and they
-// come where there is one for each, so some start only behind the shrink (100 tokens on 100 adapters of rank 8, 22.5 / 23.2; on
-// 64 of rank 64 35.5 / 34.4).
+// Whether launch_layer_small takes the plan's product.  Microseconds of lora_fused_forward, two launches / one; requests of one
+// token: 64 tokens on 32 adapters, 4096 -> 4096, 18.7 / 15.3; one token 12.0 / 9.2; 16 tokens, 4096 -> 11008, 28.1 / 23.6; 12
+// tokens, 13824 -> 5120, 44.8 / 35.9; 90 tokens on 64 adapters, 4096 -> 11008, 72.4 / 63.0; 160 tokens, 4096 -> 4096, 23.9 /
+// 17.8; longer ones: 64 tokens, rank 64, 18.4 / 12.1; 256 tokens, rank 128, 31.7 / 26.2.  Not on the 32 x 64 tiles: of those a
+// compute unit holds one workgroup, and they come where there is one for each, so some start only behind the shrink (100
+// tokens on 100 adapters of rank 8, 22.5 / 23.2; on 64 of rank 64 35.5 / 34.4).
 bool layer_small_planned(const lora_plan* p)
 {
-    if (p->dtype != LORA_BF16 || p->family != LORA_VARIANT_TILED || !p->shrink_small || p->shrink_tiles.empty() || p->unmerge ||
+    if (p->dtype != LORA_BF16 || p->family != LORA_VARIANT_TILED || p->unmerge || (p->shrink_small ? p->shrink_tiles : p->layer_shrink_tiles).empty() ||
         p->extra_ptr256.empty() || (int32_t)p->order.size() != p->T)
         return false;
     const small_tile t = choose_small_tile(p->T, p->K, p->N, LORA_BF16);
@@ -607,13 +606,14 @@ hipError_t launch_layer_small(int32_t T, int32_t K, int32_t N, const void* x, in
     // K parts: few tiles are a long chain each, many take compute units from the product, and a second part is another trip to
     // memory for each of its items.  Microseconds with 1 / 2 / 4 parts, 4096 -> 4096: 4 tiles (one token) 10.9 / 9.9 / 9.2, 16
     // (8 tokens) 12.3 / 11.8 / 12.3, 60 (32 tokens) 16.5 / 16.1 / 23.3; 30 tiles, 4096 -> 11008, 24.6 / 26.4 / 30.3
-    const int tiles = (int)p->shrink_tiles.size() / p->v_parts;
+    const bool own_tiles = p->shrink_small;
+    const int list_parts = own_tiles ? p->v_parts : 1, tiles = (int)(own_tiles ? p->shrink_tiles : p->layer_shrink_tiles).size() / list_parts;
     int parts = 1;
     while (parts < p->v_parts && 2 * parts * tiles <= 32) parts *= 2;
     row_delta_args da = row_deltas_of(p, d, v, gemm_removal{}, Bt);
     da.vsp.P = parts;
-    const shrink_args sh{d->shrink_tiles, d->perm, d->scale, (const bf16_t* const*)At, (layer_sync_slot*)d->layer_sync, tiles * parts, parts,
-                         p->v_parts, (long long)p->fused_wait_us * wall_khz[dev] / 1000};
+    const shrink_args sh{own_tiles ? d->shrink_tiles : d->layer_shrink_tiles, d->perm, d->scale, (const bf16_t* const*)At, (layer_sync_slot*)d->layer_sync, tiles * parts, parts,
+                         list_parts, (long long)p->fused_wait_us * wall_khz[dev] / 1000};
     const bool ktail = K % 64 != 0;
 #define LAYER_TILE(FB_, TB_, D_)                                                                                                           \
     if (t.fb == FB_ && t.tb == TB_)                                                                                                        \

@@ -75,6 +75,8 @@ struct lora_plan {
     std::vector<lora_tile> rows_shrink_tiles, f32_delta_tiles;
     // expand tiles of the kernel that takes rows of any length: fp32, and bf16 with ranks the tuned kernels do not take
     std::vector<lora_tile> rows_expand_tiles;
+    // shrink tiles of shrink and product in one launch; empty: shrink_tiles are of their size (shrink_small), or none
+    std::vector<lora_tile> layer_shrink_tiles;
     int32_t rows_expand_lds = 0, rows_expand_tb = 1;   // of its launch: dynamic LDS bytes, token blocks of the largest tile
     int32_t rows_shrink_fb = 1, rows_shrink_tb = 1;
     // fused GEMM: what a row (in the order above, so that both come with one round of loads) is matched against an adapter
@@ -109,6 +111,7 @@ struct lora_plan {
     lora_tile* d_rows_shrink_tiles = nullptr;
     lora_tile* d_rows_expand_tiles = nullptr;
     lora_tile* d_f32_delta_tiles = nullptr;
+    lora_tile* d_layer_shrink_tiles = nullptr;
     void* d_zeros = nullptr;          // 256 zero bytes (source of masked chunks in the fused GEMM)
     void* d_layer_sync = nullptr;     // hand-off counters of shrink and product in one launch (only where layer_small_planned)
     void* d_sync = nullptr;           // hand-off counters, 128 bytes per adapter group (only when fused_ok)

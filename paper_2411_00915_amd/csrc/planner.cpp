@@ -698,6 +698,31 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
     }
 }
 
+// Shrink tiles of 16 tokens x up to 32 rank rows for the launch that has the product of a small batch in it, where the
+// plan's own are not of that size (requests of several tokens, ranks above 64).  Batches above 512 tokens are the larger GEMMs'.
+static void build_layer_tiles(lora_plan* p)
+{
+    if (p->family != LORA_VARIANT_TILED || p->shrink_small || p->unmerge || p->T > 512) return;
+    for (size_t g = 0; g < p->group_adapter.size(); ++g) {
+        const int32_t a = p->group_adapter[g], r = p->rank[a];
+        for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16)
+            for (int32_t j = 0; j < r; j += 32) {
+                lora_tile t{};
+                t.adapter = a;
+                t.row0 = row;
+                t.nrows = std::min(16, p->group_offset[g + 1] - row);
+                t.c0 = j;
+                t.cn = std::min(32, r - j);
+                t.shape = lora_shape_code(1, t.cn > 16 ? 2 : 1);
+                t.reserved0 = r;
+                std::memcpy(&t.reserved1, &p->scale[a], sizeof(float));
+                p->layer_shrink_tiles.push_back(t);
+            }
+    }
+    std::stable_sort(p->layer_shrink_tiles.begin(), p->layer_shrink_tiles.end(),
+                     [](const lora_tile& x, const lora_tile& y) { return x.cn > y.cn; });
+}
+
 // One plan over the descriptor's segments as they stand; `unmerge` (may be null) is the removal's plan of a batch
 // in mixture mode, which the new plan takes over.
 static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_plan* unmerge, lora_plan** out)
@@ -781,6 +806,7 @@ static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_p
             build_rows_expand_tiles(p, 0);
         // (in mixture mode the removal's v must have the layout the GEMM's stages read, too)
         if (p->n_a < LORA_UNMERGE_BIT) build_gemm_tables(p, p->tiled_layout_ok && (!unmerge || unmerge->tiled_layout_ok));
+        build_layer_tiles(p);
     } catch (const std::bad_alloc&) {
         lora_plan_destroy(p);
         return LORA_ERR_NOMEM;

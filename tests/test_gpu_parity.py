@@ -310,15 +310,16 @@ def test_small_batch_gemm_tiles_and_remainders(T, K, N):
 
 
 @pytest.mark.parametrize("wait", [True, False])
-@pytest.mark.parametrize("T,K,N,tile", [
-    (1, 1024, 1000, (1, 1)), (7, 72, 264, (1, 1)), (25, 1096, 3992, (1, 2)), (37, 584, 4096, (2, 2)), (16, 520, 11008, (4, 1)),
-    (20, 512, 13824, (4, 2)), (40, 520, 13816, (4, 4)), (200, 264, 4104, (4, 2))])
-def test_small_batch_shrink_and_gemm_in_one_launch(T, K, N, tile, wait):
+@pytest.mark.parametrize("T,K,N,tile,max_seg", [
+    (1, 1024, 1000, (1, 1), 1), (7, 72, 264, (1, 1), 5), (25, 1096, 3992, (1, 2), 5), (37, 584, 4096, (2, 2), 5), (16, 520, 11008, (4, 1), 5),
+    (20, 512, 13824, (4, 2), 5), (40, 520, 13816, (4, 4), 5), (200, 264, 4104, (4, 2), 5), (61, 1032, 4096, (2, 2), 61),
+    (250, 1096, 4096, (4, 4), 150)])
+def test_small_batch_shrink_and_gemm_in_one_launch(T, K, N, tile, max_seg, wait):
     """Every tile that takes the shrink into its launch, K tails, one K part and more, remainders of tokens and features,
-    tokens without adapter, factors on 16-byte boundaries and off them.  Every call has another x: v of the call before
+    tokens without adapter, requests of many tokens and high ranks, factors on 16-byte boundaries and off them.  Every call has another x: v of the call before
     would show.  wait=False: the product never waits for the shrink and computes v itself."""
     assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, True)[1:] == tile
-    w = wl.random_case(1700 + T + K, T, K, N, 9 if T < 100 else 40, (8, 16, 40, 64), max_seg=5, frac_none=0.15 if T > 1 else 0.0, scales=(0.5, 2.0, -1.0))
+    w = wl.random_case(1700 + T + K, T, K, N, 40 if T == 200 else 9, (8, 16, 40, 64) if max_seg <= 5 else (16, 104, 128), max_seg=max_seg, frac_none=0.15 if T > 1 else 0.0, scales=(0.5, 2.0, -1.0))
     dl = device.to_device(w, DEV, with_w=True)
     plan = device.make_plan(w, tuning=None if wait else {"fused_wait_us": 1})
     _, _, ws_bytes = B.lora_plan_query(plan)
