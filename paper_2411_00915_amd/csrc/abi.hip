@@ -416,8 +416,12 @@ extern "C" lora_status lora_delta(lora_plan* p, const void* x, int64_t ldx,
     if (!p) return LORA_ERR_INVALID_ARG;
     if (!(beta == 0.f || beta == 1.f)) return LORA_ERR_INVALID_ARG;
     if (p->unmerge && !p->unmerge->perm.empty()) {             // mixture mode: removal first, see lora_expand
+        if (!x || !d_At_ptrs || !d_Bt_ptrs || !v || !y || ldx < p->K || ldy < p->N) return LORA_ERR_INVALID_ARG;
+        if (misaligned(x, elem_bytes(p->dtype)) || misaligned(y, elem_bytes(p->dtype)) || misaligned(v, 16) || misaligned(d_At_ptrs, 8) ||
+            misaligned(d_Bt_ptrs, 8))
+            return LORA_ERR_INVALID_ARG;
         // in two steps where x and y share memory (all of x is read before any of y is written), and where the shrinks go in one launch
-        if (x && y && ldx >= p->K && ldy >= p->N && (share_memory(p, x, ldx, y, ldy) || streams_both(p, x, ldx))) {
+        if (share_memory(p, x, ldx, y, ldy) || streams_both(p, x, ldx)) {
             const lora_status st = lora_shrink(p, x, ldx, d_At_ptrs, v, hip_stream);
             return st == LORA_OK ? lora_expand(p, v, d_Bt_ptrs, y, ldy, beta, hip_stream) : st;
         }

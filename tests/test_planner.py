@@ -275,6 +275,22 @@ def test_compute_calls_reject_bad_arguments_without_a_gpu():
     assert L.lora_merge(2, 64, 64, 0, f(1.0), B.LORA_BF16, B.LORA_VARIANT_AUTO, None, 64, None, None, None) == B.LORA_OK             # rank 0
 
 
+def test_mixture_delta_is_refused_before_any_launch():
+    """A lora_delta whose two shrinks go in one launch: every bad argument of the second step is seen before the first one
+    runs.  (Without a GPU a call that gets as far as its plan's upload returns LORA_ERR_DEVICE.)"""
+    w = wl.random_case(3, 1200, 1024, 256, 4, (16, 64), max_seg=200, with_w=False)
+    p = device.make_plan(w, merged_adapter=0)
+    v = B.lora_plan_export(p)
+    for tiles in (v["shrink_tiles"], v["unmerge_shrink_tiles"]):       # (only the streaming shrink's tiles hold more than 32 tokens)
+        assert len(tiles) and tiles[:, 2].max() > 32
+    good = dict(x=4096, At=1 << 24, Bt=1 << 25, v=1 << 26, y=1 << 30, ldy=256)
+    for bad in (dict(Bt=None), dict(At=None), dict(y=None), dict(v=None), dict(ldy=255), dict(y=(1 << 30) + 1), dict(Bt=(1 << 25) + 4), dict(v=(1 << 26) + 4)):
+        a = dict(good, **bad)
+        st = B._lib.lora_delta(p.handle, a["x"], 1024, a["At"], a["Bt"], a["v"], a["y"], a["ldy"], ctypes.c_float(1.0), None)
+        assert st == B.LORA_ERR_INVALID_ARG, bad
+    p.destroy()
+
+
 def test_tuning_roundtrip_changes_tiles():
     before = B.lora_tuning_get()
     try:
