@@ -311,7 +311,9 @@ __device__ __forceinline__ void gemm_small_tile_of(
             if (more) {
                 const unsigned long long target =
                     (before / (unsigned)workgroups_of_slot(n_wg, own_slot) + 1) * (unsigned)workgroups_of_slot(sh.n_wg, lane & (kSyncSlots - 1));
-                if (__ballot(seen < target) != 0) {
+                if (sh.wait_ticks == 0) {
+                    published = false;                       // (asked for: not even a look)
+                } else if (__ballot(seen < target) != 0) {
                     const long long t0 = (long long)wall_clock64();
                     for (;;) {
                         seen = ld_agent(&slot->done);

@@ -342,6 +342,40 @@ def test_small_batch_shrink_and_gemm_in_one_launch(T, K, N, tile, max_seg, wait)
     plan.destroy()
 
 
+@pytest.mark.parametrize("T,K,N", [(25, 1096, 3992), (37, 584, 4096), (20, 512, 13824), (200, 264, 4104), (64, 4096, 4096)])
+def test_small_batch_one_launch_without_waiting_computes_v_itself(T, K, N):
+    """Which of its two sources the product takes v from, shown by values that only one of them can sum.  x is zero but for
+    2^127, -2^127 next to each other at the start of K and again behind its middle, where every factor is 1 and W is 0.  The
+    shrink adds neighbours first: v = 0, y = 0.  The product's own sum runs over K with elements 0 and 2 of every eight apart,
+    each reaching 2^128: NaN in every output of a token with an adapter.  fused_wait_us = 1 is no waiting and no looking."""
+    w = wl.random_case(1800 + T, T, K, N, 9, (8, 16, 40, 64), max_seg=5, frac_none=0.2, scales=(1.0,))
+    dl = device.to_device(w, DEV, with_w=True)
+    h = (K + 63) // 64 // 2 * 64
+    cols = torch.tensor([0, 2, h, h + 2], device=DEV)
+    x = torch.zeros((T, K), dtype=torch.bfloat16, device=DEV)
+    x[:, cols] = torch.tensor([2.0 ** 127, -2.0 ** 127] * 2, dtype=torch.bfloat16, device=DEV)
+    dl.Wt[:, cols] = 0
+    keep = [torch.from_numpy(np.ascontiguousarray(a.T)).to(DEV, torch.bfloat16) for a in w.A]
+    for a in keep:
+        a[:, cols] = 1
+    At = torch.tensor([a.data_ptr() for a in keep], dtype=torch.int64, device=DEV)
+    tok = torch.from_numpy(oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)).to(DEV)
+    for wait in (True, False):
+        plan = device.make_plan(w, tuning=None if wait else {"fused_wait_us": 1})
+        ws = torch.zeros(B.lora_plan_query(plan)[2], dtype=torch.uint8, device=DEV)
+        for _ in range(3):
+            y = torch.full((T, N), 9.0, dtype=torch.bfloat16, device=DEV)
+            B.lora_fused_forward(plan, x, K, dl.Wt, K, At, dl.Bt_ptrs, y, N, ws, ws.numel())
+            torch.cuda.synchronize()
+            own = torch.isnan(y) & (tok >= 0)[:, None]
+            assert bool((y[tok < 0] == 0).all()), "tokens without adapter"
+            if wait:
+                assert bool((y == 0).all()), "v of the shrink"
+            else:
+                assert bool(own[tok >= 0].all()), "v of the product's own"
+        plan.destroy()
+
+
 @pytest.mark.parametrize("T,K,N", SMALL_GEMM_SHAPES + [(70, 100, 77)])
 def test_fp32_gemm_tiles_and_remainders(T, K, N):
     """The same kernel in fp32, also with an N that is no multiple of 4.  A sum of n = K + rank fp32 additions whose
