@@ -6,8 +6,8 @@
 // Here a workgroup (8 wavefronts) owns 16 FB features x 16 TB tokens, its wavefronts take contiguous slices of K, and
 // the partial sums meet in LDS: the chip is full from N = 4096 features on (FB = 1: 256 workgroups), no partial sum
 // ever goes to memory and no second launch is needed.  Nothing is shared between the wavefronts (each has its own k
-// range), so
-// the K loop needs no barrier: D units of 128 bytes per row are in flight per wavefront, through its own part of LDS.
+// range), so the K loop needs no barrier: D units of 128 bytes per row are in flight per wavefront, through its own part
+// of LDS.
 //
 // fp32 runs on v_mfma_f32_16x16x4_f32 the same way (fp32 products and sums); there the matrix cores bind (256
 // flops/clk per compute unit) and the same tiles serve every batch size.
@@ -15,13 +15,15 @@
 // Measured (whole lora_fused_forward, cold weights): 64 single-token requests on 32 adapters, 4096 -> 4096, 104 -> 15 us;
 // fp32, 256 tokens, 4096 -> 4096: this kernel 600 -> 73 us (the matrix cores' share of that at 2.1 GHz is 64 us).
 //
-// DELTA: tokens in adapter-sorted order; before the partial sums are added up, the wavefronts share out the items
-// (16-token block, adapter in it, rank step) of the tile's tokens and add v B_a of theirs to their own partial sums, so the
-// delta is spread over the workgroup and joins the same fp32 sum.  The shrink goes in the same launch (layer_small_kernel).  The delta costs trips to memory: an item's operands are requested
-// one item ahead, the first item's beside the K loop (32 tokens on 32 adapters, 4096 -> 11008: kernel 32.5 -> 30.0 us; 64
-// tokens, 5120 -> 13824: 52.1 -> 45.8; the product alone takes 21 and 35).  v is read as the shrink left it (fp32, K parts
-// added in order); with bf16 it is split into two bf16 terms in registers, or, for ranks off the tuned kernels, multiplied as
-// it is (fp32 products: 64 tokens on 32 adapters of ranks 4 to 100, 4096 -> 4096, 25.3 us, with two terms 24.1).
+// DELTA: tokens in adapter-sorted order; before the partial sums are added up, the wavefronts share out the deltas of the
+// tile's tokens and add v B_a of theirs to their own partial sums, so the delta is spread over the workgroup and joins the same
+// fp32 sum.  Two ways to share out (deltas_in_items chooses): items (16-token block, adapter in it, rank step), or pairs
+// (adapter, rank step) over all blocks.  The delta costs trips to memory: an item's operands are requested one item ahead, the
+// first item's beside the K loop (32 tokens on 32 adapters, 4096 -> 11008: kernel 32.5 -> 30.0 us; 64 tokens, 5120 -> 13824:
+// 52.1 -> 45.8; the product alone takes 21 and 35).  The shrink goes in the same launch where layer_small_planned says so.
+// v is read as the shrink left it (fp32, K parts added in order); with bf16 it is split into two bf16 terms in registers, or,
+// for ranks off the tuned kernels, multiplied as it is (fp32 products: 64 tokens on 32 adapters of ranks 4 to 100, 4096 ->
+// 4096, 25.3 us, with two terms 24.1).
 #include <algorithm>
 #include <atomic>
 
@@ -60,8 +62,9 @@ __device__ __forceinline__ unsigned long long ld_agent(const void* p)
     return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One tile of features x tokens.  HANDOFF: v is published during this launch (see above)
-template <typename E, int FB, int TB, int D, row_delta DELTA, bool KTAIL, bool HANDOFF>
+// One tile of features x tokens.  BY_ITEM: the deltas in items, otherwise in pairs (see there).  HANDOFF: v is published during
+// this launch (see above)
+template <typename E, int FB, int TB, int D, row_delta DELTA, bool BY_ITEM, bool KTAIL, bool HANDOFF>
 __device__ __forceinline__ void gemm_small_tile_of(
     const int wg, int T, int K, int N, const E* __restrict__ x, int64_t ldx, const E* __restrict__ Wt, int64_t ldw,
     E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, const row_delta_args& da, const shrink_args& sh)
@@ -104,8 +107,66 @@ __device__ __forceinline__ void gemm_small_tile_of(
     }
     part.start(u_begin, u_end);
 
+    // v B of rows `mine` of one 16-token block onto its sums; v as f
+    auto add_rows = [&](int b, bool mine, const op16 (&bt)[FB], const float (&f)[EPC]) __attribute__((always_inline)) {
+        auto take = [&](auto product) __attribute__((always_inline)) {
+#pragma unroll
+            for (int w = 0; w < FB; ++w) {
+                const floatx4 e = product(bt[w], acc[w][b][0]);
+                // (a product with zeros would carry the adapter's infinities over to other tokens)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[w][b][0][i] = mine ? e[i] : acc[w][b][0][i];
+            }
+        };
+        if constexpr (ES == 4) {
+            op16 vo;
+            vo.f = floatx4{f[0], f[1], f[2], f[3]};
+            take([&](const op16& w, floatx4 c) { return mma(w, vo, c, E{}); });
+        } else if constexpr (DELTA == PLAIN_DELTA) {
+            take([&](const op16& w, floatx4 c) { return mma_plain(w, f, c); });
+        } else {
+            op16 vo[2];
+            bf16_terms<2>(f, vo);
+            take([&](const op16& w, floatx4 c) { return mma(w, vo[1], mma(w, vo[0], c, E{}), E{}); });
+        }
+    };
     if constexpr (DELTA == NO_DELTA) {
         part.drain(u_begin, u_end, [] {}, [] {});
+    } else if constexpr (!BY_ITEM) {
+        // ---- adapter deltas, in pairs (adapter, KSTEP ranks) over all blocks of the tile, in turn to the wavefronts ----
+        part.drain(u_begin, u_end, [] {}, [] {});
+        int tokb[TB], turn = 0;
+#pragma unroll
+        for (int b = 0; b < TB; ++b) tokb[b] = __shfl(my_tok, 16 * b + m);
+        auto apply = [&](const E* Bt, int r, uint64_t members, const float* v, const lora_vspec& vsp) {
+            for (int j0 = 0; j0 < r; j0 += KSTEP) {
+                if ((turn++ & (WAVES - 1)) != wave) continue;
+                const int j = j0 + EPC * g;
+                op16 bt[FB];
+                float vf[TB][EPC];
+#pragma unroll
+                for (int f = 0; f < FB; ++f) {
+                    const int n = n0 + 4 * FB * (m >> 2) + 4 * f + (m & 3);
+                    bt[f] = row_chunk<E>(Bt + (int64_t)(n < N ? n : N - 1) * r, j, r);
+                }
+#pragma unroll
+                for (int b = 0; b < TB; ++b) v_values<EPC>(v, vsp, tokb[b], j, r, (members >> (16 * b + m)) & 1ull, vf[b]);
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+                    if ((members >> (16 * b)) & 0xffffull) add_rows(b, (members >> (16 * b + m)) & 1ull, bt, vf[b]);   // (wavefront-uniform)
+            }
+        };
+        uint64_t todo = __ballot(own != KEY_NONE);
+        while (todo) {
+            const int src = __ffsll((unsigned long long)todo) - 1, a = __builtin_amdgcn_readlane(own, src);
+            const uint64_t bt = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_bt, src) |
+                                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_bt >> 32), src) << 32);
+            const uint64_t members = __ballot(own == a);
+            todo &= ~members;
+            apply(reinterpret_cast<const E*>(bt), __builtin_amdgcn_readlane(my_rank, src), members, da.v, da.vsp);
+        }
+        const uint64_t removal = __ballot((my_key & LORA_UNMERGE_BIT) != 0);
+        if (removal) apply(reinterpret_cast<const E*>(da.Bt_ptrs[da.merged]), da.rank[da.merged], removal, da.v2, da.vsp2);
     } else {
         // ---- adapter deltas, in items of (16-token block, adapter in it, KSTEP ranks), in turn to the wavefronts; an item's
         // operands are requested before the item before it is multiplied, the first item's inside the K loop ----
@@ -262,29 +323,8 @@ __device__ __forceinline__ void gemm_small_tile_of(
 #pragma unroll
             for (int i = 0; i < EPC; ++i) f[i] = mine && it.j0 + EPC * g + i < it.r ? o.v[0][i >> 2][i & 3] : 0.f;
 #pragma unroll
-            for (int b = 0; b < TB; ++b) {
-                if (b != it.block) continue;
-                auto take = [&](auto product) {
-#pragma unroll
-                    for (int w = 0; w < FB; ++w) {
-                        const floatx4 e = product(o.bt[w], acc[w][b][0]);
-                        // (a product with zeros would carry the adapter's infinities over to other tokens)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) acc[w][b][0][i] = mine ? e[i] : acc[w][b][0][i];
-                    }
-                };
-                if constexpr (ES == 4) {
-                    op16 vo;
-                    vo.f = floatx4{f[0], f[1], f[2], f[3]};
-                    take([&](const op16& w, floatx4 c) { return mma(w, vo, c, E{}); });
-                } else if constexpr (DELTA == PLAIN_DELTA) {
-                    take([&](const op16& w, floatx4 c) { return mma_plain(w, f, c); });
-                } else {
-                    op16 vo[2];
-                    bf16_terms<2>(f, vo);
-                    take([&](const op16& w, floatx4 c) { return mma(w, vo[1], mma(w, vo[0], c, E{}), E{}); });
-                }
-            }
+            for (int b = 0; b < TB; ++b)
+                if (b == it.block) add_rows(b, mine, o.bt, f);
         };
         item i0, i1;
         operands o0, o1;
@@ -381,12 +421,12 @@ __device__ __forceinline__ void gemm_small_tile_of(
     }
 }
 
-template <typename E, int FB, int TB, int D, row_delta DELTA, bool KTAIL>
+template <typename E, int FB, int TB, int D, row_delta DELTA, bool BY_ITEM, bool KTAIL>
 __global__ __launch_bounds__(512) void gemm_small_kernel(
     int T, int K, int N, const E* __restrict__ x, int64_t ldx, const E* __restrict__ Wt, int64_t ldw,
     E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, row_delta_args da)
 {
-    gemm_small_tile_of<E, FB, TB, D, DELTA, KTAIL, false>((int)blockIdx.x, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, y_vec, da, shrink_args{});
+    gemm_small_tile_of<E, FB, TB, D, DELTA, BY_ITEM, KTAIL, false>((int)blockIdx.x, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, y_vec, da, shrink_args{});
 }
 
 // A tile of the shrink (16 FB rank rows x 16 tokens x a K part) in a launch that reads v: stored past this XCD's caches,
@@ -444,7 +484,7 @@ __global__ __launch_bounds__(512) void layer_small_kernel(
         if (((t.shape >> 4) & 15) == 1) publish_shrink<1, 2, KTAIL>(t, wg, K, x, ldx, v, da.vsp, sh);
         else publish_shrink<2, 1, KTAIL>(t, wg, K, x, ldx, v, da.vsp, sh);
     } else {
-        gemm_small_tile_of<bf16_t, FB, TB, D, TERMS_DELTA, KTAIL, true>(wg - sh.n_wg, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, true, da, sh);
+        gemm_small_tile_of<bf16_t, FB, TB, D, TERMS_DELTA, true, KTAIL, true>(wg - sh.n_wg, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, true, da, sh);
     }
 }
 
@@ -458,7 +498,7 @@ hipError_t allow_lds(Kernel kernel, size_t bytes, std::atomic<bool>& done)
     return e;
 }
 
-template <typename E, int FB, int TB, int D, row_delta DELTA, bool KTAIL>
+template <typename E, int FB, int TB, int D, row_delta DELTA, bool BY_ITEM, bool KTAIL>
 hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
                       const row_delta_args& da, hipStream_t stream)
 {
@@ -466,9 +506,9 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
     constexpr size_t lds_bytes = (size_t)8 * D * (2 * FB + 2 * TB) * 1024;
     static_assert(D * (2 * FB + 2 * TB) >= FB * TB && lds_bytes <= 163840, "a wavefront's partial sums go where its operands were");
     static std::atomic<bool> allowed{false};
-    const hipError_t e = allow_lds(&gemm_small_kernel<E, FB, TB, D, DELTA, KTAIL>, lds_bytes, allowed);
+    const hipError_t e = allow_lds(&gemm_small_kernel<E, FB, TB, D, DELTA, BY_ITEM, KTAIL>, lds_bytes, allowed);
     if (e != hipSuccess) return e;
-    LORA_LAUNCH(DELTA != NO_DELTA ? LORA_K_GEMM_SMALL_DELTA : LORA_K_GEMM_SMALL, (gemm_small_kernel<E, FB, TB, D, DELTA, KTAIL>),
+    LORA_LAUNCH(DELTA != NO_DELTA ? LORA_K_GEMM_SMALL_DELTA : LORA_K_GEMM_SMALL, (gemm_small_kernel<E, FB, TB, D, DELTA, BY_ITEM, KTAIL>),
                 dim3((unsigned)(tiles_n * tiles_t)), dim3(512), lds_bytes, stream, T, K, N, (const E*)x, ldx, (const E*)Wt, ldw,
                 (E*)y, ldy, tiles_n, tiles_t, ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0, da);
     return hipGetLastError();
@@ -500,12 +540,36 @@ small_tile choose_small_tile(int32_t T, int32_t K, int32_t N, int32_t dtype)
     return best;
 }
 
+// bf16 deltas in items or in pairs.  An item covers one block: its operands are requested one item ahead, the first ones beside
+// the K loop, but an adapter's part of Bt is read again for every block it is in.  A pair reads it once for the whole tile, and
+// nothing of it holds the K loop up.  Items where the tiles hold more than four adapters each, few of them in more than one
+// block, of short ranks (up to 2.5 steps on average) -- of longer ones in 64-token tiles with more than twelve items for each
+// wavefront --, and 32 features or more.  Microseconds of lora_fused_forward, pairs / items, 4096 -> 4096: 100 tokens on 100
+// adapters of rank 8 38.7 / 28.2, of rank 128 76 / 60; mixture mode, 470 tokens on 128 of rank 16 86.5 / 64.5; 310 tokens on
+// 16 of rank 100 67.3 / 75.3; 25 tokens on 32 of rank 128, mixture mode, 38.0 / 39.3; 1024 -> 4096, 197 tokens on 4 of rank 100
+// 20.5 / 23.6, 120 on 128 of rank 256 103 / 70; 4096 -> 1024, one token of rank 4 9.7 / 10.9.
+// Of 2300 calls (1 to 700 tokens, ranks 4 to 256, with and without mixture mode) items alone made 385 slower than they were with
+// pairs alone by more than 3 %, up to 1.20 times; this rule 10, up to 1.09 times.
+bool deltas_in_items(const lora_plan* p, const small_tile& t)
+{
+    if (t.fb == 1 || p->perm.empty()) return false;
+    const int64_t groups = (int64_t)p->group_adapter.size(), tokens = (int64_t)p->perm.size(), rows = 16 * t.tb;
+    const int64_t runs = groups + tokens / rows, block_runs = groups + tokens / 16;      // (adapter, tile) and (adapter, block), about
+    const int64_t tiles = (tokens + rows - 1) / rows;
+    if (2 * p->rank_steps > 5 * groups) return t.tb == 4 && runs * p->rank_steps > 96 * tiles * groups;
+    return runs > 4 * tiles && 2 * block_runs <= 3 * runs;
+}
+
 template <typename E, row_delta DELTA, bool KTAIL>
-hipError_t launch_tile(const small_tile& t, int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw,
+hipError_t launch_tile(const small_tile& t, bool items, int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw,
                        void* y, int64_t ldy, const row_delta_args& da, hipStream_t stream)
 {
-#define SMALL_TILE(FB_, TB_, D_) \
-    if (t.fb == FB_ && t.tb == TB_) return launch_one<E, FB_, TB_, D_, DELTA, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream);
+    constexpr bool MAY = DELTA != NO_DELTA, MUST = MAY && sizeof(E) == 4;                // (items; FB = 1: see deltas_in_items)
+#define SMALL_TILE(FB_, TB_, D_)                                                                                                          \
+    if (t.fb == FB_ && t.tb == TB_)                                                                                                       \
+        return MUST || (items && MAY && FB_ > 1)                                                                                          \
+                   ? launch_one<E, FB_, TB_, D_, DELTA, MUST || (MAY && FB_ > 1), KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)    \
+                   : launch_one<E, FB_, TB_, D_, DELTA, MUST, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream);
     SMALL_TILE(4, 4, 1) SMALL_TILE(2, 4, 1) SMALL_TILE(4, 2, 1) SMALL_TILE(2, 2, 1) SMALL_TILE(4, 1, 1) SMALL_TILE(1, 2, 1) SMALL_TILE(1, 1, 2)
 #undef SMALL_TILE
     return hipErrorInvalidValue;
@@ -551,7 +615,8 @@ hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, con
     const bool ktail = K % (dtype == LORA_F32 ? 32 : 64) != 0;
     const small_tile t = choose_small_tile(T, K, N, dtype);
     const row_delta_args da = delta ? row_deltas_of(p, d, v, rm, Bt) : row_delta_args{};
-#define SMALL_LAUNCH(E_, D_, KT_) launch_tile<E_, D_, KT_>(t, T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
+    const bool items = delta && deltas_in_items(p, t);
+#define SMALL_LAUNCH(E_, D_, KT_) launch_tile<E_, D_, KT_>(t, items, T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
 #define SMALL_DISPATCH(E_, D_) (ktail ? SMALL_LAUNCH(E_, D_, true) : SMALL_LAUNCH(E_, D_, false))
     if (dtype == LORA_F32) return delta ? SMALL_DISPATCH(float, PLAIN_DELTA) : SMALL_DISPATCH(float, NO_DELTA);
     if (!delta) return SMALL_DISPATCH(bf16_t, NO_DELTA);

@@ -83,6 +83,8 @@ struct lora_plan {
     // stage by: its adapter in bits 0..22 (all ones: none), bit 23 set when the removal of the merged adapter applies to it
     std::vector<int32_t> row_key;
 
+    int64_t rank_steps = 0;        // steps of 32 ranks of the adapters in use, together
+
     // Mixture mode: adapter `merged` is folded into the base weight.  This plan then holds the tokens' own branches
     // (the merged adapter's tokens count as tokens without adapter) and `unmerge` is a plan over the same tokens in
     // which every token that is not the merged adapter's uses that adapter with the negated scale.

@@ -683,6 +683,8 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
     p->row_key.resize((size_t)p->T);
     for (int32_t q = 0; q < p->T; ++q) p->row_key[q] = key[p->order[q]];
 
+    for (int32_t a : p->group_adapter) p->rank_steps += (p->rank[a] + 31) / 32;
+
     if (!stage_lists) return;
     for (int h = 0; h < 2; ++h) {
         const int32_t rows = h == 0 ? 128 : 256, cols = 64;

@@ -309,6 +309,20 @@ def test_small_batch_gemm_tiles_and_remainders(T, K, N):
         run_mixture_case(w, 2)
 
 
+@pytest.mark.parametrize("adapters,ranks,max_seg", [
+    (40, (8, 16, 64), 1), (40, (4, 12, 20), 1), (64, (100, 128), 1), (64, (100, 36), 1), (2, (8, 128), 90), (2, (12, 100), 90), (12, (24, 72), 9)])
+@pytest.mark.parametrize("T,K,N,tile", [
+    (125, 264, 4104, (4, 4)), (95, 264, 4096, (2, 4)), (90, 264, 4104, (4, 2)), (75, 136, 2056, (2, 2)), (75, 200, 3000, (4, 1)),
+    (25, 264, 2056, (1, 2)), (25, 136, 1096, (1, 1))])
+def test_small_batch_deltas_in_items_and_in_pairs(T, K, N, tile, adapters, ranks, max_seg):
+    """Both ways to share out bf16 deltas, in every tile that has them: many adapters with a row or two each, few that go over
+    blocks and tiles, ranks of one step and more, with and without those of the tuned kernels; mixture mode's removal in both."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, True) == (1, *tile)
+    w = wl.random_case(1900 + T + K + adapters, T, K, N, adapters, ranks, max_seg=max_seg, frac_none=0.1, scales=(0.5, 2.0, -1.0))
+    run_forward_case(w)
+    run_mixture_case(w, int(np.bincount(np.clip(w.seg_adapter, 0, None), minlength=adapters).argmax()))
+
+
 @pytest.mark.parametrize("wait", [True, False])
 @pytest.mark.parametrize("T,K,N,tile,max_seg", [
     (1, 1024, 1000, (1, 1), 1), (7, 72, 264, (1, 1), 5), (25, 1096, 3992, (1, 2), 5), (37, 584, 4096, (2, 2), 5), (16, 520, 11008, (4, 1), 5),
