@@ -625,19 +625,49 @@ hipError_t launch_gemm_small(int32_t T, int32_t K, int32_t N, int32_t dtype, con
 #undef SMALL_LAUNCH
 }
 
+namespace {
+// Shrink and product in one launch: the shrink's tiles, and the K parts of each.  Few tiles are a long chain each, many take
+// compute units from the product, and a second part is another trip to memory for each of its items.  Microseconds with 1 / 2 /
+// 4 parts, 4096 -> 4096: 4 tiles (one token) 10.9 / 9.9 / 9.2, 16 (8 tokens) 12.3 / 11.8 / 12.3, 60 (32 tokens) 16.5 / 16.1 /
+// 23.3; 30 tiles, 4096 -> 11008, 24.6 / 26.4 / 30.3
+struct layer_split { int64_t tiles; int list_parts, parts; };
+layer_split split_layer(const lora_plan* p)
+{
+    layer_split s;
+    s.list_parts = p->shrink_small ? p->v_parts : 1;
+    s.tiles = (int64_t)(p->shrink_small ? p->shrink_tiles : p->layer_shrink_tiles).size() / s.list_parts;
+    s.parts = 1;
+    while (s.parts < p->v_parts && 2 * s.parts * s.tiles <= 32) s.parts *= 2;
+    return s;
+}
+}  // namespace
+
 // Whether launch_layer_small takes the plan's product.  Microseconds of lora_fused_forward, two launches / one; requests of one
 // token: 64 tokens on 32 adapters, 4096 -> 4096, 18.7 / 15.3; one token 12.0 / 9.2; 16 tokens, 4096 -> 11008, 28.1 / 23.6; 12
 // tokens, 13824 -> 5120, 44.8 / 35.9; 90 tokens on 64 adapters, 4096 -> 11008, 72.4 / 63.0; 160 tokens, 4096 -> 4096, 23.9 /
-// 17.8; longer ones: 64 tokens, rank 64, 18.4 / 12.1; 256 tokens, rank 128, 31.7 / 26.2.  Not on the 32 x 64 tiles: of those a
-// compute unit holds one workgroup, and they come where there is one for each, so some start only behind the shrink (100
-// tokens on 100 adapters of rank 8, 22.5 / 23.2; on 64 of rank 64 35.5 / 34.4).
+// 17.8; 256 on 256 adapters of ranks 8 to 64 50.4 / 45.8; longer ones: 64 tokens, rank 64, 18.4 / 12.1; 256 tokens, rank 128,
+// 31.7 / 26.2.  Not
+//  - on the 32 x 64 tiles: of those a compute unit holds one workgroup, and they come where there is one for each, so some
+//    start only behind the shrink (100 tokens on 100 adapters of rank 8, 22.5 / 23.2; on 64 of rank 64 35.5 / 34.4)
+//  - on tiles that a compute unit holds two of, where shrink and product together are more than that: those of the product that
+//    start behind the shrink then share a compute unit with one that is under way (64 tokens on 64 adapters of rank 128, 4096 ->
+//    4096, 47.2 / 66.3; 62 on 64, 2048 -> 2048, 34.2 / 45.8; 228 on 256 of rank 64, 4096 -> 1024, 38.9 / 51.4)
+//  - on the 16 x 16 tiles with more than 48 tiles of the shrink: a product of 10 us ends before they do (51 tokens on 32
+//    adapters of rank 64, 4096 -> 1024, 17.8 / 19.3)
+// Of 4000 calls of up to 700 tokens, ranks 8 to 128, the choice takes 0.2 % longer than the better of the two on average; the
+// most, 1.17 times, on the largest tiles with three times as many workgroups of the shrink as compute units, and 1.11 times
+// where the product's workgroups just fill the chip and a few of them start behind the shrink.
 bool layer_small_planned(const lora_plan* p)
 {
     if (p->dtype != LORA_BF16 || p->family != LORA_VARIANT_TILED || p->unmerge || (p->shrink_small ? p->shrink_tiles : p->layer_shrink_tiles).empty() ||
         p->extra_ptr256.empty() || (int32_t)p->order.size() != p->T)
         return false;
     const small_tile t = choose_small_tile(p->T, p->K, p->N, LORA_BF16);
-    return !(t.fb == 2 && t.tb == 4);
+    if (t.fb * t.tb >= 8) return !(t.fb == 2 && t.tb == 4);
+    const layer_split s = split_layer(p);
+    if (t.fb == 1 && t.tb == 1 && s.tiles > 48) return false;
+    const int64_t product = (int64_t)((p->N + 16 * t.fb - 1) / (16 * t.fb)) * ((p->T + 16 * t.tb - 1) / (16 * t.tb));
+    return product + s.tiles * s.parts <= (product + 511) / 512 * 512;
 }
 
 namespace {
@@ -670,17 +700,12 @@ hipError_t launch_layer_small(int32_t T, int32_t K, int32_t N, const void* x, in
         wall_khz[dev] = khz;
     }
     const small_tile t = choose_small_tile(T, K, N, LORA_BF16);
-    // K parts: few tiles are a long chain each, many take compute units from the product, and a second part is another trip to
-    // memory for each of its items.  Microseconds with 1 / 2 / 4 parts, 4096 -> 4096: 4 tiles (one token) 10.9 / 9.9 / 9.2, 16
-    // (8 tokens) 12.3 / 11.8 / 12.3, 60 (32 tokens) 16.5 / 16.1 / 23.3; 30 tiles, 4096 -> 11008, 24.6 / 26.4 / 30.3
-    const bool own_tiles = p->shrink_small;
-    const int list_parts = own_tiles ? p->v_parts : 1, tiles = (int)(own_tiles ? p->shrink_tiles : p->layer_shrink_tiles).size() / list_parts;
-    int parts = 1;
-    while (parts < p->v_parts && 2 * parts * tiles <= 32) parts *= 2;
+    const layer_split sp = split_layer(p);
     row_delta_args da = row_deltas_of(p, d, v, gemm_removal{}, Bt);
-    da.vsp.P = parts;
-    const shrink_args sh{own_tiles ? d->shrink_tiles : d->layer_shrink_tiles, d->perm, d->scale, (const bf16_t* const*)At, (layer_sync_slot*)d->layer_sync, tiles * parts, parts,
-                         list_parts, (long long)p->fused_wait_us * wall_khz[dev] / 1000};
+    da.vsp.P = sp.parts;
+    const shrink_args sh{p->shrink_small ? d->shrink_tiles : d->layer_shrink_tiles, d->perm, d->scale, (const bf16_t* const*)At,
+                         (layer_sync_slot*)d->layer_sync, (int)sp.tiles * sp.parts, sp.parts, sp.list_parts,
+                         (long long)p->fused_wait_us * wall_khz[dev] / 1000};
     const bool ktail = K % 64 != 0;
 #define LAYER_TILE(FB_, TB_, D_)                                                                                                           \
     if (t.fb == FB_ && t.tb == TB_)                                                                                                        \

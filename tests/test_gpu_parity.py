@@ -356,6 +356,24 @@ def test_small_batch_shrink_and_gemm_in_one_launch(T, K, N, tile, max_seg, wait)
     plan.destroy()
 
 
+@pytest.mark.parametrize("T,K,N,tile,adapters,rank,one", [
+    (64, 520, 4096, (2, 2), 64, 128, False), (62, 520, 2048, (1, 2), 64, 128, False), (48, 520, 4096, (2, 2), 30, 128, True),
+    (51, 520, 1024, (1, 1), 32, 64, False), (20, 520, 1024, (1, 1), 11, 64, True), (256, 520, 4096, (4, 4), 256, 64, True)])
+def test_small_batch_shrinks_that_crowd_the_product_run_before_it(T, K, N, tile, adapters, rank, one):
+    """One launch for shrink and product only where the shrink's workgroups leave the product's their place."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, True) == (1, *tile)
+    w = wl.random_case(1850 + T, T, K, N, adapters, (rank,), max_seg=1)
+    dl = device.to_device(w, DEV, with_w=True)
+    plan = device.make_plan(w)
+    ws = torch.zeros(B.lora_plan_query(plan)[2], dtype=torch.uint8, device=DEV)
+    y = torch.zeros((T, N), dtype=torch.bfloat16, device=DEV)
+    names = _launched(lambda: B.lora_fused_forward(plan, dl.x, K, dl.Wt, K, dl.At_ptrs, dl.Bt_ptrs, y, N, ws, ws.numel()))
+    assert len(names) == (1 if one else 2), names
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    _assert_close(_to_np(y), oracle.forward(w.x, w.W, oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter), ad), BF16_TOL, "fused forward")
+    plan.destroy()
+
+
 @pytest.mark.parametrize("T,K,N", [(25, 1096, 3992), (37, 584, 4096), (20, 512, 13824), (200, 264, 4104), (64, 4096, 4096)])
 def test_small_batch_one_launch_without_waiting_computes_v_itself(T, K, N):
     """Which of its two sources the product takes v from, shown by values that only one of them can sum.  x is zero but for
