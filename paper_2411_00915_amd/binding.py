@@ -127,6 +127,8 @@ _lib.lora_timing_read.argtypes = [ctypes.c_int32, ctypes.POINTER(ctypes.c_int64)
                                   ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double)]
 _lib.lora_kernel_name.restype = ctypes.c_char_p
 _lib.lora_kernel_name.argtypes = [ctypes.c_int32]
+_lib.lora_layer_shrink_tiles.restype = ctypes.c_int32
+_lib.lora_layer_shrink_tiles.argtypes = [_vp, ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(ctypes.POINTER(Tile))]
 _lib.lora_kernel_count.restype = ctypes.c_int32
 
 EXPORTED = ["lora_timing_begin", "lora_timing_end", "lora_timing_read", "lora_kernel_name", "lora_kernel_count",
@@ -221,6 +223,14 @@ def lora_gemm_choice(tokens: int, k: int, n: int, dtype: int, delta: bool):
     register-staged), 5 register-staged 128 x 128; the blocks of 16 are the small kernel's tile."""
     c = int(_lib.lora_gemm_choice(int(tokens), int(k), int(n), int(dtype), int(delta)))
     return c >> 16, c >> 8 & 255, c & 255
+
+
+def lora_layer_shrink_tiles(plan: "Plan", removal: bool = False, own: bool = False):
+    """Shrink tiles that the plan (removal: its removal's) has only for lora_fused_forward's launch of shrink and product;
+    own: those that the launch takes, which may be the plan's own; none where there are two launches"""
+    p = ctypes.POINTER(Tile)()
+    n = _lib.lora_layer_shrink_tiles(plan.handle, int(removal), int(own), ctypes.byref(p))
+    return np.ctypeslib.as_array(ctypes.cast(p, _i32p), shape=(n * 8,)).copy().reshape(n, 8) if n else np.zeros((0, 8), np.int32)
 
 
 LORA_PROBE_EMPTY, LORA_PROBE_READ, LORA_PROBE_MFMA = 0, 1, 2

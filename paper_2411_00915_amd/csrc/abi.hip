@@ -465,6 +465,17 @@ extern "C" int32_t lora_gemm_choice(int32_t T, int32_t K, int32_t N, int32_t dty
     return (int32_t)route << 16 | (route == GEMM_SMALL ? gemm_small_tile(T, K, N, dtype) : 0);
 }
 
+// Not part of the ABI: the shrink tiles that a plan (removal != 0: its removal's) has only for the launch with the product in
+// it, and (own != 0) those that the launch takes, in as many K parts as the plan's own list has; for the planner's tests
+extern "C" int32_t lora_layer_shrink_tiles(const lora_plan* p, int32_t removal, int32_t own, const lora_tile** tiles)
+{
+    if (removal) p = p->unmerge;
+    if (!p) return 0;
+    const std::vector<lora_tile>& list = own && p->shrink_small ? p->shrink_tiles : p->layer_shrink_tiles;
+    *tiles = list.data();
+    return own && !layer_small_planned(p) ? 0 : (int32_t)list.size();
+}
+
 extern "C" lora_status lora_merge(int32_t L, int32_t N, int32_t K, int32_t r, float scale, int32_t dtype,
                                   int32_t variant, void* const* d_Wt_ptrs, int64_t ldw,
                                   const void* const* d_At_ptrs, const void* const* d_Bt_ptrs, void* hip_stream)

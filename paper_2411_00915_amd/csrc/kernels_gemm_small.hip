@@ -630,19 +630,15 @@ namespace {
 // compute units from the product, and a second part is another trip to memory for each of its items.  Microseconds with 1 / 2 /
 // 4 parts, 4096 -> 4096: 4 tiles (one token) 10.9 / 9.9 / 9.2, 16 (8 tokens) 12.3 / 11.8 / 12.3, 60 (32 tokens) 16.5 / 16.1 /
 // 23.3; 30 tiles, 4096 -> 11008, 24.6 / 26.4 / 30.3
-struct layer_split { int64_t tiles; int list_parts, parts; };
-layer_split split_layer(const lora_plan* p)
+int layer_parts(const lora_plan* p, int64_t tiles)
 {
-    layer_split s;
-    s.list_parts = p->shrink_small ? p->v_parts : 1;
-    s.tiles = (int64_t)(p->shrink_small ? p->shrink_tiles : p->layer_shrink_tiles).size() / s.list_parts;
-    s.parts = 1;
-    while (s.parts < p->v_parts && 2 * s.parts * s.tiles <= 32) s.parts *= 2;
-    return s;
+    int parts = 1;
+    while (parts < p->v_parts && 2 * parts * tiles <= 32) parts *= 2;
+    return parts;
 }
-}  // namespace
 
-// Whether launch_layer_small takes the plan's product.  Microseconds of lora_fused_forward, two launches / one; requests of one
+
+// Whether shrink and product of a small batch go in one launch, the shrink in so many tiles.  Microseconds of lora_fused_forward, two launches / one; requests of one
 // token: 64 tokens on 32 adapters, 4096 -> 4096, 18.7 / 15.3; one token 12.0 / 9.2; 16 tokens, 4096 -> 11008, 28.1 / 23.6; 12
 // tokens, 13824 -> 5120, 44.8 / 35.9; 90 tokens on 64 adapters, 4096 -> 11008, 72.4 / 63.0; 160 tokens, 4096 -> 4096, 23.9 /
 // 17.8; 256 on 256 adapters of ranks 8 to 64 50.4 / 45.8; longer ones: 64 tokens, rank 64, 18.4 / 12.1; 256 tokens, rank 128,
@@ -657,17 +653,24 @@ layer_split split_layer(const lora_plan* p)
 // Of 4000 calls of up to 700 tokens, ranks 8 to 128, the choice takes 0.2 % longer than the better of the two on average; the
 // most, 1.17 times, on the largest tiles with three times as many workgroups of the shrink as compute units, and 1.11 times
 // where the product's workgroups just fill the chip and a few of them start behind the shrink.
-bool layer_small_planned(const lora_plan* p)
+bool layer_takes(const lora_plan* p, int64_t tiles)
 {
-    if (p->dtype != LORA_BF16 || p->family != LORA_VARIANT_TILED || p->unmerge || (p->shrink_small ? p->shrink_tiles : p->layer_shrink_tiles).empty() ||
-        p->extra_ptr256.empty() || (int32_t)p->order.size() != p->T)
+    if (tiles == 0 || p->dtype != LORA_BF16 || p->family != LORA_VARIANT_TILED || p->unmerge || p->is_removal || p->extra_ptr256.empty() ||
+        (int32_t)p->order.size() != p->T || gemm_route(p->T, p->K, p->N, p->K, p->K, true, true) != GEMM_SMALL)
         return false;
     const small_tile t = choose_small_tile(p->T, p->K, p->N, LORA_BF16);
     if (t.fb * t.tb >= 8) return !(t.fb == 2 && t.tb == 4);
-    const layer_split s = split_layer(p);
-    if (t.fb == 1 && t.tb == 1 && s.tiles > 48) return false;
+    if (t.fb == 1 && t.tb == 1 && tiles > 48) return false;
     const int64_t product = (int64_t)((p->N + 16 * t.fb - 1) / (16 * t.fb)) * ((p->T + 16 * t.tb - 1) / (16 * t.tb));
-    return product + s.tiles * s.parts <= (product + 511) / 512 * 512;
+    return product + tiles * layer_parts(p, tiles) <= (product + 511) / 512 * 512;
+}
+// (the planner, which makes the tiles, knows no kernels)
+struct install_layer_takes { install_layer_takes() { lora_layer_takes = layer_takes; } } g_install_layer_takes;
+}  // namespace
+
+bool layer_small_planned(const lora_plan* p)
+{
+    return layer_takes(p, p->shrink_small ? (int64_t)p->shrink_tiles.size() / p->v_parts : (int64_t)p->layer_shrink_tiles.size());
 }
 
 namespace {
@@ -700,12 +703,12 @@ hipError_t launch_layer_small(int32_t T, int32_t K, int32_t N, const void* x, in
         wall_khz[dev] = khz;
     }
     const small_tile t = choose_small_tile(T, K, N, LORA_BF16);
-    const layer_split sp = split_layer(p);
+    const int list_parts = p->shrink_small ? p->v_parts : 1, tiles = (int)(p->shrink_small ? p->shrink_tiles : p->layer_shrink_tiles).size() / list_parts;
+    const int parts = layer_parts(p, tiles);
     row_delta_args da = row_deltas_of(p, d, v, gemm_removal{}, Bt);
-    da.vsp.P = sp.parts;
+    da.vsp.P = parts;
     const shrink_args sh{p->shrink_small ? d->shrink_tiles : d->layer_shrink_tiles, d->perm, d->scale, (const bf16_t* const*)At,
-                         (layer_sync_slot*)d->layer_sync, (int)sp.tiles * sp.parts, sp.parts, sp.list_parts,
-                         (long long)p->fused_wait_us * wall_khz[dev] / 1000};
+                         (layer_sync_slot*)d->layer_sync, tiles * parts, parts, list_parts, (long long)p->fused_wait_us * wall_khz[dev] / 1000};
     const bool ktail = K % 64 != 0;
 #define LAYER_TILE(FB_, TB_, D_)                                                                                                           \
     if (t.fb == FB_ && t.tb == TB_)                                                                                                        \

@@ -75,7 +75,7 @@ struct lora_plan {
     std::vector<lora_tile> rows_shrink_tiles, f32_delta_tiles;
     // expand tiles of the kernel that takes rows of any length: fp32, and bf16 with ranks the tuned kernels do not take
     std::vector<lora_tile> rows_expand_tiles;
-    // shrink tiles of shrink and product in one launch; empty: shrink_tiles are of their size (shrink_small), or none
+    // shrink tiles of shrink and product in one launch; empty: shrink_tiles are of their size (shrink_small), or two launches
     std::vector<lora_tile> layer_shrink_tiles;
     int32_t rows_expand_lds = 0, rows_expand_tb = 1;   // of its launch: dynamic LDS bytes, token blocks of the largest tile
     int32_t rows_shrink_fb = 1, rows_shrink_tb = 1;
@@ -90,6 +90,7 @@ struct lora_plan {
     // which every token that is not the merged adapter's uses that adapter with the negated scale.
     int32_t merged = -1;
     lora_plan* unmerge = nullptr;  // owned
+    bool is_removal = false;       // this plan is another's `unmerge`
 
     // device mirror (one allocation), valid when d_buf != nullptr
     int device = -1;
@@ -122,6 +123,10 @@ struct lora_plan {
 // How a plan's device tables are released: set by the translation unit that owns them (abi.hip) when the library
 // is loaded; stays null in host-only builds of the planner, where no plan ever has device tables.
 extern void (*lora_plan_device_release)(lora_plan*);
+
+// Whether lora_fused_forward takes a shrink of so many tiles (16 tokens x up to 32 rank rows) into the product's launch: set by
+// the translation unit that has the kernel; null in host-only builds of the planner.
+extern bool (*lora_layer_takes)(const lora_plan*, int64_t tiles);
 
 constexpr size_t LORA_LAYER_SYNC_BYTES = 16 * 128;
 

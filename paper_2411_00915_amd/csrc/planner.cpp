@@ -700,11 +700,17 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
     }
 }
 
-// Shrink tiles of 16 tokens x up to 32 rank rows for the launch that has the product of a small batch in it, where the
-// plan's own are not of that size (requests of several tokens, ranks above 64).  Batches above 512 tokens are the larger GEMMs'.
+// Shrink tiles of 16 tokens x up to 32 rank rows for the launch that has the product of a small batch in it, where there is
+// that launch and the plan's own are not of that size (requests of several tokens, ranks above 64).  Measured up to 512 tokens:
+// beyond, such batches take two launches.
 static void build_layer_tiles(lora_plan* p)
 {
-    if (p->family != LORA_VARIANT_TILED || p->shrink_small || p->unmerge || p->T > 512) return;
+    if (p->family != LORA_VARIANT_TILED || p->shrink_small || p->T > 512 || !lora_layer_takes) return;
+    int64_t tiles = 0;
+    for (size_t g = 0; g < p->group_adapter.size(); ++g)
+        tiles += (int64_t)((p->group_offset[g + 1] - p->group_offset[g] + 15) / 16) * ((p->rank[p->group_adapter[g]] + 31) / 32);
+    if (!lora_layer_takes(p, tiles)) return;
+    p->layer_shrink_tiles.reserve((size_t)tiles);
     for (size_t g = 0; g < p->group_adapter.size(); ++g) {
         const int32_t a = p->group_adapter[g], r = p->rank[a];
         for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16)
@@ -726,8 +732,8 @@ static void build_layer_tiles(lora_plan* p)
 }
 
 // One plan over the descriptor's segments as they stand; `unmerge` (may be null) is the removal's plan of a batch
-// in mixture mode, which the new plan takes over.
-static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_plan* unmerge, lora_plan** out)
+// in mixture mode, which the new plan takes over; is_removal: this is such a plan.
+static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_plan* unmerge, lora_plan** out, bool is_removal = false)
 {
     lora_plan* p = new (std::nothrow) lora_plan();
     if (!p) {
@@ -736,6 +742,7 @@ static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_p
     }
     p->merged = unmerge ? merged : -1;
     p->unmerge = unmerge;
+    p->is_removal = is_removal;
     try {
         p->T = d->num_tokens; p->S = d->num_segments; p->n_a = d->num_adapters;
         p->K = d->k; p->N = d->n; p->dtype = d->dtype; p->variant_req = d->variant;
@@ -837,7 +844,7 @@ extern "C" lora_status lora_plan_create(const lora_batch_desc* d, lora_plan** ou
         dr.seg_adapter = seg.data();
         dr.adapter_scale = scale.data();
         dr.merged_adapter_plus1 = 0;
-        lora_status st = create_plain(&dr, -1, nullptr, &removal);
+        lora_status st = create_plain(&dr, -1, nullptr, &removal, true);
         if (st != LORA_OK) return st;
         for (int32_t s = 0; s < d->num_segments; ++s) seg[s] = d->seg_adapter[s] == m ? -1 : d->seg_adapter[s];
         lora_batch_desc own = *d;
@@ -851,6 +858,7 @@ extern "C" lora_status lora_plan_create(const lora_batch_desc* d, lora_plan** ou
 }
 
 void (*lora_plan_device_release)(lora_plan*) = nullptr;
+bool (*lora_layer_takes)(const lora_plan*, int64_t) = nullptr;
 
 extern "C" void lora_plan_destroy(lora_plan* p)
 {

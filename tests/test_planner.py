@@ -451,3 +451,49 @@ def test_small_gemm_shapes_cover_every_tile():
         picked = [B.lora_gemm_choice(T, K, N, B.LORA_BF16, True) for T, K, N in SMALL_GEMM_SHAPES if T % 2 == odd]
         assert {c[1:] for c in picked if c[0] == 1} == tiles, odd
     assert {B.lora_gemm_choice(T, K, N, B.LORA_F32, True)[1:] for T, K, N in SMALL_GEMM_SHAPES if K >= 32} == tiles
+
+
+def _layer_batch(T, K, N, n_a, ranks, max_seg, **kw):
+    w = wl.random_case(77 + T + n_a, T, K, N, n_a, ranks, max_seg=max_seg, with_w=False)
+    return w, device.make_plan(w, **kw)
+
+
+@pytest.mark.parametrize("T,K,N,n_a,ranks,max_seg,tile,own", [
+    (64, 1032, 4096, 1, (128,), 64, (2, 2), False), (250, 1096, 4096, 5, (8, 16, 128), 150, (4, 4), False),
+    (300, 4096, 4096, 2, (64,), 300, (4, 4), False), (37, 584, 4096, 9, (8, 16, 40, 64), 5, (2, 2), True),
+    (1, 4096, 4096, 1, (64,), 1, (1, 1), True), (200, 264, 4104, 40, (8, 64), 5, (4, 2), True)])
+def test_layer_shrink_tiles_cover_the_batch_once(T, K, N, n_a, ranks, max_seg, tile, own):
+    """The tiles that go into the product's launch: 16 tokens x up to 32 rank rows, every (token, rank row) in one of them."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, True) == (1, *tile)
+    w, p = _layer_batch(T, K, N, n_a, ranks, max_seg)
+    v, tiles, extra = B.lora_plan_export(p), B.lora_layer_shrink_tiles(p, own=True), B.lora_layer_shrink_tiles(p)
+    p.destroy()
+    tok, perm = _check_tables(w, v)
+    assert len(tiles) and len(extra) == (0 if own else len(tiles))
+    for part in range(v["v_parts"] if own else 1):
+        mine = [tuple(t[:5]) for t in tiles if not own or (t[5] >> 8) & 15 == part]
+        plan_ref.check_cover(mine, tok, perm, int(w.adapter_rank.max()), adapter_rank=w.adapter_rank, rank_axis=True)
+    for t in tiles:
+        tb, jb = t[5] & 15, (t[5] >> 4) & 15
+        assert tb == 1 and t[2] <= 16 and jb in (1, 2) and t[4] <= 16 * jb and t[3] % 16 == 0
+        assert t[6] == w.adapter_rank[t[0]] and np.int32(t[7]).view(np.float32) == w.adapter_scale[t[0]]
+
+
+@pytest.mark.parametrize("T,K,N,n_a,ranks,max_seg,merged", [
+    (100, 4096, 4096, 5, (104, 128), 50, None),          # the product's tile is the one that keeps two launches
+    (512, 4096, 11008, 5, (64, 128), 200, None),         # another GEMM's product
+    (177, 2040, 1264, 128, (128,), 1, None),             # the shrink would crowd the product
+    (600, 2048, 2048, 3, (64, 128), 300, None),          # more than 512 tokens
+    (37, 584, 4096, 9, (8, 16, 40, 64), 5, 1),           # mixture mode: neither the own branches nor the removal
+    (200, 4096, 4096, 3, (64, 128), 90, 0)])
+def test_layer_shrink_tiles_are_built_only_where_they_are_read(T, K, N, n_a, ranks, max_seg, merged):
+    w, p = _layer_batch(T, K, N, n_a, ranks, max_seg, merged_adapter=merged)
+    v = B.lora_plan_export(p)
+    assert v["kernel_family"] == B.LORA_VARIANT_TILED
+    if merged is None:                                                    # not of that size themselves
+        assert v["shrink_tiles"][:, 2].max() > 16 or v["shrink_tiles"][:, 4].max() > 32
+    else:
+        assert v["num_unmerge"] > 0
+    for removal in (False, True):
+        assert len(B.lora_layer_shrink_tiles(p, removal)) == 0 and len(B.lora_layer_shrink_tiles(p, removal, own=True)) == 0
+    p.destroy()
