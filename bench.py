@@ -45,7 +45,7 @@ KERNEL_KEYS = {"shrink_tiled_kernel": "shrink", "expand_tiled_kernel": "expand",
                "shrink_stream_kernel": "shrink", "expand_stream_kernel": "expand", "v_split_kernel": "v_split",
                "gemm_tiled_kernel": "gemm", "gemm_tiled_kernel<delta>": "gemm_delta",
                "gemm_ring_kernel": "gemm", "gemm_ring_kernel<delta>": "gemm_delta",
-               "gemm_small_kernel": "gemm", "gemm_small_kernel<delta>": "gemm_delta",
+               "gemm_small_kernel": "gemm", "gemm_small_kernel<delta>": "gemm_delta", "layer_small_kernel": "gemm_delta",
                "gemm_mid_kernel": "gemm", "gemm_mid_kernel<delta>": "gemm_delta",
                "shrink_rows_kernel": "shrink", "expand_rows_kernel": "expand", "delta_f32_kernel": "delta",
                "shrink_general_kernel": "shrink", "expand_general_kernel": "expand", "gemm_general_kernel": "gemm"}

@@ -684,7 +684,7 @@ hipError_t launch_layer_one(int32_t T, int32_t K, int32_t N, const void* x, int6
     static std::atomic<bool> allowed{false};
     const hipError_t e = allow_lds(&layer_small_kernel<FB, TB, D, KTAIL>, lds_bytes, allowed);
     if (e != hipSuccess) return e;
-    LORA_LAUNCH(LORA_K_GEMM_SMALL_DELTA, (layer_small_kernel<FB, TB, D, KTAIL>), dim3((unsigned)(sh.n_wg + tiles_n * tiles_t)), dim3(512), lds_bytes,
+    LORA_LAUNCH(LORA_K_LAYER_SMALL, (layer_small_kernel<FB, TB, D, KTAIL>), dim3((unsigned)(sh.n_wg + tiles_n * tiles_t)), dim3(512), lds_bytes,
                 stream, T, K, N, (const bf16_t*)x, ldx, (const bf16_t*)Wt, ldw, (bf16_t*)y, ldy, tiles_n, tiles_t, da, v, sh);
     return hipGetLastError();
 }

@@ -26,6 +26,7 @@ enum lora_kernel_id {
     LORA_K_CLEAR,
     LORA_K_GEMM_SMALL,
     LORA_K_GEMM_SMALL_DELTA,
+    LORA_K_LAYER_SMALL,
     LORA_K_GEMM_MID,
     LORA_K_GEMM_MID_DELTA,
     LORA_K_SHRINK_ROWS,

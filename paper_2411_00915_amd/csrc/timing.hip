@@ -19,7 +19,7 @@ const char* kNames[LORA_K_COUNT] = {"shrink_general_kernel", "expand_general_ker
                                     "gemm_tiled_kernel<delta>", "delta_fused_small_kernel", "v_split_kernel",
                                     "shrink_stream_kernel", "expand_stream_kernel", "merge_kernel",
                                     "gemm_ring_kernel", "gemm_ring_kernel<delta>", "clear_words_kernel",
-                                    "gemm_small_kernel", "gemm_small_kernel<delta>", "gemm_mid_kernel",
+                                    "gemm_small_kernel", "gemm_small_kernel<delta>", "layer_small_kernel", "gemm_mid_kernel",
                                     "gemm_mid_kernel<delta>", "shrink_rows_kernel", "expand_rows_kernel",
                                     "delta_f32_kernel", "probe_empty_kernel", "probe_read_kernel", "probe_mfma_kernel"};
 long long* g_trace = nullptr;
