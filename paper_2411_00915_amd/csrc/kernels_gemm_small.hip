@@ -426,7 +426,8 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(
     int T, int K, int N, const E* __restrict__ x, int64_t ldx, const E* __restrict__ Wt, int64_t ldw,
     E* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, bool y_vec, row_delta_args da)
 {
-    gemm_small_tile_of<E, FB, TB, D, DELTA, BY_ITEM, KTAIL, false>((int)blockIdx.x, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, y_vec, da, shrink_args{});
+    gemm_small_tile_of<E, FB, TB, D, DELTA, BY_ITEM, KTAIL, false>((int)blockIdx.x, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t,
+                                                                  y_vec, da, shrink_args{});
 }
 
 // A tile of the shrink (16 FB rank rows x 16 tokens x a K part) in a launch that reads v: stored past this XCD's caches,
@@ -484,7 +485,8 @@ __global__ __launch_bounds__(512) void layer_small_kernel(
         if (((t.shape >> 4) & 15) == 1) publish_shrink<1, 2, KTAIL>(t, wg, K, x, ldx, v, da.vsp, sh);
         else publish_shrink<2, 1, KTAIL>(t, wg, K, x, ldx, v, da.vsp, sh);
     } else {
-        gemm_small_tile_of<bf16_t, FB, TB, D, TERMS_DELTA, true, KTAIL, true>(wg - sh.n_wg, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, true, da, sh);
+        gemm_small_tile_of<bf16_t, FB, TB, D, TERMS_DELTA, true, KTAIL, true>(wg - sh.n_wg, T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n,
+                                                                              tiles_t, true, da, sh);
     }
 }
 
@@ -637,12 +639,11 @@ int layer_parts(const lora_plan* p, int64_t tiles)
     return parts;
 }
 
-
-// Whether shrink and product of a small batch go in one launch, the shrink in so many tiles.  Microseconds of lora_fused_forward, two launches / one; requests of one
-// token: 64 tokens on 32 adapters, 4096 -> 4096, 18.7 / 15.3; one token 12.0 / 9.2; 16 tokens, 4096 -> 11008, 28.1 / 23.6; 12
-// tokens, 13824 -> 5120, 44.8 / 35.9; 90 tokens on 64 adapters, 4096 -> 11008, 72.4 / 63.0; 160 tokens, 4096 -> 4096, 23.9 /
-// 17.8; 256 on 256 adapters of ranks 8 to 64 50.4 / 45.8; longer ones: 64 tokens, rank 64, 18.4 / 12.1; 256 tokens, rank 128,
-// 31.7 / 26.2.  Not
+// Whether shrink and product of a small batch go in one launch, the shrink in so many tiles.  Microseconds of
+// lora_fused_forward, two launches / one; requests of one token: 64 tokens on 32 adapters, 4096 -> 4096, 18.7 / 15.3; one
+// token 12.0 / 9.2; 16 tokens, 4096 -> 11008, 28.1 / 23.6; 12 tokens, 13824 -> 5120, 44.8 / 35.9; 90 tokens on 64 adapters,
+// 4096 -> 11008, 72.4 / 63.0; 160 tokens, 4096 -> 4096, 23.9 / 17.8; 256 on 256 adapters of ranks 8 to 64 50.4 / 45.8; longer
+// ones: 64 tokens, rank 64, 18.4 / 12.1; 256 tokens, rank 128, 31.7 / 26.2.  Not
 //  - on the 32 x 64 tiles: of those a compute unit holds one workgroup, and they come where there is one for each, so some
 //    start only behind the shrink (100 tokens on 100 adapters of rank 8, 22.5 / 23.2; on 64 of rank 64 35.5 / 34.4)
 //  - on tiles that a compute unit holds two of, where shrink and product together are more than that: those of the product that
