@@ -12,8 +12,9 @@
 // fp32 runs on v_mfma_f32_16x16x4_f32 the same way (fp32 products and sums); there the matrix cores bind (256
 // flops/clk per compute unit) and the same tiles serve every batch size.
 //
-// Measured (whole lora_fused_forward, cold weights): 64 single-token requests on 32 adapters, 4096 -> 4096, 104 -> 15 us;
-// fp32, 256 tokens, 4096 -> 4096: this kernel 600 -> 73 us (the matrix cores' share of that at 2.1 GHz is 64 us).
+// Measured (whole lora_fused_forward): 64 single-token requests on 32 adapters, 4096 -> 4096, 104 -> 15.6 us, 22.5 where all
+// of W comes from memory; fp32, 256 tokens, 4096 -> 4096: this kernel 600 -> 73 us (the matrix cores' share of that at 2.1 GHz
+// is 64 us).
 //
 // DELTA: tokens in adapter-sorted order; before the partial sums are added up, the wavefronts share out the deltas of the
 // tile's tokens and add v B_a of theirs to their own partial sums, so the delta is spread over the workgroup and joins the same
