@@ -1,4 +1,5 @@
-"""Thin ctypes binding over the C-ABI library (include/lora_abi.h).
+"""Thin binding over the C-ABI library (include/lora_abi.h): ctypes, and for the compute calls, which are made per layer,
+the extension module _calls.
 
 Argument marshalling only: every step of the operator runs in the HIP kernels
 of liblora_amd.so.  There is no CPU fallback; if the library has not been built
@@ -23,6 +24,8 @@ if not os.path.exists(LIB_PATH):
         "(there is no fallback path)")
 
 _lib = ctypes.CDLL(LIB_PATH)
+
+from . import _calls  # noqa: E402
 
 LORA_OK, LORA_ERR_INVALID_ARG, LORA_ERR_UNSUPPORTED, LORA_ERR_NOMEM, LORA_ERR_WORKSPACE, LORA_ERR_DEVICE = range(6)
 LORA_F32, LORA_BF16 = 0, 1
@@ -370,42 +373,27 @@ def lora_plan_export(plan: Plan) -> dict:
                 unmerge_expand_tiles=tiles(v.unmerge_expand_tiles, v.num_unmerge_expand_tiles))
 
 
-def lora_plan_upload(plan: Plan, stream=None):
-    _check(_lib.lora_plan_upload(plan.handle, _stream(stream)), "lora_plan_upload")
+def _first_stream():
+    """torch's current stream, and the functions that give the current device and a device's current stream once torch is
+    initialised"""
+    import torch
+    return _stream(None) or 0, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
 
 
-def lora_shrink(plan: Plan, x, ldx: int, d_At_ptrs, v, stream=None):
-    _check(_lib.lora_shrink(plan.handle, _ptr(x), int(ldx), _ptr(d_At_ptrs), _ptr(v), _stream(stream)), "lora_shrink")
+def _address(function) -> int:
+    return ctypes.cast(function, ctypes.c_void_p).value
 
 
-def lora_expand(plan: Plan, v, d_Bt_ptrs, y, ldy: int, beta: float = 1.0, stream=None):
-    _check(_lib.lora_expand(plan.handle, _ptr(v), _ptr(d_Bt_ptrs), _ptr(y), int(ldy), float(beta), _stream(stream)),
-           "lora_expand")
+_calls.bind(_check, _first_stream, *(_address(f) for f in (
+    _lib.lora_plan_upload, _lib.lora_shrink, _lib.lora_expand, _lib.lora_delta, _lib.lora_delta_static, _lib.lora_base_gemm,
+    _lib.lora_fused_forward, _lib.lora_merge)))
 
-
-def lora_delta(plan: Plan, x, ldx: int, d_At_ptrs, d_Bt_ptrs, v, y, ldy: int, beta: float = 1.0, stream=None):
-    _check(_lib.lora_delta(plan.handle, _ptr(x), int(ldx), _ptr(d_At_ptrs), _ptr(d_Bt_ptrs), _ptr(v), _ptr(y), int(ldy),
-                           float(beta), _stream(stream)), "lora_delta")
-
-
-def lora_delta_static(plan: Plan, x, ldx: int, d_At_ptrs, d_Bt_ptrs, y, ldy: int, beta: float = 1.0, stream=None):
-    _check(_lib.lora_delta_static(plan.handle, _ptr(x), int(ldx), _ptr(d_At_ptrs), _ptr(d_Bt_ptrs), _ptr(y), int(ldy),
-                                  float(beta), _stream(stream)), "lora_delta_static")
-
-
-def lora_base_gemm(num_tokens: int, k: int, n: int, dtype: int, x, ldx: int, Wt, ldw: int, y, ldy: int, stream=None):
-    _check(_lib.lora_base_gemm(int(num_tokens), int(k), int(n), int(dtype), _ptr(x), int(ldx), _ptr(Wt), int(ldw),
-                               _ptr(y), int(ldy), _stream(stream)), "lora_base_gemm")
-
-
-def lora_merge(num_layers: int, n: int, k: int, rank: int, scale: float, dtype: int, d_Wt_ptrs, ldw: int,
-               d_At_ptrs, d_Bt_ptrs, variant: int = LORA_VARIANT_AUTO, stream=None):
-    _check(_lib.lora_merge(int(num_layers), int(n), int(k), int(rank), float(scale), int(dtype), int(variant),
-                           _ptr(d_Wt_ptrs), int(ldw), _ptr(d_At_ptrs), _ptr(d_Bt_ptrs), _stream(stream)), "lora_merge")
-
-
-def lora_fused_forward(plan: Plan, x, ldx: int, Wt, ldw: int, d_At_ptrs, d_Bt_ptrs, y, ldy: int,
-                       workspace, workspace_bytes: int, stream=None):
-    _check(_lib.lora_fused_forward(plan.handle, _ptr(x), int(ldx), _ptr(Wt), int(ldw), _ptr(d_At_ptrs),
-                                   _ptr(d_Bt_ptrs), _ptr(y), int(ldy), _ptr(workspace), int(workspace_bytes),
-                                   _stream(stream)), "lora_fused_forward")
+# lora_plan_upload(plan, stream=None), lora_shrink(plan, x, ldx, d_At_ptrs, v, stream=None),
+# lora_expand(plan, v, d_Bt_ptrs, y, ldy, beta=1.0, stream=None),
+# lora_delta(plan, x, ldx, d_At_ptrs, d_Bt_ptrs, v, y, ldy, beta=1.0, stream=None),
+# lora_delta_static(plan, x, ldx, d_At_ptrs, d_Bt_ptrs, y, ldy, beta=1.0, stream=None),
+# lora_base_gemm(num_tokens, k, n, dtype, x, ldx, Wt, ldw, y, ldy, stream=None),
+# lora_merge(num_layers, n, k, rank, scale, dtype, d_Wt_ptrs, ldw, d_At_ptrs, d_Bt_ptrs, variant=LORA_VARIANT_AUTO, stream=None),
+# lora_fused_forward(plan, x, ldx, Wt, ldw, d_At_ptrs, d_Bt_ptrs, y, ldy, workspace, workspace_bytes, stream=None)
+from ._calls import (lora_base_gemm, lora_delta, lora_delta_static, lora_expand, lora_fused_forward, lora_merge,  # noqa: E402,F401
+                     lora_plan_upload, lora_shrink)

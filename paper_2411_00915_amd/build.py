@@ -7,11 +7,13 @@ target machines).
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblora_amd.so")
+CALLS = os.path.join(HERE, "_calls.so")       # the extension module of the Python calls (no GPU code)
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["planner.cpp", "kernels_general.hip", "kernels_tiled.hip", "kernels_stream.hip", "kernels_gemm.hip", "kernels_gemm_small.hip", "kernels_gemm_mid.hip", "kernels_any.hip", "abi.hip", "timing.hip", "probe.hip"]
@@ -79,10 +81,17 @@ def _check_no_scratch(src, lines, kernels):
         raise RuntimeError(f"{src}: no resource report for {kernels}: cannot check that they use no scratch memory")
 
 
+def _build_calls():
+    subprocess.check_call(["g++", os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-shared", "-pthread",
+                           "-I" + sysconfig.get_paths()["include"]] + HOST_FLAGS)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        calls = ex.submit(_build_calls)
         objs = list(ex.map(_compile, SOURCES))
+        calls.result()
     cmd = ["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", OUT] + objs
     subprocess.check_call(cmd)
     if verbose:

@@ -1,0 +1,92 @@
+"""The extension module of the Python calls: what reaches the C ABI, by position and by name, and what is refused."""
+import ctypes
+import inspect
+import types
+
+import numpy as np
+import pytest
+
+pytest.importorskip("torch")                               # (before the library: both then use one HIP runtime)
+
+from paper_2411_00915_amd import _calls
+from paper_2411_00915_amd import binding as B
+
+P, I32, I64, F, Z = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
+ABI = {"lora_plan_upload": [P, P], "lora_shrink": [P, P, I64, P, P, P], "lora_expand": [P, P, P, P, I64, F, P],
+       "lora_delta": [P, P, I64, P, P, P, P, I64, F, P], "lora_delta_static": [P, P, I64, P, P, P, I64, F, P],
+       "lora_base_gemm": [I32, I32, I32, I32, P, I64, P, I64, P, I64, P],
+       "lora_fused_forward": [P, P, I64, P, I64, P, P, P, I64, P, Z, P],
+       "lora_merge": [I32, I32, I32, I32, F, I32, I32, P, I64, P, P, P]}
+
+
+class Buffer:
+    def data_ptr(self):
+        return 0xfedcba9876543210
+
+
+@pytest.fixture
+def seen():
+    """(name, arguments) of the last call that reached a stand-in for the library"""
+    last, keep = [], []
+    for name, arguments in ABI.items():
+        keep.append(ctypes.CFUNCTYPE(ctypes.c_int, *arguments)(lambda *a, name=name: (last.__setitem__(slice(None), [name, a]), last_status[0])[1]))
+    last_status = [0]
+    _calls.bind(B._check, B._first_stream, *(B._address(f) for f in keep))
+    yield last, last_status
+    _calls.bind(B._check, B._first_stream, *(B._address(getattr(B._lib, name)) for name in ABI))
+
+
+@pytest.mark.parametrize("name", list(ABI))
+def test_arguments_reach_the_abi_by_position_and_by_name(name, seen):
+    last, status = seen
+    function = getattr(B, name)
+    parameters = inspect.signature(function).parameters
+    plan = types.SimpleNamespace(handle=0x1000)
+    values, expected = {}, []
+    for i, (p, info) in enumerate(parameters.items()):
+        if p == "plan":
+            values[p], e = plan, 0x1000
+        elif p == "beta" or p == "scale":
+            values[p], e = np.float64(0.25), 0.25
+        elif p == "stream":
+            values[p], e = 0x77, 0x77
+        elif p in ("x", "v", "y", "Wt", "workspace") or p.startswith("d_"):
+            values[p], e = (Buffer(), 0xfedcba9876543210) if i % 2 else (4096 * i, 4096 * i)
+        else:
+            values[p], e = np.int64(40 + i), 40 + i
+        expected.append(e)
+    if name == "lora_merge":                                # (variant comes before the addresses in the C call)
+        expected.insert(6, expected.pop(10))
+    function(*values.values())
+    assert last[0] == name and list(last[1]) == expected
+    last[:] = []
+    function(**dict(reversed(values.items())))
+    assert last[0] == name and list(last[1]) == expected
+    # what has a default may be left out, nothing else
+    required = [p for p, info in parameters.items() if info.default is inspect.Parameter.empty]
+    function(**{p: values[p] for p in required}, stream=5)
+    for default, i in ((1.0, "beta"), (B.LORA_VARIANT_AUTO, "variant")):
+        if i in parameters:
+            assert last[1][ABI[name].index(F) if i == "beta" else 6] == default == parameters[i].default
+    last[:] = []
+    for wrong in ([values[p] for p in required][:-1], [*values.values(), 0]):
+        with pytest.raises(TypeError):
+            function(*wrong)
+    with pytest.raises(TypeError):
+        function(*values.values(), stream=0)
+    with pytest.raises(TypeError):
+        function(**values, other=0)
+    for p in required:                                      # neither an address nor a number nor a plan
+        with pytest.raises((AttributeError, TypeError)):
+            function(**{**values, p: object()})
+    assert not last
+    status[0] = B.LORA_ERR_WORKSPACE
+    with pytest.raises(B.LoraError, match=f"{name}: workspace") as e:
+        function(**values)
+    assert e.value.status == B.LORA_ERR_WORKSPACE
+
+
+def test_no_address_and_no_plan_are_null(seen):
+    last, _ = seen
+    B.lora_shrink(B.Plan(None, None), None, 8, None, None, 0)
+    assert last[1] == (None, None, 8, None, None, None)
