@@ -345,55 +345,82 @@ __device__ __forceinline__ void expand_stream_tile(
     };
     uint4 yr0[2], yr1[2], yr2[2], yr3[2];
 
-    // v operands (MFMA columns = tokens): lane holds v[token m][32 s + 8 g .. +7] (rows, ranks and parts
-    // that do not exist read the block of zeros)
+    float* patch = reinterpret_cast<float*>(lds + 2 * SLAB) + wave * (16 * PROW);
+    // v operands (MFMA columns = tokens): lane holds v[token m][32 s + 8 g .. +7] (rows and ranks that do not exist read
+    // the block of zeros).  What they cost is lines asked for: parts that are not there are not asked for, and long rows,
+    // whose operands would ask for every line twice, come as whole lines and change lanes through the patch.  Kernel
+    // times, 535 tokens on 5 adapters, N = 4096, four parts, rank 128 17.1 -> 13.6 us; one part 10.9 -> 9.5, rank 64 8.4 ->
+    // 8.1 (reading four parts, three of them zeros, before).
     op16 vhi[KS], vlo[KS];
     {
-        const float* zf = reinterpret_cast<const float*>(zeros);
-        constexpr int SB = KS;                         // (all steps at once: 128 registers at rank 128, which fit)
+        constexpr bool LINES = KS == 4;
+        float4 part[4][KS][2];                         // (all steps at once: 128 registers at rank 128, which fit)
+        auto load_part = [&](int q) {
 #pragma unroll
-        for (int s0 = 0; s0 < KS; s0 += SB) {
-            float4 pa[SB][4], pb[SB][4];
+            for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int ss = 0; ss < SB; ++ss) {
-                const int j = (s0 + ss) * 32 + g * 8;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float* vq = (vrow_ok && j < r && q < vsp.P) ? v + q * vsp.part + (int64_t)tok_v * vsp.R + j : zf;
-                    pa[ss][q] = *reinterpret_cast<const float4*>(vq);
-                    pb[ss][q] = *reinterpret_cast<const float4*>(vq + 4);
+                for (int i = 0; i < 2; ++i) {
+                    const int j = s * 32 + (LINES ? yl_c * 4 : g * 8);
+                    const bool ok = (LINES ? ((y_ok >> i) & 1) != 0 : vrow_ok) && j < r;
+                    const float* vq = v + q * vsp.part + (int64_t)(LINES ? tok_y[i] : tok_v) * vsp.R + j + (LINES ? 0 : 4 * i);
+                    part[q][s][i] = *reinterpret_cast<const float4*>(ok ? vq : reinterpret_cast<const float*>(zeros));
                 }
+        };
+        auto add_part = [&](int q) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    float4 &a = part[0][s][i], &b = part[q][s][i];
+                    a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+                }
+        };
+        load_part(0);
+        if (vsp.P > 1) load_part(1);
+        if (vsp.P > 2) {
+            load_part(2);
+            load_part(3);
+        }
+        // behind the last of v: loads return in order, so the wait for v does not wait for these, and stage 0
+        // starts as soon as its own y has arrived (in no branch: the stage loop's waits count them)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) yr0[i] = load_y(0, i);
+        load_b(1, rb0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) yr1[i] = load_y(1, i);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) yr2[i] = load_y(2, i);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) yr3[i] = load_y(3, i);
+        __builtin_amdgcn_sched_barrier(0);             // (the compiler would sink them below the wait for v)
+        if (vsp.P > 1) add_part(1);
+        if (vsp.P > 2) {
+            add_part(2);
+            add_part(3);
+        }
+#pragma unroll
+        for (int s0 = 0; s0 < KS; s0 += 2) {           // (the patch holds 64 ranks)
+            if (LINES) {
+#pragma unroll
+                for (int s = s0; s < KS && s < s0 + 2; ++s)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        *reinterpret_cast<float4*>(patch + (8 * i + yl_row) * PROW + (s - s0) * 32 + yl_c * 4) = part[0][s][i];
+                __builtin_amdgcn_wave_barrier();
             }
-            if (s0 + SB >= KS) {
-                // behind the last of v: loads return in order, so the wait for v does not wait for these, and stage 0
-                // starts as soon as its own y has arrived
-                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) yr0[i] = load_y(0, i);
-                load_b(1, rb0);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) yr1[i] = load_y(1, i);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) yr2[i] = load_y(2, i);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) yr3[i] = load_y(3, i);
-                __builtin_amdgcn_sched_barrier(0);         // (the compiler would sink them below the wait for v)
+            for (int s = s0; s < KS && s < s0 + 2; ++s) {
+                const float* pr = patch + m * PROW + (s - s0) * 32 + g * 8;
+                const float4 a = LINES ? *reinterpret_cast<const float4*>(pr) : part[0][s][0];
+                const float4 b = LINES ? *reinterpret_cast<const float4*>(pr + 4) : part[0][s][1];
+                const float f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+                split_bf16(f, vhi[s], vlo[s]);
             }
-#pragma unroll
-            for (int ss = 0; ss < SB; ++ss) {
-                const float4 (&a)[4] = pa[ss];
-                const float4 (&b)[4] = pb[ss];
-                float f[8];
-                f[0] = ((a[0].x + a[1].x) + a[2].x) + a[3].x; f[1] = ((a[0].y + a[1].y) + a[2].y) + a[3].y;
-                f[2] = ((a[0].z + a[1].z) + a[2].z) + a[3].z; f[3] = ((a[0].w + a[1].w) + a[2].w) + a[3].w;
-                f[4] = ((b[0].x + b[1].x) + b[2].x) + b[3].x; f[5] = ((b[0].y + b[1].y) + b[2].y) + b[3].y;
-                f[6] = ((b[0].z + b[1].z) + b[2].z) + b[3].z; f[7] = ((b[0].w + b[1].w) + b[2].w) + b[3].w;
-                split_bf16(f, vhi[s0 + ss], vlo[s0 + ss]);
-            }
+            if (LINES) __builtin_amdgcn_wave_barrier();
         }
     }
 
-    float* patch = reinterpret_cast<float*>(lds + 2 * SLAB) + wave * (16 * PROW);
     // one stage: MFMA rows = features (row 4q+i of block b stands for feature 16q+4b+i of the chunk, so
     // that a lane ends with 4 x 4 consecutive features of token m), results to the patch, back in the
     // layout of the y loads, y = beta y + delta, rounded once, stored; then the y registers are
