@@ -271,7 +271,7 @@ static lora_status run_shrink(lora_plan* p, const lora_dev_tables& d, const void
                               hipStream_t stream, void* vb = nullptr, bool* split_done = nullptr)
 {
     hipError_t e;
-    if (p->shrink_tiled_only && tiled_call_ok(x, ldx) && shrink_rows_supported(p, x, ldx))
+    if ((p->shrink_tiled_only || p->shrink_by_rows) && tiled_call_ok(x, ldx) && shrink_rows_supported(p, x, ldx))
         e = launch_shrink_rows(p, d, x, ldx, d_At_ptrs, v, stream);
     else if ((p->family == LORA_VARIANT_TILED || p->shrink_tiled_only) && tiled_call_ok(x, ldx))
         e = launch_shrink_tiled(p, d, x, ldx, d_At_ptrs, v, stream, vb, split_done);

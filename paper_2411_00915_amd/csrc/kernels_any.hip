@@ -479,7 +479,7 @@ hipError_t launch_shrink_rows(const lora_plan* p, const lora_dev_tables& d, cons
         return hipGetLastError();
     }
 #define SHRINK_ROWS(E_, FB_, TB_, D_, SUMS_)                                                                            \
-    if (p->rows_shrink_fb == FB_ && p->rows_shrink_tb == TB_)                                                           \
+    if (p->rows_shrink_fb == FB_ && p->rows_shrink_tb == TB_ && p->rows_shrink_d == D_)                                 \
         return p->K % (128 / (int)sizeof(E_)) ? launch_shrink_shape<E_, FB_, TB_, D_, SUMS_, true>(p, d, x, ldx, At, v, stream)  \
                                               : launch_shrink_shape<E_, FB_, TB_, D_, SUMS_, false>(p, d, x, ldx, At, v, stream);
     if (p->dtype == LORA_F32) {
@@ -487,6 +487,7 @@ hipError_t launch_shrink_rows(const lora_plan* p, const lora_dev_tables& d, cons
     } else {
         SHRINK_ROWS(bf16_t, 1, 1, 2, 1) SHRINK_ROWS(bf16_t, 2, 1, 1, 1) SHRINK_ROWS(bf16_t, 4, 1, 1, 1)
         SHRINK_ROWS(bf16_t, 2, 2, 1, 1) SHRINK_ROWS(bf16_t, 4, 2, 1, 1) SHRINK_ROWS(bf16_t, 4, 4, 1, 1)
+        SHRINK_ROWS(bf16_t, 1, 1, 4, 1) SHRINK_ROWS(bf16_t, 2, 2, 2, 1)
     }
 #undef SHRINK_ROWS
     return hipErrorInvalidValue;

@@ -49,6 +49,7 @@ struct lora_plan {
     int32_t shrink_waves = 4;      // wavefronts per shrink workgroup (split the K range), 1..16
     bool shrink_small = false;     // every shrink tile is 16 tokens x <= 32 rank rows: small kernel build
     bool shrink_stream = false;    // shrink tiles are those of the streaming kernel (prefill-sized batches)
+    bool shrink_by_rows = false;   // ... but the kernel of rows_shrink_tiles takes less (few tiles)
     bool expand_stream = false;    // likewise for the expand tiles
     int32_t expand_stream_ks = 1;  // streaming expand: largest number of 32-rank steps (1, 2, 4) among the tiles
     int32_t expand_stream_lds = 0; // streaming expand: dynamic LDS bytes of the launch
@@ -78,7 +79,7 @@ struct lora_plan {
     // shrink tiles of shrink and product in one launch; empty: shrink_tiles are of their size (shrink_small), or two launches
     std::vector<lora_tile> layer_shrink_tiles;
     int32_t rows_expand_lds = 0, rows_expand_tb = 1;   // of its launch: dynamic LDS bytes, token blocks of the largest tile
-    int32_t rows_shrink_fb = 1, rows_shrink_tb = 1;
+    int32_t rows_shrink_fb = 1, rows_shrink_tb = 1, rows_shrink_d = 1;
     // fused GEMM: what a row (in the order above, so that both come with one round of loads) is matched against an adapter
     // stage by: its adapter in bits 0..22 (all ones: none), bit 23 set when the removal of the merged adapter applies to it
     std::vector<int32_t> row_key;

@@ -160,6 +160,55 @@ static bool validate(const lora_batch_desc* d)
 
 static int32_t round_up(int32_t v, int32_t m) { return (v + m - 1) / m * m; }
 
+// Tiles of 16 fb rank rows x 16 tb tokens of one adapter that the batch is
+static int64_t rows_shrink_tiles_of(const lora_plan* p, int32_t fb, int32_t tb)
+{
+    int64_t tiles = 0;
+    for (size_t g = 0; g < p->group_adapter.size(); ++g)
+        tiles += (int64_t)((p->group_offset[g + 1] - p->group_offset[g] + 16 * tb - 1) / (16 * tb)) *
+                 ((p->rank[p->group_adapter[g]] + 16 * fb - 1) / (16 * fb));
+    return tiles;
+}
+
+struct rows_shape { int32_t fb, tb, d; };
+static const rows_shape kRowsF32[] = {{2, 2, 1}, {1, 1, 2}}, kRowsBf16[] = {{4, 4, 1}, {4, 2, 1}, {2, 2, 1}, {4, 1, 1}, {2, 1, 1}, {1, 1, 2}};
+
+// Whether a batch of the streaming shrink goes to the one that splits K over its wavefronts, and then its tile and K parts.  A
+// streaming tile walks its K part in stages, one after the other, whatever else is idle: with few tiles the launch is that
+// chain.  The other kernel's is shorter (8 wavefronts, each with `d` units of 128 bytes per row on their way), but it asks for
+// more: an adapter's rows for every 16 tb tokens, x for every 16 fb ranks.  Microseconds, fitted to 70 batches with x and At from
+// memory; a K part more is another read of v by whoever takes it.  lora_shrink, K = 11008, streaming / this: 128 tokens of rank
+// 16 14.6 / 4.7, rank 128 20.8 / 5.6; 300 tokens on 3 adapters of rank 64 15.5 / 7.7; 535 on 5 of rank 64 15.9 / 9.6, of rank 128
+// 23.6 / 16.1; not taken: 2000 on 8 of rank 64 17.5 / 19.7.
+static bool choose_rows_shrink(lora_plan* p, int32_t max_rank)
+{
+    if (p->unmerge || p->is_removal || (int64_t)p->shrink_tiles.size() * p->v_parts > 256) return false;   // (mixture mode: one launch for both)
+    static const rows_shape shapes[] = {{4, 4, 1}, {2, 2, 2}, {1, 1, 4}};
+    const double part_us = 0.3 + 0.008 * max_rank;
+    const int32_t own_parts = p->v_parts, stages = ((p->K + 31) / 32 / own_parts + 3) / 4, units = (p->K + 63) / 64;
+    double best = 3.3 + stages * (0.3 + 0.005 * max_rank) + own_parts * part_us;
+    bool rows = false;
+    for (const rows_shape& s : shapes) {
+        const int64_t tiles = rows_shrink_tiles_of(p, s.fb, s.tb);
+        for (int32_t P = 1; P <= 4 && units / P >= 8; P *= 2) {
+            // (lora_delta_static keeps v in an array of its own: parts must not be what outgrows it)
+            if (P > own_parts && (size_t)P * p->T * p->R * sizeof(float) > LORA_STATIC_V_BYTES) break;
+            const int64_t per_unit = 160 / (16 * s.d * (s.fb + s.tb)), rounds = (tiles * P + 256 * per_unit - 1) / (256 * per_unit);
+            const double trips = std::max(1.0, units / (8.0 * P * s.d)), bytes = (s.fb + s.tb) * 32.0 * p->K * tiles;
+            const double us = 2.6 + std::max(2.5 * trips * rounds, bytes / 7e6) + P * part_us;
+            if (us < best) {
+                best = us;
+                rows = true;
+                p->rows_shrink_fb = s.fb;
+                p->rows_shrink_tb = s.tb;
+                p->rows_shrink_d = s.d;
+                p->v_parts = P;
+            }
+        }
+    }
+    return rows;
+}
+
 // Tile lists of the tiled (MFMA) family.  A shrink tile is 16*TB tokens of one
 // adapter times 16*JB of its rank indices over the whole K range (the
 // workgroup's wavefronts split K).  An expand tile is 16*TB tokens times a range
@@ -338,6 +387,7 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
         const int64_t target = p->shrink_stream ? std::max(1, tu.shrink_stream_wgs / 2) : tu.shrink_target_wgs;
         while (P < 4 && (int64_t)p->shrink_tiles.size() * P < target && steps / (2 * P) >= 8) P *= 2;
         p->v_parts = P;
+        if (p->shrink_stream && p->variant_req == LORA_VARIANT_AUTO) p->shrink_by_rows = choose_rows_shrink(p, max_rank);
     }
     {
         std::vector<lora_tile> split;
@@ -531,38 +581,10 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
                      [&](const lora_tile& x, const lora_tile& y) { return weight(x) > weight(y); });
 }
 
-// Tiles of the shrink that splits K over its wavefronts.  A compute unit loads 16 (fb + tb) rows per workgroup at about
-// 100 GB/s and multiplies at 256 (bf16: 4096) flops/clk; the launch takes as long as the unit with the most workgroups;
-// a K part costs the consumers of v another read of it.  parts: K parts, 0: by the same rule
-static void build_rows_shrink_tiles(lora_plan* p, int32_t parts)
+// Tiles of the shrink that splits K over its wavefronts, of the plan's shape and K parts
+static void list_rows_shrink_tiles(lora_plan* p)
 {
-    struct shape { int32_t fb, tb; };
-    static const shape f32_shapes[] = {{2, 2}, {1, 1}}, bf16_shapes[] = {{4, 4}, {4, 2}, {2, 2}, {4, 1}, {2, 1}, {1, 1}};
-    const bool f32 = p->dtype == LORA_F32;
-    const shape* shapes = f32 ? f32_shapes : bf16_shapes;
-    const int n_shapes = f32 ? 2 : 6, G = (int)p->group_adapter.size();
-    const int32_t kunit = f32 ? 32 : 64, units = (p->K + kunit - 1) / kunit;
-    double best = 0;
-    for (int i = 0; i < n_shapes; ++i) {
-        const int32_t fb = shapes[i].fb, tb = shapes[i].tb;
-        int64_t tiles = 0;
-        for (int g = 0; g < G; ++g)
-            tiles += (int64_t)((p->group_offset[g + 1] - p->group_offset[g] + 16 * tb - 1) / (16 * tb)) *
-                     ((p->rank[p->group_adapter[g]] + 16 * fb - 1) / (16 * fb));
-        for (int32_t P = parts ? parts : 1; P <= (parts ? parts : 4); P *= 2) {
-            // (lora_delta_static keeps v in an array of its own: parts must not be what outgrows it)
-            if (!parts && P > 1 && (units / P < 8 || (size_t)P * p->T * p->R * sizeof(float) > LORA_STATIC_V_BYTES)) break;
-            const double load = (fb + tb) * 16.0 * (f32 ? 4 : 2) / 100e9, math = fb * tb * 512.0 / (f32 ? 0.54e12 : 8.6e12);
-            const double cost = (double)((tiles * P + 255) / 256) * ((double)units * kunit / P * std::max(load, math) + 0.5e-6) + (P - 1) * 0.3e-6;
-            if (best == 0 || cost < best) {
-                best = cost;
-                p->rows_shrink_fb = fb;
-                p->rows_shrink_tb = tb;
-                p->v_parts = P;
-            }
-        }
-    }
-    const int32_t fb = p->rows_shrink_fb, tb = p->rows_shrink_tb;
+    const int32_t fb = p->rows_shrink_fb, tb = p->rows_shrink_tb, G = (int)p->group_adapter.size();
     for (int g = 0; g < G; ++g) {
         const int32_t a = p->group_adapter[g], r = p->rank[a];
         for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += 16 * tb)
@@ -580,6 +602,36 @@ static void build_rows_shrink_tiles(lora_plan* p, int32_t parts)
                     p->rows_shrink_tiles.push_back(t);
                 }
     }
+}
+
+// Their shape.  A compute unit loads 16 (fb + tb) rows per workgroup at about
+// 100 GB/s and multiplies at 256 (bf16: 4096) flops/clk; the launch takes as long as the unit with the most workgroups;
+// a K part costs the consumers of v another read of it.  parts: K parts, 0: by the same rule
+static void build_rows_shrink_tiles(lora_plan* p, int32_t parts)
+{
+    const bool f32 = p->dtype == LORA_F32;
+    const rows_shape* shapes = f32 ? kRowsF32 : kRowsBf16;
+    const int n_shapes = f32 ? 2 : 6;
+    const int32_t kunit = f32 ? 32 : 64, units = (p->K + kunit - 1) / kunit;
+    double best = 0;
+    for (int i = 0; i < n_shapes; ++i) {
+        const int32_t fb = shapes[i].fb, tb = shapes[i].tb;
+        const int64_t tiles = rows_shrink_tiles_of(p, fb, tb);
+        for (int32_t P = parts ? parts : 1; P <= (parts ? parts : 4); P *= 2) {
+            // (lora_delta_static keeps v in an array of its own: parts must not be what outgrows it)
+            if (!parts && P > 1 && (units / P < 8 || (size_t)P * p->T * p->R * sizeof(float) > LORA_STATIC_V_BYTES)) break;
+            const double load = (fb + tb) * 16.0 * (f32 ? 4 : 2) / 100e9, math = fb * tb * 512.0 / (f32 ? 0.54e12 : 8.6e12);
+            const double cost = (double)((tiles * P + 255) / 256) * ((double)units * kunit / P * std::max(load, math) + 0.5e-6) + (P - 1) * 0.3e-6;
+            if (best == 0 || cost < best) {
+                best = cost;
+                p->rows_shrink_fb = fb;
+                p->rows_shrink_tb = tb;
+                p->rows_shrink_d = shapes[i].d;
+                p->v_parts = P;
+            }
+        }
+    }
+    list_rows_shrink_tiles(p);
 }
 
 // Tiles of the fp32 matrix-core kernels.
@@ -797,6 +849,7 @@ static lora_status create_plain(const lora_batch_desc* d, int32_t merged, lora_p
         else
             p->family = (n_active >= p->tuning.tiled_min_tokens) ? LORA_VARIANT_TILED : LORA_VARIANT_GENERAL;
         if (p->family == LORA_VARIANT_TILED) build_tiles(p);
+        if (p->shrink_by_rows) list_rows_shrink_tiles(p);
         if (p->dtype == LORA_F32 && p->variant_req != LORA_VARIANT_GENERAL) build_f32_tiles(p);
         // Ranks that only the expand kernels cannot take (not multiples of 8: rows of Bt_a would not be 16-byte
         // aligned; above 128): the shrink still runs on the MFMA kernels, which tile the rank axis in blocks of 16

@@ -258,8 +258,10 @@ struct split_k {
     // waits until all but the youngest n units (n < D) have landed; loads return in order
     static __device__ __forceinline__ void landed(int n)
     {
-        static_assert(D <= 2, "as many waits as units in flight");
-        if (D >= 2 && n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+        static_assert(D <= 4, "as many waits as units in flight");
+        if (D >= 4 && n == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
+        else if (D >= 3 && n == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+        else if (D >= 2 && n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     // adds units [u_begin, u_end) of 128 bytes per row: `start` requests the first D, `drain` goes through them all.  For
