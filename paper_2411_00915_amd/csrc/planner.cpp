@@ -677,7 +677,110 @@ static void build_f32_tiles(lora_plan* p)
     build_rows_expand_tiles(p, 0);
 }
 
-// Tables of the fused GEMM: it walks the tokens in adapter-sorted order, so a tile of rows holds few
+// Rows of the fused GEMM that carry a delta, dealt to segments of 64: a wavefront of the ring and of the medium GEMM adds the
+// deltas of 64 rows, adapter by adapter and 32 ranks at a time, and its tile ends with the last of them.  Sorted by adapter,
+// long requests leave wavefronts one adapter each, and the short ones share the rest: up to a dozen.  Here the adapters with
+// fewer than 64 rows go whole to the segment with the fewest steps that has room, and those with more fill what is left, the
+// cheapest where most steps are already.  An adapter is one run of rows in a segment.
+// `cheap`: rows without an adapter of their own (mixture mode's, for the removal).  Returns an empty list where that
+// does not take a third off the sum over tiles of 256 rows of the longest wavefront: dealt rows put more adapters in a tile
+// (6055 tokens on 240 adapters, 4096 -> 11008, sum 172 and 128: 523 -> 536 us; 6935 on 105, 96 and 77: 82 -> 84), or where
+// there are so many adapters that chance evens them out (8 to a segment; 4000 of them took half a millisecond to deal).
+// Sum over tiles of the longest wavefront's steps, sorted and dealt: 1111 tokens of mixed requests 21 and 9 (longest 18 and 3),
+// 16384 tokens on 256 adapters 396 and 225.  lora_fused_forward, W from memory: 96.5 -> 89.6 us in mixture mode (4096 -> 4096),
+// 1300 tokens on 64 adapters (4096 -> 4096) 67.0 -> 62.7, 2637 on 191 (11008 -> 4096) 366 -> 300, the 16384
+// tokens (5120 -> 13824) 1891 -> 1873.
+static std::vector<int32_t> deal_rows(const lora_plan* p, const std::vector<int32_t>& cheap)
+{
+    struct run { int32_t segment, group, first, count; };    // group -1: `cheap`
+    const int32_t G = (int32_t)p->group_adapter.size(), rows = (int32_t)(p->perm.size() + cheap.size()), n = (rows + 63) / 64;
+    if (n < 2 || G < 2 || G >= 8 * n) return {};
+    auto steps_of = [&](int32_t g) { return g < 0 ? 0 : (p->rank[p->group_adapter[g]] + 31) / 32; };
+    auto size_of = [&](int32_t g) { return g < 0 ? (int32_t)cheap.size() : p->group_offset[g + 1] - p->group_offset[g]; };
+    struct group { int32_t steps, size, id; };
+    std::vector<group> small, large;
+    for (int32_t g = 0; g < G; ++g) (size_of(g) < 64 ? small : large).push_back(group{steps_of(g), size_of(g), g});
+    if (small.empty()) return {};
+    if (!cheap.empty()) large.push_back(group{0, (int32_t)cheap.size(), -1});
+
+    std::vector<run> runs;
+    runs.reserve((size_t)G + n + 1);
+    std::vector<int32_t> steps((size_t)n, 0), room((size_t)n, 64);
+    room[(size_t)n - 1] = rows - 64 * (n - 1);
+    auto put = [&](int32_t i, const group& g, int32_t first, int32_t count) {
+        runs.push_back(run{i, g.id, first, count});
+        room[(size_t)i] -= count;
+        steps[(size_t)i] += g.steps;
+    };
+    std::sort(small.begin(), small.end(), [](const group& a, const group& b) {
+        return a.steps != b.steps ? a.steps > b.steps : a.size != b.size ? a.size > b.size : a.id < b.id;
+    });
+    typedef std::pair<int32_t, int32_t> entry;               // steps so far, segment: a heap, fewest steps first
+    std::vector<entry> least((size_t)n), passed;
+    for (int32_t i = 0; i < n; ++i) least[(size_t)i] = {0, i};
+    const std::greater<entry> later;
+    for (const group& g : small) {
+        bool done = false;
+        passed.clear();
+        while (!done && !least.empty() && passed.size() < 4) {
+            std::pop_heap(least.begin(), least.end(), later);
+            const int32_t i = least.back().second;
+            least.pop_back();
+            if ((done = room[(size_t)i] >= g.size)) put(i, g, 0, g.size);
+            if (room[(size_t)i]) passed.push_back({steps[(size_t)i], i});
+        }
+        if (!done) large.push_back(g);                       // in pieces, then
+        for (const entry& e : passed) {
+            least.push_back(e);
+            std::push_heap(least.begin(), least.end(), later);
+        }
+    }
+    std::stable_sort(large.begin(), large.end(), [](const group& a, const group& b) { return a.steps < b.steps; });
+    std::vector<int32_t> order((size_t)n);
+    for (int32_t i = 0; i < n; ++i) order[(size_t)i] = i;
+    const std::vector<int32_t> whole = steps;
+    std::sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return whole[(size_t)a] != whole[(size_t)b] ? whole[(size_t)a] > whole[(size_t)b] : a < b; });
+    size_t at = 0;
+    for (const group& g : large)
+        for (int32_t first = 0; first < g.size;) {
+            while (room[(size_t)order[at]] == 0) ++at;
+            const int32_t count = std::min(room[(size_t)order[at]], g.size - first);
+            put(order[at], g, first, count);
+            first += count;
+        }
+    // segments of like length to the same tile; the last one, if short, stays last
+    for (int32_t i = 0; i < n; ++i) order[(size_t)i] = i;
+    std::sort(order.begin(), order.end() - (rows % 64 ? 1 : 0), [&](int32_t a, int32_t b) {
+        return steps[(size_t)a] != steps[(size_t)b] ? steps[(size_t)a] > steps[(size_t)b] : a < b;
+    });
+
+    auto cost = [&](auto steps_at) {                         // (sum over tiles, longest)
+        std::pair<int64_t, int32_t> c{0, 0};
+        for (int32_t i = 0; i < n; i += 4) {
+            int32_t longest = 0;
+            for (int32_t q = i; q < std::min(i + 4, n); ++q) longest = std::max(longest, steps_at(q));
+            c.first += longest;
+            c.second = std::max(c.second, longest);
+        }
+        return c;
+    };
+    std::vector<int32_t> sorted_steps((size_t)n, 0);
+    for (int32_t g = 0; g < G; ++g)
+        for (int32_t i = p->group_offset[g] / 64; i <= (p->group_offset[g + 1] - 1) / 64; ++i) sorted_steps[(size_t)i] += steps_of(g);
+    const auto dealt = cost([&](int32_t i) { return steps[(size_t)order[(size_t)i]]; }), sorted = cost([&](int32_t i) { return sorted_steps[(size_t)i]; });
+    if (3 * dealt.first > 2 * sorted.first || dealt.second > sorted.second) return {};
+
+    std::vector<int32_t> out((size_t)rows), to((size_t)n);
+    for (int32_t q = 0; q < n; ++q) to[(size_t)order[(size_t)q]] = 64 * q;
+    for (const run& r : runs) {
+        const int32_t* from = (r.group < 0 ? cheap.data() : p->perm.data() + p->group_offset[r.group]) + r.first;
+        std::copy_n(from, r.count, out.begin() + to[(size_t)r.segment]);
+        to[(size_t)r.segment] += r.count;
+    }
+    return out;
+}
+
+// Tables of the fused GEMM: it walks the tokens in adapter-sorted order (or dealt, see above), so a tile of rows holds few
 // adapters, and folds each adapter's delta in (v_hi, v_lo against Bt_a; the register-staged kernels as extra
 // k-stages from the lists below, the ring kernel per wavefront from the row keys).  The full
 // blocks of 256 sorted rows are then put heaviest first (most adapter stages): workgroups start in
@@ -695,22 +798,28 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
         const int32_t a = p->token_adapter[t];
         key[t] = (a < 0 ? LORA_UNMERGE_BIT - 1 : a) | (u && u->token_adapter[t] >= 0 ? LORA_UNMERGE_BIT : 0);
     }
-    std::vector<int32_t> sorted = p->perm;
-    sorted.reserve((size_t)p->T);
-    for (int pass = 0; pass < 2; ++pass)
-        for (int32_t t = 0; t < p->T; ++t)
-            if (p->token_adapter[t] < 0 && ((key[t] & LORA_UNMERGE_BIT) != 0) == (pass == 0)) sorted.push_back(t);
+    std::vector<int32_t> removal_only, plain;
+    for (int32_t t = 0; t < p->T; ++t)
+        if (p->token_adapter[t] < 0) ((key[t] & LORA_UNMERGE_BIT) ? removal_only : plain).push_back(t);
+    std::vector<int32_t> sorted = deal_rows(p, removal_only);
+    if (sorted.empty()) {
+        sorted = p->perm;
+        sorted.insert(sorted.end(), removal_only.begin(), removal_only.end());
+    }
+    sorted.insert(sorted.end(), plain.begin(), plain.end());
 
-    // adapter stages of the rows [p0, p1) of `rows`: one per `cols` columns of [v_hi | v_lo] (2 r columns) and
-    // adapter; the rows of one adapter are adjacent
+    // adapter stages of the rows [p0, p1) of `rows`: one per `cols` columns of [v_hi | v_lo] (2 r columns) and adapter
+    std::vector<int32_t> seen((size_t)p->n_a, 0);
+    int32_t stamp = 0;
     auto stages_of = [&](const std::vector<int32_t>& rows, int32_t p0, int32_t p1, int32_t cols, std::vector<int32_t>* lst) {
-        int32_t n = 0, last = -1;
+        int32_t n = 0;
         bool removal = false;
+        ++stamp;
         for (int32_t q = p0; q < p1; ++q) {
             removal = removal || (key[rows[q]] & LORA_UNMERGE_BIT);
             const int32_t a = p->token_adapter[rows[q]];
-            if (a < 0 || a == last) continue;
-            last = a;
+            if (a < 0 || seen[(size_t)a] == stamp) continue;
+            seen[(size_t)a] = stamp;
             for (int32_t jb = 0; jb * cols < 2 * p->rank[a]; ++jb, ++n)
                 if (lst) lst->push_back(a | (jb << 24));
         }

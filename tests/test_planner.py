@@ -138,6 +138,39 @@ def test_random_mixture_tables(segs, ranks, m, N):
     _check_mixture(w, m, B.LORA_VARIANT_TILED)
 
 
+@pytest.mark.parametrize("m", [-1, 2])
+@pytest.mark.parametrize("lengths,n_a,ranks", [
+    ([200] + [3] * 40, 41, (64, 16)),                    # one long request, many short ones; a short last segment
+    ([63, 64, 65, 1, 127] * 3, 15, (8, 128)),            # around the 64 rows of a segment
+    ([17] * 30, 30, (32,)), ([40] * 19, 19, (16, 128)),  # what has no room in one piece
+    ([500, 2, 2, 1], 4, (64,)), ([5] * 12, 3, (8,)),     # two segments; no more than one
+    ([64] * 8, 8, (32,))])                               # nothing to gain: stays sorted
+def test_rows_of_the_fused_gemm_are_dealt_to_wavefronts(lengths, n_a, ranks, m):
+    """Every 64 rows hold each of their adapters as one run (a wavefront adds a delta per run), and neither the sum over the tiles of the longest wavefront nor the longest of all is above the sorted order's."""
+    lengths = np.asarray(lengths + [9, 30], np.int32)    # (and requests without adapter)
+    ads = np.concatenate([np.arange(len(lengths) - 2) % n_a, [-1, -1]]).astype(np.int32)
+    rank = np.asarray([ranks[a % len(ranks)] for a in range(n_a)], np.int32)
+    T = int(lengths.sum())
+    w = wl.Workload("h", "bf16", T, 64, 640, np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32), ads, rank,
+                    np.ones(n_a, np.float32), np.zeros((T, 64), np.float32), None)
+    v = _check_mixture(w, m, B.LORA_VARIANT_TILED)
+    if m < 0:
+        _check_gemm_tables(w, v, v["token_adapter"], v["perm"])
+    tok, order = v["token_adapter"], v["gemm_order"]
+    carries = (tok >= 0) | (np.repeat(ads, lengths) != m if m >= 0 else np.zeros(T, bool))
+    steps = lambda seg: sum((int(rank[a]) + 31) // 32 for a in set(tok[seg].tolist()) if a >= 0)
+    def cost(order):
+        per = [steps(order[i:i + 64]) for i in range(0, T, 64)]
+        return sum(max(per[i:i + 4]) for i in range(0, len(per), 4)), max(per)
+    by_adapter = np.concatenate([v["perm"], np.nonzero((tok < 0) & carries)[0], np.nonzero((tok < 0) & ~carries)[0]])
+    assert all(g <= s for g, s in zip(cost(order), cost(by_adapter)))
+    if len(lengths) > 40:
+        assert cost(order)[0] < cost(by_adapter)[0]      # (what it is for)
+    for i in range(0, T, 64):
+        a = tok[order[i:i + 64]]
+        assert len(set(a.tolist())) == 1 + int(np.sum(a[1:] != a[:-1]))
+
+
 @pytest.mark.parametrize("name", ["cfg1", "cfg2", "cfg3", "cfg4", "cfg4d", "cfg5"])
 def test_config_tables_bit_exact(name):
     w = wl.CONFIGS[name](with_w=False) if name != "cfg5" else wl.cfg5("attn", with_w=False)
