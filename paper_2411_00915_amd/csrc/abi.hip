@@ -448,7 +448,7 @@ extern "C" lora_status lora_base_gemm(int32_t T, int32_t K, int32_t N, int32_t d
     const gemm_route_id route = tiled_ok ? gemm_route(T, K, N, ldx, ldw, false, true) : GEMM_SMALL;
     if (route == GEMM_SMALL && small_ok)
         e = launch_gemm_small(T, K, N, dtype, x, ldx, Wt, ldw, y, ldy, nullptr, nullptr, nullptr, gemm_removal{}, nullptr, stream);
-    else if (route == GEMM_MID_128 || route == GEMM_MID_192)
+    else if (gemm_route_is_mid(route))
         e = launch_gemm_mid(route, T, K, N, x, ldx, Wt, ldw, y, ldy, nullptr, nullptr, nullptr, gemm_removal{}, nullptr, stream);
     else if (tiled_ok)
         e = launch_gemm_tiled(T, K, N, x, ldx, Wt, ldw, y, ldy, nullptr, nullptr, nullptr, nullptr, false, gemm_removal{}, nullptr, stream, route);
@@ -530,7 +530,7 @@ extern "C" lora_status lora_fused_forward(lora_plan* p, const void* x, int64_t l
     // (plans that asked for the general kernels: fp32 and other ranks than the tuned kernels' stay on them)
     const bool any_rank_ok = p->variant_req != LORA_VARIANT_GENERAL || (p->dtype == LORA_BF16 && stage_lists);
     const gemm_route_id route = layout_ok && any_rank_ok ? gemm_route(p->T, p->K, p->N, ldx, ldw, has_delta, stage_lists) : GEMM_SMALL;
-    const bool mid = route == GEMM_MID_128 || route == GEMM_MID_192, tiled = layout_ok && !mid && stage_lists;
+    const bool mid = gemm_route_is_mid(route), tiled = layout_ok && !mid && stage_lists;
     const bool small = !mid && rows_ok && any_rank_ok && (!tiled || route == GEMM_SMALL) &&
                        gemm_small_supported(p->T, p->K, p->N, p->dtype, x, ldx, Wt, ldw, y, ldy);
     char* const split = mid || small ? nullptr : vb;

@@ -1,21 +1,31 @@
 // Base GEMM y = x W (+ adapter deltas) of batches of some hundred to a few thousand tokens (bf16): tiles of 128 tokens x
-// 128 or 192 features, for problems that are too few 256 x 256 tiles to give every compute unit one (or that leave a
+// 64, 128 or 192 features, for problems that are too few 256 x 256 tiles to give every compute unit one (or that leave a
 // last round nearly empty).
 //
 // A workgroup (8 wavefronts, two per SIMD) has the compute unit's LDS to itself: a ring of S stages of 64 k (whole
-// 128-byte lines of 64 WA rows of W and 128 rows of x), filled straight from memory S - 1 stages ahead.  A wavefront owns
-// 16 WA features x 64 tokens (WA x 4 blocks of v_mfma_f32_16x16x32_bf16).  A stage takes 0.51 us for WA = 3 (0.43 for WA = 2)
-// with few compute units at work and 0.70 (0.53) with all of them, where the matrix cores need 768 clk (512), 0.37 us at 2.1
-// GHz, the 40 KB (32 KB) of fills 0.38 us at 105 GB/s, and the LDS reads 448 clk (no bank conflicts, by counter): none of
-// them alone; matrix part and memory part alternate, and the fills share the L2 with the other tiles'.
+// 128-byte lines of 64 WA rows of W and 128 rows of x), filled straight from memory S - 1 stages ahead.  A stage takes 0.51 us
+// for WA = 3 (0.43 for WA = 2) with few compute units at work and 0.70 (0.53) with all of them, where the matrix cores need 768
+// clk (512), 0.37 us at 2.1 GHz, and the 40 KB (32 KB) of fills 0.38 us at 105 GB/s.  What binds with W from memory is how much
+// of it is on its way: 120 KB a compute unit at 60 GB/s, 2 us (5120 -> 5120, 1111 tokens: 66 us, W in the infinity cache 54; a
+// ninth wavefront that asks for W's lines ahead took 5 to 15 % off the former and added as much to the latter).
 //
-// A phase is one k-step of 32: a memory part (the LDS reads of its operands; in a stage's second phase also the loads of
+// With adapters (DELTA) a wavefront owns 16 WA features x 64 tokens (WA x 4 blocks of v_mfma_f32_16x16x32_bf16).  A phase is
+// one k-step of 32: a memory part (the LDS reads of its operands; in a stage's second phase also the loads of
 // stage s + S - 1) and a matrix part (4 WA MFMAs), each closed by a barrier.  Wavefronts 4..7 run one part behind
 // wavefronts 0..3, with which they share the SIMDs, so one of the two reads LDS while the other issues MFMAs.
 //   RAW: stage s + 1 is first read in memory part 2 s + 2; every wavefront has waited for its own loads of it (vmcnt;
 //        loads return in order) at the end of its memory part 2 s + 1, one barrier earlier at least.
 //   WAR: stage s - 1, last read in memory part 2 s - 1, is overwritten by loads issued in memory part 2 s + 1; the LDS
 //        reads of the trailing wavefronts have returned before their MFMAs of phase 2 s - 1 issued, one barrier earlier.
+// Without adapters (APART) a wavefront multiplies 32 WA features x 64 tokens, but only one of a stage's two k-steps -- a third
+// fewer bytes read from LDS --, and the two sums meet in LDS at the end.  A stage is one memory and one matrix part.
+//   RAW: as above, with stage s read in memory part s and its successor waited for at that part's end.
+//   WAR: stage s - 1 is overwritten by loads issued in memory part s; its reads have returned before the barrier that ends
+//        memory part s - 1 (lgkmcnt), the trailing wavefronts' one barrier before the leading ones' part s.
+// lora_base_gemm, W in the infinity cache / from memory: 1024 tokens, 4096 -> 4096, 38.4 -> 33.8 / 42.8 -> 40.9 us; 900, 11008 ->
+// 4096, 85 -> 75 / 101.  (With adapters the sums' way through LDS takes what it gives: 0.95 to 1.04 times, 40 batches.)
+// Tiles of 64 features are for products of 256 to 512 tokens that leave the small kernel a second round of tiles: 300 tokens,
+// 4096 -> 4096, 34.1 -> 27.7; 11008 -> 4096 83 -> 72; 100 tokens, 5120 -> 13824, 51.7 -> 41.8.
 // The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
 //
 // DELTA: tokens in adapter-sorted order; after the K loop every wavefront adds the deltas of its own 64 tokens: per
@@ -36,16 +46,20 @@ namespace {
 constexpr int MID_TOKENS = 128;
 
 template <int WA, row_delta DELTA, bool KTAIL>
-__global__ __launch_bounds__(512) void gemm_mid_kernel(
+__device__ __forceinline__ void gemm_mid_tile(
     int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
-    bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da)
+    bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, const row_delta_args& da)
 {
     constexpr int BM = 64 * WA, NL = WA + 2, STAGE = (BM + MID_TOKENS) * 128, S = 163840 / STAGE, XOFF = BM * 128;
     int tile_n, tile_t;
     tile_of_workgroup(blockIdx.x, tiles_n, tiles_t, tile_n, tile_t);
     const int n0 = tile_n * BM, t0 = tile_t * MID_TOKENS;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
-    const int wn = (wave & 3) * 16 * WA, wt = (wave >> 2) * 64;      // the wavefront's origin in the tile
+    // without adapters the wavefronts of a SIMD share a quadrant of the tile in the K loop and take one k-step of every stage
+    // each; half of its features are a wavefront's own
+    constexpr bool APART = DELTA == NO_DELTA;
+    const int half = wave >> 2, qn = (wave & 1) * 32 * WA;
+    const int wn = APART ? qn + half * 16 * WA : (wave & 3) * 16 * WA, wt = (APART ? (wave >> 1) & 1 : half) * 64;   // the wavefront's origin in the tile
 
     // Loads: 128 bytes of 8 rows each; lane l brings the chunk that belongs in slot l % 8 of row l / 8.  Of W's rows this
     // wavefront brings 8 WA, of x's 16.  (The launcher keeps N ldw and T ldx below 2^32 bytes; rows past the end re-read
@@ -91,24 +105,27 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
                           lds0 + slot + (i < WA ? (wave * WA + i) * 1024 : XOFF + (wave * 2 + i - WA) * 1024));
     };
 
-    floatx4 acc[WA][4];
+    // sums: the wavefront's own features and tokens; APART: then those of the other half of the quadrant, over its k-steps
+    constexpr int WQ = APART ? 2 * WA : WA;
+    floatx4 acc[WQ][4];
 #pragma unroll
-    for (int a = 0; a < WA; ++a)
+    for (int a = 0; a < WQ; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
     // operand addresses of k-step 0 (k-step 1: 64 bytes away by XOR); MFMA row 4 q + i of block a is feature 4 WA q + 4 a + i
     const char* const lds_c = reinterpret_cast<const char*>(small_lds);
-    const uint32_t rw = (wn + 4 * WA * (m >> 2) + (m & 3)) * 128 + (g ^ (m & 7)) * 16;
+    const uint32_t rw = (4 * WA * (m >> 2) + (m & 3)) * 128 + (g ^ (m & 7)) * 16;
+    const uint32_t rw_half[2] = {rw + wn * 128, rw + (2 * qn + 16 * WA - wn) * 128};
     const uint32_t rx = XOFF + (wt + m) * 128 + (g ^ (m & 7)) * 16;
-    op16 w[WA], xo[4];
+    op16 w[WQ], xo[4];
     auto read = [&](uint32_t slot, int ks, bool last) {
 #pragma unroll
-        for (int a = 0; a < WA; ++a) w[a].u = *reinterpret_cast<const u32x4*>(lds_c + (slot + (rw ^ (ks * 64))) + a * 512);
+        for (int a = 0; a < WQ; ++a) w[a].u = *reinterpret_cast<const u32x4*>(lds_c + (slot + (rw_half[a / WA] ^ (ks * 64))) + a % WA * 512);
 #pragma unroll
         for (int b = 0; b < 4; ++b) xo[b].u = *reinterpret_cast<const u32x4*>(lds_c + (slot + (rx ^ (ks * 64))) + b * 2048);
         if (KTAIL && last && last_k + (ks * 4 + g) * 8 >= K) {
 #pragma unroll
-            for (int a = 0; a < WA; ++a) w[a].u = u32x4{0, 0, 0, 0};
+            for (int a = 0; a < WQ; ++a) w[a].u = u32x4{0, 0, 0, 0};
 #pragma unroll
             for (int b = 0; b < 4; ++b) xo[b].u = u32x4{0, 0, 0, 0};
         }
@@ -116,7 +133,7 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
     auto multiply = [&]() {
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int a = 0; a < WA; ++a)
+        for (int a = 0; a < WQ; ++a)
 #pragma unroll
             for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[a].v, xo[b].v, acc[a][b], 0, 0, 0);
         __builtin_amdgcn_s_setprio(0);
@@ -126,9 +143,11 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
     };
+    auto reads_returned = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
     // waits until all but the youngest n stages' loads of this wavefront have landed
     auto landed = [&](int n) {
-        if (S >= 5 && n >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
+        if (S >= 6 && n >= 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NL) : "memory");
+        else if (S >= 5 && n >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
         else if (n == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
         else if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -141,12 +160,17 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
     uint32_t slot = 0, fill = (S - 1) * STAGE;
     int s = 0;
     for (; s < stages - (S - 1); ++s) {
-        read(slot, 0, false);
-        barrier();
-        multiply();
-        barrier();
-        read(slot, 1, false);
-        issue(s + S - 1, fill);
+        read(slot, APART ? half : 0, false);
+        if constexpr (APART) {
+            issue(s + S - 1, fill);
+            reads_returned();
+        } else {
+            barrier();
+            multiply();
+            barrier();
+            read(slot, 1, false);
+            issue(s + S - 1, fill);
+        }
         landed(S - 2);
         barrier();
         multiply();
@@ -155,11 +179,15 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
         slot = next(slot);
     }
     for (; s < stages; ++s) {                                        // nothing is left to be fetched
-        read(slot, 0, s == stages - 1);
-        barrier();
-        multiply();
-        barrier();
-        read(slot, 1, s == stages - 1);
+        read(slot, APART ? half : 0, s == stages - 1);
+        if constexpr (APART) {
+            reads_returned();
+        } else {
+            barrier();
+            multiply();
+            barrier();
+            read(slot, 1, s == stages - 1);
+        }
         landed(max(stages - 2 - s, 0));
         barrier();
         multiply();
@@ -167,6 +195,19 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
         slot = next(slot);
     }
     if (wave < 4) barrier();
+    if constexpr (APART) {
+        // the sums of both k-steps meet: a wavefront hands on the half that is not its own
+        __syncthreads();                                             // (the ring has been read)
+#pragma unroll
+        for (int a = 0; a < WA; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) small_lds[((wave * WA + a) * 4 + b) * 64 + lane] = acc[WA + a][b];
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < WA; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[a][b] += small_lds[(((wave ^ 4) * WA + a) * 4 + b) * 64 + lane];
+    }
 
     // ---- adapter deltas of this wavefront's 64 tokens: v of the tile's tokens as operands in LDS (a wavefront makes those
     // of one block of 16 tokens), then (adapter, 32 ranks) by (adapter, 32 ranks), Bt one step ahead ----
@@ -333,19 +374,44 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(
 }
 
 template <int WA, row_delta DELTA, bool KTAIL>
+__global__ __launch_bounds__(512) void gemm_mid_kernel(
+    int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
+    bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da)
+{
+    gemm_mid_tile<WA, DELTA, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, da);
+}
+
+// tiles of 64 features, without adapters
+template <bool KTAIL>
+__global__ __launch_bounds__(512) void gemm_narrow_kernel(
+    int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
+    bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da)
+{
+    gemm_mid_tile<1, NO_DELTA, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, da);
+}
+
+template <int WA, row_delta DELTA, bool KTAIL>
+constexpr auto mid_kernel()
+{
+    if constexpr (WA == 1) return &gemm_narrow_kernel<KTAIL>;
+    else return &gemm_mid_kernel<WA, DELTA, KTAIL>;
+}
+
+template <int WA, row_delta DELTA, bool KTAIL>
 hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
                       const row_delta_args& da, hipStream_t stream)
 {
     const int tiles_n = (N + 64 * WA - 1) / (64 * WA), tiles_t = (T + MID_TOKENS - 1) / MID_TOKENS;
     constexpr size_t lds_bytes = 163840;
+    constexpr auto kernel = mid_kernel<WA, DELTA, KTAIL>();
     static std::atomic<bool> attr_set{false};                 // dynamic LDS above 64 KB has to be allowed once per kernel
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_mid_kernel<WA, DELTA, KTAIL>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    LORA_LAUNCH(DELTA != NO_DELTA ? LORA_K_GEMM_MID_DELTA : LORA_K_GEMM_MID, (gemm_mid_kernel<WA, DELTA, KTAIL>), dim3((unsigned)(tiles_n * tiles_t)),
+    LORA_LAUNCH(DELTA != NO_DELTA ? LORA_K_GEMM_MID_DELTA : LORA_K_GEMM_MID, kernel, dim3((unsigned)(tiles_n * tiles_t)),
                 dim3(512), lds_bytes, stream, T, K, N, (const bf16_t*)x, ldx, (const bf16_t*)Wt, ldw, (bf16_t*)y, ldy, tiles_n, tiles_t, da);
     return hipGetLastError();
 }
@@ -364,8 +430,10 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
 // loads run beside the other's stages; without adapters, whose infinities they do not keep apart).  Kernel times, small /
 // 128 / 192 / ring / register-staged: 2944 tokens, 32 -> 2568, 24.6 / 11.1 / 12.7 / - / 8.8;  4944, 128 -> 3496: 48.8 / 24.1 /
 // 21.7 / - / 18.6;  9901, 256 -> 1568: 53.4 / 24.5 / 24.6 / 23.4 / 18.1;  1452, 1024 -> 4096: 34.6 / 25.7 / 29.3 / 24.4 / 22.9.
+// Tiles of 64 features (no adapters), W from memory, before / with them: 4096 -> 4096, 300 tokens 34.1 / 27.7, 512 34.7 / 29.7;
+// 5120 -> 5120, 384, 45.9 / 40.3;  4096 -> 11008, 100, 38.8 / 31.5.
 // The constants are fitted to such times of 2000 problems (8 to 16384 tokens, K 8 to 13824, N 64 to 13824): the choice takes
-// 0.4 % longer than the best of the five on average, 1.24 times at worst.
+// 0.4 % longer than the best of the five others on average, 1.24 times at worst.
 gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool delta, bool tiled)
 {
     if ((int64_t)N * ldw * 2 >= (1ll << 32) || (int64_t)T * ldx * 2 >= (1ll << 32)) return GEMM_TILED;   // 32-bit byte offsets
@@ -388,6 +456,7 @@ gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t l
     };
     take(GEMM_MID_128, rounds(128, 128, 256, 2.0, 0.43, 0.10, 1));
     take(GEMM_MID_192, rounds(192, 128, 256, 3.1, 0.51, 0.19, 1));
+    if (!delta) take(GEMM_MID_64, rounds(64, 128, 256, 3.5, 0.36, 0.05, 1));
     if (ring) take(GEMM_TILED, rounds(256, 256, 256, 4.4, 0.95, 0.55, 2));
     if (!delta) take(GEMM_TILED_128, 0.3 + rounds(128, 128, 512, 1.7, 0.585, 0.56, 1));
     return best;
@@ -402,6 +471,7 @@ hipError_t launch_gemm_mid(gemm_route_id route, int32_t T, int32_t K, int32_t N,
     const row_delta_args da = delta ? row_deltas_of(p, d, v, rm, Bt) : row_delta_args{};
 #define MID_LAUNCH(WA_, D_, KT_) launch_one<WA_, D_, KT_>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
 #define MID_DISPATCH(D_, KT_) (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, KT_) : MID_LAUNCH(3, D_, KT_))
+    if (route == GEMM_MID_64) return delta ? hipErrorInvalidValue : K % 64 ? MID_LAUNCH(1, NO_DELTA, true) : MID_LAUNCH(1, NO_DELTA, false);
     if (!delta) return K % 64 ? MID_DISPATCH(NO_DELTA, true) : MID_DISPATCH(NO_DELTA, false);
     if (p->extra_ptr256.empty()) return K % 64 ? MID_DISPATCH(PLAIN_DELTA, true) : MID_DISPATCH(PLAIN_DELTA, false);
     return K % 64 ? MID_DISPATCH(TERMS_DELTA, true) : MID_DISPATCH(TERMS_DELTA, false);

@@ -869,6 +869,30 @@ def test_medium_batch_gemm_stages_and_remainders(T, K, N, ranks):
     run_mixture_case(w, 2, n_sample=256)
 
 
+@pytest.mark.parametrize("T,K,N,kernel", [
+    (557, 2056, 1896, 6), (250, 1400, 4104, 6), (125, 2104, 11000, 6), (300, 2112, 4096, 6), (385, 4096, 4088, 6), (65, 4152, 13000, 6),
+    (640, 8, 4096, 2), (650, 264, 4104, 2), (700, 1096, 4104, 2), (1300, 72, 776, 2), (1100, 200, 5000, 3), (1100, 264, 5000, 3), (1280, 1096, 4096, 3)])
+def test_medium_base_gemm_k_steps_in_two_halves(T, K, N, kernel):
+    """Products without adapters in the 64, 128 and 192 features of the medium GEMM, whose wavefronts take one of a stage's two
+    k-steps each: K tails of one chunk, of all but one and none, fewer stages than the ring holds (where the choice goes
+    there), remainders of tokens and features, one token past a tile; and the fused forward of a batch without adapters."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, False)[0] == kernel
+    w = wl.random_case(1750 + T + K, T, K, N, 1, (8,), max_seg=T, frac_none=1.0)
+    w.seg_adapter[:] = -1
+    dl = device.to_device(w, DEV, with_w=True)
+    ref = oracle.base(w.x, w.W)
+    y = torch.full((T + 1, N), 9.0, dtype=torch.bfloat16, device=DEV)
+    assert _launched(lambda: B.lora_base_gemm(T, K, N, dl.dtype, dl.x, K, dl.Wt, K, y, N)) == {"gemm_mid_kernel"}
+    _assert_close(_to_np(y)[:T], ref, BF16_TOL, "base gemm")
+    plan = device.make_plan(w)
+    ws = torch.empty(max(B.lora_plan_query(plan)[2], 256), dtype=torch.uint8, device=DEV)
+    z = torch.full((T + 1, N), 9.0, dtype=torch.bfloat16, device=DEV)
+    B.lora_fused_forward(plan, dl.x, K, dl.Wt, K, dl.At_ptrs, dl.Bt_ptrs, z, N, ws, ws.numel())
+    torch.cuda.synchronize()
+    assert torch.equal(z, y) and bool((y[T] == 9.0).all())
+    plan.destroy()
+
+
 @pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])
 def test_ring_gemm_shortest_rings_and_k_tails(K):
     """The 256 x 256 ring at its fewest stages (three of 64 k: prologue and drain only), one and two more, with and

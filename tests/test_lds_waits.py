@@ -60,3 +60,13 @@ def test_lds_reads_return_before_the_second_barrier_after_them(src, name, builds
         assert sum(l.startswith("ds_read") for l in lines) > 20 and sum(l.startswith("s_barrier") for l in lines) > 8, symbol
         late = _late_reads(lines)
         assert not late, f"{symbol}: {len(late)} LDS reads not waited for, first: {late[0]}"
+
+
+def test_lds_reads_of_the_narrow_tiles_return_before_the_second_barrier_after_them(tmp_path):
+    """the tiles of 64 features: one memory part to a stage, so fewer reads and barriers to a kernel"""
+    kernels = _kernels("kernels_gemm_mid.hip", "gemm_narrow_kernel", tmp_path)
+    assert len(kernels) == 2
+    for symbol, lines in kernels.items():
+        assert sum(l.startswith("ds_read") for l in lines) >= 12 and sum(l.startswith("s_barrier") for l in lines) > 5, symbol
+        late = _late_reads(lines)
+        assert not late, f"{symbol}: {len(late)} LDS reads not waited for, first: {late[0]}"

@@ -140,7 +140,7 @@ def test_random_mixture_tables(segs, ranks, m, N):
 
 @pytest.mark.parametrize("m", [-1, 2])
 @pytest.mark.parametrize("lengths,n_a,ranks", [
-    ([200] + [3] * 40, 41, (64, 16)),                    # one long request, many short ones; a short last segment
+    ([400] + [2] * 60, 61, (64, 16)),                    # one long request, many short ones; a short last segment
     ([63, 64, 65, 1, 127] * 3, 15, (8, 128)),            # around the 64 rows of a segment
     ([17] * 30, 30, (32,)), ([40] * 19, 19, (16, 128)),  # what has no room in one piece
     ([500, 2, 2, 1], 4, (64,)), ([5] * 12, 3, (8,)),     # two segments; no more than one
