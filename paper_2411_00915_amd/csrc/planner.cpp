@@ -542,12 +542,12 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
 {
     if (p->N < 8 || (int64_t)p->N * LORA_MAX_RANK >= (1ll << 31)) return;   // the kernel fetches whole chunks, by 32-bit offsets
     const int G = (int)p->group_adapter.size();
+    int32_t max_rank = 0;
+    for (int g = 0; g < G; ++g) max_rank = std::max(max_rank, p->rank[p->group_adapter[g]]);
     if (per == 0 && p->variant_req == LORA_VARIANT_AUTO) {
         int64_t products = 0;
-        int32_t max_rank = 0;
         for (int g = 0; g < G; ++g) {
             const int32_t r = p->rank[p->group_adapter[g]];
-            max_rank = std::max(max_rank, r);
             products += (int64_t)(p->group_offset[g + 1] - p->group_offset[g]) * (r + 8) * p->N;
         }
         if (products < 12000000 && (p->dtype == LORA_BF16 || max_rank <= 16)) return;
@@ -559,8 +559,15 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
         return n;
     };
     const int64_t blocks = (p->N + 255) / 256;
-    if (per == 0) per = token_tiles(16) * blocks <= 512 ? 16 : 32;
-    const int32_t n_tile = 256 * (int32_t)std::max<int64_t>(1, std::min(blocks, token_tiles(per) * blocks / 1024));
+    // bf16 of one MFMA step: little of Bt to read again and little v to hold, so 16 tokens, and two or four blocks of features for
+    // v and the rows' numbers once they are enough tiles all the same.  lora_delta, K = 512, 32 tokens / so: 2188 tokens of
+    // rank 20 -> 11008, 41.5 / 37.3 us; 5715 of rank 12 on 64 adapters -> 5120, 52.8 / 44.2; 1114 of rank 4 -> 4096, 16.4 / 13.9;
+    // 1060 batches of rank 4 to 20, 100 to 6600 tokens, 1.11 times as fast, the slowest 0.97.  Higher ranks lose by it:
+    // 4708 of rank 100 -> 4096, 68.0 / 71.4.
+    const bool one_step = per == 0 && p->dtype == LORA_BF16 && max_rank <= 32;
+    if (per == 0) per = one_step || token_tiles(16) * blocks <= 512 ? 16 : 32;
+    const int64_t tiles = token_tiles(per) * blocks, wide = one_step ? (tiles < 1024 ? 1 : tiles < 2560 ? 2 : 4) : tiles / 1024;
+    const int32_t n_tile = 256 * (int32_t)std::max<int64_t>(1, std::min(blocks, wide));
     for (int g = 0; g < G; ++g)
         for (int32_t row = p->group_offset[g]; row < p->group_offset[g + 1]; row += per)
             for (int32_t n0 = 0; n0 < p->N; n0 += n_tile) {

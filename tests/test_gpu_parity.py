@@ -671,6 +671,30 @@ def test_expand_takes_the_general_kernel_where_it_is_faster(T, N, ranks, dtype, 
     assert kernel in names and len([n for n in names if "expand" in n]) == 1, names
 
 
+@pytest.mark.parametrize("T,N,ranks", [
+    (960, 4100, (4, 20, 31)), (1040, 4100, (32, 1)), (1100, 4100, (12,)), (2600, 4100, (4, 20)), (2600, 1000, (4, 31)), (2600, 4352, (9, 32, 17))])
+def test_any_rank_expand_of_one_step(T, N, ranks):
+    """Ranks of one MFMA step: about 1000 and 2600 tiles of 16 tokens x 256 features, from where two and four blocks of
+    features share a tile, and their remainders (N of 4, 17 and a bit, and 17 blocks); against the oracle and, every value,
+    against one rounding of the general kernel's sum."""
+    w = wl.random_case(1850 + T + N, T, 64, N, 3, ranks, max_seg=90, frac_none=0.1, scales=(0.5, 2.0, -1.0))
+    dl = device.to_device(w, DEV, with_w=False)
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    out = []
+    for variant in (B.LORA_VARIANT_AUTO, B.LORA_VARIANT_GENERAL):
+        plan = device.make_plan(w, variant)
+        v = torch.zeros(max(B.lora_plan_query(plan)[1] // 4, 4), dtype=torch.float32, device=DEV)
+        y = torch.from_numpy(_y_in(w)).to(DEV, torch.bfloat16)
+        names = _launched(lambda: B.lora_delta(plan, dl.x, w.K, dl.At_ptrs, dl.Bt_ptrs, v, y, N, 1.0))
+        assert ("expand_rows_kernel" in names) == (variant == B.LORA_VARIANT_AUTO), names
+        out.append(_to_np(y))
+        plan.destroy()
+    _assert_close(out[0], oracle.expand(w.x, tok, ad, w.N, y_in=_y_in(w).astype(np.float64)), BF16_TOL, "delta")
+    # two roundings of sums that agree to fp32's accuracy: one unit in the last place, 2^-7 at most
+    assert np.all(np.abs(out[0] - out[1]) <= 2.0 ** -7 * np.abs(out[1]) + 1e-4)
+
+
 def _one_adapter_plan(T, K, N, rank, variant=B.LORA_VARIANT_TILED):
     return B.lora_plan(T, np.array([0, T], np.int32), np.array([0], np.int32), np.array([rank], np.int32), np.array([1.0], np.float32),
                        K, N, B.LORA_BF16, variant)
