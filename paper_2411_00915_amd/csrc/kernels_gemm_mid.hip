@@ -24,7 +24,7 @@
 //        memory part s - 1 (lgkmcnt), the trailing wavefronts' one barrier before the leading ones' part s.
 // lora_base_gemm, W in the infinity cache / from memory: 1024 tokens, 4096 -> 4096, 38.4 -> 33.8 / 42.8 -> 40.9 us; 900, 11008 ->
 // 4096, 85 -> 75 / 101.  (With adapters the sums' way through LDS takes what it gives: 0.95 to 1.04 times, 40 batches.)
-// Tiles of 64 features are for products of 256 to 512 tokens that leave the small kernel a second round of tiles: 300 tokens,
+// Tiles of 64 features are for products of 64 to 640 tokens that leave the small kernel a second round of tiles: 300 tokens,
 // 4096 -> 4096, 34.1 -> 27.7; 11008 -> 4096 83 -> 72; 100 tokens, 5120 -> 13824, 51.7 -> 41.8.
 // The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
 //
