@@ -899,7 +899,8 @@ def test_medium_batch_gemm_stages_and_remainders(T, K, N, ranks):
 def test_medium_base_gemm_k_steps_in_two_halves(T, K, N, kernel):
     """Products without adapters in the 64, 128 and 192 features of the medium GEMM, whose wavefronts take one of a stage's two
     k-steps each: K tails of one chunk, of all but one and none, fewer stages than the ring holds (where the choice goes
-    there), remainders of tokens and features, one token past a tile; and the fused forward of a batch without adapters."""
+    there), remainders of tokens and features, one token past a tile; rows apart; and the fused forward of a batch without
+    adapters."""
     assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, False)[0] == kernel
     w = wl.random_case(1750 + T + K, T, K, N, 1, (8,), max_seg=T, frac_none=1.0)
     w.seg_adapter[:] = -1
@@ -915,6 +916,11 @@ def test_medium_base_gemm_k_steps_in_two_halves(T, K, N, kernel):
     torch.cuda.synchronize()
     assert torch.equal(z, y) and bool((y[T] == 9.0).all())
     plan.destroy()
+    # rows apart, each by another distance: the same tiles, the same sums; nothing written between the rows of y
+    xs, ws, ys = (torch.full((rows, width), 9.0, dtype=torch.bfloat16, device=DEV) for rows, width in ((T, K + 8), (N, K + 24), (T, N + 16)))
+    xs[:, :K], ws[:, :K] = dl.x.view(T, K), dl.Wt.view(N, K)
+    assert _launched(lambda: B.lora_base_gemm(T, K, N, dl.dtype, xs, K + 8, ws, K + 24, ys, N + 16)) == {"gemm_mid_kernel"}
+    assert torch.equal(ys[:, :N], y[:T]) and bool((ys[:, N:] == 9.0).all())
 
 
 @pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])
