@@ -17,13 +17,16 @@
 //        loads return in order) at the end of its memory part 2 s + 1, one barrier earlier at least.
 //   WAR: stage s - 1, last read in memory part 2 s - 1, is overwritten by loads issued in memory part 2 s + 1; the LDS
 //        reads of the trailing wavefronts have returned before their MFMAs of phase 2 s - 1 issued, one barrier earlier.
-// Without adapters (APART) a wavefront multiplies 32 WA features x 64 tokens, but only one of a stage's two k-steps -- a third
+// Without adapters and with more than 24 stages (APART) a wavefront multiplies 32 WA features x 64 tokens, but only one of a stage's two k-steps -- a third
 // fewer bytes read from LDS --, and the two sums meet in LDS at the end.  A stage is one memory and one matrix part.
 //   RAW: as above, with stage s read in memory part s and its successor waited for at that part's end.
 //   WAR: stage s - 1 is overwritten by loads issued in memory part s; its reads have returned before the barrier that ends
 //        memory part s - 1 (lgkmcnt), the trailing wavefronts' one barrier before the leading ones' part s.
 // lora_base_gemm, W in the infinity cache / from memory: 1024 tokens, 4096 -> 4096, 38.4 -> 33.8 / 42.8 -> 40.9 us; 900, 11008 ->
-// 4096, 85 -> 75 / 101.  (With adapters the sums' way through LDS takes what it gives: 0.95 to 1.04 times, 40 batches.)
+// 4096, 85 -> 75 / 101.  (With adapters the sums' way through LDS takes what it gives: 0.95 to 1.04 times, 40 batches.)  That way
+// takes about 0.3 us (WA = 3: 0.5), which short products do not get back.  lora_base_gemm, W from memory, APART / not, mean of
+// 60 to 580 drawn products: 2 stages 1.09, 3 1.04, 5 to 8 1.02, 9 to 16 1.005 (WA = 3: 1.02), 21 to 24 0.998 (1.002), 25 to 32
+// 0.996 (1.000), above 50 0.99.
 // Tiles of 64 features are for products of 64 to 640 tokens that leave the small kernel a second round of tiles: 300 tokens,
 // 4096 -> 4096, 34.1 -> 27.7; 11008 -> 4096 83 -> 72; 100 tokens, 5120 -> 13824, 51.7 -> 41.8.
 // The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
@@ -45,7 +48,7 @@ namespace {
 
 constexpr int MID_TOKENS = 128;
 
-template <int WA, row_delta DELTA, bool KTAIL>
+template <int WA, row_delta DELTA, bool APART, bool KTAIL>
 __device__ __forceinline__ void gemm_mid_tile(
     int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
     bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, const row_delta_args& da)
@@ -55,9 +58,9 @@ __device__ __forceinline__ void gemm_mid_tile(
     tile_of_workgroup(blockIdx.x, tiles_n, tiles_t, tile_n, tile_t);
     const int n0 = tile_n * BM, t0 = tile_t * MID_TOKENS;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
-    // without adapters the wavefronts of a SIMD share a quadrant of the tile in the K loop and take one k-step of every stage
-    // each; half of its features are a wavefront's own
-    constexpr bool APART = DELTA == NO_DELTA;
+    // APART: the wavefronts of a SIMD share a quadrant of the tile in the K loop and take one k-step of every stage each; half
+    // of its features are a wavefront's own
+    static_assert(!APART || DELTA == NO_DELTA, "built without adapters only");
     const int half = wave >> 2, qn = (wave & 1) * 32 * WA;
     const int wn = APART ? qn + half * 16 * WA : (wave & 3) * 16 * WA, wt = (APART ? (wave >> 1) & 1 : half) * 64;   // the wavefront's origin in the tile
 
@@ -373,12 +376,12 @@ __device__ __forceinline__ void gemm_mid_tile(
     }
 }
 
-template <int WA, row_delta DELTA, bool KTAIL>
+template <int WA, row_delta DELTA, bool APART, bool KTAIL>
 __global__ __launch_bounds__(512) void gemm_mid_kernel(
     int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
     bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da)
 {
-    gemm_mid_tile<WA, DELTA, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, da);
+    gemm_mid_tile<WA, DELTA, APART, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, da);
 }
 
 // tiles of 64 features, without adapters
@@ -387,23 +390,23 @@ __global__ __launch_bounds__(512) void gemm_narrow_kernel(
     int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
     bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da)
 {
-    gemm_mid_tile<1, NO_DELTA, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, da);
+    gemm_mid_tile<1, NO_DELTA, true, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, da);
 }
 
-template <int WA, row_delta DELTA, bool KTAIL>
+template <int WA, row_delta DELTA, bool APART, bool KTAIL>
 constexpr auto mid_kernel()
 {
     if constexpr (WA == 1) return &gemm_narrow_kernel<KTAIL>;
-    else return &gemm_mid_kernel<WA, DELTA, KTAIL>;
+    else return &gemm_mid_kernel<WA, DELTA, APART, KTAIL>;
 }
 
-template <int WA, row_delta DELTA, bool KTAIL>
+template <int WA, row_delta DELTA, bool APART, bool KTAIL>
 hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ldx, const void* Wt, int64_t ldw, void* y, int64_t ldy,
                       const row_delta_args& da, hipStream_t stream)
 {
     const int tiles_n = (N + 64 * WA - 1) / (64 * WA), tiles_t = (T + MID_TOKENS - 1) / MID_TOKENS;
     constexpr size_t lds_bytes = 163840;
-    constexpr auto kernel = mid_kernel<WA, DELTA, KTAIL>();
+    constexpr auto kernel = mid_kernel<WA, DELTA, APART, KTAIL>();
     static std::atomic<bool> attr_set{false};                 // dynamic LDS above 64 KB has to be allowed once per kernel
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -469,12 +472,12 @@ hipError_t launch_gemm_mid(gemm_route_id route, int32_t T, int32_t K, int32_t N,
 {
     const bool delta = p && (!p->perm.empty() || rm.plan);
     const row_delta_args da = delta ? row_deltas_of(p, d, v, rm, Bt) : row_delta_args{};
-#define MID_LAUNCH(WA_, D_, KT_) launch_one<WA_, D_, KT_>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
-#define MID_DISPATCH(D_, KT_) (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, KT_) : MID_LAUNCH(3, D_, KT_))
-    if (route == GEMM_MID_64) return delta ? hipErrorInvalidValue : K % 64 ? MID_LAUNCH(1, NO_DELTA, true) : MID_LAUNCH(1, NO_DELTA, false);
-    if (!delta) return K % 64 ? MID_DISPATCH(NO_DELTA, true) : MID_DISPATCH(NO_DELTA, false);
-    if (p->extra_ptr256.empty()) return K % 64 ? MID_DISPATCH(PLAIN_DELTA, true) : MID_DISPATCH(PLAIN_DELTA, false);
-    return K % 64 ? MID_DISPATCH(TERMS_DELTA, true) : MID_DISPATCH(TERMS_DELTA, false);
+#define MID_LAUNCH(WA_, D_, A_, KT_) launch_one<WA_, D_, A_, KT_>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
+#define MID_DISPATCH(D_, A_) (K % 64 ? (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, A_, true) : MID_LAUNCH(3, D_, A_, true))    \
+                                     : (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, A_, false) : MID_LAUNCH(3, D_, A_, false)))
+    if (route == GEMM_MID_64) return delta ? hipErrorInvalidValue : K % 64 ? MID_LAUNCH(1, NO_DELTA, true, true) : MID_LAUNCH(1, NO_DELTA, true, false);
+    if (!delta) return K > 24 * 64 ? MID_DISPATCH(NO_DELTA, true) : MID_DISPATCH(NO_DELTA, false);
+    return p->extra_ptr256.empty() ? MID_DISPATCH(PLAIN_DELTA, false) : MID_DISPATCH(TERMS_DELTA, false);
 #undef MID_DISPATCH
 #undef MID_LAUNCH
 }

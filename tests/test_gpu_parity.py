@@ -897,7 +897,8 @@ def test_medium_batch_gemm_stages_and_remainders(T, K, N, ranks):
 
 @pytest.mark.parametrize("T,K,N,kernel", [
     (557, 2056, 1896, 6), (250, 1400, 4104, 6), (125, 2104, 11000, 6), (300, 2112, 4096, 6), (385, 4096, 4088, 6), (65, 4152, 13000, 6),
-    (640, 8, 4096, 2), (650, 264, 4104, 2), (700, 1096, 4104, 2), (1300, 72, 776, 2), (1100, 200, 5000, 3), (1100, 264, 5000, 3), (1280, 1096, 4096, 3)])
+    (640, 8, 4096, 2), (650, 264, 4104, 2), (700, 1096, 4104, 2), (1300, 72, 776, 2), (1100, 200, 5000, 3), (1100, 264, 5000, 3), (1280, 1096, 4096, 3),
+    (513, 1544, 4104, 2), (385, 2104, 5000, 2), (513, 1600, 4096, 2), (1100, 1544, 4104, 3), (777, 2104, 5000, 3), (1100, 1600, 4096, 3)])
 def test_medium_base_gemm_k_steps_in_two_halves(T, K, N, kernel):
     """Products without adapters in the 64, 128 and 192 features of the medium GEMM, whose wavefronts take one of a stage's two
     k-steps each: K tails of one chunk, of all but one and none, fewer stages than the ring holds (where the choice goes
@@ -923,6 +924,26 @@ def test_medium_base_gemm_k_steps_in_two_halves(T, K, N, kernel):
     xs[:, :K], ws[:, :K] = dl.x.view(T, K), dl.Wt.view(N, K)
     assert _launched(lambda: B.lora_base_gemm(T, K, N, dl.dtype, xs, K + 8, ws, K + 24, ys, N + 16)) == {"gemm_mid_kernel"}
     assert torch.equal(ys[:, :N], y[:T]) and bool((ys[:, N:] == 9.0).all())
+
+
+@pytest.mark.parametrize("T,K,N", [(640, 8, 4096), (1300, 72, 776), (650, 264, 4104), (640, 1536, 4096), (1100, 200, 5000), (1280, 1480, 4096),
+                                   (1280, 1536, 4096)])
+def test_short_medium_products_are_summed_in_one_chain(T, K, N):
+    """Up to 24 stages the base product goes through K step by step, as the product with adapters does (two sums, one for either
+    k-step, take longer to meet than they save): the bits of the fused forward whose adapter adds zeros."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, False)[0] == B.lora_gemm_choice(T, K, N, B.LORA_BF16, True)[0] in (2, 3)
+    w = wl.random_case(1900 + T + K, T, K, N, 1, (8,), max_seg=T, frac_none=0.0)
+    dl = device.to_device(w, DEV, with_w=True)
+    zeros = torch.zeros((N, 8), dtype=torch.bfloat16, device=DEV)
+    Bt_ptrs = torch.full((1,), zeros.data_ptr(), dtype=torch.int64, device=DEV)
+    plan = device.make_plan(w)
+    ws = torch.empty(B.lora_plan_query(plan)[2], dtype=torch.uint8, device=DEV)
+    y, z = (torch.full((T, N), 9.0, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    assert _launched(lambda: B.lora_base_gemm(T, K, N, dl.dtype, dl.x, K, dl.Wt, K, y, N)) == {"gemm_mid_kernel"}
+    assert "gemm_mid_kernel<delta>" in _launched(
+        lambda: B.lora_fused_forward(plan, dl.x, K, dl.Wt, K, dl.At_ptrs, Bt_ptrs, z, N, ws, ws.numel()))
+    assert torch.equal(y, z)
+    plan.destroy()
 
 
 @pytest.mark.parametrize("K", [136, 184, 192, 248, 320, 648])

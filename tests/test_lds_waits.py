@@ -52,7 +52,7 @@ def _late_reads(lines):
     return late
 
 
-@pytest.mark.parametrize("src,name,builds", [("kernels_gemm.hip", "gemm_ring_kernel", 4), ("kernels_gemm_mid.hip", "gemm_mid_kernel", 12)])
+@pytest.mark.parametrize("src,name,builds", [("kernels_gemm.hip", "gemm_ring_kernel", 4), ("kernels_gemm_mid.hip", "gemm_mid_kernel", 16)])
 def test_lds_reads_return_before_the_second_barrier_after_them(src, name, builds, tmp_path):
     kernels = _kernels(src, name, tmp_path)
     assert len(kernels) == builds
