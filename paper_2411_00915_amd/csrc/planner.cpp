@@ -195,7 +195,9 @@ static bool choose_rows_shrink(lora_plan* p, int32_t max_rank)
             if (P > own_parts && (size_t)P * p->T * p->R * sizeof(float) > LORA_STATIC_V_BYTES) break;
             const int64_t per_unit = 160 / (16 * s.d * (s.fb + s.tb)), rounds = (tiles * P + 256 * per_unit - 1) / (256 * per_unit);
             const double trips = std::max(1.0, units / (8.0 * P * s.d)), bytes = (s.fb + s.tb) * 32.0 * p->K * tiles;
-            const double us = 2.6 + std::max(2.5 * trips * rounds, bytes / 7e6) + P * part_us;
+            // (the 64 x 64 tile: eight wavefronts' sums of 16 blocks meet at its end.  Without that microsecond 87 of 700 drawn
+            // lora_delta calls at the line took over 1.02 times as long, 1500 tokens of rank 64, 11008 -> 4096, 27.9 -> 29.8 us)
+            const double us = 2.6 + (s.fb == 4 ? 1.0 : 0.0) + std::max(2.5 * trips * rounds, bytes / 7e6) + P * part_us;
             if (us < best) {
                 best = us;
                 rows = true;

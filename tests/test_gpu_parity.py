@@ -1162,7 +1162,7 @@ def test_tiled_request_with_unaligned_leading_dimension_is_refused():
 @pytest.mark.parametrize("T,K,N,n_a,ranks,max_seg", [
     (128, 1096, 512, 1, (16,), 128), (140, 4104, 264, 1, (8,), 140), (130, 4104, 72, 1, (128,), 128), (210, 1160, 264, 2, (24, 40), 105),
     (535, 2056, 264, 5, (64,), 107), (400, 4104, 200, 4, (128,), 100), (1500, 1032, 200, 2, (128, 8), 750), (1000, 4096, 256, 8, (128,), 125),
-    (1100, 2056, 200, 11, (16, 128), 100)])
+    (1100, 2056, 200, 11, (16, 128), 100), (1400, 4104, 200, 4, (128,), 350), (1900, 2056, 200, 4, (128,), 350)])
 def test_batches_of_few_streaming_tiles_split_k_over_wavefronts(T, K, N, n_a, ranks, max_seg):
     # each tile and depth that choose_rows_shrink picks from, 1, 2 and 4 K parts; K off a unit of 64, fewer units than are
     # in flight, remainders of tokens and ranks; the expand that reads as many parts
@@ -1170,6 +1170,13 @@ def test_batches_of_few_streaming_tiles_split_k_over_wavefronts(T, K, N, n_a, ra
     names = _launched(lambda: run_delta_case(w))
     assert "shrink_rows_kernel" in names and "shrink_stream_kernel" not in names
     run_forward_case(w, n_sample=96)
+
+
+@pytest.mark.parametrize("T,K,N,ranks,max_seg", [(1505, 11008, 512, (64,), 400), (1931, 5120, 264, (64,), 600), (1812, 13824, 264, (64,), 300)])
+def test_batches_of_few_streaming_tiles_keep_them_where_little_is_gained(T, K, N, ranks, max_seg):
+    w = wl.random_case(2650 + T, T, K, N, 2, ranks, max_seg=max_seg, frac_none=0.0)
+    names = _launched(lambda: run_delta_case(w))
+    assert "shrink_stream_kernel" in names and "shrink_rows_kernel" not in names
 
 
 # ---------------------------------------------------------------- shape table
