@@ -401,7 +401,10 @@ const char* lora_status_str(lora_status s);
  * of at least 64 tokens, or 128 tokens in all, use them too; 2^30 or more
  * switches the streaming kernels off),
  * shrink_stream_wgs (the streaming kernels use 64-token tiles when 128-token tiles
- * would give fewer workgroups than this), expand_stream_stages (stages of 64
+ * would give fewer workgroups than this, and split K until the shrink has half as
+ * many; with LORA_VARIANT_AUTO and neither of these two given another value than its
+ * default, batches that make few streaming tiles run a shrink that splits K over
+ * the wavefronts of a workgroup instead), expand_stream_stages (stages of 64
  * features per wavefront that one workgroup of the streaming expand walks).
  * Entries <= 0 keep the current value; plans made
  * earlier are unaffected.  Host only, thread-safe.

@@ -18,7 +18,7 @@
 
 namespace {
 std::mutex g_tuning_mutex;                       // guards the process defaults and the shape table
-lora_tuning g_lora_tuning = {
+constexpr lora_tuning kDefaultTuning = {
     /*shrink_waves*/ 8,
     /*shrink_tb2_min_rows*/ 64,
     /*shrink_max_jb*/ 4,
@@ -37,6 +37,7 @@ lora_tuning g_lora_tuning = {
     /*shrink_stream_wgs*/ 512,
     /*expand_stream_stages*/ 16,
 };
+lora_tuning g_lora_tuning = kDefaultTuning;
 
 // The shape table the library ships with: written by the offline search (autotune.py) on MI355X.
 const lora_tuning_entry kShippedTable[] = {
@@ -179,9 +180,13 @@ static const rows_shape kRowsF32[] = {{2, 2, 1}, {1, 1, 2}}, kRowsBf16[] = {{4, 
 // more: an adapter's rows for every 16 tb tokens, x for every 16 fb ranks.  Microseconds, fitted to 70 batches with x and At from
 // memory; a K part more is another read of v by whoever takes it.  lora_shrink, K = 11008, streaming / this: 128 tokens of rank
 // 16 14.6 / 4.7, rank 128 20.8 / 5.6; 300 tokens on 3 adapters of rank 64 15.5 / 7.7; 535 on 5 of rank 64 15.9 / 9.6, of rank 128
-// 23.6 / 16.1; not taken: 2000 on 8 of rank 64 17.5 / 19.7.
+// 23.6 / 16.1; not taken: 2000 on 8 of rank 64 17.5 / 19.7.  Not where the streaming shrink's own tunables were given other values
+// than the defaults: whoever gives them steers, or searches, that kernel's tiles and K parts.
 static bool choose_rows_shrink(lora_plan* p, int32_t max_rank)
 {
+    if (p->tuning.shrink_stream_min_tokens != kDefaultTuning.shrink_stream_min_tokens ||
+        p->tuning.shrink_stream_wgs != kDefaultTuning.shrink_stream_wgs)
+        return false;
     if (p->unmerge || p->is_removal || (int64_t)p->shrink_tiles.size() * p->v_parts > 256) return false;   // (mixture mode: one launch for both)
     static const rows_shape shapes[] = {{4, 4, 1}, {2, 2, 2}, {1, 1, 4}};
     const double part_us = 0.3 + 0.008 * max_rank;

@@ -171,6 +171,40 @@ def test_rows_of_the_fused_gemm_are_dealt_to_wavefronts(lengths, n_a, ranks, m):
         assert len(set(a.tolist())) == 1 + int(np.sum(a[1:] != a[:-1]))
 
 
+@pytest.mark.parametrize("T,n_a,r,K", [(300, 3, 64, 11008), (128, 1, 128, 4096), (1100, 4, 16, 4096)])
+def test_given_tunables_of_the_streaming_shrink_are_what_it_runs_with(T, n_a, r, K):
+    """Batches of few streaming tiles: the number of K parts that shrink_stream_wgs asks for, whether it comes from the
+    descriptor, the process defaults or the shape table; without it, the planner's choice."""
+    w = wl.random_case(31 + T, T, 8, 512, n_a, (r,), max_seg=T // n_a, frac_none=0.0)
+    def plan(**tuning):
+        p = B.lora_plan(w.T, w.seg_indptr, w.seg_adapter, w.adapter_rank, w.adapter_scale, K, w.N, B.LORA_BF16, tuning=tuning)
+        v = B.lora_plan_export(p)
+        assert B.lora_plan_query(p)[1] == v["v_parts"] * T * v["v_row_stride"] * 4
+        p.destroy()
+        return v
+    def tiles(wgs):                                          # 64-token tiles where 128-token tiles are fewer than wgs / 4
+        groups = np.diff(v["group_offset"])
+        return int(np.sum(-(-groups // (64 if 4 * np.sum(-(-groups // 128)) < wgs else 128))))
+    v = plan()
+    for wgs in (2, 40, 100, 511, 4000):
+        want = 1
+        while want < 4 and tiles(wgs) * want < max(1, wgs // 2) and K // 32 // (2 * want) >= 8:
+            want *= 2
+        assert plan(shrink_stream_wgs=wgs)["v_parts"] == want, wgs
+        default = B.lora_tuning_get()["shrink_stream_wgs"]
+        B.lora_tuning_set(shrink_stream_wgs=wgs)
+        try:
+            assert plan()["v_parts"] == want, wgs
+        finally:
+            B.lora_tuning_set(shrink_stream_wgs=default)
+        B.lora_tuning_table_set([dict(tokens=T, k=K, n=w.N, max_rank=r, group_class=gc, tunables=dict(shrink_stream_wgs=wgs)) for gc in (0, 1, 2)])
+        try:
+            assert plan()["v_parts"] == want, wgs
+        finally:
+            B.lora_tuning_table_set(None)
+    assert plan()["v_parts"] == v["v_parts"]
+
+
 @pytest.mark.parametrize("name", ["cfg1", "cfg2", "cfg3", "cfg4", "cfg4d", "cfg5"])
 def test_config_tables_bit_exact(name):
     w = wl.CONFIGS[name](with_w=False) if name != "cfg5" else wl.cfg5("attn", with_w=False)
