@@ -476,6 +476,13 @@ extern "C" int32_t lora_layer_shrink_tiles(const lora_plan* p, int32_t removal, 
     return own && !layer_small_planned(p) ? 0 : (int32_t)list.size();
 }
 
+// Not part of the ABI: the plan's tiles of the expand for rows of any length, for the planner's tests
+extern "C" int32_t lora_rows_expand_tiles(const lora_plan* p, const lora_tile** tiles)
+{
+    *tiles = p->rows_expand_tiles.data();
+    return (int32_t)p->rows_expand_tiles.size();
+}
+
 extern "C" lora_status lora_merge(int32_t L, int32_t N, int32_t K, int32_t r, float scale, int32_t dtype,
                                   int32_t variant, void* const* d_Wt_ptrs, int64_t ldw,
                                   const void* const* d_At_ptrs, const void* const* d_Bt_ptrs, void* hip_stream)

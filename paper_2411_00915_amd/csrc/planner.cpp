@@ -550,9 +550,12 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     if (p->N < 8 || (int64_t)p->N * LORA_MAX_RANK >= (1ll << 31)) return;   // the kernel fetches whole chunks, by 32-bit offsets
     const int G = (int)p->group_adapter.size();
     int32_t max_rank = 0, min_rank = LORA_MAX_RANK;
+    bool odd_above_24 = false;
     for (int g = 0; g < G; ++g) {
-        max_rank = std::max(max_rank, p->rank[p->group_adapter[g]]);
-        min_rank = std::min(min_rank, p->rank[p->group_adapter[g]]);
+        const int32_t r = p->rank[p->group_adapter[g]];
+        max_rank = std::max(max_rank, r);
+        min_rank = std::min(min_rank, r);
+        odd_above_24 = odd_above_24 || (r > 24 && r % 2);
     }
     if (per == 0 && p->variant_req == LORA_VARIANT_AUTO) {
         int64_t products = 0;
@@ -572,10 +575,14 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     // bf16 of one MFMA step: little of Bt to read again and little v to hold, so 16 tokens, and two or four blocks of features for
     // v and the rows' numbers once they are enough tiles all the same.  lora_delta, K = 512, 32 tokens / so: 2188 tokens of
     // rank 20 -> 11008, 41.5 / 37.3 us; 5715 of rank 12 on 64 adapters -> 5120, 52.8 / 44.2; 1114 of rank 4 -> 4096, 16.4 / 13.9;
-    // 1060 batches of rank 4 to 20, 100 to 6600 tokens, 1.11 times as fast, the slowest 0.97.  Higher ranks lose by 16 tokens:
-    // 4708 of rank 100 -> 4096, 68.0 / 71.4.
-    const bool one_step = per == 0 && p->dtype == LORA_BF16 && max_rank <= 32;
-    const bool by_rule = per == 0;
+    // 5400 batches of ranks up to 32, 100 to 6600 tokens, 1.12 times as fast, the slowest 0.97.  Odd ranks above 24, whose rows'
+    // elements all have to be shifted into place, where that fills tiles (above half as many again, requests of more than 16 tokens)
+    // only between 1024 tiles so and 3072 tiles of 32 tokens: below, 700 tokens of rank 31, 5120 -> 5120, 15.3 -> 16.2; above,
+    // 5379 of rank 25 -> 11008, 89.4 -> 100.9; 97 of 605 batches there over 1.02 times as long, 7 of the 1199 other odd ones.  Higher ranks lose by 16 tokens: 4708 of rank 100 -> 4096, 68.0 / 71.4.
+    const bool one_step = per == 0 && p->dtype == LORA_BF16 && max_rank <= 32 &&
+                          (!odd_above_24 || 2 * token_tiles(16) <= 3 * token_tiles(32) ||
+                           (token_tiles(16) * blocks >= 1024 && token_tiles(32) * blocks < 3072));
+    const bool higher = per == 0 && p->dtype == LORA_BF16 && max_rank > 32;
     if (per == 0) per = one_step || token_tiles(16) * blocks <= 512 ? 16 : 32;
     const int64_t tiles = token_tiles(per) * blocks;
     int64_t wide = one_step ? (tiles < 1024 ? 1 : tiles < 2560 ? 2 : 4) : tiles / 1024;
@@ -583,7 +590,7 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     // two or four.  lora_delta: 3683 tokens of rank 256, 512 -> 4096 (1840 tiles of one block), 83.0 -> 64.7 us; 1388 of rank 36,
     // 4096 -> 11008, 40.9 -> 33.1; 109 batches of such tiles 1.14 times as fast, the slowest 0.97.  (With ranks of 4 to 256 in
     // one batch the rounds are not full: 0.94 on average.)
-    if (by_rule && per == 32 && p->dtype == LORA_BF16 && 4 * min_rank >= 3 * max_rank)
+    if (higher && per == 32 && 4 * min_rank >= 3 * max_rank)
         for (int64_t n : {2, 4}) {
             const int64_t held = token_tiles(32) * ((blocks + n - 1) / n);
             if (blocks >= n && held <= 512 && tiles >= 384 * n) wide = n;

@@ -564,3 +564,34 @@ def test_layer_shrink_tiles_are_built_only_where_they_are_read(T, K, N, n_a, ran
     for removal in (False, True):
         assert len(B.lora_layer_shrink_tiles(p, removal)) == 0 and len(B.lora_layer_shrink_tiles(p, removal, own=True)) == 0
     p.destroy()
+
+
+@pytest.mark.parametrize("T,n_a,ranks,N,rows,blocks", [
+    # up to rank 32: 16 tokens, one, two and four blocks of 256 features
+    (700, 2, (30, 4), 4096, 16, 1), (1100, 2, (31, 12), 4096, 16, 2), (2800, 2, (27, 20), 4096, 16, 4), (1500, 200, (31,), 11008, 16, 4),
+    # odd ranks above 24: 32 tokens where tiles of 16 are below 1024 or tiles of 32 are 3072 and more
+    (700, 2, (31, 9), 4096, 32, 1), (260, 1, (25,), 13824, 32, 1), (4800, 2, (25,), 11008, 32, 6), (2400, 1, (31,), 11008, 32, 3),
+    # higher ranks of about one length: a full round of two or four blocks
+    (1500, 2, (100,), 4096, 32, 2), (3600, 3, (200, 256), 4096, 32, 4), (900, 60, (200, 256), 3712, 32, 2)])
+def test_tiles_of_the_expand_for_rows_of_any_length(T, n_a, ranks, N, rows, blocks):
+    """Tokens and features of the largest tile, and that the tiles are every row and feature of every adapter once."""
+    lengths = np.full(n_a, T // n_a)
+    lengths[:T % n_a] += 1
+    rank = np.asarray([ranks[a % len(ranks)] for a in range(n_a)], np.int32)
+    p = B.lora_plan(T, np.concatenate([[0], np.cumsum(lengths)]), np.arange(n_a), rank, np.ones(n_a), 512, N, B.LORA_BF16)
+    fn, ptr = B._lib.lora_rows_expand_tiles, ctypes.POINTER(B.Tile)()
+    fn.argtypes, fn.restype = [ctypes.c_void_p, ctypes.c_void_p], ctypes.c_int32
+    tiles = [ptr[i] for i in range(fn(p.handle, ctypes.byref(ptr)))]
+    group = dict(zip(range(n_a), zip(np.cumsum(lengths) - lengths, np.cumsum(lengths))))
+    covered = np.zeros((T, -(-N // 256)), np.int32)
+    for t in tiles:
+        lo, hi = group[t.adapter]
+        assert lo <= t.row0 and t.row0 + t.nrows <= hi and t.c0 % 256 == 0 and (t.cn % 256 == 0 or t.c0 + t.cn == N)
+        covered[t.row0:t.row0 + t.nrows, t.c0 // 256:-(-(t.c0 + t.cn) // 256)] += 1
+    assert np.all(covered == 1)
+    steps = {t.row0 - group[t.adapter][0] for t in tiles} - {0}
+    assert not steps or min(steps) == rows
+    if max(lengths) > 16:
+        assert max(t.nrows for t in tiles) == min(rows, max(lengths))
+    assert max(-(-t.cn // 256) for t in tiles) == min(blocks, -(-N // 256))
+    p.destroy()
