@@ -575,10 +575,11 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     // bf16 of one MFMA step: little of Bt to read again and little v to hold, so 16 tokens, and two or four blocks of features for
     // v and the rows' numbers once they are enough tiles all the same.  lora_delta, K = 512, 32 tokens / so: 2188 tokens of
     // rank 20 -> 11008, 41.5 / 37.3 us; 5715 of rank 12 on 64 adapters -> 5120, 52.8 / 44.2; 1114 of rank 4 -> 4096, 16.4 / 13.9;
-    // 5400 batches of ranks up to 32, 100 to 6600 tokens, 1.12 times as fast, the slowest 0.97.  Odd ranks above 24, whose rows'
+    // 5400 batches of ranks up to 32, 100 to 6600 tokens, 1.12 times as fast.  Odd ranks above 24, whose rows'
     // elements all have to be shifted into place, where that fills tiles (above half as many again, requests of more than 16 tokens)
     // only between 1024 tiles so and 3072 tiles of 32 tokens: below, 700 tokens of rank 31, 5120 -> 5120, 15.3 -> 16.2; above,
-    // 5379 of rank 25 -> 11008, 89.4 -> 100.9; 97 of 605 batches there over 1.02 times as long, 7 of the 1199 other odd ones.  Higher ranks lose by 16 tokens: 4708 of rank 100 -> 4096, 68.0 / 71.4.
+    // 5379 of rank 25 -> 11008, 89.4 -> 100.9; 97 of 605 batches there over 1.02 times as long, 7 of the 1199 other odd ones.
+    // Higher ranks lose by 16 tokens: 4708 of rank 100 -> 4096, 68.0 / 71.4.
     const bool one_step = per == 0 && p->dtype == LORA_BF16 && max_rank <= 32 &&
                           (!odd_above_24 || 2 * token_tiles(16) <= 3 * token_tiles(32) ||
                            (token_tiles(16) * blocks >= 1024 && token_tiles(32) * blocks < 3072));
@@ -588,9 +589,10 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     int64_t wide = one_step ? (tiles < 1024 ? 1 : tiles < 2560 ? 2 : 4) : tiles / 1024;
     // Higher ranks, all about as long: the chip holds 512 tiles, so two or four blocks a tile where that makes one full round of
     // two or four.  lora_delta: 3683 tokens of rank 256, 512 -> 4096 (1840 tiles of one block), 83.0 -> 64.7 us; 1388 of rank 36,
-    // 4096 -> 11008, 40.9 -> 33.1; 109 batches of such tiles 1.14 times as fast, the slowest 0.97.  (With ranks of 4 to 256 in
-    // one batch the rounds are not full: 0.94 on average.)
-    if (higher && per == 32 && 4 * min_rank >= 3 * max_rank)
+    // 4096 -> 11008, 40.9 -> 33.1; 199 batches of such tiles 1.11 times as fast, the slowest 0.99.  (With ranks of 4 to 256 in
+    // one batch the rounds are not full: 0.94 on average.)  With fewer than eight tokens a tile Bt alone is what it reads, and
+    // more and shorter workgroups read it the faster: 270 tokens on 103 adapters of rank 100, 52.2 -> 54.7, 38 batches 0.995.
+    if (higher && per == 32 && 4 * min_rank >= 3 * max_rank && (int64_t)p->perm.size() >= 8 * token_tiles(32))
         for (int64_t n : {2, 4}) {
             const int64_t held = token_tiles(32) * ((blocks + n - 1) / n);
             if (blocks >= n && held <= 512 && tiles >= 384 * n) wide = n;
