@@ -800,6 +800,21 @@ bool gemm_tiled_supported(int32_t T, int32_t K, int32_t N, int32_t dtype, const 
     return tiles < (1ll << 31);
 }
 
+// The ring kernel: at least three stages of 64 k; rows of W and x addressed by 32-bit byte offsets
+static bool ring_takes(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw)
+{
+    return K > 2 * RK && (int64_t)N * ldw * 2 < (1ll << 32) && (int64_t)T * ldx * 2 < (1ll << 32);
+}
+
+// (the planner, which orders the rows, knows no kernels)
+static bool product_by_stage_lists(const lora_plan* p)
+{
+    return gemm_route(p->T, p->K, p->N, p->K, p->K, true, true) == GEMM_TILED && !ring_takes(p->T, p->K, p->N, p->K, p->K);
+}
+namespace {
+struct install_by_stage_lists { install_by_stage_lists() { lora_product_by_stage_lists = product_by_stage_lists; } } g_install_by_stage_lists;
+}  // namespace
+
 // p != nullptr: fold the adapter delta in; v holds the shrink's output and vb (room for T*2*R bf16) receives its split
 // (split_done: the shrink has written it already);
 // rm: likewise for the removal of the merged adapter (mixture mode)
@@ -809,10 +824,9 @@ hipError_t launch_gemm_tiled(int32_t T, int32_t K, int32_t N, const void* x, int
                              const gemm_removal& rm, const void* const* Bt, hipStream_t stream, gemm_route_id route)
 {
     const bool delta = p && (!p->perm.empty() || rm.plan);
-    // the ring kernel: at least three stages of 64 k; rows of W and x addressed by 32-bit byte offsets, in its delta
-    // part also the split of v.  The register-staged kernel takes what it does not: 256 x 256 tiles once there are enough
-    // of them to fill the 256 compute units
-    const bool ring_ok = route == GEMM_TILED && K > 2 * RK && (int64_t)N * ldw * 2 < (1ll << 32) && (int64_t)T * ldx * 2 < (1ll << 32) &&
+    // (the ring kernel's delta part has 32-bit byte offsets of the split of v, too.)  The register-staged kernel takes what the
+    // ring does not: 256 x 256 tiles once there are enough of them to fill the 256 compute units
+    const bool ring_ok = route == GEMM_TILED && ring_takes(T, K, N, ldx, ldw) &&
                          (!delta || ((int64_t)T * p->R * 4 < (1ll << 32) && (!rm.plan || (int64_t)T * rm.plan->R * 4 < (1ll << 32))));
     const bool big = route == GEMM_TILED && (int64_t)((N + 255) / 256) * ((T + 255) / 256) >= 192;
     gemm_delta_args da{};

@@ -129,6 +129,10 @@ extern void (*lora_plan_device_release)(lora_plan*);
 // the translation unit that has the kernel; null in host-only builds of the planner.
 extern bool (*lora_layer_takes)(const lora_plan*, int64_t tiles);
 
+// Whether lora_fused_forward's product is the kernel that walks the stage lists; set by the translation unit that has it, null in
+// host-only builds of the planner.
+extern bool (*lora_product_by_stage_lists)(const lora_plan*);
+
 constexpr size_t LORA_LAYER_SYNC_BYTES = 16 * 128;
 
 // stage ids and row keys of the fused GEMM: bit 23 marks the stages / the rows of the merged adapter's removal

@@ -817,6 +817,30 @@ static std::vector<int32_t> deal_rows(const lora_plan* p, const std::vector<int3
     return out;
 }
 
+// Time, in stages, of a product by the stage lists: tiles of 256 rows of `stages` stages each, in that order, times `columns` tiles
+// of features, on 256 compute units; a tile's base stages, start and stores are about four.
+static int64_t time_by_stage_lists(const std::vector<int32_t>& stages, int32_t columns)
+{
+    typedef std::pair<int64_t, int32_t> units;               // free from then on, how many
+    std::vector<units> heap{{0, 256}};
+    const std::greater<units> later;
+    int64_t end = 0;
+    for (int32_t s : stages)
+        for (int32_t left = columns; left > 0;) {
+            std::pop_heap(heap.begin(), heap.end(), later);
+            units& u = heap.back();
+            const int32_t take = std::min(u.second, left);
+            const units busy{u.first + 4 + s, take};
+            left -= take;
+            if ((u.second -= take) == 0) heap.pop_back();
+            else std::push_heap(heap.begin(), heap.end(), later);
+            heap.push_back(busy);
+            std::push_heap(heap.begin(), heap.end(), later);
+            end = std::max(end, busy.first);
+        }
+    return end;
+}
+
 // Tables of the fused GEMM: it walks the tokens in adapter-sorted order (or dealt, see above), so a tile of rows holds few
 // adapters, and folds each adapter's delta in (v_hi, v_lo against Bt_a; the register-staged kernels as extra
 // k-stages from the lists below, the ring kernel per wavefront from the row keys).  The full
@@ -838,12 +862,10 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
     std::vector<int32_t> removal_only, plain;
     for (int32_t t = 0; t < p->T; ++t)
         if (p->token_adapter[t] < 0) ((key[t] & LORA_UNMERGE_BIT) ? removal_only : plain).push_back(t);
-    std::vector<int32_t> sorted = deal_rows(p, removal_only);
-    if (sorted.empty()) {
-        sorted = p->perm;
-        sorted.insert(sorted.end(), removal_only.begin(), removal_only.end());
-    }
+    std::vector<int32_t> sorted = p->perm, dealt = deal_rows(p, removal_only);
+    sorted.insert(sorted.end(), removal_only.begin(), removal_only.end());
     sorted.insert(sorted.end(), plain.begin(), plain.end());
+    if (!dealt.empty()) dealt.insert(dealt.end(), plain.begin(), plain.end());
 
     // adapter stages of the rows [p0, p1) of `rows`: one per `cols` columns of [v_hi | v_lo] (2 r columns) and adapter
     std::vector<int32_t> seen((size_t)p->n_a, 0);
@@ -867,11 +889,37 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
     };
 
     const int32_t full = p->T / 256;
-    std::vector<int32_t> weight((size_t)full), blocks((size_t)full);
-    for (int32_t b = 0; b < full; ++b) {
-        weight[b] = stages_of(sorted, b * 256, b * 256 + 256, 64, nullptr);
-        blocks[b] = b;
+    std::vector<int32_t> weight, blocks((size_t)full);
+    auto weigh = [&](const std::vector<int32_t>& rows) {
+        weight.resize((size_t)full);
+        for (int32_t b = 0; b < full; ++b) weight[b] = stages_of(rows, b * 256, b * 256 + 256, 64, nullptr);
+    };
+    if (!dealt.empty()) {
+        // The kernel that walks the stage lists has every wavefront go through all stages of its 256 rows: dealt rows even
+        // these out, too, but are more in all.  Both ways are laid out on the compute units; K <= 128, 1449 drawn batches that
+        // could be dealt: 0.81 times as long if all are, but one in ten longer (10764 tokens on 203 adapters, 8 -> 1272, 66 ->
+        // 82 us; 2559 on 77, 40 -> 7256, 115 -> 142); so 0.82, three of them above 1.03.
+        bool take = true;
+        if (stage_lists && lora_product_by_stage_lists && lora_product_by_stage_lists(p)) {
+            const int32_t columns = (p->N + 255) / 256;
+            int64_t time[2], work[2];
+            for (int i = 0; i < 2; ++i) {
+                const std::vector<int32_t>& rows = i ? dealt : sorted;
+                weigh(rows);
+                std::sort(weight.begin(), weight.end(), std::greater<int32_t>());
+                if (full * 256 < p->T) weight.push_back(stages_of(rows, full * 256, p->T, 64, nullptr));
+                time[i] = time_by_stage_lists(weight, columns);
+                work[i] = 4 + *std::max_element(weight.begin(), weight.end()) / 2;
+                int64_t sum = 0;
+                for (int32_t w : weight) sum += w;
+                work[i] += sum * columns / 256;
+            }
+            take = time[1] < time[0] && 20 * work[1] < 19 * work[0];
+        }
+        if (take) sorted.swap(dealt);
     }
+    weigh(sorted);
+    for (int32_t b = 0; b < full; ++b) blocks[b] = b;
     std::stable_sort(blocks.begin(), blocks.end(), [&](int32_t x, int32_t y) { return weight[x] > weight[y]; });
     p->order.resize((size_t)p->T);
     for (int32_t b = 0; b < full; ++b)
@@ -1058,6 +1106,7 @@ extern "C" lora_status lora_plan_create(const lora_batch_desc* d, lora_plan** ou
 
 void (*lora_plan_device_release)(lora_plan*) = nullptr;
 bool (*lora_layer_takes)(const lora_plan*, int64_t) = nullptr;
+bool (*lora_product_by_stage_lists)(const lora_plan*) = nullptr;
 
 extern "C" void lora_plan_destroy(lora_plan* p)
 {

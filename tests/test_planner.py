@@ -171,6 +171,36 @@ def test_rows_of_the_fused_gemm_are_dealt_to_wavefronts(lengths, n_a, ranks, m):
         assert len(set(a.tolist())) == 1 + int(np.sum(a[1:] != a[:-1]))
 
 
+@pytest.mark.parametrize("T,n_a,ranks,K,N,zipf,m,dealt", [
+    (5072, 118, (64, 8, 128, 16, 32), 8, 2992, 0.0, -1, False), (10764, 203, (64, 8, 128, 16, 32), 48, 1400, 0.0, -1, False),
+    (3286, 65, (16, 32, 64, 128), 64, 4800, 0.0, -1, False), (2559, 77, (64,), 40, 7256, 0.0, 0, False),
+    (2623, 120, (16, 32, 64, 128), 64, 5176, 1.1, -1, True), (1812, 122, (16, 32, 64, 128), 16, 6840, 1.1, 0, True)])
+def test_rows_of_the_product_by_stage_lists_are_dealt_where_that_is_less(T, n_a, ranks, K, N, zipf, m, dealt):
+    """K <= 128 and 192 tiles of 256 x 256 and more: the kernel that walks the stage lists, whose tiles take as long as all their
+    adapters' stages.  Single tokens; dealt rows neither raise the longest tile nor take more rounds."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, True)[0] == 4 and (-(-T // 256)) * (-(-N // 256)) >= 192
+    rng = np.random.default_rng(7)
+    share = 1.0 / np.arange(1, n_a + 1) ** zipf
+    ads = rng.choice(n_a, size=T, p=share / share.sum()).astype(np.int32)
+    rank = np.asarray([ranks[a % len(ranks)] for a in range(n_a)], np.int32)
+    p = B.lora_plan(T, np.arange(T + 1), ads, rank, np.ones(n_a), K, N, B.LORA_BF16, merged_adapter=m if m >= 0 else None)
+    v = B.lora_plan_export(p)
+    p.destroy()
+    tok, order = v["token_adapter"], v["gemm_order"]
+    per_tile = np.diff(v["gemm_stage_offset"])
+    carries = (tok >= 0) | (ads != m if m >= 0 else np.zeros(T, bool))
+    by_adapter = np.concatenate([v["perm"], np.nonzero((tok < 0) & carries)[0], np.nonzero((tok < 0) & ~carries)[0]])
+    def stages(rows):
+        own = sum(-(-2 * int(rank[a]) // 64) for a in set(tok[rows].tolist()) if a >= 0)
+        return own + (-(-2 * int(rank[m]) // 64) if m >= 0 and carries[rows].any() else 0)
+    in_order = np.asarray([stages(by_adapter[i:i + 256]) for i in range(0, T, 256)])
+    assert np.array_equal(per_tile, [stages(order[i:i + 256]) for i in range(0, T, 256)])
+    if dealt:
+        assert per_tile.max() < 0.7 * in_order.max()
+    else:
+        assert sorted(per_tile) == sorted(in_order)
+
+
 @pytest.mark.parametrize("T,n_a,r,K", [(300, 3, 64, 11008), (128, 1, 128, 4096), (1100, 4, 16, 4096)])
 def test_given_tunables_of_the_streaming_shrink_are_what_it_runs_with(T, n_a, r, K):
     """Batches of few streaming tiles: the number of K parts that shrink_stream_wgs asks for, whether it comes from the
