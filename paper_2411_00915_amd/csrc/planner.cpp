@@ -722,11 +722,13 @@ static void build_f32_tiles(lora_plan* p)
 // `cheap`: rows without an adapter of their own (mixture mode's, for the removal).  Returns an empty list where that
 // does not take a third off the sum over tiles of 256 rows of the longest wavefront: dealt rows put more adapters in a tile
 // (6055 tokens on 240 adapters, 4096 -> 11008, sum 172 and 128: 523 -> 536 us; 6935 on 105, 96 and 77: 82 -> 84), or where
-// there are so many adapters that chance evens them out (8 to a segment; 4000 of them took half a millisecond to deal).
+// there are eight adapters and more to a segment: uniform ones are evened out by chance, and 4000 took half a millisecond to deal
+// (very uneven popularity would still gain: 825 single tokens on 201 adapters, sum 125 and 74).
 // Sum over tiles of the longest wavefront's steps, sorted and dealt: 1111 tokens of mixed requests 21 and 9 (longest 18 and 3),
 // 16384 tokens on 256 adapters 396 and 225.  lora_fused_forward, W from memory: 96.5 -> 89.6 us in mixture mode (4096 -> 4096),
-// 1300 tokens on 64 adapters (4096 -> 4096) 67.0 -> 62.7, 2637 on 191 (11008 -> 4096) 366 -> 300, the 16384
-// tokens (5120 -> 13824) 1891 -> 1873.
+// 1300 tokens on 64 adapters (4096 -> 4096) 67.0 -> 62.7, 2637 on 191 (11008 -> 4096) 366 -> 300.  The cost is that of the ring and
+// of the medium GEMM; in the small one, whose wavefronts share the adapters of 16 to 64 rows, 5800 drawn batches that are
+// dealt take 0.94 times as long, 47 of them over 1.02 (up to 1.09).
 static std::vector<int32_t> deal_rows(const lora_plan* p, const std::vector<int32_t>& cheap)
 {
     struct run { int32_t segment, group, first, count; };    // group -1: `cheap`
@@ -734,6 +736,26 @@ static std::vector<int32_t> deal_rows(const lora_plan* p, const std::vector<int3
     if (n < 2 || G < 2 || G >= 8 * n) return {};
     auto steps_of = [&](int32_t g) { return g < 0 ? 0 : (p->rank[p->group_adapter[g]] + 31) / 32; };
     auto size_of = [&](int32_t g) { return g < 0 ? (int32_t)cheap.size() : p->group_offset[g + 1] - p->group_offset[g]; };
+    auto cost = [&](auto steps_at) {                         // (sum over tiles, longest)
+        std::pair<int64_t, int32_t> c{0, 0};
+        for (int32_t i = 0; i < n; i += 4) {
+            int32_t longest = 0;
+            for (int32_t q = i; q < std::min(i + 4, n); ++q) longest = std::max(longest, steps_at(q));
+            c.first += longest;
+            c.second = std::max(c.second, longest);
+        }
+        return c;
+    };
+    // Dealing costs a plan up to 80 us, and few batches end with it: those are sent back first that cannot, because the steps
+    // of whole requests, spread evenly, are too many already.  lora_plan_create of 8192 tokens on 128 adapters 192 -> 163 us.
+    std::vector<int32_t> sorted_steps((size_t)n, 0);
+    int64_t fewest = 0;
+    for (int32_t g = 0; g < G; ++g) {
+        for (int32_t i = p->group_offset[g] / 64; i <= (p->group_offset[g + 1] - 1) / 64; ++i) sorted_steps[(size_t)i] += steps_of(g);
+        fewest += (int64_t)steps_of(g) * ((size_of(g) + 63) / 64);
+    }
+    const auto sorted = cost([&](int32_t i) { return sorted_steps[(size_t)i]; });
+    if (3 * ((fewest + 3) / 4) > 2 * sorted.first) return {};
     struct group { int32_t steps, size, id; };
     std::vector<group> small, large;
     for (int32_t g = 0; g < G; ++g) (size_of(g) < 64 ? small : large).push_back(group{steps_of(g), size_of(g), g});
@@ -791,20 +813,7 @@ static std::vector<int32_t> deal_rows(const lora_plan* p, const std::vector<int3
         return steps[(size_t)a] != steps[(size_t)b] ? steps[(size_t)a] > steps[(size_t)b] : a < b;
     });
 
-    auto cost = [&](auto steps_at) {                         // (sum over tiles, longest)
-        std::pair<int64_t, int32_t> c{0, 0};
-        for (int32_t i = 0; i < n; i += 4) {
-            int32_t longest = 0;
-            for (int32_t q = i; q < std::min(i + 4, n); ++q) longest = std::max(longest, steps_at(q));
-            c.first += longest;
-            c.second = std::max(c.second, longest);
-        }
-        return c;
-    };
-    std::vector<int32_t> sorted_steps((size_t)n, 0);
-    for (int32_t g = 0; g < G; ++g)
-        for (int32_t i = p->group_offset[g] / 64; i <= (p->group_offset[g + 1] - 1) / 64; ++i) sorted_steps[(size_t)i] += steps_of(g);
-    const auto dealt = cost([&](int32_t i) { return steps[(size_t)order[(size_t)i]]; }), sorted = cost([&](int32_t i) { return sorted_steps[(size_t)i]; });
+    const auto dealt = cost([&](int32_t i) { return steps[(size_t)order[(size_t)i]]; });
     if (3 * dealt.first > 2 * sorted.first || dealt.second > sorted.second) return {};
 
     std::vector<int32_t> out((size_t)rows), to((size_t)n);
@@ -867,33 +876,46 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
     sorted.insert(sorted.end(), plain.begin(), plain.end());
     if (!dealt.empty()) dealt.insert(dealt.end(), plain.begin(), plain.end());
 
-    // adapter stages of the rows [p0, p1) of `rows`: one per `cols` columns of [v_hi | v_lo] (2 r columns) and adapter
-    std::vector<int32_t> seen((size_t)p->n_a, 0);
-    int32_t stamp = 0;
-    auto stages_of = [&](const std::vector<int32_t>& rows, int32_t p0, int32_t p1, int32_t cols, std::vector<int32_t>* lst) {
-        int32_t n = 0;
+    // adapter stages of a block of 256 rows, one per 64 columns of [v_hi | v_lo] (2 r columns) and adapter, the removal's last;
+    // in lists, if there are any, those of the block and those of each half
+    struct lists { std::vector<int32_t> ptr128{0}, of128, ptr256{0}, of256; };
+    std::vector<int32_t> seen128((size_t)p->n_a, 0), seen256((size_t)p->n_a, 0);
+    int32_t halves = 0, wholes = 0;
+    auto stages_of = [&](const std::vector<int32_t>& rows, int32_t block, lists* to) {
+        int32_t n = 0, last = LORA_UNMERGE_BIT - 1;
         bool removal = false;
-        ++stamp;
-        for (int32_t q = p0; q < p1; ++q) {
-            removal = removal || (key[rows[q]] & LORA_UNMERGE_BIT);
-            const int32_t a = p->token_adapter[rows[q]];
-            if (a < 0 || seen[(size_t)a] == stamp) continue;
-            seen[(size_t)a] = stamp;
-            for (int32_t jb = 0; jb * cols < 2 * p->rank[a]; ++jb, ++n)
-                if (lst) lst->push_back(a | (jb << 24));
+        ++wholes;
+        for (int32_t lo = 256 * block; lo < std::min(256 * block + 256, p->T); lo += 128) {
+            bool half_removal = false;
+            ++halves;
+            last = LORA_UNMERGE_BIT - 1;
+            for (int32_t q = lo; q < std::min(lo + 128, p->T); ++q) {
+                const int32_t k = key[(size_t)rows[(size_t)q]];
+                if (k == last) continue;                     // (of a run of rows only the first)
+                last = k;
+                half_removal = half_removal || (k & LORA_UNMERGE_BIT);
+                const int32_t a = k & (LORA_UNMERGE_BIT - 1);
+                if (a == LORA_UNMERGE_BIT - 1 || seen128[(size_t)a] == halves) continue;
+                seen128[(size_t)a] = halves;
+                const bool first = seen256[(size_t)a] != wholes;
+                seen256[(size_t)a] = wholes;
+                for (int32_t jb = 0; jb * 64 < 2 * p->rank[a]; ++jb) {
+                    n += first;
+                    if (to) to->of128.push_back(a | (jb << 24));
+                    if (to && first) to->of256.push_back(a | (jb << 24));
+                }
+            }
+            for (int32_t jb = 0; half_removal && to && jb * 64 < 2 * p->rank[p->merged]; ++jb) to->of128.push_back(p->merged | LORA_UNMERGE_BIT | (jb << 24));
+            if (to) to->ptr128.push_back((int32_t)to->of128.size());
+            removal = removal || half_removal;
         }
-        if (removal)
-            for (int32_t jb = 0; jb * cols < 2 * p->rank[p->merged]; ++jb, ++n)
-                if (lst) lst->push_back(p->merged | LORA_UNMERGE_BIT | (jb << 24));
+        for (int32_t jb = 0; removal && jb * 64 < 2 * p->rank[p->merged]; ++jb, ++n)
+            if (to) to->of256.push_back(p->merged | LORA_UNMERGE_BIT | (jb << 24));
+        if (to) to->ptr256.push_back((int32_t)to->of256.size());
         return n;
     };
 
-    const int32_t full = p->T / 256;
-    std::vector<int32_t> weight, blocks((size_t)full);
-    auto weigh = [&](const std::vector<int32_t>& rows) {
-        weight.resize((size_t)full);
-        for (int32_t b = 0; b < full; ++b) weight[b] = stages_of(rows, b * 256, b * 256 + 256, 64, nullptr);
-    };
+    const int32_t full = p->T / 256, all = (p->T + 255) / 256;
     if (!dealt.empty()) {
         // The kernel that walks the stage lists has every wavefront go through all stages of its 256 rows: dealt rows even
         // these out, too, but are more in all.  Both ways are laid out on the compute units; K <= 128, 1449 drawn batches that
@@ -904,45 +926,44 @@ static void build_gemm_tables(lora_plan* p, bool stage_lists)
             const int32_t columns = (p->N + 255) / 256;
             int64_t time[2], work[2];
             for (int i = 0; i < 2; ++i) {
-                const std::vector<int32_t>& rows = i ? dealt : sorted;
-                weigh(rows);
-                std::sort(weight.begin(), weight.end(), std::greater<int32_t>());
-                if (full * 256 < p->T) weight.push_back(stages_of(rows, full * 256, p->T, 64, nullptr));
-                time[i] = time_by_stage_lists(weight, columns);
-                work[i] = 4 + *std::max_element(weight.begin(), weight.end()) / 2;
+                std::vector<int32_t> stages((size_t)all);
                 int64_t sum = 0;
-                for (int32_t w : weight) sum += w;
-                work[i] += sum * columns / 256;
+                for (int32_t b = 0; b < all; ++b) sum += stages[(size_t)b] = stages_of(i ? dealt : sorted, b, nullptr);
+                std::sort(stages.begin(), stages.begin() + full, std::greater<int32_t>());
+                time[i] = time_by_stage_lists(stages, columns);
+                work[i] = 4 + *std::max_element(stages.begin(), stages.end()) / 2 + sum * columns / 256;
             }
             take = time[1] < time[0] && 20 * work[1] < 19 * work[0];
         }
         if (take) sorted.swap(dealt);
     }
-    weigh(sorted);
-    for (int32_t b = 0; b < full; ++b) blocks[b] = b;
-    std::stable_sort(blocks.begin(), blocks.end(), [&](int32_t x, int32_t y) { return weight[x] > weight[y]; });
-    p->order.resize((size_t)p->T);
-    for (int32_t b = 0; b < full; ++b)
-        std::copy(sorted.begin() + (size_t)blocks[b] * 256, sorted.begin() + (size_t)blocks[b] * 256 + 256,
-                  p->order.begin() + (size_t)b * 256);
-    std::copy(sorted.begin() + (size_t)full * 256, sorted.end(), p->order.begin() + (size_t)full * 256);
+
+    lists found;
+    std::vector<int32_t> weight((size_t)all), blocks((size_t)all);
+    for (int32_t b = 0; b < all; ++b) {
+        weight[(size_t)b] = stages_of(sorted, b, stage_lists ? &found : nullptr);
+        blocks[(size_t)b] = b;
+    }
+    std::stable_sort(blocks.begin(), blocks.begin() + full, [&](int32_t x, int32_t y) { return weight[(size_t)x] > weight[(size_t)y]; });
+    p->order.reserve((size_t)p->T);
+    for (int32_t b : blocks) p->order.insert(p->order.end(), sorted.begin() + (size_t)b * 256, sorted.begin() + std::min(b * 256 + 256, p->T));
     p->row_key.resize((size_t)p->T);
     for (int32_t q = 0; q < p->T; ++q) p->row_key[q] = key[p->order[q]];
 
     for (int32_t a : p->group_adapter) p->rank_steps += (p->rank[a] + 31) / 32;
 
     if (!stage_lists) return;
-    for (int h = 0; h < 2; ++h) {
-        const int32_t rows = h == 0 ? 128 : 256, cols = 64;
-        std::vector<int32_t>& ptr = h == 0 ? p->extra_ptr128 : p->extra_ptr256;
-        std::vector<int32_t>& lst = h == 0 ? p->extra128 : p->extra256;
-        const int32_t tiles = (p->T + rows - 1) / rows;
-        ptr.assign(1, 0);
-        lst.clear();
-        for (int32_t tile = 0; tile < tiles; ++tile) {
-            stages_of(p->order, tile * rows, std::min(tile * rows + rows, p->T), cols, &lst);
-            ptr.push_back((int32_t)lst.size());
-        }
+    auto append = [](std::vector<int32_t>& ptr, std::vector<int32_t>& lst, const std::vector<int32_t>& from_ptr, const std::vector<int32_t>& from, int32_t tile) {
+        lst.insert(lst.end(), from.begin() + from_ptr[(size_t)tile], from.begin() + from_ptr[(size_t)tile + 1]);
+        ptr.push_back((int32_t)lst.size());
+    };
+    p->extra_ptr128.assign(1, 0);
+    p->extra_ptr256.assign(1, 0);
+    p->extra128.reserve(found.of128.size());
+    p->extra256.reserve(found.of256.size());
+    for (int32_t b : blocks) {
+        append(p->extra_ptr256, p->extra256, found.ptr256, found.of256, b);
+        for (int32_t half = 2 * b; half < 2 * b + 2 && half * 128 < p->T; ++half) append(p->extra_ptr128, p->extra128, found.ptr128, found.of128, half);
     }
 }
 
