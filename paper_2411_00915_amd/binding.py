@@ -25,7 +25,13 @@ if not os.path.exists(LIB_PATH):
 
 _lib = ctypes.CDLL(LIB_PATH)
 
-from . import _calls  # noqa: E402
+try:
+    from . import _calls
+except ImportError as e:
+    if not os.environ.get("LORA_AMD_LIBRARY"):
+        raise ImportError(f"the extension module _calls is missing or cannot be loaded ({e}): build it with "
+                          "`python -m paper_2411_00915_amd.build`") from e
+    from . import calls_ctypes as _calls               # a library built elsewhere, in a tree that has not been built
 
 LORA_OK, LORA_ERR_INVALID_ARG, LORA_ERR_UNSUPPORTED, LORA_ERR_NOMEM, LORA_ERR_WORKSPACE, LORA_ERR_DEVICE = range(6)
 LORA_F32, LORA_BF16 = 0, 1
@@ -395,5 +401,6 @@ _calls.bind(_check, _first_stream, *(_address(f) for f in (
 # lora_base_gemm(num_tokens, k, n, dtype, x, ldx, Wt, ldw, y, ldy, stream=None),
 # lora_merge(num_layers, n, k, rank, scale, dtype, d_Wt_ptrs, ldw, d_At_ptrs, d_Bt_ptrs, variant=LORA_VARIANT_AUTO, stream=None),
 # lora_fused_forward(plan, x, ldx, Wt, ldw, d_At_ptrs, d_Bt_ptrs, y, ldy, workspace, workspace_bytes, stream=None)
-from ._calls import (lora_base_gemm, lora_delta, lora_delta_static, lora_expand, lora_fused_forward, lora_merge,  # noqa: E402,F401
-                     lora_plan_upload, lora_shrink)
+(lora_plan_upload, lora_shrink, lora_expand, lora_delta, lora_delta_static, lora_base_gemm, lora_fused_forward, lora_merge) = (
+    _calls.lora_plan_upload, _calls.lora_shrink, _calls.lora_expand, _calls.lora_delta, _calls.lora_delta_static,
+    _calls.lora_base_gemm, _calls.lora_fused_forward, _calls.lora_merge)

@@ -13,7 +13,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblora_amd.so")
-CALLS = os.path.join(HERE, "_calls.so")       # the extension module of the Python calls (no GPU code)
+# the extension module of the Python calls (no GPU code), named for the interpreter whose ABI it is compiled for
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["planner.cpp", "kernels_general.hip", "kernels_tiled.hip", "kernels_stream.hip", "kernels_gemm.hip", "kernels_gemm_small.hip", "kernels_gemm_mid.hip", "kernels_any.hip", "abi.hip", "timing.hip", "probe.hip"]
@@ -82,6 +83,9 @@ def _check_no_scratch(src, lines, kernels):
 
 
 def _build_calls():
+    untagged = os.path.join(HERE, "_calls.so")         # (any interpreter would load it, whatever it was compiled for)
+    if os.path.exists(untagged):
+        os.remove(untagged)
     subprocess.check_call(["g++", os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-shared", "-pthread",
                            "-I" + sysconfig.get_paths()["include"]] + HOST_FLAGS)
 

@@ -1,6 +1,11 @@
 """The extension module of the Python calls: what reaches the C ABI, by position and by name, and what is refused."""
 import ctypes
 import inspect
+import os
+import shutil
+import subprocess
+import sys
+import sysconfig
 import types
 
 import numpy as np
@@ -8,7 +13,7 @@ import pytest
 
 pytest.importorskip("torch")                               # (before the library: both then use one HIP runtime)
 
-from paper_2411_00915_amd import _calls
+from paper_2411_00915_amd import _calls, calls_ctypes
 from paper_2411_00915_amd import binding as B
 
 P, I32, I64, F, Z = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
@@ -90,3 +95,71 @@ def test_no_address_and_no_plan_are_null(seen):
     last, _ = seen
     B.lora_shrink(B.Plan(None, None), None, 8, None, None, 0)
     assert last[1] == (None, None, 8, None, None, None)
+
+
+def _import_binding(tmp_path, calls, library, code):
+    """Runs `code` after the import of binding from a copy of the package's Python files, with the extension module or without"""
+    here = os.path.dirname(B.__file__)
+    copy = tmp_path / "paper_2411_00915_amd"
+    copy.mkdir()
+    for name in os.listdir(here):
+        if name.endswith(".py") or (calls and name.startswith("_calls.")):
+            shutil.copy(os.path.join(here, name), copy / name)
+    if not library:
+        os.symlink(B.LIB_PATH, copy / "liblora_amd.so")
+    env = {k: v for k, v in os.environ.items() if k != "LORA_AMD_LIBRARY"}
+    if library:
+        env["LORA_AMD_LIBRARY"] = B.LIB_PATH
+    return subprocess.run([sys.executable, "-c", "import torch\nfrom paper_2411_00915_amd import binding as B\n" + code], cwd=tmp_path, env=env,
+                          capture_output=True, text=True)
+
+
+def test_a_library_built_elsewhere_needs_no_extension_module(tmp_path):
+    """LORA_AMD_LIBRARY in a tree that has not been built: the same functions, by ctypes"""
+    out = _import_binding(tmp_path, False, True, """
+import inspect
+plan = B.lora_plan(4, [0, 4], [0], [8], [1.0], 8, 8, B.LORA_F32)
+assert B.lora_plan_query(plan)[0] == 8
+for name, call in (("lora_shrink", lambda: B.lora_shrink(B.Plan(None, None), None, 8, None, None, 0)),
+                   ("lora_delta", lambda: B.lora_delta(plan, None, 8, None, None, None, None, 8, 1.0, stream=0)),
+                   ("lora_base_gemm", lambda: B.lora_base_gemm(-1, 8, 8, B.LORA_F32, None, 8, None, 8, None, 8, stream=0))):
+    try:
+        call()
+    except B.LoraError as e:
+        assert e.status == B.LORA_ERR_INVALID_ARG and str(e).startswith(name), e
+    else:
+        raise AssertionError(name)
+for name in %r:
+    print(name, inspect.signature(getattr(B, name)))
+""" % (list(ABI),))
+    assert out.returncode == 0, out.stderr
+    assert out.stdout.split("\n")[:-1] == [f"{name} {inspect.signature(getattr(B, name))}" for name in ABI]
+
+
+def test_a_missing_extension_module_says_how_to_build(tmp_path):
+    out = _import_binding(tmp_path, False, False, "")
+    assert out.returncode and "python -m paper_2411_00915_amd.build" in out.stderr.strip().split("\n")[-1]
+
+
+def test_extension_module_is_named_for_its_interpreter(tmp_path):
+    assert os.path.basename(_calls.__file__) == "_calls" + sysconfig.get_config_var("EXT_SUFFIX")
+    out = _import_binding(tmp_path, True, False, "from paper_2411_00915_amd import _calls\nassert B.lora_delta is _calls.lora_delta")
+    assert out.returncode == 0, out.stderr
+
+
+@pytest.mark.parametrize("name", list(ABI))
+def test_arguments_reach_the_abi_by_ctypes_too(name):
+    """The stand-in for the extension module: every argument of every function, in place"""
+    seen = []
+    keep = [ctypes.CFUNCTYPE(ctypes.c_int, *arguments)(lambda *a, n=n: (seen.append((n, list(a))), 0)[1]) for n, arguments in ABI.items()]
+    order = ["lora_plan_upload", "lora_shrink", "lora_expand", "lora_delta", "lora_delta_static", "lora_base_gemm", "lora_fused_forward", "lora_merge"]
+    calls_ctypes.bind(B._check, None, *(B._address(keep[list(ABI).index(n)]) for n in order))
+    parameters = list(inspect.signature(getattr(B, name)).parameters)
+    values = [types.SimpleNamespace(handle=0x1000) if p == "plan" else 0.25 if p in ("beta", "scale") else Buffer() if p in ("x", "y") else 64 + i
+              for i, p in enumerate(parameters)]
+    expected = [0x1000 if p == "plan" else 0xfedcba9876543210 if p in ("x", "y") else v for p, v in zip(parameters, values)]
+    if name == "lora_merge":
+        expected.insert(6, expected.pop(10))
+    getattr(calls_ctypes, name)(*values)
+    getattr(calls_ctypes, name)(**dict(zip(parameters, values)))
+    assert seen == [(name, expected)] * 2
