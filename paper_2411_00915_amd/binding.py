@@ -383,7 +383,9 @@ def _first_stream():
     """torch's current stream, and the functions that give the current device and a device's current stream once torch is
     initialised"""
     import torch
-    return _stream(None) or 0, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    # (torch's own, below its Python layer; the public functions where a torch has them under no such name)
+    return (_stream(None) or 0, getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device),
+            getattr(torch._C, "_cuda_getCurrentRawStream", lambda device: torch.cuda.current_stream(device).cuda_stream))
 
 
 def _address(function) -> int:

@@ -97,6 +97,30 @@ def test_no_address_and_no_plan_are_null(seen):
     assert last[1] == (None, None, 8, None, None, None)
 
 
+@pytest.mark.parametrize("private", [True, False])
+def test_no_stream_is_the_current_one_with_and_without_torchs_private_functions(private, seen, monkeypatch):
+    import torch
+    current = {0: 0x50, 1: 0x60}
+    device = [0]
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: device[0])
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d=None: types.SimpleNamespace(cuda_stream=current[device[0] if d is None else d]))
+    for name, stand_in in (("_cuda_getDevice", lambda: device[0]), ("_cuda_getCurrentRawStream", lambda d: current[d])):
+        if private:
+            monkeypatch.setattr(torch._C, name, stand_in, raising=False)
+        else:
+            monkeypatch.delattr(torch._C, name, raising=False)
+    last, _ = seen
+    plan = types.SimpleNamespace(handle=0x1000)
+    for device[0], want in ((0, 0x50), (0, 0x50), (1, 0x60), (0, 0x50)):       # (the first call initialises torch's side)
+        B.lora_plan_upload(plan)
+        assert last[1] == (0x1000, want)
+        B.lora_plan_upload(plan, stream=None)
+        assert last[1] == (0x1000, want)
+    current[0] = 0x70
+    B.lora_plan_upload(plan)
+    assert last[1] == (0x1000, 0x70)
+
+
 def _import_binding(tmp_path, calls, library, code):
     """Runs `code` after the import of binding from a copy of the package's Python files, with the extension module or without"""
     here = os.path.dirname(B.__file__)
