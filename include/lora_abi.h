@@ -187,9 +187,12 @@ typedef struct {
     const int32_t* group_offset;    /* [num_groups+1] exclusive prefix sums into perm */
     const lora_tile* shrink_tiles;  int32_t num_shrink_tiles;
     const lora_tile* expand_tiles;  int32_t num_expand_tiles;
-    /* Tables of lora_fused_forward's GEMM (empty when the plan cannot use the MFMA kernels): the row order it walks
-     * (tokens sorted by adapter, then tokens without adapter; whole blocks of 256 rows ordered by decreasing number
-     * of adapter stages), and per tile of 256 rows of that order its adapter stages: one entry
+    /* Tables of lora_fused_forward's GEMM (empty when the plan cannot use the MFMA kernels): the row order it walks,
+     * a permutation of the tokens -- those that carry a delta, then the others, and of that whole blocks of 256 rows
+     * ordered by decreasing number of adapter stages.  Rows that carry a delta are sorted by adapter, or dealt to
+     * segments of 64 rows where that leaves these more equal: in any 64 rows that start at a multiple of 64 every
+     * adapter is one run, but over the whole order it may be in many places (perm and group_offset have every
+     * adapter's tokens together) --, and per tile of 256 rows of that order its adapter stages: one entry
      * adapter | block << 24 per adapter present and per block of 64 columns of the adapter's [v_hi | v_lo]
      * (2 r columns).  The register-staged GEMM kernels walk these lists; the 256 x 256 ring kernel uses the row
      * order alone (each wavefront finds the adapters of its own 64 rows). */
@@ -200,8 +203,9 @@ typedef struct {
     const int32_t* gemm_stage;           /* [gemm_stage_offset[num_gemm_tiles]] */
     /* Mixture mode (merged_adapter_plus1 > 0 and that adapter has rank > 0); otherwise -1 / 0 / NULL.  The stage
      * list of a tile that holds a token the removal applies to ends with the entries
-     * merged_adapter | 1 << 23 | block << 24, one per block of the merged adapter's 2 r columns; gemm_order then
-     * lists tokens with an adapter of their own, tokens without one, and last the merged adapter's tokens. */
+     * merged_adapter | 1 << 23 | block << 24, one per block of the merged adapter's 2 r columns.  All tokens that are
+     * not m's then carry a delta, so gemm_order has those without an adapter of their own behind or among those with
+     * one, and m's tokens last. */
     int32_t        merged_adapter;       /* m, or -1 */
     int32_t        num_unmerge;          /* tokens the removal applies to: all that are not m's */
     int32_t        unmerge_v_row_stride; /* row stride (floats) and parts of the removal's share of v */
@@ -333,8 +337,8 @@ lora_status lora_base_gemm(int32_t num_tokens, int32_t k, int32_t n, int32_t dty
  * single rounding of y (unmerged inference at close to the cost of merged
  * inference, sections 2 and 4.4).  Runs the shrink into `workspace` (which
  * holds v and its split into two bf16 terms; size from lora_plan_query,
- * 256-byte aligned), then one GEMM kernel that walks the tokens in
- * adapter-sorted order and adds each adapter's v B_a to the accumulators of
+ * 256-byte aligned), then one GEMM kernel that walks the tokens in the
+ * plan's row order and adds each adapter's v B_a to the accumulators of
  * the rows that carry it (as extra k-stages of its pipeline, or wavefront by
  * wavefront after the K loop, depending on the kernel).  Small bf16 batches run
  * as one launch: the product's workgroups need v only behind their K loop and wait

@@ -6,7 +6,7 @@
 // sections 1-2); adding the delta to the fp32 accumulators before y is rounded
 // makes unmerged inference cost close to merged inference (section 4.4).
 //
-// Both kernels walk the tokens in adapter-sorted order, so that neighbouring rows share an adapter.
+// Both kernels walk the tokens in the plan's row order, in which neighbouring rows share an adapter.
 //   gemm_ring_kernel: after the K loop every wavefront adds the deltas of its own 64 tokens to its accumulators,
 //     adapter by adapter and 32 ranks at a time, with Bt_a[its features, ranks] and the tokens' v (split into two
 //     bf16 terms v_hi + v_lo) straight from memory as MFMA operands (see the kernel).
@@ -68,7 +68,7 @@ extern __shared__ uint4 gemm_lds[];
 constexpr int META_MAX = 256;      // adapter stages of a tile whose metadata is cached in LDS (more are read from memory)
 
 struct gemm_delta_args {
-    const int32_t* order;          // [T] tokens sorted by adapter, then tokens without adapter; nullptr = identity
+    const int32_t* order;          // [T] tokens in the plan's row order; nullptr = identity
     const int32_t* row_key;        // [T] in the order above: the token's adapter (bits 0..22; all ones: none) | removal bit
     const int32_t* rank;
     const int32_t* extra_ptr;      // [token tiles + 1]
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(512) void gemm_ring_kernel(
     int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
     bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, gemm_delta_args da)
 {
-    // DELTA: the rows of the tile are tokens in adapter-sorted order, and after the K loop every wavefront adds the
+    // DELTA: the rows of the tile are tokens in the plan's row order, and after the K loop every wavefront adds the
     // adapter deltas of its own 64 tokens to its accumulators by itself: for each adapter among them (one or two,
     // mostly) and each block of 32 ranks, Bt_a[its 128 features, 32 ranks] as the MFMA row operand straight from
     // memory, and the tokens' v (its two bf16 terms) as the column operands, masked to the adapter's tokens.  No LDS,

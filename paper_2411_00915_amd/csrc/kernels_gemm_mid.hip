@@ -31,7 +31,7 @@
 // 4096 -> 4096, 34.1 -> 27.7; 11008 -> 4096 83 -> 72; 100 tokens, 5120 -> 13824, 51.7 -> 41.8.
 // The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
 //
-// DELTA: tokens in adapter-sorted order; after the K loop every wavefront adds the deltas of its own 64 tokens: per
+// DELTA: tokens in the plan's row order; after the K loop every wavefront adds the deltas of its own 64 tokens: per
 // adapter and 32 ranks, Bt_a[its features] and v (as the shrink left it, split into two bf16 terms, or, for ranks off the
 // tuned kernels, in fp32 products: 1111 tokens of ranks 100 and 20, 5120 -> 5120, 109 us, with two terms 99) as MFMA operands.
 // (v read by every wavefront for itself, step by step behind Bt: lora_fused_forward of 1111 tokens in mixture mode, 5120 ->

@@ -16,7 +16,7 @@
 // of W comes from memory; fp32, 256 tokens, 4096 -> 4096: this kernel 600 -> 73 us (the matrix cores' share of that at 2.1 GHz
 // is 64 us).
 //
-// DELTA: tokens in adapter-sorted order; before the partial sums are added up, the wavefronts share out the deltas of the
+// DELTA: tokens in the plan's row order; before the partial sums are added up, the wavefronts share out the deltas of the
 // tile's tokens and add v B_a of theirs to their own partial sums, so the delta is spread over the workgroup and joins the same
 // fp32 sum.  Two ways to share out (deltas_in_items chooses): items (16-token block, adapter in it, rank step), or pairs
 // (adapter, rank step) over all blocks.  The delta costs trips to memory: an item's operands are requested one item ahead, the

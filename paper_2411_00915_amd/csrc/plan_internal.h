@@ -61,8 +61,9 @@ struct lora_plan {
     std::vector<int32_t> token_adapter, perm, group_adapter, group_offset, rank;
     std::vector<float> scale;
     std::vector<lora_tile> shrink_tiles, expand_tiles;
-    // fused GEMM: row order (tokens sorted by adapter, then tokens without adapter) and, per token tile of 128
-    // or 256 rows of that order, the adapter stages present: packed adapter | (64-column block of the
+    // fused GEMM: row order -- tokens that carry a delta, sorted by adapter or dealt to segments of 64 rows in which every
+    // adapter is one run (which share_out of the small GEMM depends on for its blocks of 16), then the others; whole
+    // blocks of 256 by their stages -- and, per token tile of 128 or 256 rows of that order, the adapter stages present: packed adapter | (64-column block of the
     // adapter's [v_hi | v_lo] concatenation) << 24.  (The 256 x 256 ring kernel uses the row order only: its
     // wavefronts find the adapters of their own 64 rows themselves.)
     std::vector<int32_t> order, extra_ptr128, extra128, extra_ptr256, extra256;

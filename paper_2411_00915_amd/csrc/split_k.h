@@ -135,7 +135,7 @@ __device__ __forceinline__ void bf16_terms(const float (&f)[8], op16 (&o)[TERMS]
 // fp32 products (fp32, and bf16 with ranks off the tuned kernels, whose v was always taken whole)
 enum row_delta { NO_DELTA, TERMS_DELTA, PLAIN_DELTA };
 struct row_delta_args {
-    const int32_t* order;          // [T] tokens sorted by adapter, then tokens without adapter
+    const int32_t* order;          // [T] tokens in the plan's row order
     const int32_t* row_key;        // [T] in that order: adapter of the token (bits 0..22; all ones: none) | removal bit
     const int32_t* rank;
     const float* v;

@@ -169,6 +169,9 @@ def test_rows_of_the_fused_gemm_are_dealt_to_wavefronts(lengths, n_a, ranks, m):
     for i in range(0, T, 64):
         a = tok[order[i:i + 64]]
         assert len(set(a.tolist())) == 1 + int(np.sum(a[1:] != a[:-1]))
+    # rows without a delta fill whole blocks of 256, but for one block that has both kinds (those without last) and the end
+    plain = [~carries[order[i:i + 256]] for i in range(0, T, 256)]
+    assert sum(bool(p.any() and not p.all()) for p in plain) <= 1 and all(np.all(np.diff(p.astype(int)) >= 0) for p in plain)
 
 
 @pytest.mark.parametrize("T,n_a,ranks,K,N,zipf,m,dealt", [
