@@ -27,8 +27,9 @@
 // takes about 0.3 us (WA = 3: 0.5), which short products do not get back.  lora_base_gemm, W from memory, APART / not, mean of
 // 60 to 580 drawn products: 2 stages 1.09, 3 1.04, 5 to 8 1.02, 9 to 16 1.005 (WA = 3: 1.02), 21 to 24 0.998 (1.002), 25 to 32
 // 0.996 (1.000), above 50 0.99.
-// Tiles of 64 features are for products of 64 to 640 tokens that leave the small kernel a second round of tiles: 300 tokens,
-// 4096 -> 4096, 34.1 -> 27.7; 11008 -> 4096 83 -> 72; 100 tokens, 5120 -> 13824, 51.7 -> 41.8.
+// Tiles of 64 features are for products of 21 stages and more that are one round of them (129 to 256 tiles), which leave the small
+// kernel a second round of its own: 300 tokens, 4096 -> 4096, 34.1 -> 27.7; 11008 -> 4096 83 -> 72; 100 tokens, 5120 -> 13824,
+// 51.7 -> 41.8; 7785 drawn products of 641 to 16000 tokens 0.78 times as long as what they took before, three above 1.03.
 // The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
 //
 // DELTA: tokens in the plan's row order; after the K loop every wavefront adds the deltas of its own 64 tokens: per
@@ -435,8 +436,9 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
 // 21.7 / - / 18.6;  9901, 256 -> 1568: 53.4 / 24.5 / 24.6 / 23.4 / 18.1;  1452, 1024 -> 4096: 34.6 / 25.7 / 29.3 / 24.4 / 22.9.
 // Tiles of 64 features (no adapters), W from memory, before / with them: 4096 -> 4096, 300 tokens 34.1 / 27.7, 512 34.7 / 29.7;
 // 5120 -> 5120, 384, 45.9 / 40.3;  4096 -> 11008, 100, 38.8 / 31.5.
-// The constants are fitted to such times of 2000 problems (8 to 16384 tokens, K 8 to 13824, N 64 to 13824): the choice takes
-// 0.4 % longer than the best of the five others on average, 1.24 times at worst.
+// The constants of the five others are fitted to such times of 2000 problems (8 to 16384 tokens, K 8 to 13824, N 64 to 13824): with
+// the kernels of that time the choice took 0.4 % longer than the best of the five on average, 1.24 times at worst.  Those of
+// 128 and 192 features are 1 % faster without adapters since, from 25 stages on: a distance that the fit does not see.
 gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool delta, bool tiled)
 {
     if ((int64_t)N * ldw * 2 >= (1ll << 32) || (int64_t)T * ldx * 2 >= (1ll << 32)) return GEMM_TILED;   // 32-bit byte offsets

@@ -898,6 +898,7 @@ def test_medium_batch_gemm_stages_and_remainders(T, K, N, ranks):
 @pytest.mark.parametrize("T,K,N,kernel", [
     (557, 2056, 1896, 6), (250, 1400, 4104, 6), (125, 2104, 11000, 6), (300, 2112, 4096, 6), (385, 4096, 4088, 6), (65, 4152, 13000, 6),
     (640, 8, 4096, 2), (650, 264, 4104, 2), (700, 1096, 4104, 2), (1300, 72, 776, 2), (1100, 200, 5000, 3), (1100, 264, 5000, 3), (1280, 1096, 4096, 3),
+    (1025, 1608, 968, 6), (1100, 2104, 904, 6), (2049, 1672, 520, 6), (4097, 1544, 232, 6), (12289, 1992, 72, 6),
     (513, 1544, 4104, 2), (385, 2104, 5000, 2), (513, 1600, 4096, 2), (1100, 1544, 4104, 3), (777, 2104, 5000, 3), (1100, 1600, 4096, 3)])
 def test_medium_base_gemm_k_steps_in_two_halves(T, K, N, kernel):
     """Products without adapters in the 64, 128 and 192 features of the medium GEMM, whose wavefronts take one of a stage's two
