@@ -180,7 +180,9 @@ static const rows_shape kRowsF32[] = {{2, 2, 1}, {1, 1, 2}}, kRowsBf16[] = {{4, 
 // more: an adapter's rows for every 16 tb tokens, x for every 16 fb ranks.  Microseconds, fitted to 70 batches with x and At from
 // memory; a K part more is another read of v by whoever takes it.  lora_shrink, K = 11008, streaming / this: 128 tokens of rank
 // 16 14.6 / 4.7, rank 128 20.8 / 5.6; 300 tokens on 3 adapters of rank 64 15.5 / 7.7; 535 on 5 of rank 64 15.9 / 9.6, of rank 128
-// 23.6 / 16.1; not taken: 2000 on 8 of rank 64 17.5 / 19.7.  Not where the streaming shrink's own tunables were given other values
+// 23.6 / 16.1; not taken: 2000 on 8 of rank 64 17.5 / 19.7.  What it is chosen for is lora_delta: fewer parts are the expand's gain,
+// and lora_shrink by itself loses near the line (391 drawn calls 0.83 times as long, 55 of them over 1.02: 1831 tokens of rank
+// 16, K = 4096, four parts to one, 7.1 -> 8.1).  Not where the streaming shrink's own tunables were given other values
 // than the defaults: whoever gives them steers, or searches, that kernel's tiles and K parts.
 static bool choose_rows_shrink(lora_plan* p, int32_t max_rank)
 {
@@ -575,14 +577,14 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     // bf16 of one MFMA step: little of Bt to read again and little v to hold, so 16 tokens, and two or four blocks of features for
     // v and the rows' numbers once they are enough tiles all the same.  lora_delta, K = 512, 32 tokens / so: 2188 tokens of
     // rank 20 -> 11008, 41.5 / 37.3 us; 5715 of rank 12 on 64 adapters -> 5120, 52.8 / 44.2; 1114 of rank 4 -> 4096, 16.4 / 13.9;
-    // 5400 batches of ranks up to 32, 100 to 6600 tokens, 1.12 times as fast.  Odd ranks above 24, whose rows'
-    // elements all have to be shifted into place, where that fills tiles (above half as many again, requests of more than 16 tokens)
-    // only between 1024 tiles so and 3072 tiles of 32 tokens: below, 700 tokens of rank 31, 5120 -> 5120, 15.3 -> 16.2; above,
-    // 5379 of rank 25 -> 11008, 89.4 -> 100.9; 97 of 605 batches there over 1.02 times as long, 7 of the 1199 other odd ones.
-    // Higher ranks lose by 16 tokens: 4708 of rank 100 -> 4096, 68.0 / 71.4.
+    // 5400 batches of ranks up to 32, 100 to 6600 tokens, 1.12 times as fast.  Odd ranks above 24, whose rows' elements all have to
+    // be shifted into place, only above 1024 tiles so and below 3072 tiles of 32 tokens where requests of more than 16 tokens fill
+    // these (tiles of 16 are half as many again): 702 tokens of rank 31, 5120 -> 5120, 15.3 / 16.2; 1018 of ranks 31 and 9, 4096 ->
+    // 4096, 15.1 / 15.9; 5379 of rank 25 -> 11008, 89.4 / 100.9; 97 of 605 such batches over 1.02 times as long, of the 1199
+    // others 7.  Higher ranks lose by 16 tokens: 4708 of rank 100 -> 4096, 68.0 / 71.4.
     const bool one_step = per == 0 && p->dtype == LORA_BF16 && max_rank <= 32 &&
                           (!odd_above_24 || 2 * token_tiles(16) <= 3 * token_tiles(32) ||
-                           (token_tiles(16) * blocks >= 1024 && token_tiles(32) * blocks < 3072));
+                           (token_tiles(16) * blocks > 1024 && token_tiles(32) * blocks < 3072));
     const bool higher = per == 0 && p->dtype == LORA_BF16 && max_rank > 32;
     if (per == 0) per = one_step || token_tiles(16) * blocks <= 512 ? 16 : 32;
     const int64_t tiles = token_tiles(per) * blocks;

@@ -602,8 +602,8 @@ def test_layer_shrink_tiles_are_built_only_where_they_are_read(T, K, N, n_a, ran
 @pytest.mark.parametrize("T,n_a,ranks,N,rows,blocks", [
     # up to rank 32: 16 tokens, one, two and four blocks of 256 features
     (700, 2, (30, 4), 4096, 16, 1), (1100, 2, (31, 12), 4096, 16, 2), (2800, 2, (27, 20), 4096, 16, 4), (1500, 200, (31,), 11008, 16, 4),
-    # odd ranks above 24: 32 tokens where tiles of 16 are below 1024 or tiles of 32 are 3072 and more
-    (700, 2, (31, 9), 4096, 32, 1), (260, 1, (25,), 13824, 32, 1), (4800, 2, (25,), 11008, 32, 6), (2400, 1, (31,), 11008, 32, 3),
+    # odd ranks above 24: 32 tokens where tiles of 16 are 1024 and fewer or tiles of 32 are 3072 and more
+    (700, 2, (31, 9), 4096, 32, 1), (1018, 1, (31,), 4096, 32, 1), (260, 1, (25,), 13824, 32, 1), (4800, 2, (25,), 11008, 32, 6), (2400, 1, (31,), 11008, 32, 3),
     # higher ranks of about one length: a full round of two or four blocks, for requests of eight tokens a tile on average
     (1500, 2, (100,), 4096, 32, 2), (3600, 3, (200, 256), 4096, 32, 4), (270, 108, (100,), 4096, 32, 1), (280, 90, (200, 256), 5120, 32, 1),
     (380, 60, (200, 256), 3712, 32, 1), (900, 60, (200, 256), 3712, 32, 2)])
