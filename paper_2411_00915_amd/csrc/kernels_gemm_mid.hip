@@ -17,8 +17,9 @@
 //        loads return in order) at the end of its memory part 2 s + 1, one barrier earlier at least.
 //   WAR: stage s - 1, last read in memory part 2 s - 1, is overwritten by loads issued in memory part 2 s + 1; the LDS
 //        reads of the trailing wavefronts have returned before their MFMAs of phase 2 s - 1 issued, one barrier earlier.
-// Without adapters and with more than 24 stages (APART) a wavefront multiplies 32 WA features x 64 tokens, but only one of a stage's two k-steps -- a third
-// fewer bytes read from LDS --, and the two sums meet in LDS at the end.  A stage is one memory and one matrix part.
+// Without adapters and with more than 24 stages (APART) a wavefront multiplies 32 WA features x 64 tokens, but only one of a
+// stage's two k-steps -- a third fewer bytes read from LDS (WA = 3: 29 %; cycles, by counter, with the sums' way 30 and 25) --,
+// and the two sums meet in LDS at the end.  A stage is one memory and one matrix part.
 //   RAW: as above, with stage s read in memory part s and its successor waited for at that part's end.
 //   WAR: stage s - 1 is overwritten by loads issued in memory part s; its reads have returned before the barrier that ends
 //        memory part s - 1 (lgkmcnt), the trailing wavefronts' one barrier before the leading ones' part s.
