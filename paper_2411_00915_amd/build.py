@@ -51,7 +51,7 @@ def _compile(src: str) -> str:
 # inline assembly): a register spill would put scratch loads and stores, which the same counter counts, between
 # them.  The build fails if the compiler reports scratch use or spills for one of them.
 NO_SCRATCH = {"kernels_gemm.hip": ("gemm_ring_kernel",), "kernels_gemm_small.hip": ("gemm_small_kernel", "layer_small_kernel"),
-              "kernels_gemm_mid.hip": ("gemm_mid_kernel", "gemm_narrow_kernel"), "kernels_any.hip": ("shrink_rows_kernel",)}
+              "kernels_gemm_mid.hip": ("gemm_mid_kernel", "gemm_narrow_kernel", "gemm_wide_kernel"), "kernels_any.hip": ("shrink_rows_kernel",)}
 REMARK = "[-Rpass-analysis=kernel-resource-usage]"
 
 

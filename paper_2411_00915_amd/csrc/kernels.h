@@ -100,8 +100,8 @@ struct gemm_removal {
 
 // which of the GEMMs below a bf16 problem that gemm_tiled_supported takes goes to; tiled: whether launch_gemm_tiled may take it;
 // GEMM_TILED_128: launch_gemm_tiled with its 128 x 128 tiles
-enum gemm_route_id { GEMM_SMALL = 1, GEMM_MID_128 = 2, GEMM_MID_192 = 3, GEMM_TILED = 4, GEMM_TILED_128 = 5, GEMM_MID_64 = 6 };
-inline bool gemm_route_is_mid(gemm_route_id r) { return r == GEMM_MID_64 || r == GEMM_MID_128 || r == GEMM_MID_192; }
+enum gemm_route_id { GEMM_SMALL = 1, GEMM_MID_128 = 2, GEMM_MID_192 = 3, GEMM_TILED = 4, GEMM_TILED_128 = 5, GEMM_MID_64 = 6, GEMM_MID_256 = 7 };
+inline bool gemm_route_is_mid(gemm_route_id r) { return r == GEMM_MID_64 || r == GEMM_MID_128 || r == GEMM_MID_192 || r == GEMM_MID_256; }
 gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool delta, bool tiled);
 
 // base GEMM  y = x Wt^T  (+ optional adapter delta in the epilogue when p != nullptr)

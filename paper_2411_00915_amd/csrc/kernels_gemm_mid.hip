@@ -1,5 +1,5 @@
 // Base GEMM y = x W (+ adapter deltas) of batches of some hundred to a few thousand tokens (bf16): tiles of 128 tokens x
-// 64, 128 or 192 features, for problems that are too few 256 x 256 tiles to give every compute unit one (or that leave a
+// 64, 128, 192 or 256 features, for problems that are too few 256 x 256 tiles to give every compute unit one (or that leave a
 // last round nearly empty).
 //
 // A workgroup (8 wavefronts, two per SIMD) has the compute unit's LDS to itself: a ring of S stages of 64 k (whole
@@ -31,6 +31,12 @@
 // Tiles of 64 features are for products of 21 stages and more that are one round of them (129 to 256 tiles), which leave the small
 // kernel a second round of its own: 300 tokens, 4096 -> 4096, 34.1 -> 27.7; 11008 -> 4096 83 -> 72; 100 tokens, 5120 -> 13824,
 // 51.7 -> 41.8; 7785 drawn products of 641 to 16000 tokens 0.78 times as long as what they took before, three above 1.03.
+// Tiles of 256 features (a ring of three stages) are for what would be a round and a bit of the narrower ones and half a round
+// of 256 x 256: 2048 tokens, 4096 -> 4096, 74.3 -> 61.9 us; 1536, 5120 -> 5120, 90.6 -> 76.3; 1428, 13824 -> 5120, 219 -> 165; 1106,
+// 5120 -> 13824, 163 -> 139.  All four widths are bound by their fills: with the LDS reads and the MFMAs taken out the same
+// launches take 0.95 to 0.98 of their time, without the fills 0.6 (1024 tokens, 4096 -> 4096, 39.0 / 38.4 / 24.1 us), however
+// many stages are on their way (two, three or four: the same to 1 %) and whether a stage's loads go out in its memory part or
+// between its MFMAs; so what a tile costs is its rows, (64 WA + 128) x 128 bytes a stage, and wider ones fetch less in all.
 // The loads are issued from inline assembly, so the compiler does not count them: the waits are written out.
 //
 // DELTA: tokens in the plan's row order; after the K loop every wavefront adds the deltas of its own 64 tokens: per
@@ -395,10 +401,20 @@ __global__ __launch_bounds__(512) void gemm_narrow_kernel(
     gemm_mid_tile<1, NO_DELTA, true, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, da);
 }
 
+// tiles of 256 features
+template <row_delta DELTA, bool APART, bool KTAIL>
+__global__ __launch_bounds__(512) void gemm_wide_kernel(
+    int T, int K, int N, const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ Wt, int64_t ldw,
+    bf16_t* __restrict__ y, int64_t ldy, int tiles_n, int tiles_t, row_delta_args da)
+{
+    gemm_mid_tile<4, DELTA, APART, KTAIL>(T, K, N, x, ldx, Wt, ldw, y, ldy, tiles_n, tiles_t, da);
+}
+
 template <int WA, row_delta DELTA, bool APART, bool KTAIL>
 constexpr auto mid_kernel()
 {
     if constexpr (WA == 1) return &gemm_narrow_kernel<KTAIL>;
+    else if constexpr (WA == 4) return &gemm_wide_kernel<DELTA, APART, KTAIL>;
     else return &gemm_mid_kernel<WA, DELTA, APART, KTAIL>;
 }
 
@@ -429,6 +445,9 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
 //   4096 -> 4096,  256 tokens 16 / 31 / 35 / 64 / 16,  640: 42 / 33 / 36 / 63 / 45,  1280: 79 / 64 / 44 / 68 / 70,
 //                  1536: - / 67 / 79 / 69 / 75,  2048: - / 68 / 80 / 72 / 77,  3072: - / 111 / 128 / 85 / 85
 //   5120 -> 5120,  1024 tokens 91 / 79 / 53 / 84 / 85,  2048: - / 116 / 99 / 84 / 137
+// 128 / 192 / 256 features / 256 x 256 ring, where 256 features are the choice: 2048 tokens, 4096 -> 4096, 75 / 80 / 62 / 76;  1500,
+// 11008 -> 4096, 189 / 201 / 151 / 200;  2607, 3288 -> 3064, 75 / 86 / 58 / 67;  and just where they are not: 2321, 5120 -> 5120,
+// 118 / 140 / 115 / 100;  3000, 4096 -> 4096, 110 / 116 / 109 / 80;  991, 5120 -> 5120, 71 / 49 / 56 / 83.
 //   4096 -> 11008, 256 tokens 42 / 34 / 38 / 65 / 42,  512: 80 / 64 / 45 / - / 71,  1024: 157 / 98 / 84 / 73 / 115
 //   5120 -> 13824, 320 tokens 108 / 87 / 66 / - / 86,  640: 180 / 128 / 116 / 95 / 138
 // Products of few stages are the register-staged 128 x 128 tiles' (two on a compute unit, so that one's stores and first
@@ -439,7 +458,10 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
 // 5120 -> 5120, 384, 45.9 / 40.3;  4096 -> 11008, 100, 38.8 / 31.5.
 // The constants of the five others are fitted to such times of 2000 problems (8 to 16384 tokens, K 8 to 13824, N 64 to 13824): with
 // the kernels of that time the choice took 0.4 % longer than the best of the five on average, 1.24 times at worst.  Those of
-// 128 and 192 features are 1 % faster without adapters since, from 25 stages on: a distance that the fit does not see.
+// 128 and 192 features are 1 % faster without adapters since, from 25 stages on: a distance that the fit does not see.  Those of
+// 256 features are fitted to 8 products; against the others 44 of 50 drawn products of 300 to 7000 tokens (the rest are smaller
+// tiles') took 1.003 times as long as the best of them, without these tiles 1.033, and 40 fused calls 1.000 and 1.007; 44 drawn calls
+// that go to them, K from 8 to 1600, 1.001 and 1.16, the slowest 1.04.
 gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool delta, bool tiled)
 {
     if ((int64_t)N * ldw * 2 >= (1ll << 32) || (int64_t)T * ldx * 2 >= (1ll << 32)) return GEMM_TILED;   // 32-bit byte offsets
@@ -462,6 +484,7 @@ gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t l
     };
     take(GEMM_MID_128, rounds(128, 128, 256, 2.0, 0.43, 0.10, 1));
     take(GEMM_MID_192, rounds(192, 128, 256, 3.1, 0.51, 0.19, 1));
+    take(GEMM_MID_256, rounds(256, 128, 256, 4.0, 0.70, 0.20, 1));
     if (!delta) take(GEMM_MID_64, rounds(64, 128, 256, 3.5, 0.36, 0.05, 1));
     if (ring) take(GEMM_TILED, rounds(256, 256, 256, 4.4, 0.95, 0.55, 2));
     if (!delta) take(GEMM_TILED_128, 0.3 + rounds(128, 128, 512, 1.7, 0.585, 0.56, 1));
@@ -476,11 +499,12 @@ hipError_t launch_gemm_mid(gemm_route_id route, int32_t T, int32_t K, int32_t N,
     const bool delta = p && (!p->perm.empty() || rm.plan);
     const row_delta_args da = delta ? row_deltas_of(p, d, v, rm, Bt) : row_delta_args{};
 #define MID_LAUNCH(WA_, D_, A_, KT_) launch_one<WA_, D_, A_, KT_>(T, K, N, x, ldx, Wt, ldw, y, ldy, da, stream)
-#define MID_DISPATCH(D_, A_) (K % 64 ? (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, A_, true) : MID_LAUNCH(3, D_, A_, true))    \
-                                     : (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, A_, false) : MID_LAUNCH(3, D_, A_, false)))
+#define MID_WIDTH(D_, A_, KT_) (route == GEMM_MID_128 ? MID_LAUNCH(2, D_, A_, KT_) : route == GEMM_MID_192 ? MID_LAUNCH(3, D_, A_, KT_) : MID_LAUNCH(4, D_, A_, KT_))
+#define MID_DISPATCH(D_, A_) (K % 64 ? MID_WIDTH(D_, A_, true) : MID_WIDTH(D_, A_, false))
     if (route == GEMM_MID_64) return delta ? hipErrorInvalidValue : K % 64 ? MID_LAUNCH(1, NO_DELTA, true, true) : MID_LAUNCH(1, NO_DELTA, true, false);
     if (!delta) return K > 24 * 64 ? MID_DISPATCH(NO_DELTA, true) : MID_DISPATCH(NO_DELTA, false);
     return p->extra_ptr256.empty() ? MID_DISPATCH(PLAIN_DELTA, false) : MID_DISPATCH(TERMS_DELTA, false);
 #undef MID_DISPATCH
+#undef MID_WIDTH
 #undef MID_LAUNCH
 }

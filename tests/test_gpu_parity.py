@@ -927,6 +927,35 @@ def test_medium_base_gemm_k_steps_in_two_halves(T, K, N, kernel):
     assert torch.equal(ys[:, :N], y[:T]) and bool((ys[:, N:] == 9.0).all())
 
 
+@pytest.mark.parametrize("T,K,N,ranks", [
+    (1300, 8, 5000, (8, 16)), (1153, 136, 5000, (24, 128)), (1500, 200, 4104, (1, 5, 20, 100, 256)), (2049, 264, 3080, (8, 64, 128)),
+    (6000, 72, 1032, (64,)), (1500, 328, 4104, (16, 64))])
+def test_wide_tiles_of_the_medium_gemm_with_adapters(T, K, N, ranks):
+    """Tiles of 128 tokens x 256 features: fewer stages than the ring of three holds, as many, more; K tails of one chunk, of
+    all but one and half; one token past a tile, remainders of tokens and features; any rank, tokens without adapter, mixture mode."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, True)[0] == 7
+    w = wl.random_case(2100 + T + K, T, K, N, 12, ranks, max_seg=60, frac_none=0.15, scales=(1.0, -1.0))
+    assert "gemm_mid_kernel<delta>" in _launched(lambda: run_forward_case(w, n_sample=256))
+    run_mixture_case(w, 2, n_sample=256)
+
+
+@pytest.mark.parametrize("T,K,N", [(1153, 1096, 5000), (1500, 1536, 4104), (1300, 1544, 5000), (2049, 1592, 3080), (1500, 1600, 4104), (3325, 2104, 2056)])
+def test_wide_tiles_of_the_medium_base_gemm(T, K, N):
+    """... without adapters, up to 24 stages in one chain of k-steps and above in two, with and without a K tail; rows apart,
+    nothing written behind the last row or between the rows of y."""
+    assert B.lora_gemm_choice(T, K, N, B.LORA_BF16, False)[0] == 7
+    w = wl.random_case(2300 + T + K, T, K, N, 1, (8,), max_seg=T)
+    dl = device.to_device(w, DEV, with_w=True)
+    y = torch.full((T + 1, N), 9.0, dtype=torch.bfloat16, device=DEV)
+    assert _launched(lambda: B.lora_base_gemm(T, K, N, dl.dtype, dl.x, K, dl.Wt, K, y, N)) == {"gemm_mid_kernel"}
+    _assert_close(_to_np(y)[:T], oracle.base(w.x, w.W), BF16_TOL, "base gemm")
+    assert bool((y[T] == 9.0).all())
+    xs, ws, ys = (torch.full((rows, width), 9.0, dtype=torch.bfloat16, device=DEV) for rows, width in ((T, K + 8), (N, K + 24), (T, N + 16)))
+    xs[:, :K], ws[:, :K] = dl.x.view(T, K), dl.Wt.view(N, K)
+    B.lora_base_gemm(T, K, N, dl.dtype, xs, K + 8, ws, K + 24, ys, N + 16)
+    assert torch.equal(ys[:, :N], y[:T]) and bool((ys[:, N:] == 9.0).all())
+
+
 @pytest.mark.parametrize("T,K,N", [(640, 8, 4096), (1300, 72, 776), (650, 264, 4104), (640, 1536, 4096), (1100, 200, 5000), (1280, 1480, 4096),
                                    (1280, 1536, 4096)])
 def test_short_medium_products_are_summed_in_one_chain(T, K, N):

@@ -89,3 +89,12 @@ def test_lds_reads_of_the_narrow_tiles_return_before_the_first_barrier_after_the
     kernels = _kernels("kernels_gemm_mid.hip", "gemm_narrow_kernel", tmp_path)
     assert len(kernels) == 2
     _check(kernels, 1, 12, 6)
+
+
+def test_lds_reads_of_the_wide_tiles_return_before_the_barrier_their_loop_allows(tmp_path):
+    """the tiles of 256 features: builds <deltas, k-steps apart, K tail>"""
+    kernels = _kernels("kernels_gemm_mid.hip", "gemm_wide_kernel", tmp_path)
+    apart = {s: l for s, l in kernels.items() if re.search(r"row_deltaE\dELb1ELb[01]E", s)}
+    assert len(kernels) == 8 and len(apart) == 2
+    _check({s: l for s, l in kernels.items() if s not in apart}, 2, 21, 9)
+    _check(apart, 1, 21, 9)
