@@ -122,6 +122,10 @@ __device__ __forceinline__ void finish16(E* yp, const u32x4 (&yin)[sizeof(E)], c
 // matrix, from before their place (N >= 8: there is a whole chunk); what is not theirs is shifted out and masked when
 // they are used.
 // 1000 tokens on 24 adapters of ranks 4 to 256, N = 4096: 123 us (one token per workgroup, Bt a row per thread) -> 15.
+// bf16: two steps of Bt on their way, as in the tiles of 16 tokens, leave the tiles of 32 registers for three workgroups on a
+// compute unit; a tile is a chain of trips (descriptor, tokens, Bt and y, v, Bt again) of 7 to 15 us, so that what shortens a
+// launch is more of them side by side: lora_delta, two workgroups with four steps / three with two: 997 single tokens on 71
+// adapters of rank 100, 4096 -> 4096, 52.2 / 48.5; 672 on 61 of rank 100, 5120 -> 13824, 37.6 / 34.4; 299 on 114, 80.1 / 76.4.
 template <typename E>
 __device__ __forceinline__ u32x4 own_elements(u32x4 b, uint32_t drop, int keep)
 {
@@ -165,7 +169,7 @@ __device__ __forceinline__ void expand_rows_tile(
     const E* __restrict__ Bt, E* __restrict__ y, int64_t ldy, int N, float beta, bool y_vec, op16* lds)
 {
     constexpr int ES = (int)sizeof(E), EPC = 16 / ES, KSTEP = 4 * EPC, TERMS = ES == 2 ? 3 : 1;
-    constexpr int KS = TB == 1 ? 2 : 4;                      // steps of KSTEP ranks whose loads go out together (as many as registers hold)
+    constexpr int KS = TB == 1 || ES == 2 ? 2 : 4;           // steps of KSTEP ranks whose loads go out together (as many as registers hold)
     constexpr int SUMS = ES == 4 ? 4 / TB : 1;               // (see mma_apart)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
     const int r = t.reserved0, n_end = t.c0 + t.cn, steps = (r + KSTEP - 1) / KSTEP;
@@ -280,7 +284,7 @@ extern __shared__ op16 expand_rows_lds[];
 // TBMAX: token blocks of the plan's largest tile (the kernel's register count is that of its widest case: small batches
 // get more wavefronts onto a compute unit)
 template <typename E, int TBMAX>
-__global__ __launch_bounds__(256, TBMAX == 1 ? 3 : 2) void expand_rows_kernel(
+__global__ __launch_bounds__(256, TBMAX == 1 || sizeof(E) == 2 ? 3 : 2) void expand_rows_kernel(
     const lora_tile* __restrict__ tiles, const int32_t* __restrict__ perm, const float* __restrict__ v, lora_vspec vsp,
     const E* const* __restrict__ Bt_ptrs, E* __restrict__ y, int64_t ldy, int N, float beta, bool y_vec)
 {
