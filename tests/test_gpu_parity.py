@@ -673,11 +673,11 @@ def test_expand_takes_the_general_kernel_where_it_is_faster(T, N, ranks, dtype, 
 
 @pytest.mark.parametrize("T,N,ranks", [
     (960, 4100, (4, 20, 31)), (1040, 4100, (32, 1)), (1100, 4100, (12,)), (2600, 4100, (4, 20)), (2600, 1000, (4, 31)), (2600, 4352, (9, 32, 17)),
-    (1550, 4100, (90, 100)), (3000, 2060, (84, 100)), (3500, 4100, (255, 200))])
+    (1550, 4100, (90, 100)), (3000, 2060, (84, 100)), (3500, 4100, (255, 200)), (750, 4100, (4, 100, 256)), (333, 2060, (12, 131, 7))])
 def test_any_rank_expand_of_one_step(T, N, ranks):
     """Ranks of one MFMA step: about 1000 and 2600 tiles of 16 tokens x 256 features, from where two and four blocks of
     features share a tile, and their remainders (N of 4, 17 and a bit, and 17 blocks); higher ranks of about one length, where two or four
-    blocks make a full round of tiles; against the oracle and, every value,
+    blocks make a full round of tiles; ranks above 128 in tiles of 16 tokens among short ones; against the oracle and, every value,
     against one rounding of the general kernel's sum."""
     w = wl.random_case(1850 + T + N, T, 64, N, 3, ranks, max_seg=90, frac_none=0.1, scales=(0.5, 2.0, -1.0))
     dl = device.to_device(w, DEV, with_w=False)

@@ -629,3 +629,25 @@ def test_tiles_of_the_expand_for_rows_of_any_length(T, n_a, ranks, N, rows, bloc
         assert max(t.nrows for t in tiles) == min(rows, max(lengths))
     assert max(-(-t.cn // 256) for t in tiles) == min(blocks, -(-N // 256))
     p.destroy()
+
+
+@pytest.mark.parametrize("lengths,ranks,N,rows_of_long", [
+    ((190, 180, 200, 180), (4, 100, 12, 256), 4096, 16), ((40, 33, 30, 17, 16, 1), (4, 100, 12, 256, 20, 129), 13824, 16),
+    ((500, 500), (8, 160), 13824, 32), ((300, 300), (256, 200), 8192, 32), ((300, 300), (128, 40), 8192, 32)])
+def test_long_ranks_among_short_ones_have_tiles_of_16_tokens_where_that_ends_earlier(lengths, ranks, N, rows_of_long):
+    """... of the expand for rows of any length: not where the chip holds no more of them, not where all ranks are long; every
+    row and feature of every adapter once."""
+    T, n_a = sum(lengths), len(lengths)
+    p = B.lora_plan(T, np.concatenate([[0], np.cumsum(lengths)]), np.arange(n_a), np.asarray(ranks, np.int32), np.ones(n_a), 512, N, B.LORA_BF16)
+    fn, ptr = B._lib.lora_rows_expand_tiles, ctypes.POINTER(B.Tile)()
+    fn.argtypes, fn.restype = [ctypes.c_void_p, ctypes.c_void_p], ctypes.c_int32
+    tiles = [ptr[i] for i in range(fn(p.handle, ctypes.byref(ptr)))]
+    ends = np.cumsum(lengths)
+    covered = np.zeros((T, -(-N // 256)), np.int32)
+    for t in tiles:
+        lo, hi = ends[t.adapter] - lengths[t.adapter], ends[t.adapter]
+        rows = rows_of_long if ranks[t.adapter] > 128 else 32
+        assert lo <= t.row0 and (t.row0 - lo) % rows == 0 and t.nrows == min(rows, hi - t.row0)
+        covered[t.row0:t.row0 + t.nrows, t.c0 // 256:-(-(t.c0 + t.cn) // 256)] += 1
+    assert tiles and np.all(covered == 1)
+    p.destroy()
