@@ -465,23 +465,27 @@ __device__ __forceinline__ void expand_stream_tile(
     load_b(2, rb1);
     __syncthreads();
     // stage s multiplies from slab buffer s%2; the slab of stage s+1 (in registers since two stages ago)
-    // goes to the other buffer, and the slab of stage s+3 is requested.  Stages past the last one work
-    // on zeros and store nothing.
-    int s = 0;
-    do {
+    // goes to the other buffer, and the slab of stage s+3 is requested.  Four stages a round without a branch, then those that
+    // are left: a branch between the stages of the loop, were it only the one that leaves it, makes all of them 4 % slower.
 #define EXPAND_STAGE(BUF_, S_, YR_, RB_)                 \
         stage(BUF_, S_, YR_);                            \
         __builtin_amdgcn_sched_barrier(0);               \
         store_b(1 - BUF_, RB_);                          \
         load_b((S_) + 3, RB_);                           \
         __syncthreads();
+    int s = 0;
+    for (; s + 4 <= n_stages; s += 4) {
         EXPAND_STAGE(0, s, yr0, rb0)
         EXPAND_STAGE(1, s + 1, yr1, rb1)
         EXPAND_STAGE(0, s + 2, yr2, rb0)
         EXPAND_STAGE(1, s + 3, yr3, rb1)
+    }
+    if (s >= n_stages) return;
+    EXPAND_STAGE(0, s, yr0, rb0)
+    if (s + 1 >= n_stages) return;
+    EXPAND_STAGE(1, s + 1, yr1, rb1)
+    if (s + 2 < n_stages) stage(0, s + 2, yr2);
 #undef EXPAND_STAGE
-        s += 4;
-    } while (s < n_stages);
 }
 
 extern __shared__ uint4 expand_stream_lds[];

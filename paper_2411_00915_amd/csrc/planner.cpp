@@ -218,6 +218,105 @@ static bool choose_rows_shrink(lora_plan* p, int32_t max_rank)
     return rows;
 }
 
+// Tiles of the streaming expand from its token tiles: `stages` stages of features each, or, with stages = 0, as many as end the
+// launch earliest.  A compute unit has one tile at a time, and a tile takes about as long for few tokens as for many, for short
+// ranks as for long (few tokens take more features a stage, and short ranks too): microseconds by time stamps in a launch of 992
+// tiles, 3.3, 4.6 and 5.5 until the first stage with ranks up to 32, 64 and 128, and 1.1 to 1.4 a stage.  What a launch loses is its
+// last round: that one took 114 where its tiles took 90 for each compute unit.  So the feature ranges are as long as some number of
+// rounds of the 256 compute units makes them, the one that ends first with the longest tiles first, and half of the longest
+// tile is counted for what tiles of one model differ by.  lora_delta, 16 stages, halved down to four while there were fewer than
+// 512 tiles / so: 8192 mixed tokens on 128 adapters, 4096 -> 11008, 139.9 / 131.7 us; 4671 on 3 of rank 64, 11008 -> 4096, 64.6 /
+// 55.9; 1732 on 23 of rank 16, 4840 -> 4304, 22.0 / 19.4; 468 on 3, 4096 -> 4096, 13.4 / 10.7; 329 on 4, 5120 -> 5120, 15.5 / 11.8;
+// 40 drawn calls 1.07 times as fast, the slowest 0.995.  (Without that half, 3 % slower for the first of these.)
+static void deal_expand_features(lora_plan* p, const std::vector<lora_tile>& blocks, int32_t stages)
+{
+    constexpr int64_t kComputeUnits = 256;
+    auto features = [](const lora_tile& t) { return 64 * lora_shape_jb(t.shape); };          // of a stage
+    auto all_stages = [&](const lora_tile& t) { return (p->N + features(t) - 1) / features(t); };
+    // tile i of n: an equal share of the stages
+    auto share = [&](const lora_tile& t, int32_t longest) {
+        const int32_t all = all_stages(t), n = (all + longest - 1) / longest;
+        return (all + n - 1) / n;
+    };
+    auto nanoseconds = [](const lora_tile& t, int32_t n) {
+        return t.reserved0 <= 32 ? 3300 + 1130 * (int64_t)n : t.reserved0 <= 64 ? 4600 + 1360 * (int64_t)n : 5500 + 1330 * (int64_t)n;
+    };
+    int32_t longest = stages;
+    if (stages == 0) {
+        struct kind { int64_t ns, tiles; };
+        std::vector<kind> runs;
+        int32_t most = 1, tried = 0;
+        for (const lora_tile& t : blocks) most = std::max(most, all_stages(t));
+        int64_t best = 0;
+        for (int64_t rounds = 1; rounds <= 6; ++rounds) {
+            if ((int64_t)blocks.size() > rounds * kComputeUnits && rounds < 6) continue;
+            int32_t lo = 1, hi = most;                       // the shortest ranges that make no more tiles than that
+            while (lo < hi) {
+                const int32_t mid = (lo + hi) / 2;
+                int64_t n = 0;
+                for (const lora_tile& t : blocks) n += (all_stages(t) + mid - 1) / mid;
+                if (n <= rounds * kComputeUnits) hi = mid;
+                else lo = mid + 1;
+            }
+            if (lo == tried) break;
+            tried = lo;
+            runs.clear();
+            int64_t tiles = 0, sum = 0;
+            for (const lora_tile& t : blocks) {
+                const int32_t all = all_stages(t), per = share(t, lo), n = (all + per - 1) / per;
+                if (n > 1) runs.push_back({nanoseconds(t, per), n - 1});
+                runs.push_back({nanoseconds(t, all - (n - 1) * per), 1});
+                tiles += n;
+                sum += (n - 1) * nanoseconds(t, per) + runs.back().ns;
+            }
+            std::sort(runs.begin(), runs.end(), [](const kind& x, const kind& y) { return x.ns > y.ns; });
+            int64_t end = runs[0].ns;
+            if (tiles > 2 * kComputeUnits) {
+                end = std::max(end, sum / kComputeUnits + runs.back().ns / 2);
+            } else if (tiles > kComputeUnits) {              // the second round's longest behind the first's shortest
+                size_t i = 0, j;
+                int64_t first = kComputeUnits;               // tiles of runs 0..i that are left of the first round
+                while (runs[i].tiles < first) first -= runs[i++].tiles;
+                j = i;
+                int64_t second = runs[i].tiles - first, left = tiles - kComputeUnits;
+                while (left > 0) {
+                    if (second == 0) second = runs[++j].tiles;
+                    if (first == 0) first = runs[--i].tiles;
+                    end = std::max(end, runs[i].ns + runs[j].ns);
+                    const int64_t n = std::min({first, second, left});
+                    first -= n;
+                    second -= n;
+                    left -= n;
+                }
+            }
+            end += runs[0].ns / 2;
+            if (best != 0 && end >= best) break;
+            best = end;
+            longest = lo;
+        }
+    }
+    // (a block's tiles are all as long, the last one aside: sorted by blocks)
+    struct run { int64_t ns; int32_t block, first, end, per; };
+    std::vector<run> runs;
+    for (int32_t i = 0; i < (int32_t)blocks.size(); ++i) {
+        const int32_t all = all_stages(blocks[i]), per = stages ? stages : share(blocks[i], longest), whole = all / per * per;
+        if (stages || whole == all) {
+            runs.push_back({nanoseconds(blocks[i], per), i, 0, all, per});
+        } else {
+            if (whole > 0) runs.push_back({nanoseconds(blocks[i], per), i, 0, whole, per});
+            runs.push_back({nanoseconds(blocks[i], all - whole), i, whole, all, per});
+        }
+    }
+    if (stages == 0) std::stable_sort(runs.begin(), runs.end(), [](const run& x, const run& y) { return x.ns > y.ns; });
+    for (const run& r : runs)
+        for (int32_t st = r.first; st < r.end; st += r.per) {
+            lora_tile t = blocks[r.block];
+            t.c0 = st * features(t);
+            t.cn = std::min<int32_t>(r.per * features(t), p->N - t.c0);
+            p->expand_tiles.push_back(t);
+        }
+}
+
 // Tile lists of the tiled (MFMA) family.  A shrink tile is 16*TB tokens of one
 // adapter times 16*JB of its rank indices over the whole K range (the
 // workgroup's wavefronts split K).  An expand tile is 16*TB tokens times a range
@@ -276,6 +375,7 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
         const int64_t n_tt = token_tiles(expand_tokens);
         while (expand_stages > 4 && n_tt * ((p->N + expand_stages * 64 - 1) / (expand_stages * 64)) < 512) expand_stages /= 2;
     }
+    std::vector<lora_tile> expand_blocks;                    // streaming expand: token tiles, features not yet dealt out
     for (int g = 0; g < G; ++g) {
         const int32_t a = p->group_adapter[g];
         const int32_t r = p->rank[a];
@@ -338,19 +438,15 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
                 const int nblk = (nrows + 15) / 16;
                 const int nb = nblk > 4 ? 8 : (nblk > 2 ? 4 : (nblk > 1 ? 2 : 1));
                 const int fw = std::min(8 / nb, fw_max);
-                const int32_t n_tile = expand_stages * 64 * fw;
-                for (int32_t n0 = 0; n0 < p->N; n0 += n_tile) {
-                    lora_tile t{};
-                    t.adapter = a; t.row0 = row; t.nrows = nrows;
-                    t.c0 = n0; t.cn = std::min<int32_t>(n_tile, p->N - n0);
-                    t.shape = lora_shape_code(nb, fw);
-                    t.reserved0 = r;
-                    t.reserved1 = g;
-                    p->expand_small = false;
-                    p->expand_stream_ks = std::max(p->expand_stream_ks, ks);
-                    p->expand_stream_lds = std::max(p->expand_stream_lds, fw * ks * 4 * 2048 + 8 * 16 * 68 * 4);
-                    p->expand_tiles.push_back(t);
-                }
+                lora_tile t{};
+                t.adapter = a; t.row0 = row; t.nrows = nrows;
+                t.shape = lora_shape_code(nb, fw);
+                t.reserved0 = r;
+                t.reserved1 = g;
+                p->expand_small = false;
+                p->expand_stream_ks = std::max(p->expand_stream_ks, ks);
+                p->expand_stream_lds = std::max(p->expand_stream_lds, fw * ks * 4 * 2048 + 8 * 16 * 68 * 4);
+                expand_blocks.push_back(t);
             }
         } else
         // ---- expand ----
@@ -382,6 +478,8 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
             }
         }
     }
+    const bool expand_by_rounds = p->expand_stream && tu.expand_stream_stages == kDefaultTuning.expand_stream_stages;
+    if (p->expand_stream) deal_expand_features(p, expand_blocks, expand_by_rounds ? 0 : expand_stages);
     // wavefronts per shrink workgroup: they split K in steps of 32; the LDS
     // reduction buffer (1 KB per wavefront and 16x16 block) stays within 64 KB
     const int steps = (p->K + 31) / 32;
@@ -476,7 +574,7 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
     std::stable_sort(p->shrink_tiles.begin(), p->shrink_tiles.end(),
                      [&](const lora_tile& x, const lora_tile& y) { return weight(x) > weight(y); });
     // (the streaming expand's tiles differ in size by up to 8x: the same for them)
-    if (p->expand_stream) {
+    if (p->expand_stream && !expand_by_rounds) {
         std::stable_sort(p->expand_tiles.begin(), p->expand_tiles.end(),
                          [&](const lora_tile& x, const lora_tile& y) { return weight(x) > weight(y); });
         // Workgroups start in index order, one per compute unit at a time.  With equal tiles a launch of 3.3

@@ -697,6 +697,34 @@ def test_any_rank_expand_of_one_step(T, N, ranks):
     assert np.all(np.abs(out[0] - out[1]) <= 2.0 ** -7 * np.abs(out[1]) + 1e-4)
 
 
+@pytest.mark.parametrize("T,N,ranks,max_seg", [
+    (300, 4104, (16, 64), 150), (500, 4104, (128,), 500), (600, 8200, (24, 128), 200), (900, 8200, (64, 8), 400),
+    (1300, 8200, (16, 64, 128), 300), (1500, 9000, (64,), 700), (700, 13832, (128,), 700)])
+def test_streaming_expand_of_one_to_eight_stages(T, N, ranks, max_seg):
+    """Tiles whose feature ranges the planner makes as long as the rounds of the compute units ask for: one to eight stages (whole
+    rounds of four and what is left of them), one to eight 64-feature chunks a stage, remainders of tokens and features; every
+    K part count of v that comes with them; beta 0 and 1; nothing written between the rows of y."""
+    w = wl.random_case(2500 + T + N, T, 1024, N, 4, ranks, max_seg=max_seg, frac_none=0.1, scales=(0.5, 2.0, -1.0))
+    dl = device.to_device(w, DEV, with_w=False)
+    tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
+    ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
+    plan = device.make_plan(w)
+    v = torch.zeros(B.lora_plan_query(plan)[1] // 4, dtype=torch.float32, device=DEV)
+    y0 = torch.from_numpy(_y_in(w)).to(DEV, torch.bfloat16)
+    ref = oracle.expand(w.x, tok, ad, N)
+    has = torch.from_numpy(np.where(tok >= 0, w.adapter_rank[np.clip(tok, 0, None)], 0) > 0)
+    for beta in (1.0, 0.0):
+        y = torch.full((T, N + 8), 9.0, dtype=torch.bfloat16, device=DEV)
+        y[:, :N] = y0
+        names = _launched(lambda: B.lora_delta(plan, dl.x, w.K, dl.At_ptrs, dl.Bt_ptrs, v, y, N + 8, beta))
+        assert "expand_stream_kernel" in names, names
+        got = _to_np(y)
+        want = ref + _to_np(y0).astype(np.float64) * beta
+        _assert_close(got[has.numpy()][:, :N], want[has.numpy()], BF16_TOL, f"delta, beta {beta}")
+        assert np.array_equal(got[~has.numpy()][:, :N], _to_np(y0)[~has.numpy()]) and np.all(got[:, N:] == 9.0)
+    plan.destroy()
+
+
 def _one_adapter_plan(T, K, N, rank, variant=B.LORA_VARIANT_TILED):
     return B.lora_plan(T, np.array([0, T], np.int32), np.array([0], np.int32), np.array([rank], np.int32), np.array([1.0], np.float32),
                        K, N, B.LORA_BF16, variant)

@@ -651,3 +651,28 @@ def test_long_ranks_among_short_ones_have_tiles_of_16_tokens_where_that_ends_ear
         covered[t.row0:t.row0 + t.nrows, t.c0 // 256:-(-(t.c0 + t.cn) // 256)] += 1
     assert tiles and np.all(covered == 1)
     p.destroy()
+
+
+@pytest.mark.parametrize("T,N,ranks,max_seg", [(300, 4104, (16, 64), 150), (1300, 8200, (16, 64, 128), 300), (1500, 9000, (64,), 700),
+                                               (8192, 11008, (64, 8, 128, 16, 32), 100), (40000, 1032, (64, 16), 300)])
+def test_feature_ranges_of_the_streaming_expand(T, N, ranks, max_seg):
+    """Every feature of every token tile once, in equal shares of its stages, the longest tiles first."""
+    rng = np.random.default_rng(T + N)
+    lengths = []
+    while sum(lengths) < T:
+        lengths.append(min(T - sum(lengths), int(rng.integers(1, max_seg + 1))))
+    rank = np.asarray([ranks[a % len(ranks)] for a in range(24)], np.int32)
+    p = B.lora_plan(T, np.concatenate([[0], np.cumsum(lengths)]), rng.integers(0, 24, len(lengths)), rank, np.ones(24), 1024, N, B.LORA_BF16)
+    tiles = B.lora_plan_export(p)["expand_tiles"]
+    stages, blocks = [], {}
+    for adapter, row0, nrows, c0, cn, shape, r, _ in tiles.tolist():
+        width = 64 * (shape >> 4 & 15)
+        assert c0 % width == 0 and (cn % width == 0 or c0 + cn == N)
+        stages.append((3300 + 1130 * -(-cn // width), 4600 + 1360 * -(-cn // width), 5500 + 1330 * -(-cn // width))[0 if r <= 32 else 1 if r <= 64 else 2])
+        blocks.setdefault((adapter, row0, nrows, width), []).append((c0, cn))
+    assert stages == sorted(stages, reverse=True)
+    for (_, _, _, width), ranges in blocks.items():
+        ranges.sort()
+        assert ranges[0][0] == 0 and ranges[-1][0] + ranges[-1][1] == N
+        assert all(a + n == b for (a, n), (b, _) in zip(ranges, ranges[1:])) and len({n for _, n in ranges[:-1]}) <= 1
+    p.destroy()
