@@ -409,7 +409,8 @@ const char* lora_status_str(lora_status s);
  * many; with LORA_VARIANT_AUTO and neither of these two given another value than its
  * default, batches that make few streaming tiles run a shrink that splits K over
  * the wavefronts of a workgroup instead), expand_stream_stages (stages of 64
- * features per wavefront that one workgroup of the streaming expand walks).
+ * features per wavefront that one workgroup of the streaming expand walks; with
+ * the default value the planner chooses the ranges by rounds of the compute units).
  * Entries <= 0 keep the current value; plans made
  * earlier are unaffected.  Host only, thread-safe.
  */

@@ -290,7 +290,10 @@ static void deal_expand_features(lora_plan* p, const std::vector<lora_tile>& blo
                 }
             }
             end += runs[0].ns / 2;
-            if (best != 0 && end >= best) break;
+            // (not at the first that ends later: 113.6, 113.7, 110.8 and 108.2 us for two to five rounds of the 8192 tokens above, and
+            // with two of them 141 us where it takes 134 with five)
+            if (best != 0 && 20 * end >= 21 * best) break;
+            if (best != 0 && end >= best) continue;
             best = end;
             longest = lo;
         }
@@ -359,8 +362,9 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
         for (int g = 0; g < G; ++g) n128 += (p->group_offset[g + 1] - p->group_offset[g] + 127) / 128;
         if (n128 * 4 < tu.shrink_stream_wgs) stream_tokens = 64;
     }
-    // streaming expand: feature range per workgroup, in stages; halved while the launch would have
-    // fewer than two workgroups per CU (but at least 4 stages: the start-up of a tile has to pay off)
+    // streaming expand: feature range per workgroup, in stages, where the caller gave one (another than the default, or in the
+    // shape table); halved while the launch would have fewer than two workgroups per CU (but at least 4 stages: the start-up
+    // of a tile has to pay off).  Otherwise it only decides the token tiles here, and deal_expand_features the ranges.
     int32_t expand_stages = std::max(1, tu.expand_stream_stages);
     // (its token tiles: 128 tokens -- every token tile of an adapter fetches Bt_a again, and the launch has feature
     // ranges to make workgroups of -- unless that leaves fewer than two rounds of tiles)
@@ -687,7 +691,7 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     if (per == 0) per = one_step || token_tiles(16) * blocks <= 512 ? 16 : 32;
     const int64_t tiles = token_tiles(per) * blocks;
     int64_t wide = one_step ? (tiles < 1024 ? 1 : tiles < 2560 ? 2 : 4) : tiles / 1024;
-    // Higher ranks, all about as long: the chip holds 512 tiles, so two or four blocks a tile where that makes one full round of
+    // Higher ranks, all about as long: 512 tiles are two on each compute unit, so two or four blocks a tile where that makes one full round of
     // two or four.  lora_delta: 3683 tokens of rank 256, 512 -> 4096 (1840 tiles of one block), 83.0 -> 64.7 us; 1388 of rank 36,
     // 4096 -> 11008, 40.9 -> 33.1; 199 batches of such tiles 1.11 times as fast, the slowest 0.99.  (With ranks of 4 to 256 in
     // one batch the rounds are not full: 0.94 on average.)  With fewer than eight tokens a tile Bt alone is what it reads, and
