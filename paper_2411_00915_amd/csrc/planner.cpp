@@ -218,24 +218,52 @@ static bool choose_rows_shrink(lora_plan* p, int32_t max_rank)
     return rows;
 }
 
+// When a launch ends whose tiles, `count` times `ns` each, longest first, are taken by 256 compute units as these get free
+struct equal_tiles { int64_t ns, count; };
+static int64_t list_schedule_end(const std::vector<equal_tiles>& longest_first)
+{
+    typedef std::pair<int64_t, int64_t> units;               // free from then on, how many
+    std::vector<units> heap{{0, 256}};
+    const std::greater<units> later;
+    int64_t end = 0;
+    for (const equal_tiles& t : longest_first)
+        for (int64_t left = t.count; left > 0;) {
+            std::pop_heap(heap.begin(), heap.end(), later);
+            units& u = heap.back();
+            const int64_t take = std::min(u.second, left);
+            const units busy{u.first + t.ns, take};
+            left -= take;
+            if ((u.second -= take) == 0) heap.pop_back();
+            else std::push_heap(heap.begin(), heap.end(), later);
+            heap.push_back(busy);
+            std::push_heap(heap.begin(), heap.end(), later);
+            end = std::max(end, busy.first);
+        }
+    return end;
+}
+
 // Tiles of the streaming expand from its token tiles: `stages` stages of features each, or, with stages = 0, as many as end the
 // launch earliest.  A compute unit has one tile at a time, and a tile takes about as long for few tokens as for many, for short
 // ranks as for long (few tokens take more features a stage, and short ranks too): microseconds by time stamps in a launch of 992
 // tiles, 3.3, 4.6 and 5.5 until the first stage with ranks up to 32, 64 and 128, and 1.1 to 1.4 a stage.  What a launch loses is its
 // last round: that one took 114 where its tiles took 90 for each compute unit.  So the feature ranges are as long as some number of
 // rounds of the 256 compute units makes them, the one that ends first with the longest tiles first, and half of the longest
-// tile is counted for what tiles of one model differ by.  lora_delta, 16 stages, halved down to four while there were fewer than
-// 512 tiles / so: 8192 mixed tokens on 128 adapters, 4096 -> 11008, 139.9 / 131.7 us; 4671 on 3 of rank 64, 11008 -> 4096, 64.6 /
-// 55.9; 1732 on 23 of rank 16, 4840 -> 4304, 22.0 / 19.4; 468 on 3, 4096 -> 4096, 13.4 / 10.7; 329 on 4, 5120 -> 5120, 15.5 / 11.8;
-// 40 drawn calls 1.07 times as fast, the slowest 0.995.  (Without that half, 3 % slower for the first of these.)
+// tile is counted for what tiles of one model differ by.  A launch of many rounds takes no less than memory does, y
+// and each adapter's Bt once at 5 TB/s: up to there shorter tiles, whose starts then are hidden, cost nothing.
+// lora_delta, 16 stages, halved down to four while there were fewer than
+// 512 tiles / so: 8192 mixed tokens on 128 adapters, 4096 -> 11008, 136.6 / 132.2 us; 4671 on 3 of rank 64, 11008 -> 4096, 64.6 /
+// 55.9; 1732 on 23 of rank 16, 4840 -> 4304, 22.0 / 19.4; 468 on 3, 4096 -> 4096, 13.4 / 10.7; 49608 on 412 of rank 64, 1024 -> 11008,
+// 532 / 509 (604 with y uncut, 414 tiles, which end a second round with 158); 70000 on 40 of rank 128, 1024 -> 4096, 300 / 300 (uncut
+// 395).  200 drawn calls of 128 to 70000 tokens 1.07 times as fast, seven below 0.95 (36287 on 2 of rank 64, 1024 -> 4096, 141 / 155:
+// the estimate takes 13 stages, 8 are the best).  (Without that half, 3 % slower for the first of these.)
 static void deal_expand_features(lora_plan* p, const std::vector<lora_tile>& blocks, int32_t stages)
 {
     constexpr int64_t kComputeUnits = 256;
     auto features = [](const lora_tile& t) { return 64 * lora_shape_jb(t.shape); };          // of a stage
     auto all_stages = [&](const lora_tile& t) { return (p->N + features(t) - 1) / features(t); };
-    // tile i of n: an equal share of the stages
-    auto share = [&](const lora_tile& t, int32_t longest) {
-        const int32_t all = all_stages(t), n = (all + longest - 1) / longest;
+    // stages of a tile: an equal share
+    auto share = [](int32_t all, int32_t longest) {
+        const int32_t n = (all + longest - 1) / longest;
         return (all + n - 1) / n;
     };
     auto nanoseconds = [](const lora_tile& t, int32_t n) {
@@ -243,56 +271,54 @@ static void deal_expand_features(lora_plan* p, const std::vector<lora_tile>& blo
     };
     int32_t longest = stages;
     if (stages == 0) {
-        struct kind { int64_t ns, tiles; };
-        std::vector<kind> runs;
-        int32_t most = 1, tried = 0;
-        for (const lora_tile& t : blocks) most = std::max(most, all_stages(t));
+        // token tiles of a kind have the same stages and take the same time: three lengths of rank, one to eight chunks a stage
+        struct kind { const lora_tile* tile; int32_t all; int64_t count; };
+        kind kinds[3][9] = {};
+        std::vector<kind> in_use;
+        int32_t most = 1;
+        int64_t moved = 0;                                   // values of each feature: of y, read and written, and of Bt, once
+        int32_t group = -1;
+        for (const lora_tile& t : blocks) {
+            kind& k = kinds[t.reserved0 <= 32 ? 0 : t.reserved0 <= 64 ? 1 : 2][lora_shape_jb(t.shape)];
+            if (k.count++ == 0) k = kind{&t, all_stages(t), 1};
+            moved += 2 * (int64_t)t.nrows + (t.reserved1 != group ? t.reserved0 : 0);
+            group = t.reserved1;
+        }
+        for (const auto& of_rank : kinds)
+            for (const kind& k : of_rank)
+                if (k.count) {
+                    in_use.push_back(k);
+                    most = std::max(most, k.all);
+                }
+        const int64_t at_least = moved * 2 * p->N / 5000;
+        auto tiles_of = [&](int32_t n) {
+            int64_t tiles = 0;
+            for (const kind& k : in_use) tiles += k.count * ((k.all + n - 1) / n);
+            return tiles;
+        };
+        std::vector<equal_tiles> runs;
         int64_t best = 0;
-        for (int64_t rounds = 1; rounds <= 6; ++rounds) {
-            if ((int64_t)blocks.size() > rounds * kComputeUnits && rounds < 6) continue;
+        int32_t tried = 0;
+        for (int64_t rounds = std::max<int64_t>(1, ((int64_t)blocks.size() + kComputeUnits - 1) / kComputeUnits); tried != 1; rounds += std::max<int64_t>(1, rounds / 4)) {
             int32_t lo = 1, hi = most;                       // the shortest ranges that make no more tiles than that
             while (lo < hi) {
                 const int32_t mid = (lo + hi) / 2;
-                int64_t n = 0;
-                for (const lora_tile& t : blocks) n += (all_stages(t) + mid - 1) / mid;
-                if (n <= rounds * kComputeUnits) hi = mid;
+                if (tiles_of(mid) <= rounds * kComputeUnits) hi = mid;
                 else lo = mid + 1;
             }
-            if (lo == tried) break;
+            if (lo == tried) continue;                       // (more rounds may still make shorter ones)
             tried = lo;
             runs.clear();
-            int64_t tiles = 0, sum = 0;
-            for (const lora_tile& t : blocks) {
-                const int32_t all = all_stages(t), per = share(t, lo), n = (all + per - 1) / per;
-                if (n > 1) runs.push_back({nanoseconds(t, per), n - 1});
-                runs.push_back({nanoseconds(t, all - (n - 1) * per), 1});
-                tiles += n;
-                sum += (n - 1) * nanoseconds(t, per) + runs.back().ns;
+            int64_t sum = 0;
+            for (const kind& k : in_use) {
+                const int32_t per = share(k.all, lo), n = (k.all + per - 1) / per;
+                if (n > 1) runs.push_back({nanoseconds(*k.tile, per), (n - 1) * k.count});
+                runs.push_back({nanoseconds(*k.tile, k.all - (n - 1) * per), k.count});
+                sum += k.count * ((n - 1) * nanoseconds(*k.tile, per) + runs.back().ns);
             }
-            std::sort(runs.begin(), runs.end(), [](const kind& x, const kind& y) { return x.ns > y.ns; });
-            int64_t end = runs[0].ns;
-            if (tiles > 2 * kComputeUnits) {
-                end = std::max(end, sum / kComputeUnits + runs.back().ns / 2);
-            } else if (tiles > kComputeUnits) {              // the second round's longest behind the first's shortest
-                size_t i = 0, j;
-                int64_t first = kComputeUnits;               // tiles of runs 0..i that are left of the first round
-                while (runs[i].tiles < first) first -= runs[i++].tiles;
-                j = i;
-                int64_t second = runs[i].tiles - first, left = tiles - kComputeUnits;
-                while (left > 0) {
-                    if (second == 0) second = runs[++j].tiles;
-                    if (first == 0) first = runs[--i].tiles;
-                    end = std::max(end, runs[i].ns + runs[j].ns);
-                    const int64_t n = std::min({first, second, left});
-                    first -= n;
-                    second -= n;
-                    left -= n;
-                }
-            }
-            end += runs[0].ns / 2;
-            // (not at the first that ends later: 113.6, 113.7, 110.8 and 108.2 us for two to five rounds of the 8192 tokens above, and
-            // with two of them 141 us where it takes 134 with five)
-            if (best != 0 && 20 * end >= 21 * best) break;
+            if (best != 0 && sum / kComputeUnits >= best) break;         // and more tiles are more in all
+            std::sort(runs.begin(), runs.end(), [](const equal_tiles& x, const equal_tiles& y) { return x.ns > y.ns; });
+            const int64_t end = std::max(list_schedule_end(runs), at_least) + runs[0].ns / 2;
             if (best != 0 && end >= best) continue;
             best = end;
             longest = lo;
@@ -302,7 +328,7 @@ static void deal_expand_features(lora_plan* p, const std::vector<lora_tile>& blo
     struct run { int64_t ns; int32_t block, first, end, per; };
     std::vector<run> runs;
     for (int32_t i = 0; i < (int32_t)blocks.size(); ++i) {
-        const int32_t all = all_stages(blocks[i]), per = stages ? stages : share(blocks[i], longest), whole = all / per * per;
+        const int32_t all = all_stages(blocks[i]), per = stages ? stages : share(all, longest), whole = all / per * per;
         if (stages || whole == all) {
             runs.push_back({nanoseconds(blocks[i], per), i, 0, all, per});
         } else {
