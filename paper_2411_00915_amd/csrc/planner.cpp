@@ -341,7 +341,7 @@ static void deal_expand_features(lora_plan* p, const std::vector<lora_tile>& blo
         for (int32_t st = r.first; st < r.end; st += r.per) {
             lora_tile t = blocks[r.block];
             t.c0 = st * features(t);
-            t.cn = std::min<int32_t>(r.per * features(t), p->N - t.c0);
+            t.cn = (int32_t)std::min<int64_t>((int64_t)r.per * features(t), p->N - t.c0);
             p->expand_tiles.push_back(t);
         }
 }
@@ -401,9 +401,10 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
             for (int g = 0; g < G; ++g) n += (p->group_offset[g + 1] - p->group_offset[g] + per - 1) / per;
             return n;
         };
-        if (token_tiles(128) * ((p->N + expand_stages * 64 - 1) / (expand_stages * 64)) < 512) expand_tokens = stream_tokens;
+        auto ranges = [&](int64_t features) { return (p->N + features - 1) / features; };   // (given stages may be more than 32 bits of features)
+        if (token_tiles(128) * ranges((int64_t)expand_stages * 64) < 512) expand_tokens = stream_tokens;
         const int64_t n_tt = token_tiles(expand_tokens);
-        while (expand_stages > 4 && n_tt * ((p->N + expand_stages * 64 - 1) / (expand_stages * 64)) < 512) expand_stages /= 2;
+        while (expand_stages > 4 && n_tt * ranges((int64_t)expand_stages * 64) < 512) expand_stages /= 2;
     }
     std::vector<lora_tile> expand_blocks;                    // streaming expand: token tiles, features not yet dealt out
     for (int g = 0; g < G; ++g) {

@@ -729,3 +729,17 @@ def test_feature_ranges_of_the_streaming_expand_end_the_launch_soon(T, adapters,
                 counts[ns(r, stages % share)] += n
         best = min(best or 1e18, estimate(counts))
     assert estimate(chosen) <= 1.02 * best, (estimate(chosen), best)
+
+
+@pytest.mark.parametrize("stages", [1 << 25, 1 << 26, 1 << 29])
+@pytest.mark.parametrize("T,adapters,N", [(3000, 1, 4096), (66000, 4, 4096), (1100, 8, 1000)])
+def test_given_expand_stages_beyond_any_row(stages, T, adapters, N):
+    """Stages whose features are past 32 bits: the tiles of a length that is past every row, too, but small."""
+    lengths = np.full(adapters, T // adapters) + (np.arange(adapters) < T % adapters)
+    tables = (T, np.concatenate([[0], np.cumsum(lengths)]), np.arange(adapters), np.full(adapters, 64, np.int32), np.ones(adapters), 1024, N, B.LORA_BF16)
+    tiles = []
+    for given in (stages, 1 << 16):
+        p = B.lora_plan(*tables, tuning=dict(expand_stream_stages=given))
+        tiles.append(B.lora_plan_export(p)["expand_tiles"])
+        p.destroy()
+    assert np.array_equal(*tiles) and int(tiles[0][:, 4].min()) > 0
