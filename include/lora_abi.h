@@ -100,6 +100,7 @@ extern "C" {
 
 #define LORA_MAX_RANK 256
 #define LORA_TUNING_COUNT 17     /* number of planner tunables, see lora_tuning_set */
+#define LORA_EXPAND_BY_ROUNDS (1 << 30)   /* expand_stream_stages: not a length, the planner chooses the feature ranges */
 
 typedef enum {
     LORA_OK = 0,
@@ -409,8 +410,9 @@ const char* lora_status_str(lora_status s);
  * many; with LORA_VARIANT_AUTO and neither of these two given another value than its
  * default, batches that make few streaming tiles run a shrink that splits K over
  * the wavefronts of a workgroup instead), expand_stream_stages (stages of 64
- * features per wavefront that one workgroup of the streaming expand walks; with
- * the default value the planner chooses the ranges by rounds of the compute units).
+ * features per wavefront that one workgroup of the streaming expand walks, fewer
+ * where that leaves the launch few workgroups; LORA_EXPAND_BY_ROUNDS or more, the
+ * default: the planner chooses the ranges by rounds of the compute units).
  * Entries <= 0 keep the current value; plans made
  * earlier are unaffected.  Host only, thread-safe.
  */

@@ -39,7 +39,7 @@ DECODE_GRID = {"shrink_target_wgs": [384, 768, 1152, 1536], "expand_wave_bytes":
 # prefill-sized classes (some adapter group of 64 tokens or more)
 PREFILL_TOKENS = [1024, 2048, 4096, 8192, 16384]
 PREFILL_RANKS = [16, 64, 128]
-PREFILL_GRID = {"shrink_stream_wgs": [256, 512, 1024, 2048], "expand_stream_stages": [4, 8, 16, 32]}
+PREFILL_GRID = {"shrink_stream_wgs": [256, 512, 1024, 2048], "expand_stream_stages": [4, 8, 16, 32, 1 << 30]}   # 2^30: by rounds
 
 
 class Case:

@@ -38,6 +38,7 @@ LORA_F32, LORA_BF16 = 0, 1
 LORA_VARIANT_AUTO, LORA_VARIANT_GENERAL, LORA_VARIANT_TILED = 0, 1, 2
 LORA_MAX_RANK = 256
 LORA_TUNING_COUNT = 17
+LORA_EXPAND_BY_ROUNDS = 1 << 30
 LORA_STATIC_V_BYTES = 16 << 20
 LORA_STATIC_MAX_GROUPS = 4096
 

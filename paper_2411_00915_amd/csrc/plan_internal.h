@@ -35,7 +35,7 @@ struct lora_tuning {
     int32_t shrink_tb4_min_rows;   // groups with at least this many tokens use 64-token shrink tiles
     int32_t shrink_stream_min_tokens;  // batches with at least this many adapter tokens use the streaming shrink
     int32_t shrink_stream_wgs;     // streaming shrink: 64-token tiles when 128-token tiles give fewer workgroups than this
-    int32_t expand_stream_stages;  // streaming expand: stages (of 64 features per wavefront) one workgroup walks; default: by rounds
+    int32_t expand_stream_stages;  // streaming expand: stages (of 64 features per wavefront) one workgroup walks, or LORA_EXPAND_BY_ROUNDS
 };
 static_assert(sizeof(lora_tuning) == LORA_TUNING_COUNT * sizeof(int32_t), "lora_tuning and LORA_TUNING_COUNT disagree");
 

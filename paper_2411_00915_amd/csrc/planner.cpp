@@ -35,7 +35,7 @@ constexpr lora_tuning kDefaultTuning = {
     /*shrink_tb4_min_rows*/ 64,
     /*shrink_stream_min_tokens*/ 1024,
     /*shrink_stream_wgs*/ 512,
-    /*expand_stream_stages*/ 16,
+    /*expand_stream_stages*/ LORA_EXPAND_BY_ROUNDS,
 };
 lora_tuning g_lora_tuning = kDefaultTuning;
 
@@ -388,12 +388,14 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
         for (int g = 0; g < G; ++g) n128 += (p->group_offset[g + 1] - p->group_offset[g] + 127) / 128;
         if (n128 * 4 < tu.shrink_stream_wgs) stream_tokens = 64;
     }
-    // streaming expand: feature range per workgroup, in stages, where the caller gave one (another than the default, or in the
-    // shape table); halved while the launch would have fewer than two workgroups per CU (but at least 4 stages: the start-up
-    // of a tile has to pay off).  Otherwise it only decides the token tiles here, and deal_expand_features the ranges.
-    int32_t expand_stages = std::max(1, tu.expand_stream_stages);
+    // streaming expand: feature range per workgroup, in stages, where the caller or the shape table gives one; halved while the
+    // launch would have fewer than two workgroups per CU (but at least 4 stages: the start-up of a tile has to pay off).
+    // Otherwise deal_expand_features chooses the ranges.
+    const bool expand_by_rounds = tu.expand_stream_stages >= LORA_EXPAND_BY_ROUNDS;
+    int32_t expand_stages = expand_by_rounds ? 16 : std::max(1, tu.expand_stream_stages);
     // (its token tiles: 128 tokens -- every token tile of an adapter fetches Bt_a again, and the launch has feature
-    // ranges to make workgroups of -- unless that leaves fewer than two rounds of tiles)
+    // ranges to make workgroups of -- unless that leaves fewer than two rounds of tiles, counted with ranges of 16 stages
+    // where they are not chosen yet)
     int32_t expand_tokens = 128;
     if (p->expand_stream) {
         auto token_tiles = [&](int32_t per) {
@@ -509,7 +511,6 @@ static void build_tiles(lora_plan* p, bool shrink_only = false)
             }
         }
     }
-    const bool expand_by_rounds = p->expand_stream && tu.expand_stream_stages == kDefaultTuning.expand_stream_stages;
     if (p->expand_stream) deal_expand_features(p, expand_blocks, expand_by_rounds ? 0 : expand_stages);
     // wavefronts per shrink workgroup: they split K in steps of 32; the LDS
     // reduction buffer (1 KB per wavefront and 16x16 block) stays within 64 KB

@@ -743,3 +743,31 @@ def test_given_expand_stages_beyond_any_row(stages, T, adapters, N):
         tiles.append(B.lora_plan_export(p)["expand_tiles"])
         p.destroy()
     assert np.array_equal(*tiles) and int(tiles[0][:, 4].min()) > 0
+
+
+def test_every_length_of_expand_ranges_can_be_given_and_by_rounds_is_a_value_of_its_own():
+    """16 stages are a length like 8 and 32 (513 token tiles, so that nothing is halved; the list's end is cut); the default,
+    which a descriptor can ask for over another process default, is LORA_EXPAND_BY_ROUNDS; the plan's view says which."""
+    tables = (65664, np.array([0, 65664]), np.array([0]), np.full(1, 64, np.int32), np.ones(1), 1024, 11008, B.LORA_BF16)
+    before = B.lora_tuning_get()["expand_stream_stages"]
+    assert before == B.LORA_EXPAND_BY_ROUNDS
+
+    def ranges(**tuning):
+        p = B.lora_plan(*tables, tuning=tuning)
+        view = B.lora_plan_export(p)
+        p.destroy()
+        return view["tuning"]["expand_stream_stages"], view["expand_tiles"]
+
+    for stages in (8, 16, 32):
+        told, tiles = ranges(expand_stream_stages=stages)
+        assert told == stages and int(tiles[:, 4].max()) == 64 * stages and np.mean(tiles[:, 4] == 64 * stages) > 0.8
+    told, tiles = ranges()
+    assert told == before and int(tiles[:, 4].max()) % (64 * 16) != 0
+    try:
+        B.lora_tuning_set(expand_stream_stages=8)
+        assert ranges()[0] == 8 and int(ranges()[1][:, 4].max()) == 64 * 8
+        again, same = ranges(expand_stream_stages=B.LORA_EXPAND_BY_ROUNDS)
+        assert again == before and np.array_equal(same, tiles)
+    finally:
+        B.lora_tuning_set(expand_stream_stages=before)
+    assert np.array_equal(ranges()[1], tiles)
