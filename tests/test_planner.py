@@ -803,3 +803,19 @@ def test_shipped_expand_ranges_are_not_far_behind_the_chosen_ones(shape_class, v
         assert view["tuning_source"] == (3 if tuning else 1)
         ends.append(_expand_launch_end(view["expand_tiles"].tolist()))
     assert ends[0] <= 1.1 * ends[1], ends
+
+
+@pytest.mark.parametrize("lengths,ranks,N", [
+    ((30, 25, 18, 27, 26, 28), (129, 64), 13824),                    # 324 tiles, 486 with those of rank 129 in 16 tokens: a half more
+    ((499, 500), (256, 100), 4096),                                  # 512, 768: as many as have a place, but a half more
+    ((60,) + 11 * (30,), (160,) + 11 * (8,), 13824)])                # 702, 810: more than have a place
+def test_long_ranks_stay_in_tiles_of_32_tokens_where_these_are_too_many_more(lengths, ranks, N):
+    T, n_a = sum(lengths), len(lengths)
+    rank = np.asarray([ranks[a % len(ranks)] for a in range(n_a)], np.int32)
+    p = B.lora_plan(T, np.concatenate([[0], np.cumsum(lengths)]), np.arange(n_a), rank, np.ones(n_a), 512, N, B.LORA_BF16)
+    fn, ptr = B._lib.lora_rows_expand_tiles, ctypes.POINTER(B.Tile)()
+    fn.argtypes, fn.restype = [ctypes.c_void_p, ctypes.c_void_p], ctypes.c_int32
+    tiles = [ptr[i] for i in range(fn(p.handle, ctypes.byref(ptr)))]
+    long_tiles = [t for t in tiles if rank[t.adapter] > 128]
+    assert long_tiles and max(t.nrows for t in long_tiles) > 16
+    p.destroy()
