@@ -719,16 +719,18 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     if (per == 0) per = one_step || token_tiles(16) * blocks <= 512 ? 16 : 32;
     const int64_t tiles = token_tiles(per) * blocks;
     int64_t wide = one_step ? (tiles < 1024 ? 1 : tiles < 2560 ? 2 : 4) : tiles / 1024;
-    // Higher ranks, all about as long: 512 tiles are two on each compute unit, so two or four blocks a tile where that makes one full round of
-    // two or four.  lora_delta: 3683 tokens of rank 256, 512 -> 4096 (1840 tiles of one block), 83.0 -> 64.7 us; 1388 of rank 36,
-    // 4096 -> 11008, 40.9 -> 33.1; 199 batches of such tiles 1.11 times as fast, the slowest 0.99.  (With ranks of 4 to 256 in
-    // one batch the rounds are not full: 0.94 on average.)  With fewer than eight tokens a tile Bt alone is what it reads, and
-    // more and shorter workgroups read it the faster: 270 tokens on 103 adapters of rank 100, 52.2 -> 54.7, 38 batches 0.995.
-    if (higher && per == 32 && 4 * min_rank >= 3 * max_rank && (int64_t)p->perm.size() >= 8 * token_tiles(32))
-        for (int64_t n : {2, 4}) {
-            const int64_t held = token_tiles(32) * ((blocks + n - 1) / n);
-            if (blocks >= n && held <= 512 && tiles >= 384 * n) wide = n;
-        }
+    // Higher ranks, all about as long: the chip holds 768 tiles, so two blocks a tile where that makes at most one round of them (odd
+    // ranks, whose elements all have to be shifted into place: two thirds of one), else four where that makes two thirds of one.
+    // lora_delta, one block / so: 1329 tokens of rank 256, 5120 -> 5120 (840 tiles of one block), 54.2 / 47.2 us; 741 on 28 of rank 34,
+    // 1920 -> 7720 (1209), 25.2 / 19.9; 1021 on 4 of rank 160, 4096 -> 11008 (1419), 48.5 / 41.4; 1272 on 9 of ranks 90 and 100, 4096 ->
+    // 11008 (1892), 50.1 / 42.2; 100 drawn batches of 1024 to 1536 tiles 1.06 times as fast, the slowest 0.976; with ranks 255 and 200
+    // 0.955, 2234 tokens, 4096 -> 4096, 82.1 / 93.6.  (With ranks of 4 to 256 in one batch the rounds are not full: 0.94 on average.)
+    // With fewer than eight tokens a tile Bt alone is what it reads, and more and shorter workgroups read it the faster.
+    if (higher && per == 32 && 4 * min_rank >= 3 * max_rank && (int64_t)p->perm.size() >= 8 * token_tiles(32)) {
+        auto held = [&](int64_t n) { return token_tiles(32) * ((blocks + n - 1) / n); };
+        if (blocks >= 2 && tiles >= 768 && held(2) <= (odd_above_24 ? 512 : 768)) wide = 2;
+        else if (blocks >= 4 && tiles >= 1536 && held(4) <= 512) wide = 4;
+    }
     const int32_t n_tile = 256 * (int32_t)std::max<int64_t>(1, std::min(blocks, wide));
     // Ranks of very different length in one batch: the launch then is its longest tiles, which all start first (microseconds of a
     // tile of 32 tokens, by time stamps in a launch of 640: ranks up to 48 7.1, 100 8.2 to 10.4, 256 11 to 15).  Those of ranks

@@ -608,7 +608,9 @@ def test_layer_shrink_tiles_are_built_only_where_they_are_read(T, K, N, n_a, ran
     (700, 2, (31, 9), 4096, 32, 1), (1018, 1, (31,), 4096, 32, 1), (260, 1, (25,), 13824, 32, 1), (4800, 2, (25,), 11008, 32, 6), (2400, 1, (31,), 11008, 32, 3),
     # higher ranks of about one length: a full round of two or four blocks, for requests of eight tokens a tile on average
     (1500, 2, (100,), 4096, 32, 2), (3600, 3, (200, 256), 4096, 32, 4), (270, 108, (100,), 4096, 32, 1), (280, 90, (200, 256), 5120, 32, 1),
-    (380, 60, (200, 256), 3712, 32, 1), (900, 60, (200, 256), 3712, 32, 2)])
+    (380, 60, (200, 256), 3712, 32, 1), (900, 60, (200, 256), 3712, 32, 2),
+    # two blocks up to 768 tiles of them, odd ranks up to 512, else four up to 512 of them
+    (3040, 1, (160,), 4096, 32, 2), (2000, 1, (100,), 4096, 32, 2), (2200, 1, (101,), 4096, 32, 1), (1130, 1, (256,), 11008, 32, 4), (3300, 1, (101,), 4096, 32, 4)])
 def test_tiles_of_the_expand_for_rows_of_any_length(T, n_a, ranks, N, rows, blocks):
     """Tokens and features of the largest tile, and that the tiles are every row and feature of every adapter once."""
     lengths = np.full(n_a, T // n_a)
