@@ -229,8 +229,9 @@ def lora_tuning_table_get() -> list:
 
 
 def lora_gemm_choice(tokens: int, k: int, n: int, dtype: int, delta: bool):
-    """(kernel, feature blocks, token blocks): what an aligned product takes; kernel 1 small, 2, 3 and 6 medium, 4 ring (or
-    register-staged), 5 register-staged 128 x 128; the blocks of 16 are the small kernel's tile."""
+    """(kernel, feature blocks, token blocks): what an aligned product takes; kernel 1 small; 6, 2, 3 and 7 medium,
+    of 64, 128, 192 and 256 features; 4 ring (or register-staged), 5 register-staged 128 x 128; the blocks of 16 are the small
+    kernel's tile."""
     c = int(_lib.lora_gemm_choice(int(tokens), int(k), int(n), int(dtype), int(delta)))
     return c >> 16, c >> 8 & 255, c & 255
 

@@ -697,31 +697,41 @@ def test_any_rank_expand_of_one_step(T, N, ranks):
     assert np.all(np.abs(out[0] - out[1]) <= 2.0 ** -7 * np.abs(out[1]) + 1e-4)
 
 
-@pytest.mark.parametrize("T,N,ranks,max_seg", [
-    (300, 4104, (16, 64), 150), (500, 4104, (128,), 500), (600, 8200, (24, 128), 200), (900, 8200, (64, 8), 400),
-    (1300, 8200, (16, 64, 128), 300), (1500, 9000, (64,), 700), (700, 13832, (128,), 700)])
-def test_streaming_expand_of_one_to_eight_stages(T, N, ranks, max_seg):
-    """Tiles whose feature ranges the planner makes as long as the rounds of the compute units ask for: one to eight stages (whole
-    rounds of four and what is left of them), one to eight 64-feature chunks a stage, remainders of tokens and features; every
-    K part count of v that comes with them; beta 0 and 1; nothing written between the rows of y."""
-    w = wl.random_case(2500 + T + N, T, 1024, N, 4, ranks, max_seg=max_seg, frac_none=0.1, scales=(0.5, 2.0, -1.0))
+@pytest.mark.parametrize("T,K,N,ranks,max_seg,parts,shapes", [
+    (300, 1024, 4104, (16, 64), 150, 1, {(4, 1), (2, 1)}), (500, 1024, 4104, (128,), 500, 1, {(2, 1), (2, 2)}),
+    (600, 1024, 8200, (24, 128), 200, 1, {(2, 2), (2, 3), (8, 2), (8, 3)}),
+    (900, 1024, 8200, (64, 8), 400, 1, {(2, 0), (2, 1), (4, 0), (4, 1), (8, 0), (8, 1)}),
+    (1300, 1024, 8200, (16, 64, 128), 300, 1, {(2, 1), (4, 1), (4, 3)}), (1500, 1024, 9000, (64,), 700, 1, {(2, 0), (2, 3), (4, 0)}),
+    (700, 1024, 13832, (128,), 700, 1, {(2, 1), (2, 2)}), (9000, 1024, 8200, (16,), 1500, 2, {(1, 1), (1, 2), (2, 1), (2, 2)}),
+    (16500, 1024, 4104, (64, 16), 2000, 2, {(1, 1), (2, 3)}), (16500, 1024, 4360, (64,), 2000, 2, {(1, 2), (1, 3)}),
+    (7500, 2048, 9000, (128,), 2000, 4, {(1, 2), (1, 3), (2, 1), (2, 2)}), (7500, 2048, 9064, (16, 128, 64), 2000, 4, {(1, 0), (1, 2)}),
+    (9000, 2048, 4104, (16, 64), 900, 4, {(2, 1), (2, 2), (4, 0), (4, 1)}), (2500, 8192, 4104, (128, 64), 700, 4, {(2, 1), (2, 3), (4, 1), (4, 2)})])
+def test_streaming_expand_of_whole_rounds_of_stages_and_what_is_left(T, K, N, ranks, max_seg, parts, shapes):
+    """Tiles whose feature ranges the planner makes as long as the rounds of the compute units ask for: one, two, four and eight
+    64-feature chunks a stage, each with whole rounds of four stages and with one, two and three stages left (shapes: chunks and
+    stages left, of all tiles), behind v in one, two and four K parts; remainders of tokens and features; beta 0 and 1; nothing
+    written between the rows of y."""
+    w = wl.random_case(2500 + T + N, T, K, N, 4, ranks, max_seg=max_seg, frac_none=0.1, scales=(0.5, 2.0, -1.0))
     dl = device.to_device(w, DEV, with_w=False)
     tok = oracle.token_adapter(w.T, w.seg_indptr, w.seg_adapter)
     ad = oracle.Adapters(w.adapter_rank, w.adapter_scale, w.A, w.B)
     plan = device.make_plan(w)
+    view = B.lora_plan_export(plan)
+    chunks = view["expand_tiles"][:, 5] >> 4 & 15
+    assert view["v_parts"] == parts and set(zip(chunks.tolist(), (-(-view["expand_tiles"][:, 4] // (64 * chunks)) % 4).tolist())) == shapes
     v = torch.zeros(B.lora_plan_query(plan)[1] // 4, dtype=torch.float32, device=DEV)
     y0 = torch.from_numpy(_y_in(w)).to(DEV, torch.bfloat16)
-    ref = oracle.expand(w.x, tok, ad, N)
-    has = torch.from_numpy(np.where(tok >= 0, w.adapter_rank[np.clip(tok, 0, None)], 0) > 0)
+    rows = np.arange(T) if T * N < 1 << 24 else np.sort(np.random.default_rng(T).choice(T, size=1 << 11, replace=False))
+    ref = oracle.expand(w.x, tok, ad, N, rows=rows)
+    has = np.where(tok >= 0, w.adapter_rank[np.clip(tok, 0, None)], 0) > 0
     for beta in (1.0, 0.0):
         y = torch.full((T, N + 8), 9.0, dtype=torch.bfloat16, device=DEV)
         y[:, :N] = y0
         names = _launched(lambda: B.lora_delta(plan, dl.x, w.K, dl.At_ptrs, dl.Bt_ptrs, v, y, N + 8, beta))
         assert "expand_stream_kernel" in names, names
-        got = _to_np(y)
-        want = ref + _to_np(y0).astype(np.float64) * beta
-        _assert_close(got[has.numpy()][:, :N], want[has.numpy()], BF16_TOL, f"delta, beta {beta}")
-        assert np.array_equal(got[~has.numpy()][:, :N], _to_np(y0)[~has.numpy()]) and np.all(got[:, N:] == 9.0)
+        assert bool((y[:, N:] == 9.0).all()) and torch.equal(y[torch.from_numpy(~has), :N], y0[torch.from_numpy(~has)])
+        got, was = _to_np(y[rows, :N]), _to_np(y0[rows]).astype(np.float64)
+        _assert_close(got[has[rows]], (ref + was * beta)[has[rows]], BF16_TOL, f"delta, beta {beta}")
     plan.destroy()
 
 
@@ -879,10 +889,10 @@ def test_any_rank_fused_forward_of_infinities(T, N, rank, kernel):
 @pytest.mark.parametrize("T,N,dtype,ranks,kernel", [
     (90, 520, "f32", (8, 20), "small"), (90, 520, "bf16", (8, 16), "small"), (90, 520, "bf16", (5, 100), "small"),
     (700, 5000, "bf16", (8, 16), "mid"), (700, 5000, "bf16", (5, 100), "mid"), (3585, 3600, "bf16", (8, 16), "ring"),
-    (95, 4096, "bf16", (8, 16), "small")])
+    (95, 4096, "bf16", (8, 16), "small"), (2049, 3080, "bf16", (8, 16), "mid"), (2049, 3080, "bf16", (5, 100), "mid")])
 def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, N, dtype, ranks, kernel):
     """One adapter's factors hold infinities and NaN: the tokens of all other adapters, and of none, come out bit for bit
-    as with that adapter's factors finite (small, medium and ring GEMM, fp32 and any rank)."""
+    as with that adapter's factors finite (small GEMM, medium of 128 or 192 and of 256 features, ring, fp32 and any rank)."""
     w = wl.random_case(2300 + T + ranks[0], T, 264, N, 6, ranks, dtype=dtype, max_seg=7, frac_none=0.2)
     dl = device.to_device(w, DEV, with_w=True)
     tdt = device.torch_dtype(w)
@@ -900,6 +910,7 @@ def test_fused_forward_keeps_an_adapters_infinities_to_its_tokens(T, N, dtype, r
         y = torch.empty((w.T, w.N), dtype=tdt, device=DEV)
         names = _launched(lambda: B.lora_fused_forward(plan, dl.x, w.K, dl.Wt, w.K, dl.At_ptrs, Bt, y, w.N, ws, ws.numel()))
         assert names & {f"gemm_{kernel}_kernel<delta>", f"layer_{kernel}_kernel"}
+        assert (T == 2049) == (kernel == "mid" and B.lora_gemm_choice(T, w.K, N, B.LORA_BF16, True)[0] == 7)
         out.append(y)
     others = torch.from_numpy(tok != bad).to(DEV)
     assert bool(others.any()) and bool(torch.isfinite(out[0]).all())
