@@ -126,6 +126,8 @@ __device__ __forceinline__ void finish16(E* yp, const u32x4 (&yin)[sizeof(E)], c
 // compute unit; a tile is a chain of trips (descriptor, tokens, Bt and y, v, Bt again) of 7 to 15 us, so that what shortens a
 // launch is more of them side by side: lora_delta, two workgroups with four steps / three with two: 997 single tokens on 71
 // adapters of rank 100, 4096 -> 4096, 52.2 / 48.5; 672 on 61 of rank 100, 5120 -> 13824, 37.6 / 34.4; 299 on 114, 80.1 / 76.4.
+// Launches of 300 to 512 tiles, which had a place each before, lose nothing by the shorter reach: 16 batches of ranks 97 to 256
+// 1.02 times as fast, between 0.992 and 1.072 (420 tokens on 19 of rank 256, 4096 -> 4096, 30.5 / 28.6).
 template <typename E>
 __device__ __forceinline__ u32x4 own_elements(u32x4 b, uint32_t drop, int keep)
 {

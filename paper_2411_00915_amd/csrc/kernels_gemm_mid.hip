@@ -445,11 +445,11 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
 //   4096 -> 4096,  256 tokens 16 / 31 / 35 / 64 / 16,  640: 42 / 33 / 36 / 63 / 45,  1280: 79 / 64 / 44 / 68 / 70,
 //                  1536: - / 67 / 79 / 69 / 75,  2048: - / 68 / 80 / 72 / 77,  3072: - / 111 / 128 / 85 / 85
 //   5120 -> 5120,  1024 tokens 91 / 79 / 53 / 84 / 85,  2048: - / 116 / 99 / 84 / 137
+//   4096 -> 11008, 256 tokens 42 / 34 / 38 / 65 / 42,  512: 80 / 64 / 45 / - / 71,  1024: 157 / 98 / 84 / 73 / 115
+//   5120 -> 13824, 320 tokens 108 / 87 / 66 / - / 86,  640: 180 / 128 / 116 / 95 / 138
 // 128 / 192 / 256 features / 256 x 256 ring, where 256 features are the choice: 2048 tokens, 4096 -> 4096, 75 / 80 / 62 / 76;  1500,
 // 11008 -> 4096, 189 / 201 / 151 / 200;  2607, 3288 -> 3064, 75 / 86 / 58 / 67;  and just where they are not: 2321, 5120 -> 5120,
 // 118 / 140 / 115 / 100;  3000, 4096 -> 4096, 110 / 116 / 109 / 80;  991, 5120 -> 5120, 71 / 49 / 56 / 83.
-//   4096 -> 11008, 256 tokens 42 / 34 / 38 / 65 / 42,  512: 80 / 64 / 45 / - / 71,  1024: 157 / 98 / 84 / 73 / 115
-//   5120 -> 13824, 320 tokens 108 / 87 / 66 / - / 86,  640: 180 / 128 / 116 / 95 / 138
 // Products of few stages are the register-staged 128 x 128 tiles' (two on a compute unit, so that one's stores and first
 // loads run beside the other's stages; without adapters, whose infinities they do not keep apart).  Kernel times, small /
 // 128 / 192 / ring / register-staged: 2944 tokens, 32 -> 2568, 24.6 / 11.1 / 12.7 / - / 8.8;  4944, 128 -> 3496: 48.8 / 24.1 /
@@ -459,9 +459,9 @@ hipError_t launch_one(int32_t T, int32_t K, int32_t N, const void* x, int64_t ld
 // The constants of the five others are fitted to such times of 2000 problems (8 to 16384 tokens, K 8 to 13824, N 64 to 13824): with
 // the kernels of that time the choice took 0.4 % longer than the best of the five on average, 1.24 times at worst.  Those of
 // 128 and 192 features are 1 % faster without adapters since, from 25 stages on: a distance that the fit does not see.  Those of
-// 256 features are fitted to 8 products; against the others 44 of 50 drawn products of 300 to 7000 tokens (the rest are smaller
-// tiles') took 1.003 times as long as the best of them, without these tiles 1.033, and 40 fused calls 1.000 and 1.007; 44 drawn calls
-// that go to them, K from 8 to 1600, 1.001 and 1.16, the slowest 1.04.
+// 256 features are fitted to 8 products.  Drawn calls that go to them, forced to each kernel in turn: 70 of lora_base_gemm (K from
+// 1264; shorter ones mostly are the register-staged tiles') 1.16 times as fast as the best of all others, two below 0.98 (2933 tokens,
+// 1704 -> 11112, 133 us, ring 125); 70 of lora_fused_forward, K from 8, 1.15, two below 0.98 (1183, 120 -> 5768, 42.2, 192 features 38.4).
 gemm_route_id gemm_route(int32_t T, int32_t K, int32_t N, int64_t ldx, int64_t ldw, bool delta, bool tiled)
 {
     if ((int64_t)N * ldw * 2 >= (1ll << 32) || (int64_t)T * ldx * 2 >= (1ll << 32)) return GEMM_TILED;   // 32-bit byte offsets

@@ -734,11 +734,12 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
     const int32_t n_tile = 256 * (int32_t)std::max<int64_t>(1, std::min(blocks, wide));
     // Ranks of very different length in one batch: the launch then is its longest tiles, which all start first (microseconds of a
     // tile of 32 tokens, by time stamps in a launch of 640: ranks up to 48 7.1, 100 8.2 to 10.4, 256 11 to 15).  Those of ranks
-    // above 128 are of 16 tokens where all tiles have a place on the chip at once then (768) and are a quarter more at most: each
-    // reads Bt again.  lora_delta, 32 / 16 tokens: 726 on 4 adapters of ranks 140 and 8, 11008 -> 4096, 20.5 / 18.1 us; 914 single tokens
+    // above 128 are of 16 tokens where all tiles have a place on the chip at once then (768, and a twelfth more, which begin as the
+    // first short ones end) and are a quarter more at most: each reads Bt again.  lora_delta, 32 / 16 tokens: 726 on 4 adapters of ranks 140 and 8, 11008 -> 4096, 20.5 / 18.1 us; 914 single tokens
     // on 7 of ranks 4 to 256, 26.1 / 23.9; 742 on 40, 1416 -> 4016, 22.9 / 20.9; not taken: 154 on 6 of ranks 129 and 64, 5120 -> 13824,
     // 23.3 / 27.2 (378 and 486 tiles); 999 on 2 of 256 and 100, 11008 -> 4096, 35.4 / 40.5 (512 and 800).  120 drawn batches that
-    // are cut so 1.07 times as fast, three below 0.98 (219 on 7 of 129 and 64, 2136 -> 12144, 28.8 / 30.8).
+    // are cut so 1.07 times as fast, three below 0.98 (219 on 7 of 129 and 64, 2136 -> 12144, 28.8 / 30.8);
+    // of 769 to 832 tiles 29 drawn ones 1.03 times as fast, four below 0.98; of 833 to 960 46 1.003, 13 below 0.98.
     int32_t long_rank = LORA_MAX_RANK + 1;                   // ranks from here on: tiles of 16 tokens
     if (higher && per == 32 && max_rank > 128 && 2 * min_rank < max_rank) {
         int64_t shorter = 0;
@@ -746,7 +747,7 @@ static void build_rows_expand_tiles(lora_plan* p, int32_t per)
             const int32_t own = p->rank[p->group_adapter[g]] > 128 ? 16 : per;
             shorter += (p->group_offset[g + 1] - p->group_offset[g] + own - 1) / own;
         }
-        if (shorter * ((p->N + n_tile - 1) / n_tile) <= 768 && 4 * shorter <= 5 * token_tiles(32)) long_rank = 129;
+        if (shorter * ((p->N + n_tile - 1) / n_tile) <= 832 && 4 * shorter <= 5 * token_tiles(32)) long_rank = 129;
     }
     for (int g = 0; g < G; ++g)
         for (int32_t row = p->group_offset[g], own = p->rank[p->group_adapter[g]] >= long_rank ? 16 : per; row < p->group_offset[g + 1]; row += own)

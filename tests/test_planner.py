@@ -810,7 +810,7 @@ def test_shipped_expand_ranges_are_not_far_behind_the_chosen_ones(shape_class, v
 @pytest.mark.parametrize("lengths,ranks,N", [
     ((30, 25, 18, 27, 26, 28), (129, 64), 13824),                    # 324 tiles, 486 with those of rank 129 in 16 tokens: a half more
     ((499, 500), (256, 100), 4096),                                  # 512, 768: as many as have a place, but a half more
-    ((60,) + 11 * (30,), (160,) + 11 * (8,), 13824)])                # 702, 810: more than have a place
+    ((60,) + 12 * (30,), (160,) + 12 * (8,), 13824)])                # 756, 864: more than have a place
 def test_long_ranks_stay_in_tiles_of_32_tokens_where_these_are_too_many_more(lengths, ranks, N):
     T, n_a = sum(lengths), len(lengths)
     rank = np.asarray([ranks[a % len(ranks)] for a in range(n_a)], np.int32)
